@@ -98,7 +98,8 @@ int dr_conv2d_fwd(const dr_tensor* xd, const void* x, const dr_conv* cd, const v
  * (xd, cd): 0 when the layer would not be cut (then ws may be NULL); cd with the stride of a slim
  * layer gives the slim layer's size.  ws: device memory, 256-byte aligned, of at least that size
  * (else DR_ERR_WORKSPACE), used only until the call's work on `stream` has finished.  fp32 NCHW layers
- * are cut; every other layer runs exactly as in dr_conv2d_fwd. */
+ * are cut; bf16 NHWC layers of few output pixels add their products in up to eight shares of the contraction (fp32, then
+ * added in a fixed order), which needs no scratch; every other layer runs exactly as in dr_conv2d_fwd. */
 int dr_conv2d_workspace_bytes(const dr_tensor* xd, const dr_conv* cd, size_t* bytes);
 int dr_conv2d_fwd_ws(const dr_tensor* xd, const void* x, const dr_conv* cd, const void* w, const float* bias,
                      const dr_tensor* yd, void* y, int y_c_offset, void* ws, size_t ws_bytes, void* stream);
@@ -232,8 +233,9 @@ typedef struct { int kind; dr_conv conv; dr_pool pool; } dr_step;
 typedef struct { int n_steps; dr_step steps[DR_MAX_STEPS]; } dr_branch;
 
 /* How the module is executed.  0 = the layer-by-layer form the paper times: every ReLU is its own
- * kernel and the branch outputs are gathered by a concat kernel.  Flags remove passes without
- * changing the function computed: */
+ * kernel and the branch outputs are gathered by a concat kernel.  (In every mode the bf16 NHWC convolutions at one depth of
+ * the branches, and a 3x3 pooling step beside them, may share a launch where each is small; each still reads its whole
+ * input and writes its whole output.)  Flags remove passes without changing the function computed: */
 #define DR_FUSE_RELU   1   /* ReLU in the convolution's store */
 #define DR_FUSE_CONCAT 2   /* a branch ending in a convolution writes its channel range of y directly
                               (that convolution then also applies its ReLU in the store) */

@@ -172,7 +172,7 @@ size_t conv_scratch_bytes(const dr_tensor& xd, const dr_conv& cd)
 
 int conv_run(const char* who, const dr_tensor& xd, const void* x, const dr_conv& cd, const void* w, const float* bias,
              const void* residual, int res_ctot, const dr_tensor& yd, void* y, int y_c_offset, hipStream_t st, int c_logical = 0,
-             void* scratch = nullptr, size_t scratch_bytes = 0)
+             void* scratch = nullptr, size_t scratch_bytes = 0, bool small = true)
 {
     if (xd.c != cd.c) return fail(DR_ERR_SHAPE, "%s: input has %d channels, filters expect %d", who, xd.c, cd.c);
     const dr_tensor o = conv_out(xd, cd);
@@ -194,6 +194,11 @@ int conv_run(const char* who, const dr_tensor& xd, const void* x, const dr_conv&
     g.c_logical = c_logical;
     if (xd.dtype == DR_F32)
         return launch_conv_f32(g, (const float*)x, (const float*)w, bias, (const float*)residual, (float*)y, st, scratch, scratch_bytes);
+    if (small && conv_bf16_small_takes(g, x, w)) {
+        TraceScope trace("conv_bf16", &g, g.Ng, st);
+        const ConvSmall job{g, (const uint16_t*)x, (const uint16_t*)w, bias, (const uint16_t*)residual, (uint16_t*)y, nullptr};
+        return launch_conv_bf16_small(&job, 1, st);
+    }
     return launch_conv_bf16(g, (const uint16_t*)x, (const uint16_t*)w, bias, (const uint16_t*)residual, (uint16_t*)y, st);
 }
 
@@ -431,9 +436,10 @@ BranchStreams* branch_streams()
 
 // The stacked first steps of a module (see inception_run).  Marks the branches it has served in `stacked`
 // and leaves their step-0 outputs in `dst` (workspace buffers; NULL for a one-step branch that wrote y).
-// Serves nothing, without error, when the parameters are not laid out for it.
+// Serves nothing, without error, when the parameters are not laid out for it.  sp: destinations of the stacked layer; job
+// (may be NULL): a layer that the small-layer kernel takes is not launched but left there for the caller (job->w set).
 int run_stacked_first_steps(const dr_tensor& xd, const void* x, const dr_inception& d, const ParamCursor& wts, const ParamCursor& bss,
-                            const dr_tensor& yd, void* y, Arena& ar, hipStream_t st, bool* stacked, void** dst)
+                            const dr_tensor& yd, void* y, Arena& ar, hipStream_t st, bool* stacked, void** dst, ConvSplit& sp, ConvSmall* job)
 {
     const char* who = "dr_inception_fwd";
     const bool fuse_cat = d.mode & DR_FUSE_CONCAT;
@@ -487,7 +493,6 @@ int run_stacked_first_steps(const dr_tensor& xd, const void* x, const dr_incepti
     if (g.Ng == 0 || !x) return DR_OK;
     if (f32 ? ((size_t)g.Ng * g.C * 4 >= (1ull << 31) || (size_t)ktot * g.C * 4 >= (1ull << 31)) : !conv_bf16_dma_eligible(g, x, w0))
         return DR_OK;
-    ConvSplit sp;
     sp.n = nb;
     for (int i = 0; i < nb; ++i) {
         const dr_branch& br = d.branches[members[i]];
@@ -502,8 +507,146 @@ int run_stacked_first_steps(const dr_tensor& xd, const void* x, const dr_incepti
     g.y_ctot = sp.dst[0].ctot; g.y_coff = sp.dst[0].c_offset;
     if (f32)
         return launch_conv_f32(g, (const float*)x, (const float*)w0, (const float*)b0, nullptr, (float*)sp.dst[0].y, st, nullptr, 0, &sp);
+    const ConvSmall small{g, (const uint16_t*)x, (const uint16_t*)w0, (const float*)b0, nullptr, (uint16_t*)sp.dst[0].y, &sp};
+    const bool takes = conv_bf16_small_takes(g, x, w0);
+    if (takes && job) { *job = small; return DR_OK; }
     TraceScope trace("conv_bf16", &g, g.Ng, st);
-    return launch_conv_bf16_dma(g, (const uint16_t*)x, (const uint16_t*)w0, (const float*)b0, nullptr, (uint16_t*)sp.dst[0].y, st, &sp);
+    if (takes) return launch_conv_bf16_small(&small, 1, st);
+    return launch_conv_bf16_dma(g, small.x, small.w, small.bias, nullptr, small.y, st, &sp);
+}
+
+// A module of small bf16 layers, step by step instead of branch by branch: the convolutions at the same depth of the branches
+// (and a 3x3 pooling step beside them) are independent of one another and share launches of the small-layer kernel.
+// Steps that kernel does not take run one by one.  ReLU layers that the mode keeps apart and the concat remain kernels of
+// their own.
+struct SmallGroup {
+    hipStream_t st;
+    int n = 0;
+    ConvSmall jobs[SMALL_GROUP_MAX];
+    int flush()
+    {
+        const int k = n;
+        n = 0;
+        return k ? launch_conv_bf16_small(jobs, k, st) : DR_OK;
+    }
+    int add(const ConvSmall& j)
+    {
+        if (n == SMALL_GROUP_MAX) DR_TRY(flush());
+        jobs[n++] = j;
+        return DR_OK;
+    }
+};
+
+// A max-pooling step as a job of the small-layer kernel: 3x3 windows, whole 16-byte channel groups, few pixels.
+bool small_pool_job(const dr_tensor& t, const void* x, const dr_tensor& o, void* y, const dr_pool& p, ConvSmall* job)
+{
+    const long ng = (long)o.n * o.h * o.w;
+    if (p.kh != 3 || p.kw != 3 || t.c % 8 != 0 || (((uintptr_t)x | (uintptr_t)y) & 15) != 0 || ng == 0 || ng > 4096 || (long)o.h * o.w > 65536) return false;
+    ConvGeom g{};
+    g.N = t.n; g.C = g.K = t.c; g.H = t.h; g.W = t.w;
+    g.R = g.S = 3; g.sh = p.stride_h; g.sw = p.stride_w; g.ph = p.pad_h; g.pw = p.pad_w;
+    g.P = o.h; g.Q = o.w; g.Ng = (int)ng;
+    *job = ConvSmall{g, (const uint16_t*)x, nullptr, nullptr, nullptr, (uint16_t*)y, nullptr};
+    return true;
+}
+
+// How many convolutions of the module the small-layer kernel takes.
+int inception_small_steps(const dr_tensor& xd, const void* x, const dr_inception& d)
+{
+    if (xd.dtype != DR_BF16 || xd.layout != DR_NHWC) return 0;
+    int n = 0;
+    for (int b = 0; b < d.n_branches; ++b) {
+        dr_tensor t = xd;
+        for (int s = 0; s < d.branches[b].n_steps; ++s) {
+            const dr_step& stp = d.branches[b].steps[s];
+            const dr_tensor o = stp.kind == DR_STEP_CONV ? conv_out(t, stp.conv) : pool_out(t, stp.pool);
+            if (stp.kind == DR_STEP_CONV && tensor_elems(o) && conv_bf16_small_takes(conv_geom(t, stp.conv, o), s == 0 ? x : nullptr, nullptr)) ++n;
+            t = o;
+        }
+    }
+    return n;
+}
+
+int inception_run_levels(const dr_tensor& xd, const void* x, const dr_inception& d, ParamCursor& wts, ParamCursor& bss, const dr_tensor& yd, void* y,
+                         Arena& ar, hipStream_t st)
+{
+    const char* who = "dr_inception_fwd";
+    const bool fuse_relu = d.mode & DR_FUSE_RELU, fuse_cat = d.mode & DR_FUSE_CONCAT;
+    if (!x) return fail(DR_ERR_NULL, "%s: x is NULL", who);
+    SmallGroup group{st};
+    void* stacked_dst[DR_MAX_BRANCHES] = {};
+    bool stacked[DR_MAX_BRANCHES] = {};
+    ConvSplit sp;
+    if (d.mode & DR_FUSE_STACK) {
+        ConvSmall job{};
+        DR_TRY(run_stacked_first_steps(xd, x, d, wts, bss, yd, y, ar, st, stacked, stacked_dst, sp, &job));
+        if (job.w) DR_TRY(group.add(job));
+    }
+    struct Branch { dr_tensor t; const void* cur; int c_off, param; ConcatSeg seg; } br[DR_MAX_BRANCHES];
+    int c_off = 0, param = 0, depth = 0;
+    for (int b = 0; b < d.n_branches; ++b) {
+        br[b] = Branch{xd, x, c_off, param, ConcatSeg{nullptr, 0, 0}};
+        int c = xd.c;
+        for (int s = 0; s < d.branches[b].n_steps; ++s)
+            if (d.branches[b].steps[s].kind == DR_STEP_CONV) { c = d.branches[b].steps[s].conv.k; ++param; }
+        c_off += c;
+        depth = std::max(depth, d.branches[b].n_steps);
+    }
+    for (int s = 0; s < depth; ++s) {
+        struct Relu { void* p; size_t n; } relus[DR_MAX_BRANCHES];
+        int n_relu = 0;
+        for (int b = 0; b < d.n_branches; ++b) {
+            if (s >= d.branches[b].n_steps) continue;
+            const dr_step& stp = d.branches[b].steps[s];
+            const bool last = s == d.branches[b].n_steps - 1;
+            Branch& q = br[b];
+            dr_tensor o;
+            void* dst;
+            if (stp.kind == DR_STEP_CONV) {
+                dr_conv cd = stp.conv;
+                const bool relu_after = cd.relu != 0, direct = last && fuse_cat;
+                cd.relu = relu_after && (fuse_relu || direct);
+                o = conv_out(q.t, cd);
+                const void* w = wts.p[q.param];
+                const float* bias = (const float*)bss.p[q.param];
+                ++q.param;
+                const bool done = s == 0 && stacked[b];
+                dst = direct ? y : done ? stacked_dst[b] : ar.take(tensor_bytes(o));
+                if (!dst) return fail(DR_ERR_WORKSPACE, "%s: workspace too small", who);
+                if (!done) {
+                    if (!w) return fail(DR_ERR_NULL, "%s: missing weights of branch %d step %d", who, b, s);
+                    ConvGeom g = conv_geom(q.t, cd, o);
+                    if (tensor_elems(o) && conv_bf16_small_takes(g, q.cur, w)) {
+                        if (direct) { g.y_ctot = yd.c; g.y_coff = q.c_off; }
+                        DR_TRY(group.add(ConvSmall{g, (const uint16_t*)q.cur, (const uint16_t*)w, bias, nullptr, (uint16_t*)dst, nullptr}));
+                    } else {
+                        DR_TRY(conv_run(who, q.t, q.cur, cd, w, bias, nullptr, 0, direct ? yd : o, dst, direct ? q.c_off : 0, st));
+                    }
+                    if (relu_after && !cd.relu) relus[n_relu++] = Relu{dst, tensor_elems(o)};
+                }
+                if (last && !direct) q.seg = ConcatSeg{dst, o.c, q.c_off};
+            } else {
+                o = pool_out(q.t, stp.pool);
+                dst = ar.take(tensor_bytes(o));
+                if (!dst) return fail(DR_ERR_WORKSPACE, "%s: workspace too small", who);
+                ConvSmall job{};
+                if (small_pool_job(q.t, q.cur, o, dst, stp.pool, &job)) DR_TRY(group.add(job));
+                else DR_TRY(launch_maxpool(q.t, q.cur, o, dst, stp.pool, st));
+                if (last) q.seg = ConcatSeg{dst, o.c, q.c_off};
+            }
+            q.cur = dst;
+            q.t = o;
+        }
+        DR_TRY(group.flush());
+        for (int i = 0; i < n_relu; ++i) DR_TRY(launch_relu(DR_BF16, relus[i].p, relus[i].p, relus[i].n, st));
+    }
+    wts.i += param;
+    bss.i += param;
+    ConcatSeg segs[DR_MAX_BRANCHES];
+    int nseg = 0;
+    for (int b = 0; b < d.n_branches; ++b)
+        if (br[b].seg.src) segs[nseg++] = br[b].seg;
+    return nseg ? launch_concat(yd, nseg, segs, y, st) : DR_OK;
 }
 
 // Runs (or, with a measuring arena, only plans) one module.  y may be NULL when measuring.
@@ -512,6 +655,9 @@ int inception_run(const dr_tensor& xd, const void* x, const dr_inception& d, Par
 {
     const char* who = "dr_inception_fwd";
     const bool fuse_relu = d.mode & DR_FUSE_RELU, fuse_cat = d.mode & DR_FUSE_CONCAT;
+    // A trace of every kernel (no label filter) is there to time each kernel on its own: it runs the branches in turn.
+    const bool full_trace = g_trace.active && !g_trace.filter[0];
+    if (!ar.measure && !g_trace.active && wts.p && bss.p && inception_small_steps(xd, x, d) >= 2) return inception_run_levels(xd, x, d, wts, bss, yd, y, ar, main_st);
     ConcatSeg segs[DR_MAX_BRANCHES];
     int nseg = 0, c_off = 0;
     // DR_FUSE_STACK (Eq. (12)): first-step 1x1 convolutions on the module input run as one convolution
@@ -519,14 +665,12 @@ int inception_run(const dr_tensor& xd, const void* x, const dr_inception& d, Par
     // stacked filter bank as they are; each keeps its own destination.  bf16 channels-last and fp32 NCHW.
     void* stacked_dst[DR_MAX_BRANCHES] = {};
     bool stacked[DR_MAX_BRANCHES] = {};
+    ConvSplit sp;
     if ((d.mode & DR_FUSE_STACK) && !ar.measure && wts.p &&
         ((xd.dtype == DR_BF16 && xd.layout == DR_NHWC) || (xd.dtype == DR_F32 && xd.layout == DR_NCHW)))
-        DR_TRY(run_stacked_first_steps(xd, x, d, wts, bss, yd, y, ar, main_st, stacked, stacked_dst));
-    // A trace of every kernel (no label filter) is there to time each kernel on its own: it runs the
-    // branches in turn.
+        DR_TRY(run_stacked_first_steps(xd, x, d, wts, bss, yd, y, ar, main_st, stacked, stacked_dst, sp, nullptr));
     BranchStreams* bs = nullptr;
     hipEvent_t fork = nullptr;
-    const bool full_trace = g_trace.active && !g_trace.filter[0];
     if ((d.mode & DR_CONCURRENT_BRANCHES) && d.n_branches > 1 && !ar.measure && !full_trace) {
         bs = branch_streams();
         if (!bs) return fail(DR_ERR_HIP, "%s: cannot create the branch streams", who);
@@ -896,7 +1040,8 @@ int dr_conv2d_fwd(const dr_tensor* xd, const void* x, const dr_conv* cd, const v
     DR_TRY(check_tensor(who, "xd", xd));
     DR_TRY(check_tensor(who, "yd", yd));
     DR_TRY(check_conv_desc(who, cd));
-    return conv_run(who, *xd, x, *cd, w, bias, nullptr, 0, *yd, y, y_c_offset, (hipStream_t)stream);
+    // (no small-layer kernel: this entry point's sums run in one order over (r, s, c) at every size)
+    return conv_run(who, *xd, x, *cd, w, bias, nullptr, 0, *yd, y, y_c_offset, (hipStream_t)stream, 0, nullptr, 0, false);
 }
 
 int dr_conv2d_workspace_bytes(const dr_tensor* xd, const dr_conv* cd, size_t* bytes)

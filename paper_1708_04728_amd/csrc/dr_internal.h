@@ -69,6 +69,21 @@ struct ConvSplit { int n; ConvDest dst[4]; };
 int launch_conv_bf16_dma(const ConvGeom& g, const uint16_t* x, const uint16_t* w, const float* bias,
                          const uint16_t* residual, uint16_t* y, hipStream_t st, const ConvSplit* split = nullptr);
 
+// conv_bf16_small.hip: layers of few output pixels, several of them per launch.  A job is a convolution the streaming kernel takes
+// (split as above, may be NULL) or, with w = NULL, a 3x3 max-pooling layer of channels-last bf16 tensors with C % 8 == 0 and
+// 16-byte aligned pointers (g: its input, output and window; y its output).
+constexpr int SMALL_GROUP_MAX = 4;
+struct ConvSmall {
+    ConvGeom g;
+    const uint16_t *x, *w;
+    const float* bias;
+    const uint16_t* res;
+    uint16_t* y;
+    const ConvSplit* split;
+};
+bool conv_bf16_small_takes(const ConvGeom& g, const void* x, const void* w);
+int launch_conv_bf16_small(const ConvSmall* jobs, int n, hipStream_t st);
+
 // conv_bf16_patch.hip: filters of several taps at stride 1, C % 64 == 0, maps at most 256 pixels wide whose patch of
 // TH + R - 1 input rows fits LDS: the tile's input patch is loaded once and every tap multiplies from there
 bool conv_bf16_patch_eligible(const ConvGeom& g, const void* x, const void* w, const void* y);

@@ -1,0 +1,98 @@
+"""GPU parity of the small-layer bf16 convolution kernel (the contraction of a 32 x 32 tile shared by the waves of a
+workgroup, several layers per launch) against the fp64 oracle, where it can go wrong: fewer slices than waves, one slice more than a
+multiple of the waves, both slice modes, ragged filters / pixels / channel runs, every border, the scalar store, the
+largest layer it takes; and modules whose branches share launches, with the pooling step in them."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from paper_1708_04728_amd import binding as B
+from util import TOL_BF16, case_seed, close, empty_nhwc, gpu, gpu_nhwc, host_nhwc
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+CUS = 256
+
+
+def takes(N, C, H, W, K, R, S, stride, pad):
+    """The launcher's rule, restated."""
+    n = N * oracle.conv_out_size(H, R, stride, pad) * oracle.conv_out_size(W, S, stride, pad)
+    if R * S == 1:
+        return n <= 1024 and C > 256
+    return -(-n // 32) * -(-K // 32) <= 2 * CUS
+
+
+@pytest.mark.parametrize("case", [
+    # N, C, H, W, K, R, S, stride, pad
+    (1, 8, 5, 7, 8, 3, 3, 1, 1),          # 72 values: fewer slices than waves, one channel chunk per tap
+    (1, 24, 9, 11, 40, 3, 3, 1, 1),       # slices that run on from filter row to filter row, ragged filters
+    (2, 40, 13, 10, 100, 5, 5, 2, 2),     # stride 2, filters no multiple of 8 (scalar store at the end)
+    (1, 64, 6, 6, 33, 3, 3, 1, 1),        # whole taps, 9 slices for 8 waves, a second filter block of one filter
+    (3, 128, 7, 9, 64, 3, 3, 2, 1),       # two slices per tap
+    (1, 16, 4, 4, 16, 3, 1, 1, 0),        # a filter row shorter than a slice: no run-on
+    (1, 264, 3, 5, 24, 1, 1, 1, 0),       # 1x1, ragged run: 5 slices
+    (4, 832, 16, 16, 72, 1, 1, 1, 0),     # 1x1 at the largest pixel count
+    (1, 320, 9, 9, 56, 1, 1, 2, 0),       # strided 1x1
+    (2, 48, 64, 64, 64, 3, 3, 1, 1),      # 512 tiles, the most it takes: four waves per workgroup
+    (1, 1032, 2, 3, 8, 3, 3, 1, 1),       # long contraction, 146 slices
+])
+def test_small_layer(case):
+    N, C, H, W, K, R, S, stride, pad = case
+    assert takes(*case)
+    rng = np.random.default_rng(case_seed(case))
+    x = workloads.round_to_bf16(rng.standard_normal((N, C, H, W)).astype(np.float32))
+    w = workloads.round_to_bf16(rng.standard_normal((K, C, R, S)).astype(np.float32) * np.float32(np.sqrt(2.0 / (C * R * S))))
+    for bias, relu in ((True, True), (False, False)):
+        b = (rng.standard_normal(K) * 0.1).astype(np.float32) if bias else None
+        ref = oracle.conv2d(x, w, b, stride, pad, relu)
+        y = empty_nhwc(ref.shape, "bf16")
+        cd = B.conv_desc(K, C, R, S, stride, pad, relu, B.DR_KRSC)
+        B.conv2d_fwd_ws(gpu_nhwc(x, "bf16"), cd, B.pack_filters(gpu(w, "bf16")), None if b is None else gpu(b), y, None)
+        torch.cuda.synchronize()
+        got = host_nhwc(y)
+        # one rounding of an fp32 sum: within one unit of the last place of the rounded exact result
+        assert close(got, oracle.round_bf16(ref), 2.0 ** -7, "within one bf16 unit of the oracle")
+
+
+def test_small_layer_into_an_odd_channel_range():
+    """A destination that 8-byte stores do not fit, other channels untouched."""
+    rng = np.random.default_rng(3)
+    x = workloads.round_to_bf16(rng.standard_normal((1, 16, 6, 6)).astype(np.float32))
+    w = workloads.round_to_bf16(rng.standard_normal((20, 16, 3, 3)).astype(np.float32) * np.float32(0.1))
+    ref = oracle.round_bf16(oracle.conv2d(x, w, None, 1, 1, False))
+    wide = B.NHWC(torch.full((1, 6, 6, 33), -3.0, dtype=torch.bfloat16, device="cuda"))
+    B.conv2d_fwd_ws(gpu_nhwc(x, "bf16"), B.conv_desc(20, 16, 3, 3, 1, 1, False, B.DR_KRSC), B.pack_filters(gpu(w, "bf16")), None, wide, None, y_c_offset=7)
+    torch.cuda.synchronize()
+    got = host_nhwc(wide)
+    assert close(got[:, 7:27], ref, 2.0 ** -7)
+    assert (got[:, :7] == -3.0).all() and (got[:, 27:] == -3.0).all()
+
+
+@pytest.mark.parametrize("n,hw", [(1, (14, 14)), (2, (9, 13)), (5, (7, 7))])
+@pytest.mark.parametrize("form", ["original", "slim"])
+def test_module_whose_branches_share_launches(form, n, hw):
+    """An inception module small enough for step-by-step execution, in every mode: against the oracle (the storage rule
+    mirrored), stacked first steps with the bits of one convolution per branch."""
+    from test_gpu_bf16_nets import run_net_bf16
+    layer = (workloads.inception_original if form == "original" else workloads.inception_slim)("4b")
+    rng = np.random.default_rng(17 + n)
+    x = workloads.round_to_bf16(np.abs(rng.standard_normal((n, 512) + hw)).astype(np.float32))
+    params = []
+    workloads._walk(rng, [layer], 512, "bf16", params)
+    ref = oracle.forward([layer], params, x, mirror_bf16=True)
+    base = B.DR_FUSE_RELU | B.DR_FUSE_CONCAT
+    plain = run_net_bf16([layer], params, x, inception_mode=base)
+    for mode in (0, B.DR_CONCURRENT_BRANCHES, B.DR_FUSE_RELU, base, base | B.DR_CONCURRENT_BRANCHES):
+        got = run_net_bf16([layer], params, x, inception_mode=mode)
+        assert close(got, ref, TOL_BF16, "mode %d" % mode)
+        assert np.array_equal(got, plain), mode
+    from paper_1708_04728_amd import graph as G
+    xg = G.to_device(x, "bf16", nhwc=True)
+    net = B.Net(G.net_descs([layer], 512, inception_mode=base | B.DR_FUSE_STACK, pack="bf16"))
+    y = G.empty_like_desc(net.output_desc(B.desc(xg)))
+    ws = torch.empty(max(net.workspace_bytes(B.desc(xg)), 256), dtype=torch.uint8, device="cuda")
+    net.fwd(xg, G.stack_first_steps([layer], G.flat_params(params, "bf16", pack=True)), y, ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(G.to_host(y), plain)
