@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 
 import torch
 
@@ -109,14 +110,14 @@ _SIGNATURES = {
     "dr_conv2d_bwd_params": ([_P(dr_tensor), _vp, _P(dr_conv), _P(dr_tensor), _vp, _vp, _vp, _vp, _z, _vp], _i),
     "dr_sgd_step": ([_z, _vp, _vp, _f, _vp], _i),
     "dr_inception_workspace_bytes": ([_P(dr_tensor), _P(dr_inception), _P(_z)], _i),
-    "dr_inception_fwd": ([_P(dr_tensor), _vp, _P(dr_inception), _P(_vp), _P(_vp), _P(dr_tensor), _vp, _vp, _z, _vp], _i),
+    "dr_inception_fwd": ([_P(dr_tensor), _vp, _P(dr_inception), _vp, _vp, _P(dr_tensor), _vp, _vp, _z, _vp], _i),
     "dr_net_create": ([_P(dr_layer_desc), _i, _P(_vp)], _i),
     "dr_net_destroy": ([_vp], None),
     "dr_net_num_params": ([_vp, _P(_i)], _i),
     "dr_net_output_desc": ([_vp, _P(dr_tensor), _P(dr_tensor)], _i),
     "dr_net_workspace_bytes": ([_vp, _P(dr_tensor), _P(_z)], _i),
-    "dr_net_fwd": ([_vp, _P(dr_tensor), _vp, _P(_vp), _P(dr_tensor), _vp, _vp, _z, _vp], _i),
-    "dr_net_capture": ([_vp, _P(dr_tensor), _vp, _P(_vp), _P(dr_tensor), _vp, _vp, _z, _vp, _P(_vp)], _i),
+    "dr_net_fwd": ([_vp, _P(dr_tensor), _vp, _vp, _P(dr_tensor), _vp, _vp, _z, _vp], _i),
+    "dr_net_capture": ([_vp, _P(dr_tensor), _vp, _vp, _P(dr_tensor), _vp, _vp, _z, _vp, _P(_vp)], _i),
     "dr_capture_begin": ([_vp], _i),
     "dr_capture_end": ([_vp, _P(_vp)], _i),
     "dr_graph_launch": ([_vp, _vp], _i),
@@ -155,12 +156,14 @@ def last_error():
 
 
 # ---------------------------------------------------------------------------------- marshalling
+_DTYPES = {torch.float32: DR_F32, torch.bfloat16: DR_BF16}
+
+
 def _dtype_code(t):
-    if t.dtype == torch.float32:
-        return DR_F32
-    if t.dtype == torch.bfloat16:
-        return DR_BF16
-    raise TypeError("unsupported dtype %s" % t.dtype)
+    try:
+        return _DTYPES[t.dtype]
+    except KeyError:
+        raise TypeError("unsupported dtype %s" % t.dtype) from None
 
 
 class NHWC:
@@ -175,26 +178,55 @@ class NHWC:
         return getattr(self.t, name)
 
 
+# One call of a small network costs the host as much as it costs the GPU, so what every call marshals is kept lean: one shape
+# tuple per tensor, plain integers for pointers (ctypes converts them), and pointer arrays packed in one go.
+
 def desc(t):
     """dr_tensor of a contiguous torch tensor: 4-d (n, c, h, w), 2-d {n, c, 1, 1}, or NHWC(...)."""
     if isinstance(t, NHWC):
-        if not t.t.is_contiguous():
-            raise ValueError("tensor must be contiguous")
-        n, h, w, c = t.t.shape
-        return dr_tensor(n, c, h, w, _dtype_code(t.t), DR_NHWC)
+        t = t.t
+        n, h, w, c = t.shape
+        layout = DR_NHWC
+    else:
+        shape = t.shape
+        n, c, h, w = shape if len(shape) == 4 else (tuple(shape) + (1, 1, 1, 1))[:4]
+        layout = DR_NCHW
     if not t.is_contiguous():
         raise ValueError("tensor must be contiguous")
-    shape = tuple(t.shape) + (1,) * (4 - t.dim())
-    return dr_tensor(shape[0], shape[1], shape[2], shape[3], _dtype_code(t), DR_NCHW)
+    return dr_tensor(n, c, h, w, _dtype_code(t), layout)
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else (t.t if isinstance(t, NHWC) else t).data_ptr()
+
+
+_pack_pointers = {}                     # number of pointers -> struct.Struct("nQ").pack
+
+
+def _ptrs(ts):
+    """Host array of the tensors' device pointers (bytes, read during the call only); None -> NULL."""
+    n = len(ts)
+    pack = _pack_pointers.get(n)
+    if pack is None:
+        pack = _pack_pointers[n] = struct.Struct("%dQ" % n).pack
+    return pack(*[0 if t is None else t.data_ptr() for t in ts])
+
+
+def _nbytes(t):
+    return 0 if t is None else t.numel() * t.element_size()
+
+
+# the current stream's handle without building a Stream object, where this torch offers it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None and _device is not None and torch.cuda.is_initialized():
+        return _raw_stream(_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def conv_desc(k, c, r, s=None, stride=1, pad=0, relu=False, layout=DR_KCRS):
@@ -358,11 +390,7 @@ def inception_workspace_bytes(x, idesc):
 
 
 def inception_fwd(x, idesc, weights, biases, y, ws, stream=None):
-    nw = len(weights)
-    wp = (C.c_void_p * nw)(*[0 if w is None else w.data_ptr() for w in weights])
-    bp = (C.c_void_p * nw)(*[0 if b is None else b.data_ptr() for b in biases])
-    _check(lib().dr_inception_fwd(desc(x), _ptr(x), idesc, wp, bp, desc(y), _ptr(y), _ptr(ws),
-                                  0 if ws is None else ws.numel() * ws.element_size(), _stream(stream)))
+    _check(lib().dr_inception_fwd(desc(x), _ptr(x), idesc, _ptrs(weights), _ptrs(biases), desc(y), _ptr(y), _ptr(ws), _nbytes(ws), _stream(stream)))
     return y
 
 
@@ -474,18 +502,14 @@ class Net:
         return n.value
 
     def fwd(self, x, params, y, ws, stream=None):
-        pp = (C.c_void_p * max(len(params), 1))(*[p.data_ptr() for p in params])
-        _check(lib().dr_net_fwd(self._h, desc(x), _ptr(x), pp, desc(y), _ptr(y), _ptr(ws),
-                                0 if ws is None else ws.numel() * ws.element_size(), _stream(stream)))
+        _check(lib().dr_net_fwd(self._h, desc(x), _ptr(x), _ptrs(params), desc(y), _ptr(y), _ptr(ws), _nbytes(ws), _stream(stream)))
         return y
 
     def capture(self, x, params, y, ws, stream):
         """The forward for these tensors as a HIP graph (see dr_net_capture).  `stream`: a torch stream other than
         the default one, used for the capture only.  The tensors must outlive the returned Graph."""
-        pp = (C.c_void_p * max(len(params), 1))(*[p.data_ptr() for p in params])
         h = C.c_void_p()
-        _check(lib().dr_net_capture(self._h, desc(x), _ptr(x), pp, desc(y), _ptr(y), _ptr(ws),
-                                    0 if ws is None else ws.numel() * ws.element_size(), _stream(stream), C.byref(h)))
+        _check(lib().dr_net_capture(self._h, desc(x), _ptr(x), _ptrs(params), desc(y), _ptr(y), _ptr(ws), _nbytes(ws), _stream(stream), C.byref(h)))
         return Graph(h, (x, params, y, ws))
 
     def set_timing(self, enabled):
