@@ -196,7 +196,7 @@ int conv_run(const char* who, const dr_tensor& xd, const void* x, const dr_conv&
         return launch_conv_f32(g, (const float*)x, (const float*)w, bias, (const float*)residual, (float*)y, st, scratch, scratch_bytes);
     if (small && conv_bf16_small_takes(g, x, w)) {
         TraceScope trace("conv_bf16", &g, g.Ng, st);
-        const ConvSmall job{g, (const uint16_t*)x, (const uint16_t*)w, bias, (const uint16_t*)residual, (uint16_t*)y, nullptr};
+        const ConvSmall job{g, x, w, bias, residual, y, nullptr};
         return launch_conv_bf16_small(&job, 1, st);
     }
     return launch_conv_bf16(g, (const uint16_t*)x, (const uint16_t*)w, bias, (const uint16_t*)residual, (uint16_t*)y, st);
@@ -434,6 +434,13 @@ BranchStreams* branch_streams()
     return &pool;
 }
 
+// Layers the small-layer kernels take (a tensor without elements: none)
+bool small_takes(int dtype, const ConvGeom& g, const void* x, const void* w)
+{
+    if (g.Ng == 0) return false;
+    return dtype == DR_BF16 ? conv_bf16_small_takes(g, x, w) : conv_f32_small_takes(g, true);
+}
+
 // The stacked first steps of a module (see inception_run).  Marks the branches it has served in `stacked`
 // and leaves their step-0 outputs in `dst` (workspace buffers; NULL for a one-step branch that wrote y).
 // Serves nothing, without error, when the parameters are not laid out for it.  sp: destinations of the stacked layer; job
@@ -505,29 +512,30 @@ int run_stacked_first_steps(const dr_tensor& xd, const void* x, const dr_incepti
         stacked[members[i]] = true;
     }
     g.y_ctot = sp.dst[0].ctot; g.y_coff = sp.dst[0].c_offset;
+    const ConvSmall small{g, x, w0, (const float*)b0, nullptr, sp.dst[0].y, &sp};
+    if (job && small_takes(f32 ? DR_F32 : DR_BF16, g, x, w0)) { *job = small; return DR_OK; }
     if (f32)
         return launch_conv_f32(g, (const float*)x, (const float*)w0, (const float*)b0, nullptr, (float*)sp.dst[0].y, st, nullptr, 0, &sp);
-    const ConvSmall small{g, (const uint16_t*)x, (const uint16_t*)w0, (const float*)b0, nullptr, (uint16_t*)sp.dst[0].y, &sp};
-    const bool takes = conv_bf16_small_takes(g, x, w0);
-    if (takes && job) { *job = small; return DR_OK; }
     TraceScope trace("conv_bf16", &g, g.Ng, st);
-    if (takes) return launch_conv_bf16_small(&small, 1, st);
-    return launch_conv_bf16_dma(g, small.x, small.w, small.bias, nullptr, small.y, st, &sp);
+    if (conv_bf16_small_takes(g, x, w0)) return launch_conv_bf16_small(&small, 1, st);
+    return launch_conv_bf16_dma(g, (const uint16_t*)x, (const uint16_t*)w0, (const float*)b0, nullptr, (uint16_t*)sp.dst[0].y, st, &sp);
 }
 
-// A module of small bf16 layers, step by step instead of branch by branch: the convolutions at the same depth of the branches
+// A module of small layers, step by step instead of branch by branch: the convolutions at the same depth of the branches
 // (and a 3x3 pooling step beside them) are independent of one another and share launches of the small-layer kernel.
 // Steps that kernel does not take run one by one.  ReLU layers that the mode keeps apart and the concat remain kernels of
 // their own.
 struct SmallGroup {
     hipStream_t st;
+    int dtype;
     int n = 0;
     ConvSmall jobs[SMALL_GROUP_MAX];
     int flush()
     {
         const int k = n;
         n = 0;
-        return k ? launch_conv_bf16_small(jobs, k, st) : DR_OK;
+        if (!k) return DR_OK;
+        return dtype == DR_BF16 ? launch_conv_bf16_small(jobs, k, st) : launch_conv_f32_small(jobs, k, st);
     }
     int add(const ConvSmall& j)
     {
@@ -541,26 +549,26 @@ struct SmallGroup {
 bool small_pool_job(const dr_tensor& t, const void* x, const dr_tensor& o, void* y, const dr_pool& p, ConvSmall* job)
 {
     const long ng = (long)o.n * o.h * o.w;
-    if (p.kh != 3 || p.kw != 3 || t.c % 8 != 0 || (((uintptr_t)x | (uintptr_t)y) & 15) != 0 || ng == 0 || ng > 4096 || (long)o.h * o.w > 65536) return false;
+    if (t.dtype != DR_BF16 || p.kh != 3 || p.kw != 3 || t.c % 8 != 0 || (((uintptr_t)x | (uintptr_t)y) & 15) != 0 || ng == 0 || ng > 4096 || (long)o.h * o.w > 65536) return false;
     ConvGeom g{};
     g.N = t.n; g.C = g.K = t.c; g.H = t.h; g.W = t.w;
     g.R = g.S = 3; g.sh = p.stride_h; g.sw = p.stride_w; g.ph = p.pad_h; g.pw = p.pad_w;
     g.P = o.h; g.Q = o.w; g.Ng = (int)ng;
-    *job = ConvSmall{g, (const uint16_t*)x, nullptr, nullptr, nullptr, (uint16_t*)y, nullptr};
+    *job = ConvSmall{g, x, nullptr, nullptr, nullptr, y, nullptr};
     return true;
 }
 
 // How many convolutions of the module the small-layer kernel takes.
 int inception_small_steps(const dr_tensor& xd, const void* x, const dr_inception& d)
 {
-    if (xd.dtype != DR_BF16 || xd.layout != DR_NHWC) return 0;
+    if (xd.layout != (xd.dtype == DR_BF16 ? DR_NHWC : DR_NCHW)) return 0;
     int n = 0;
     for (int b = 0; b < d.n_branches; ++b) {
         dr_tensor t = xd;
         for (int s = 0; s < d.branches[b].n_steps; ++s) {
             const dr_step& stp = d.branches[b].steps[s];
             const dr_tensor o = stp.kind == DR_STEP_CONV ? conv_out(t, stp.conv) : pool_out(t, stp.pool);
-            if (stp.kind == DR_STEP_CONV && tensor_elems(o) && conv_bf16_small_takes(conv_geom(t, stp.conv, o), s == 0 ? x : nullptr, nullptr)) ++n;
+            if (stp.kind == DR_STEP_CONV && small_takes(xd.dtype, conv_geom(t, stp.conv, o), s == 0 ? x : nullptr, nullptr)) ++n;
             t = o;
         }
     }
@@ -573,7 +581,7 @@ int inception_run_levels(const dr_tensor& xd, const void* x, const dr_inception&
     const char* who = "dr_inception_fwd";
     const bool fuse_relu = d.mode & DR_FUSE_RELU, fuse_cat = d.mode & DR_FUSE_CONCAT;
     if (!x) return fail(DR_ERR_NULL, "%s: x is NULL", who);
-    SmallGroup group{st};
+    SmallGroup group{st, xd.dtype};
     void* stacked_dst[DR_MAX_BRANCHES] = {};
     bool stacked[DR_MAX_BRANCHES] = {};
     ConvSplit sp;
@@ -616,11 +624,13 @@ int inception_run_levels(const dr_tensor& xd, const void* x, const dr_inception&
                 if (!done) {
                     if (!w) return fail(DR_ERR_NULL, "%s: missing weights of branch %d step %d", who, b, s);
                     ConvGeom g = conv_geom(q.t, cd, o);
-                    if (tensor_elems(o) && conv_bf16_small_takes(g, q.cur, w)) {
+                    if (small_takes(xd.dtype, g, q.cur, w)) {
                         if (direct) { g.y_ctot = yd.c; g.y_coff = q.c_off; }
-                        DR_TRY(group.add(ConvSmall{g, (const uint16_t*)q.cur, (const uint16_t*)w, bias, nullptr, (uint16_t*)dst, nullptr}));
+                        DR_TRY(group.add(ConvSmall{g, q.cur, w, bias, nullptr, dst, nullptr}));
                     } else {
-                        DR_TRY(conv_run(who, q.t, q.cur, cd, w, bias, nullptr, 0, direct ? yd : o, dst, direct ? q.c_off : 0, st));
+                        const size_t sbytes = conv_scratch_bytes(q.t, cd);
+                        void* sc = sbytes ? ar.take(sbytes) : nullptr;
+                        DR_TRY(conv_run(who, q.t, q.cur, cd, w, bias, nullptr, 0, direct ? yd : o, dst, direct ? q.c_off : 0, st, 0, sc, sc ? sbytes : 0));
                     }
                     if (relu_after && !cd.relu) relus[n_relu++] = Relu{dst, tensor_elems(o)};
                 }
@@ -638,7 +648,7 @@ int inception_run_levels(const dr_tensor& xd, const void* x, const dr_inception&
             q.t = o;
         }
         DR_TRY(group.flush());
-        for (int i = 0; i < n_relu; ++i) DR_TRY(launch_relu(DR_BF16, relus[i].p, relus[i].p, relus[i].n, st));
+        for (int i = 0; i < n_relu; ++i) DR_TRY(launch_relu(xd.dtype, relus[i].p, relus[i].p, relus[i].n, st));
     }
     wts.i += param;
     bss.i += param;

@@ -313,7 +313,7 @@ SmallJob small_job(const ConvSmall& c, int bm, int bn, int nth)
 {
     const ConvGeom& g = c.g;
     SmallJob j{};
-    j.x = c.x; j.w = c.w; j.bias = c.bias; j.res = c.res;
+    j.x = (const uint16_t*)c.x; j.w = (const uint16_t*)c.w; j.bias = c.bias; j.res = (const uint16_t*)c.res;
     j.res_ctot = g.res_ctot;
     j.C = g.C; j.H = g.H; j.W = g.W; j.K = g.K; j.R = g.R; j.S = g.S; j.sh = g.sh; j.sw = g.sw; j.ph = g.ph; j.pw = g.pw;
     j.P = g.P; j.Q = g.Q; j.Kg = g.Kg; j.Ng = g.Ng; j.relu = g.relu;
@@ -322,7 +322,7 @@ SmallJob small_job(const ConvSmall& c, int bm, int bn, int nth)
     j.m_q = ((1ull << 40) + (unsigned)g.Q - 1) / (unsigned)g.Q;
     for (int d = 0; d < 3; ++d) j.split_end[d] = 0x7FFFFFFF;
     if (!c.w) {                                          // max-pooling
-        j.y_seg[0] = c.y;
+        j.y_seg[0] = (uint16_t*)c.y;
         j.tiles = (g.Ng * j.c8 + nth - 1) / nth;
         return j;
     }
@@ -354,7 +354,7 @@ SmallJob small_job(const ConvSmall& c, int bm, int bn, int nth)
             if (d + 1 < j.nsplit) j.split_end[d] = start;
         }
     } else {
-        dest(0, c.y, g.y_ctot, g.y_coff, 0);
+        dest(0, (uint16_t*)c.y, g.y_ctot, g.y_coff, 0);
     }
     return j;
 }

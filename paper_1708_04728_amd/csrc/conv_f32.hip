@@ -579,6 +579,10 @@ int launch_conv_f32(const ConvGeom& g, const float* x, const float* w, const flo
                     float* y, hipStream_t st, void* ws, size_t ws_bytes, const ConvSplit* split)
 {
     TraceScope trace("conv_f32", &g, g.Ng, st);
+    if (conv_f32_small_takes(g, ws != nullptr)) {
+        const ConvSmall job{g, x, w, bias, residual, y, split};
+        return launch_conv_f32_small(&job, 1, st);
+    }
     KArgs a;
     a.x = x; a.w = w; a.bias = bias; a.res = residual; a.y = y; a.g = g;
     a.grid_m = a.grid_n = 0;

@@ -58,6 +58,21 @@ int launch_conv_f32(const ConvGeom& g, const float* x, const float* w, const flo
 int launch_conv_bf16(const ConvGeom& g, const uint16_t* x, const uint16_t* w, const float* bias,
                      const uint16_t* residual, uint16_t* y, hipStream_t st);
 
+// conv_f32_small.hip, conv_bf16_small.hip: layers of few output pixels, several of them per launch (one data type each).  fp32: NCHW,
+// C % 16 == 0, KRSC filters or 1x1.  bf16: a convolution the streaming kernel takes or, with w = NULL, a 3x3 max-pooling
+// layer of channels-last tensors with C % 8 == 0 and 16-byte aligned pointers (g: its input, output and window).
+constexpr int SMALL_GROUP_MAX = 4;
+struct ConvSmall {
+    ConvGeom g;
+    const void *x, *w;
+    const float* bias;
+    const void* res;
+    void* y;
+    const ConvSplit* split;      // destinations of a stacked convolution, or NULL
+};
+bool conv_f32_small_takes(const ConvGeom& g, bool scratch);      // scratch: the caller can have the contraction cut over workgroups instead
+int launch_conv_f32_small(const ConvSmall* jobs, int n, hipStream_t st);
+
 // conv_bf16_dma.hip: the main bf16 kernel (NHWC, KRSC filters, C % 8 == 0, 16-byte aligned tensors)
 bool conv_bf16_dma_eligible(const ConvGeom& g, const void* x, const void* w);
 // Destinations of a stacked convolution (Eq. (12)): the first k filters write channels [c_offset, c_offset + k)
@@ -69,18 +84,6 @@ struct ConvSplit { int n; ConvDest dst[4]; };
 int launch_conv_bf16_dma(const ConvGeom& g, const uint16_t* x, const uint16_t* w, const float* bias,
                          const uint16_t* residual, uint16_t* y, hipStream_t st, const ConvSplit* split = nullptr);
 
-// conv_bf16_small.hip: layers of few output pixels, several of them per launch.  A job is a convolution the streaming kernel takes
-// (split as above, may be NULL) or, with w = NULL, a 3x3 max-pooling layer of channels-last bf16 tensors with C % 8 == 0 and
-// 16-byte aligned pointers (g: its input, output and window; y its output).
-constexpr int SMALL_GROUP_MAX = 4;
-struct ConvSmall {
-    ConvGeom g;
-    const uint16_t *x, *w;
-    const float* bias;
-    const uint16_t* res;
-    uint16_t* y;
-    const ConvSplit* split;
-};
 bool conv_bf16_small_takes(const ConvGeom& g, const void* x, const void* w);
 int launch_conv_bf16_small(const ConvSmall* jobs, int n, hipStream_t st);
 

@@ -1,0 +1,67 @@
+"""GPU parity of the small-layer fp32 convolution kernel (NCHW; the contraction of a 32 x 32 tile shared by the waves of a
+workgroup) against the fp64 oracle where it can go wrong: fewer slices than waves, ragged filters and pixels, every border and
+stride, both numbers of waves, the largest layer it takes and the first it does not; and a module whose branches share launches."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from paper_1708_04728_amd import binding as B
+from util import TOL_F32, case_seed, close, gpu, host
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("case", [
+    # N, C, H, W, K, R, S, stride, pad, packed
+    (1, 16, 3, 5, 8, 1, 1, 1, 0, False),         # one slice for eight waves
+    (1, 16, 9, 7, 33, 3, 3, 1, 1, True),         # nine slices, a second filter block of one filter
+    (2, 48, 13, 10, 100, 5, 5, 2, 2, True),      # stride 2, 75 slices, ragged pixels
+    (3, 32, 8, 8, 64, 3, 1, 1, 0, True),         # unequal filter sides, no padding
+    (1, 144, 6, 11, 40, 1, 1, 2, 0, False),      # strided 1x1 in KCRS order
+    (4, 32, 32, 32, 40, 1, 1, 1, 0, True),       # 1x1 at the largest pixel count
+    (2, 16, 64, 64, 64, 3, 3, 1, 1, True),       # 512 tiles: the most with eight waves
+    (2, 16, 64, 66, 64, 3, 3, 1, 1, True),       # four waves
+    (1, 16, 128, 176, 40, 3, 3, 1, 1, True),     # 1408 tiles, the largest layer
+    (1, 16, 128, 177, 40, 3, 3, 1, 1, True),     # one more pixel tile column than that: the 64 x 64 tiles
+    (1, 272, 4, 4, 24, 3, 3, 1, 1, True),        # few tiles, long contraction: cut over workgroups when scratch is given
+])
+def test_small_layer(case):
+    N, C, H, W, K, R, S, stride, pad, packed = case
+    rng = np.random.default_rng(case_seed(case))
+    x = rng.standard_normal((N, C, H, W)).astype(np.float32)
+    w = (rng.standard_normal((K, C, R, S)) * np.sqrt(2.0 / (C * R * S))).astype(np.float32)
+    xg, wg = gpu(x), gpu(w)
+    if packed:
+        wg = B.pack_filters(wg)
+    for bias, relu in ((True, True), (False, False)):
+        b = (rng.standard_normal(K) * 0.1).astype(np.float32) if bias else None
+        ref = oracle.conv2d(x, w, b, stride, pad, relu)
+        cd = B.conv_desc(K, C, R, S, stride, pad, relu, B.DR_KRSC if packed else B.DR_KCRS)
+        y = torch.full(ref.shape, float("nan"), device="cuda")
+        need = B.conv2d_workspace_bytes(xg, cd)
+        for ws in (None, torch.empty(need, dtype=torch.uint8, device="cuda")) if need else (None,):
+            if ws is None:
+                B.conv2d_fwd(xg, cd, wg, None if b is None else gpu(b), y)
+            else:
+                B.conv2d_fwd_ws(xg, cd, wg, None if b is None else gpu(b), y, ws)
+            torch.cuda.synchronize()
+            assert close(host(y), ref, TOL_F32)
+
+
+@pytest.mark.parametrize("form", ["original", "slim"])
+def test_module_whose_branches_share_launches(form):
+    """A module on two ragged maps in every mode, packed filters, channel ranges of the output, stacked first steps."""
+    from test_gpu_blocks import _run_stacked, run_inception
+    layer = (workloads.inception_original if form == "original" else workloads.inception_slim)("4e")
+    rng = np.random.default_rng(23)
+    x = np.abs(rng.standard_normal((2, 528, 13, 15))).astype(np.float32)
+    params = []
+    workloads._walk(rng, [layer], 528, "f32", params)
+    ref = oracle.forward([layer], params, x)
+    base = B.DR_FUSE_RELU | B.DR_FUSE_CONCAT
+    for mode in (0, B.DR_CONCURRENT_BRANCHES, B.DR_FUSE_RELU, base):
+        assert close(run_inception(layer, params, x, mode, pack=True), ref, TOL_F32, "mode %d" % mode)
+    for mode in (base | B.DR_FUSE_STACK, B.DR_FUSE_RELU | B.DR_FUSE_STACK):
+        assert close(_run_stacked(layer, params, x, mode, True), ref, TOL_F32, "mode %d" % mode)
