@@ -29,7 +29,9 @@
 //        covers the small-channel first layers this path is for); an element's k is the same for a
 //        whole wave, so its table entry arrives by one broadcast LDS read and the lane adds its
 //        pixel's base offset; with padding it also tests the (r, s) bits of two per-lane masks of
-//        valid window rows and columns.  Longer contractions decode (c, r, s) per element.
+//        valid window rows and columns.  Filters of at most 31 taps use one word per entry (offset and tap) and one
+//        per-lane mask of taps, for contractions of up to KTAB1 elements (3x3 64 -> 192 at stride 2 on 56 x 56 x 32, which
+//        decoded (c, r, s) element by element before: 81 -> 69 us).  Longer contractions decode (c, r, s) per element.
 //        Without padding and with a filter width S that rounds up to a multiple of 4 cheaply (11 -> 12,
 //        7 -> 8), k instead runs over (c, r, groups of 4 taps): the four activations of a group are
 //        neighbours in memory and arrive by one 16-byte load per lane (consecutive pixels at stride 4
@@ -54,7 +56,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int NT = 256;       // threads per workgroup
-constexpr int KTAB = 512;     // CF = false: contraction elements (or groups of 4 taps) whose table entries fit the 4 KB LDS table
+constexpr int KTAB = 512;     // CF = false: contraction elements (or groups of 4 taps) whose two-word table entries are used
+constexpr int KTAB1 = 2048;   // CF = false, at most 31 taps: elements whose one-word entries fit the LDS table (8 KB)
 
 struct KArgs {
     const float* x;
@@ -100,8 +103,11 @@ __device__ __forceinline__ float buf_load(__amdgpu_buffer_rsrc_t r, int voff, in
 // in slices; CF: slice order (see above); FR, FS: compile-time filter size for CF = false (0 = taken
 // from the geometry at run time); SPLIT: the workgroup takes range blockIdx.y of the contraction and
 // stores raw partial sums.
+// The tile is computed by workgroup `block` of the layer's grid_m grid_n.  The LDS arrays (two buffers of BM resp. BN rows, the
+// table of CF = false) are separate objects of the kernel: carved out of one array, the compiler orders every read of one
+// operand behind the writes of the other (20 % slower).
 template <int BM, int BN, int WGM, int WGN, int BK, int PF, bool CF, int FR, int FS, bool SPLIT>
-__global__ __launch_bounds__(NT) void conv_f32_kernel(const KArgs a)
+__device__ __forceinline__ void conv_f32_tile(const KArgs a, const int block, float (*const As)[BM * (BK + 4)], float (*const Bs)[BN * (BK + 4)], int* const ktab)
 {
     constexpr int WM = BM / WGM, WN = BN / WGN;   // wave tile
     constexpr int TM = WM / 32, TN = WN / 32;     // 32x32 MFMA tiles per wave
@@ -118,10 +124,6 @@ __global__ __launch_bounds__(NT) void conv_f32_kernel(const KArgs a)
     static_assert(B_F4 % NT == 0, "BN * BK must be a multiple of 1024");
     static_assert(BN <= NT && NT % BN == 0, "one n per thread");
 
-    __shared__ __attribute__((aligned(16))) float As[2][BM * LDT];
-    __shared__ __attribute__((aligned(16))) float Bs[2][BN * LDT];
-    __shared__ __attribute__((aligned(16))) int ktab[CF ? 4 : 2 * KTAB];   // CF = false: {byte offset, r | s << 8} per k
-
     const ConvGeom& g = a.g;
     const int R = FR ? FR : g.R, S = FS ? FS : g.S;
     const int RS = R * S;
@@ -133,7 +135,7 @@ __global__ __launch_bounds__(NT) void conv_f32_kernel(const KArgs a)
     // Workgroup -> tile.  Consecutive workgroup ids are dealt round-robin to the 8 XCDs; the remap
     // gives each XCD a contiguous range of tiles (m fastest), so the tiles that share an input
     // region share an L2.
-    int bid = blockIdx.x;
+    int bid = block;
     const int nblk = a.grid_m * a.grid_n;
     if (nblk % 8 == 0) bid = (bid & 7) * (nblk >> 3) + (bid >> 3);
     const int m0 = (bid % a.grid_m) * BM;
@@ -168,10 +170,28 @@ __global__ __launch_bounds__(NT) void conv_f32_kernel(const KArgs a)
     const int S4 = (S + 3) & ~3;
     const int kg_eff = rg ? g.C * R * S4 : g.Kg;     // contraction length including the taps added by rounding S up
     const int ktab_n = (kg_eff + BK - 1) / BK * BK;
-    const bool use_tab = !CF && !rg && ktab_n <= KTAB && R <= 31 && S <= 31;
+    const bool use_tab1 = !CF && !rg && RS <= 31 && ktab_n <= KTAB1 && (long)g.C * HW < (1l << 26);
+    const bool use_tab = !CF && !rg && !use_tab1 && ktab_n <= KTAB && R <= 31 && S <= 31;
     const bool nopad = g.ph == 0 && g.pw == 0;      // then every window lies inside the image
     unsigned rowmask = 0, colmask = 0;
+    unsigned tap_out = 0xFFFFFFFFu;                  // (one-word table) bit r S + s: that tap lies outside the image; bits beyond: set
     if constexpr (!CF) {
+        if (use_tab1) {
+            // one word per k: (offset of x[0][c][r][s] in elements) << 5 | tap, tap 31 beyond the contraction
+            for (int k = tid; k < ktab_n; k += NT) {
+                int e = 31;
+                if (k < g.Kg) {
+                    const int c = k / RS, rs = k - c * RS, r = rs / S;
+                    e = (c * HW + r * g.W + rs - r * S) << 5 | rs;
+                }
+                ktab[k] = e;
+            }
+            if (n_ok)
+                for (int r = 0, bit = 0; r < R; ++r)
+                    for (int s_ = 0; s_ < S; ++s_, ++bit)
+                        if ((unsigned)(ih0 + r) < (unsigned)g.H && (unsigned)(iw0 + s_) < (unsigned)g.W) tap_out &= ~(1u << bit);
+            lds_barrier();                            // the table is complete before the first slice is gathered
+        }
         if (use_tab) {
             for (int k = tid; k < ktab_n; k += NT) {
                 int off = OOB, rs_bits = 31;          // beyond the contraction: the load returns 0 (mask bit 31 is never set)
@@ -205,7 +225,7 @@ __global__ __launch_bounds__(NT) void conv_f32_kernel(const KArgs a)
             lds_barrier();
         }
     }
-    const int bbase = n_ok ? xoff0 * 4 : OOB;        // (table path) byte offset of this lane's window origin
+    const int bbase = n_ok ? xoff0 * 4 : OOB;        // (table paths) byte offset of this lane's window origin
 
     // ---- per-thread state for A: rows f / KQ of the slice, byte offset of the row start
     const bool vecA = (g.Kg & 3) == 0;
@@ -312,7 +332,20 @@ __global__ __launch_bounds__(NT) void conv_f32_kernel(const KArgs a)
                     ra[SET][i] = v;
                 }
             }
-            if (use_tab) {
+            if (use_tab1) {
+                typedef int i32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+                for (int i = 0; i < B_PER; ++i) {
+                    const i32x4 e = *reinterpret_cast<const i32x4*>(&ktab[k0 + (bkq0 + i * BKQ_STEP) * 4]);   // the same for the whole wave
+                    f32x4 v;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int vo = bbase + ((int)((unsigned)e[j] >> 5) << 2);
+                        v[j] = buf_load(rx, (int)((tap_out >> (e[j] & 31)) << 31) | vo, 0);     // a tap outside: sign bit set, beyond the buffer
+                    }
+                    rb[SET][i] = v;
+                }
+            } else if (use_tab) {
 #pragma unroll
                 for (int i = 0; i < B_PER; ++i) {
                     const int gk = k0 + (bkq0 + i * BKQ_STEP) * 4;            // the same for the whole wave
@@ -458,6 +491,35 @@ __global__ __launch_bounds__(NT) void conv_f32_kernel(const KArgs a)
     }
 }
 
+template <int BM, int BN, int WGM, int WGN, int BK, int PF, bool CF, int FR, int FS, bool SPLIT>
+__global__ __launch_bounds__(NT) void conv_f32_kernel(const KArgs a)
+{
+    __shared__ __attribute__((aligned(16))) float As[2][BM * (BK + 4)];
+    __shared__ __attribute__((aligned(16))) float Bs[2][BN * (BK + 4)];
+    __shared__ __attribute__((aligned(16))) int ktab[CF ? 4 : KTAB1];   // CF = false: {byte offset, r | s << 8} per k
+    conv_f32_tile<BM, BN, WGM, WGN, BK, PF, CF, FR, FS, SPLIT>(a, (int)blockIdx.x, As, Bs, ktab);
+}
+
+// Several layers in one launch (KRSC filters or 1x1; each with the tile it would have by itself): the layers' tiles fill the device
+// together, where each by itself ends in a round that leaves most compute units idle.
+struct GroupArgs {
+    int n;
+    int first[SMALL_GROUP_MAX];                   // first workgroup of each layer
+    int rows32[SMALL_GROUP_MAX];                  // 32 x 128 tiles instead of 64 x 64
+    KArgs job[SMALL_GROUP_MAX];
+};
+__global__ __launch_bounds__(NT) void conv_f32_group_kernel(const GroupArgs args)
+{
+    __shared__ __attribute__((aligned(16))) float As[2 * 64 * 20];
+    __shared__ __attribute__((aligned(16))) float Bs[2 * 128 * 20];
+    int ji = 0;
+    while (ji + 1 < args.n && (int)blockIdx.x >= args.first[ji + 1]) ++ji;
+    const KArgs a = args.job[ji];
+    const int block = (int)blockIdx.x - args.first[ji];
+    if (args.rows32[ji]) conv_f32_tile<32, 128, 1, 4, 16, 2, true, 0, 0, false>(a, block, (float (*)[32 * 20])As, (float (*)[128 * 20])Bs, nullptr);
+    else conv_f32_tile<64, 64, 2, 2, 16, 2, true, 0, 0, false>(a, block, (float (*)[64 * 20])As, (float (*)[64 * 20])Bs, nullptr);
+}
+
 // y = bias + residual + sum over the ranges of a split contraction, ReLU: one thread per output element,
 // consecutive threads along n (these layers are small: what counts is the number of loads in flight).
 __global__ __launch_bounds__(256) void conv_f32_reduce_kernel(const float* __restrict__ part, int splits, ConvGeom g,
@@ -500,7 +562,7 @@ template <int BK>
 int contraction_slices(const ConvGeom& g, int* row_groups)
 {
     *row_groups = 0;
-    if (g.w_krsc) return g.R * g.S * (g.C / BK);
+    if (g.C % BK == 0 && (g.w_krsc || g.R * g.S == 1)) return g.R * g.S * (g.C / BK);
     const int S4 = (g.S + 3) & ~3;
     const long kg4 = (long)g.C * g.R * S4;
     if (g.ph == 0 && g.pw == 0 && S4 * 4 <= g.S * 5 && (kg4 + BK - 1) / BK * BK <= 4 * KTAB) {
@@ -546,7 +608,7 @@ int launch_tile(const KArgs& base, void* ws, size_t ws_bytes, hipStream_t st)
         if (a.part) hipLaunchKernelGGL((conv_f32_kernel<BM, BN, WGM, WGN, BK, PF, CF, FR, FS, true>), grid, block, 0, st, a);   \
         else hipLaunchKernelGGL((conv_f32_kernel<BM, BN, WGM, WGN, BK, PF, CF, FR, FS, false>), grid, block, 0, st, a);         \
     } while (0)
-    if (a.w_krsc) DR_LAUNCH(true, 0, 0);
+    if (a.g.C % BK == 0 && (a.w_krsc || R * S == 1)) DR_LAUNCH(true, 0, 0);      // (a 1x1 filter bank is the same array in both orders)
     else if (R == 1 && S == 1) DR_LAUNCH(false, 1, 1);
     else if (R == 3 && S == 3) DR_LAUNCH(false, 3, 3);
     else if (R == 5 && S == 5) DR_LAUNCH(false, 5, 5);
@@ -568,24 +630,15 @@ int launch_tile(const KArgs& base, void* ws, size_t ws_bytes, hipStream_t st)
 
 }  // namespace
 
-size_t conv_f32_scratch_bytes(const ConvGeom& g)
+// Destinations of a (stacked) layer, tensor sizes.
+static KArgs base_args(const ConvGeom& g, const float* x, const float* w, const float* bias, const float* residual, float* y, const ConvSplit* split)
 {
-    const bool rows32 = (g.K + 31) / 32 * 32 < (g.K + 63) / 64 * 64;
-    if (g.w_krsc && g.C % 32 == 0) return rows32 ? split_bytes<32, 128, 32>(g) : split_bytes<64, 64, 32>(g);
-    return rows32 ? split_bytes<32, 128, 16>(g) : split_bytes<64, 64, 16>(g);
-}
-
-int launch_conv_f32(const ConvGeom& g, const float* x, const float* w, const float* bias, const float* residual,
-                    float* y, hipStream_t st, void* ws, size_t ws_bytes, const ConvSplit* split)
-{
-    TraceScope trace("conv_f32", &g, g.Ng, st);
-    if (conv_f32_small_takes(g, ws != nullptr)) {
-        const ConvSmall job{g, x, w, bias, residual, y, split};
-        return launch_conv_f32_small(&job, 1, st);
-    }
     KArgs a;
     a.x = x; a.w = w; a.bias = bias; a.res = residual; a.y = y; a.g = g;
     a.grid_m = a.grid_n = 0;
+    a.row_groups = 0;
+    a.part = nullptr;
+    a.splits = a.slices_per_split = 0;
     a.nsplit = 0;
     for (int d = 0; d < 4; ++d) { a.y_seg[d] = nullptr; a.ctot_seg[d] = 0; if (d < 3) a.split_end[d] = 0x7FFFFFFF; }
     if (split && split->n > 1) {
@@ -600,19 +653,72 @@ int launch_conv_f32(const ConvGeom& g, const float* x, const float* w, const flo
             if (d < 3 && d + 1 < split->n) a.split_end[d] = start;
         }
     }
+    a.x_bytes = (int)((size_t)g.N * g.C * g.H * g.W * 4);
+    a.w_bytes = (int)((size_t)g.K * g.Kg * 4);
+    a.w_krsc = g.w_krsc;
+    return a;
+}
+
+// 32-row tiles when they pad the filter count less than 64-row tiles (16, 32, 96 filters ...), else 64 x 64 tiles
+static bool rows_of_32(const ConvGeom& g) { return (g.K + 31) / 32 * 32 < (g.K + 63) / 64 * 64; }
+
+// Depth of a slice: 32 channels where the count allows, which halves the barriers; 16 for 1x1 filters (short contractions; the
+// same depth whatever the number of filters, so that stacked filter banks keep their sums) and for layers of more 64 x 64
+// tiles than the device holds at 32 (four workgroups per compute unit, seven at 16: 3x3 64 -> 192 on 28 x 28 x 32, 1176
+// tiles, 65 -> 56 us).
+static bool slices_of_32(const ConvGeom& g)
+{
+    return g.w_krsc && g.C % 32 == 0 && g.R * g.S > 1 && (rows_of_32(g) || ((long)g.K + 63) / 64 * (((long)g.Ng + 63) / 64) <= 4 * device_cus());
+}
+
+bool conv_f32_group_takes(const ConvGeom& g)
+{
+    const size_t xb = (size_t)g.N * g.C * g.H * g.W * 4, wb = (size_t)g.K * g.Kg * 4;
+    return !g.nhwc && g.w_krsc && g.C % 16 == 0 && xb < (1ull << 31) && wb < (1ull << 31) && g.Ng > 0;
+}
+
+int launch_conv_f32_group(const ConvSmall* jobs, int n, hipStream_t st)
+{
+    GroupArgs a{};
+    a.n = n;
+    int order[SMALL_GROUP_MAX], blocks = 0;
+    for (int i = 0; i < n; ++i) order[i] = i;
+    std::sort(order, order + n, [&](int p, int q) { return jobs[p].g.Kg > jobs[q].g.Kg; });      // the longest tiles first
+    for (int i = 0; i < n; ++i) {
+        const ConvSmall& c = jobs[order[i]];
+        a.job[i] = base_args(c.g, (const float*)c.x, (const float*)c.w, c.bias, (const float*)c.res, (float*)c.y, c.split);
+        a.rows32[i] = rows_of_32(c.g);
+        a.job[i].grid_m = a.rows32[i] ? (c.g.K + 31) / 32 : (c.g.K + 63) / 64;
+        a.job[i].grid_n = a.rows32[i] ? (c.g.Ng + 127) / 128 : (c.g.Ng + 63) / 64;
+        a.first[i] = blocks;
+        blocks += a.job[i].grid_m * a.job[i].grid_n;
+    }
+    hipLaunchKernelGGL(conv_f32_group_kernel, dim3((unsigned)blocks), dim3(NT), 0, st, a);
+    return check_launch("conv_f32_group");
+}
+
+size_t conv_f32_scratch_bytes(const ConvGeom& g)
+{
+    if (slices_of_32(g)) return rows_of_32(g) ? split_bytes<32, 128, 32>(g) : split_bytes<64, 64, 32>(g);
+    return rows_of_32(g) ? split_bytes<32, 128, 16>(g) : split_bytes<64, 64, 16>(g);
+}
+
+int launch_conv_f32(const ConvGeom& g, const float* x, const float* w, const float* bias, const float* residual,
+                    float* y, hipStream_t st, void* ws, size_t ws_bytes, const ConvSplit* split)
+{
+    TraceScope trace("conv_f32", &g, g.Ng, st);
+    if (conv_f32_small_takes(g, ws != nullptr)) {
+        const ConvSmall job{g, x, w, bias, residual, y, split};
+        return launch_conv_f32_small(&job, 1, st);
+    }
     const size_t xb = (size_t)g.N * g.C * g.H * g.W * 4, wb = (size_t)g.K * g.Kg * 4;
     if (xb >= (1ull << 31) || wb >= (1ull << 31))
         return fail(DR_ERR_UNSUPPORTED, "conv_f32: input (%zu bytes) or filter tensor (%zu bytes) is 2 GiB or larger", xb, wb);
-    a.x_bytes = (int)xb; a.w_bytes = (int)wb;
-    a.w_krsc = g.w_krsc;
-    // Tile choice (from sweeps on the inception / streamline shapes): 32-row tiles when they pad the
-    // filter count less than 64-row tiles (16, 32, 96 filters ...), else 64 x 64 tiles; both give the
-    // grid several workgroups per compute unit, which matters more here than operand reuse.  The
-    // deepest slice the channel count allows, two slices of prefetch.
-    const bool rows32 = (g.K + 31) / 32 * 32 < (g.K + 63) / 64 * 64;
-    if (g.w_krsc && g.C % 32 == 0)      // (32-deep slices with the groups-of-4-taps order: measured 10 % slower)
-        return rows32 ? launch_tile<32, 128, 1, 4, 32, 2>(a, ws, ws_bytes, st) : launch_tile<64, 64, 2, 2, 32, 2>(a, ws, ws_bytes, st);
-    return rows32 ? launch_tile<32, 128, 1, 4, 16, 2>(a, ws, ws_bytes, st) : launch_tile<64, 64, 2, 2, 16, 2>(a, ws, ws_bytes, st);
+    const KArgs a = base_args(g, x, w, bias, residual, y, split);
+    // (32-deep slices with the groups-of-4-taps order: measured 10 % slower)
+    if (slices_of_32(g))
+        return rows_of_32(g) ? launch_tile<32, 128, 1, 4, 32, 2>(a, ws, ws_bytes, st) : launch_tile<64, 64, 2, 2, 32, 2>(a, ws, ws_bytes, st);
+    return rows_of_32(g) ? launch_tile<32, 128, 1, 4, 16, 2>(a, ws, ws_bytes, st) : launch_tile<64, 64, 2, 2, 16, 2>(a, ws, ws_bytes, st);
 }
 
 }  // namespace dr

@@ -62,7 +62,7 @@ __global__ __launch_bounds__(NW * 64) void conv_f32_small_kernel(const SmallArgs
     // the job and the tile; a die (workgroup id & 7) takes a contiguous range of tiles, filter block by filter block
     int ji = 0;
     while (ji + 1 < args.n && (int)blockIdx.x >= args.job[ji + 1].first) ++ji;
-    const SmallJobF& j = args.job[ji];
+    const SmallJobF j = args.job[ji];
     const int b = (int)blockIdx.x - j.first, die = b & 7, s_die = b >> 3, per = j.tiles >> 3, odd = j.tiles & 7;
     if (s_die >= per + (die < odd ? 1 : 0)) return;
     const int t = die * per + min(die, odd) + s_die;

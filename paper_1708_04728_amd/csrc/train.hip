@@ -4,16 +4,19 @@
 //
 //   regression_loss_grad   dz = 2 (f - y) where f > 0 else 0,  L = sum (f - y)^2
 //   conv_wgrad             dw[k][c,r,s] = sum_{n,p,q} dz[n,k,p,q] x[n,c,p*sh+r-ph,q*sw+s-pw],  db[k] = sum dz[n,k,p,q]
-//                          (db is column C*R*S of the same GEMM: the gathered operand is 1 there)
+//                          (db: the row sums of the GEMM's first operand, kept by the first column tile's workgroups)
 //   sgd_step               w -= lr * dw
 //
-// The weight gradient is a GEMM  D[m][n] = sum_l A[m][l] B[l][n]  with m = filter, n = (c, r, s) and the
+// The weight gradient is a GEMM  D[m][n] = sum_l A[m][l] B[l][n]  with m = filter, n = (tap, channel) and the
 // contraction over l = (image, p, q): A is dz (for one image and filter the (p, q) run is contiguous), B is
-// gathered from x.  A workgroup owns a 64 x 64 tile of D for a range of images, stages 32 l at a time in LDS
-// (l contiguous per row, rows padded by 4 floats) and multiplies with v_mfma_f32_32x32x2_f32, each lane half
-// taking 16 consecutive l of the slice so that an operand is four 128-bit LDS reads.  The ranges of images
+// gathered from x.  A workgroup owns a 64 x 64 tile of D for a range of slices of 32 l (each inside one image), stages
+// a slice at a time in LDS (l contiguous per row, rows padded by 4 floats) and multiplies with v_mfma_f32_32x32x2_f32,
+// each lane half taking 16 consecutive l of the slice so that an operand is four 128-bit LDS reads.  The ranges
 // give enough workgroups to fill the device; their partial sums go to workspace and are added in a fixed
 // order by a second kernel, so the result does not depend on scheduling.
+#include <algorithm>
+#include <type_traits>
+
 #include "dr_internal.h"
 
 namespace dr {
@@ -94,83 +97,124 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const float* __restri
 struct WArgs {
     const float* x;
     const float* dz;
-    float* out;            // the partial sums [splits][K][CRS + 1] (splits > 1), else unused
+    float* out;            // the partial sums [splits][K][cols], then those of the bias gradient [splits][K] (splits > 1)
     float* dw;             // splits == 1: the results themselves
     float* db;             // (may be NULL)
     int N, C, H, W, K, R, S, sh, sw, ph, pw, P, Q;
-    int CRS, grid_m, grid_n, splits, imgs_per_split;    // the GEMM has CRS + 1 columns: column CRS is db
+    int CRS, grid_m, grid_n, splits, slices_per_img, slices;
+    int cb_log2, cblocks, cols;                         // channels per column tile; channel blocks; columns of the partial sums (grid_n BN)
     int x_bytes, dz_bytes;
 };
 
 constexpr int BM = 64, BN = 64, BL = 32, LDT = BL + 4;
 
+// dw[m][c R S + rs] of column `col`: tile col / BN holds 64 >> cb_log2 taps x (1 << cb_log2) channels; -1 for padding
+__device__ __forceinline__ int wgrad_column(int col, int C, int RS, int cb_log2, int cblocks)
+{
+    const int nt = col / BN, l = col % BN, tg = nt / cblocks, cblk = nt - tg * cblocks;
+    const int rs = tg * (BN >> cb_log2) + (l >> cb_log2), c = (cblk << cb_log2) + (l & ((1 << cb_log2) - 1));
+    return rs < RS && c < C ? c * RS + rs : -1;
+}
+
+// Barrier that orders LDS traffic only (the global loads of the next slices stay in flight across it).
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// TPT: taps per column tile (64 channels of one tap, 32 of two, 16 of four).  Bound by the fp32 matrix cores; what the loop adds to the
+// 16 matrix instructions of a slice is kept to a couple of instructions per loaded element: a thread's eight columns
+// belong to TPT taps, so the padding test is made TPT times per slice (with columns in (c, r, s) order it was made for every
+// element and that arithmetic took longer than the multiplications), the rest of an address is a per-thread constant, and
+// (p, q) advances by addition.  Two LDS buffers, one barrier per slice, loads two slices ahead.  3x3 64 -> 192 at stride 2 on
+// 56 x 56 x 32 images: 118 -> 71 us (78 TFLOP/s).
+template <int TPT>
 __global__ __launch_bounds__(256) void conv_wgrad_f32_kernel(const WArgs a)
 {
-    __shared__ __attribute__((aligned(16))) float As[BM * LDT];
-    __shared__ __attribute__((aligned(16))) float Bs[BN * LDT];
+    __shared__ __attribute__((aligned(16))) float As[2][BM * LDT];
+    __shared__ __attribute__((aligned(16))) float Bs[2][BN * LDT];
+    constexpr int CB = BN / TPT, IPT = 8 / TPT;            // channels per tile; a thread's columns per tap
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1, half = lane >> 5, l32 = lane & 31;
-    int bid = blockIdx.x;
+    // workgroup b runs on die b & 7: a die takes a contiguous range of (split, column tile, row tile), so that the tiles of one
+    // range of slices read x and dz through one L2
+    const int die = blockIdx.x & 7, share = (int)gridDim.x >> 3, odd = gridDim.x & 7;
+    int bid = die * share + min(die, odd) + (int)(blockIdx.x >> 3);
     const int mt = bid % a.grid_m; bid /= a.grid_m;
     const int nt = bid % a.grid_n, sp = bid / a.grid_n;
-    const int m0 = mt * BM, n0 = nt * BN;
-    const int img_lo = sp * a.imgs_per_split, img_hi = min(a.N, img_lo + a.imgs_per_split);
-    const int PQ = a.P * a.Q, HW = a.H * a.W;
+    const int m0 = mt * BM;
+    const int lo = (int)((long)a.slices * sp / a.splits), total = (int)((long)a.slices * (sp + 1) / a.splits) - lo;
+    const int PQ = a.P * a.Q, HW = a.H * a.W, RS = a.R * a.S;
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)a.x, 0, a.x_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rz = __builtin_amdgcn_make_buffer_rsrc((void*)a.dz, 0, a.dz_bytes, 0x00020000);
 
-    // loader: this thread fetches l = tid % 32 of the slice for rows tid / 32 + 8 i of both tiles
+    // loader: this thread fetches element l = tid % 32 of the slice for rows tid / 32 + 8 i of both tiles.  A row or column that
+    // does not exist has the offset OOB; whatever is then read belongs to an output that is not stored.
     const int ll = tid & 31, row0 = tid >> 5;
-    int a_off[8];                 // dz: element offset of (image 0, filter m0 + row, pq 0) or OOB
-    int b_off[8], b_r[8], b_s[8]; // x: element offset of (image 0, c, r - ph, s - pw) and the tap, or OOB
+    const int tg = nt / a.cblocks, c0 = (nt - tg * a.cblocks) * CB;
+    int a_row[8], b_row[8], tap_r[TPT], tap_s[TPT];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        const int m = m0 + row0 + 8 * i;
-        a_off[i] = m < a.K ? m * PQ : OOB;
-        const int n = n0 + row0 + 8 * i;
-        if (n < a.CRS) {
-            const int c = n / (a.R * a.S), rs = n - c * a.R * a.S, r = rs / a.S, s = rs - r * a.S;
-            b_off[i] = c * HW + (r - a.ph) * a.W + (s - a.pw);
-            b_r[i] = r - a.ph; b_s[i] = s - a.pw;
-        } else {
-            b_off[i] = OOB; b_r[i] = n == a.CRS ? 1 : 0; b_s[i] = 0;      // b_r = 1: the column of ones (bias gradient)
-        }
+        const int m = m0 + row0 + 8 * i, c = c0 + row0 + 8 * (i % IPT);
+        a_row[i] = m < a.K ? m * PQ * 4 : OOB;
+        b_row[i] = c < a.C && tg * TPT + i / IPT < RS ? c * HW * 4 : OOB;
     }
-    const int slices_per_img = (PQ + BL - 1) / BL;
-    const int total = (img_hi - img_lo) * slices_per_img;
-
-    float ra[8], rb[8];
-    auto fetch = [&](int sl) __attribute__((always_inline)) {
-        const int img = img_lo + sl / slices_per_img, pq = (sl % slices_per_img) * BL + ll;
-        const bool l_on = pq < PQ;
-        const int p = pq / a.Q, q = pq - p * a.Q;
-        const int ih0 = p * a.sh, iw0 = q * a.sw;
-        const int xo = ih0 * a.W + iw0;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int ao = (l_on && a_off[i] != OOB) ? (a_off[i] + pq) * 4 : OOB;
-            ra[i] = buf_load(rz, ao, img * a.K * PQ * 4);
-            const bool in = l_on && b_off[i] != OOB && (unsigned)(ih0 + b_r[i]) < (unsigned)a.H && (unsigned)(iw0 + b_s[i]) < (unsigned)a.W;
-            rb[i] = buf_load(rx, in ? (b_off[i] + xo) * 4 : OOB, img * a.C * HW * 4);
-            if (b_off[i] == OOB && b_r[i] == 1 && l_on) rb[i] = 1.f;
+    for (int t = 0; t < TPT; ++t) {
+        const int rs = tg * TPT + t, r = rs / a.S;
+        tap_r[t] = r - a.ph; tap_s[t] = rs - r * a.S - a.pw;
+    }
+    // the slice being fetched: image, first (p, q) run element and this thread's own
+    int img = lo / a.slices_per_img, left = a.slices_per_img - (lo - img * a.slices_per_img);   // slices left in the image
+    const int p_ll = ll / a.Q, q_ll = ll - p_ll * a.Q, step_p = BL / a.Q, step_q = BL - step_p * a.Q;
+    int pq = (a.slices_per_img - left) * BL + ll, p = pq / a.Q, q = pq - p * a.Q;
+    float ra[2][8], rb[2][8];
+    auto fetch = [&](auto set_c) __attribute__((always_inline)) {
+        constexpr int SET = decltype(set_c)::value;
+        const bool on = pq < PQ;
+        const int za = on ? pq * 4 : OOB, soff_a = img * a.K * PQ * 4, soff_b = img * a.C * HW * 4;
+        const int ih0 = p * a.sh, iw0 = q * a.sw;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) ra[SET][i] = buf_load(rz, a_row[i] + za, soff_a);
+#pragma unroll
+        for (int t = 0; t < TPT; ++t) {
+            const int ih = ih0 + tap_r[t], iw = iw0 + tap_s[t];
+            const int xo = on && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W ? (ih * a.W + iw) * 4 : OOB;
+#pragma unroll
+            for (int i = t * IPT; i < (t + 1) * IPT; ++i) rb[SET][i] = buf_load(rx, b_row[i] + xo, soff_b);
+        }
+        if (--left == 0) {
+            ++img; left = a.slices_per_img;
+            pq = ll; p = p_ll; q = q_ll;
+        } else {
+            pq += BL; p += step_p; q += step_q;
+            if (q >= a.Q) { q -= a.Q; ++p; }
         }
     };
-
+    float dbs[8];                                          // this thread's share of the bias gradient (first column tile)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) dbs[i] = 0.f;
+    auto put = [&](int buf, auto set_c) __attribute__((always_inline)) {
+        constexpr int SET = decltype(set_c)::value;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            As[buf][(row0 + 8 * i) * LDT + ll] = ra[SET][i];
+            Bs[buf][(row0 + 8 * i) * LDT + ll] = rb[SET][i];
+        }
+        if (nt == 0) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) dbs[i] += ra[SET][i];
+        }
+    };
     f32x16 acc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-    if (total > 0) fetch(0);
-    for (int sl = 0; sl < total; ++sl) {
-        __syncthreads();                                   // the previous slice has been read by every wave
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            As[(row0 + 8 * i) * LDT + ll] = ra[i];
-            Bs[(row0 + 8 * i) * LDT + ll] = rb[i];
-        }
-        __syncthreads();
-        if (sl + 1 < total) fetch(sl + 1);                 // in flight during the multiplications
-        const float* ap = As + (wm * 32 + l32) * LDT + half * 16;
-        const float* bp = Bs + (wn * 32 + l32) * LDT + half * 16;
+    auto step = [&](int sl, auto set_c) __attribute__((always_inline)) {     // set_c: the registers that hold slice sl + 1
+        const int buf = sl & 1;
+        const float* ap = As[buf] + (wm * 32 + l32) * LDT + half * 16;
+        const float* bp = Bs[buf] + (wn * 32 + l32) * LDT + half * 16;
         f32x4 av[4], bv[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -179,33 +223,65 @@ __global__ __launch_bounds__(256) void conv_wgrad_f32_kernel(const WArgs a)
         }
 #pragma unroll
         for (int j = 0; j < 16; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[j >> 2][j & 3], bv[j >> 2][j & 3], acc, 0, 0, 0);
+        if (sl + 1 < total) {
+            put(buf ^ 1, set_c);
+            if (sl + 3 < total) fetch(set_c);
+        }
+        lds_barrier();
+    };
+    using S0 = std::integral_constant<int, 0>;
+    using S1 = std::integral_constant<int, 1>;
+    if (total > 0) {
+        fetch(S0{});
+        put(0, S0{});
+        if (1 < total) fetch(S1{});
+        if (2 < total) fetch(S0{});
+    }
+    lds_barrier();
+    for (int sl = 0; sl < total; sl += 2) {
+        step(sl, S1{});
+        if (sl + 1 < total) step(sl + 1, S0{});
     }
     // register v holds row 8 (v / 4) + 4 half + v % 4 of column lane % 32
-    const int CRS1 = a.CRS + 1;
-    float* out = a.out + (size_t)sp * a.K * CRS1;
-    const int n = n0 + wn * 32 + l32;
+    const int col = nt * BN + wn * 32 + l32, n = wgrad_column(col, a.C, RS, __builtin_ctz(CB), a.cblocks);
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const int m = m0 + wm * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
-        if (m >= a.K || n > a.CRS) continue;
-        if (a.splits > 1) out[(size_t)m * CRS1 + n] = acc[v];
-        else if (n < a.CRS) a.dw[(size_t)m * a.CRS + n] = acc[v];
-        else if (a.db) a.db[m] = acc[v];
+        if (m >= a.K) continue;
+        if (a.splits > 1) a.out[((size_t)sp * a.K + m) * a.cols + col] = acc[v];
+        else if (n >= 0) a.dw[(size_t)m * a.CRS + n] = acc[v];
+    }
+    if (nt == 0) {
+        float* const db = a.splits > 1 ? a.out + (size_t)a.splits * a.K * a.cols + (size_t)sp * a.K : a.db;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            float t = dbs[i];
+#pragma unroll
+            for (int d = 16; d >= 1; d >>= 1) t += __shfl_down(t, d, 32);
+            const int m = m0 + row0 + 8 * i;
+            if (ll == 0 && m < a.K && db) db[m] = t;
+        }
     }
 }
 
-// element i of the [K][CRS + 1] result = sum over the splits, in split order; column CRS goes to db
-__global__ __launch_bounds__(256) void sum_splits_kernel(const float* __restrict__ part, int splits, int K, int CRS, float* __restrict__ dw,
-                                                         float* __restrict__ db)
+// The sum of the partial results over the splits, in split order: column by column of the [K][cols] sums, then the bias gradient.
+// (Eight loads in flight per thread: a chain of single loads took 10 us for 14 MB.)
+__global__ __launch_bounds__(256) void sum_splits_kernel(const float* __restrict__ part, int splits, int K, int C, int RS, int cb_log2, int cblocks, int cols,
+                                                         float* __restrict__ dw, float* __restrict__ db)
 {
-    const size_t count = (size_t)K * (CRS + 1);
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (size_t)gridDim.x * 256) {
+    const size_t count = (size_t)K * cols, all = count + (size_t)K;
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < all; i += (size_t)gridDim.x * 256) {
+        const bool bias = i >= count;
+        const size_t m = bias ? i - count : i / cols;
+        const int n = bias ? 0 : wgrad_column((int)(i - m * cols), C, RS, cb_log2, cblocks);
+        if (n < 0 || (bias && !db)) continue;
+        const float* src = bias ? part + (size_t)splits * count + m : part + i;
+        const size_t stride = bias ? (size_t)K : count;
         float s = 0.f;
-        for (int sp = 0; sp < splits; ++sp) s += part[(size_t)sp * count + i];
-        const size_t m = i / (CRS + 1);
-        const int n = (int)(i - m * (CRS + 1));
-        if (n < CRS) dw[m * CRS + n] = s;
-        else if (db) db[m] = s;
+#pragma unroll 8
+        for (int sp = 0; sp < splits; ++sp) s += src[(size_t)sp * stride];
+        if (bias) db[m] = s;
+        else dw[m * ((size_t)C * RS) + n] = s;
     }
 }
 
@@ -214,15 +290,25 @@ __global__ __launch_bounds__(256) void sgd_step_kernel(float* __restrict__ w, co
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (size_t)gridDim.x * 256) w[i] = w[i] - lr * dw[i];
 }
 
-int wgrad_splits(int N, int K, int CRS, int* imgs_per_split)
+// How the gradient's GEMM is tiled and split: column tiles of 64, 32 or 16 channels per tap (whichever gives the fewest), and as many
+// ranges of slices as make up to four workgroups per compute unit, of at least four slices each.
+struct WPlan { int cb_log2, cblocks, grid_m, grid_n, slices_per_img, slices, splits; };
+WPlan wgrad_plan(const ConvGeom& g)
 {
-    if (N < 1) { *imgs_per_split = 1; return 1; }
-    const int tiles = ((K + BM - 1) / BM) * ((CRS + 1 + BN - 1) / BN);
-    int want = (1024 + tiles - 1) / tiles;                  // about four workgroups per compute unit
-    if (want > N) want = N;
-    if (want < 1) want = 1;
-    *imgs_per_split = (N + want - 1) / want;
-    return (N + *imgs_per_split - 1) / *imgs_per_split;
+    WPlan p{};
+    const int RS = g.R * g.S;
+    int best = 0;
+    for (int l = 6; l >= 4; --l) {
+        const int tpt = BN >> l, cblocks = (g.C + (1 << l) - 1) >> l, n = (RS + tpt - 1) / tpt * cblocks;
+        if (best && n >= best) continue;
+        best = n; p.cb_log2 = l; p.cblocks = cblocks; p.grid_n = n;
+    }
+    p.grid_m = (g.K + BM - 1) / BM;
+    p.slices_per_img = std::max(1, (g.P * g.Q + BL - 1) / BL);
+    p.slices = g.P * g.Q > 0 ? g.N * p.slices_per_img : 0;
+    const int tiles = p.grid_m * p.grid_n;
+    p.splits = std::max(1, std::min(4 * device_cus() / tiles, p.slices / 4));
+    return p;
 }
 
 }  // namespace
@@ -242,34 +328,37 @@ int launch_regression_loss_grad(const float* f, const float* y, float* dz, size_
 
 size_t conv_wgrad_workspace_bytes(const ConvGeom& g)
 {
-    int ips = 0;
-    const int splits = wgrad_splits(g.N, g.K, g.Kg, &ips);
-    return splits > 1 ? (size_t)splits * g.K * (g.Kg + 1) * sizeof(float) : 0;
+    const WPlan p = wgrad_plan(g);
+    return p.splits > 1 ? (size_t)p.splits * g.K * ((size_t)p.grid_n * BN + 1) * sizeof(float) : 0;
 }
 
 int launch_conv_wgrad_f32(const ConvGeom& g, const float* x, const float* dz, float* dw, float* db, void* ws, hipStream_t st)
 {
+    const WPlan p = wgrad_plan(g);
     WArgs a;
     a.x = x; a.dz = dz;
     a.N = g.N; a.C = g.C; a.H = g.H; a.W = g.W; a.K = g.K; a.R = g.R; a.S = g.S;
-    a.sh = g.sh; a.sw = g.sw; a.ph = g.ph; a.pw = g.pw; a.P = g.P; a.Q = g.Q;
+    a.sh = g.sh; a.sw = g.sw; a.ph = g.ph; a.pw = g.pw; a.P = g.P; a.Q = std::max(1, g.Q);
     a.CRS = g.Kg;
-    a.grid_m = (g.K + BM - 1) / BM;
-    a.grid_n = (g.Kg + 1 + BN - 1) / BN;
-    a.splits = wgrad_splits(g.N, g.K, g.Kg, &a.imgs_per_split);
+    a.grid_m = p.grid_m; a.grid_n = p.grid_n; a.splits = p.splits; a.slices_per_img = p.slices_per_img; a.slices = p.slices;
+    a.cb_log2 = p.cb_log2; a.cblocks = p.cblocks; a.cols = p.grid_n * BN;
     a.x_bytes = (int)((size_t)g.N * g.C * g.H * g.W * 4);
     a.dz_bytes = (int)((size_t)g.N * g.K * g.P * g.Q * 4);
     a.out = (float*)ws; a.dw = dw; a.db = db;
     {
         ConvGeom t = g;
         TraceScope trace("conv_wgrad_f32", &t, g.Ng, st);
-        hipLaunchKernelGGL(conv_wgrad_f32_kernel, dim3((unsigned)(a.grid_m * a.grid_n * a.splits)), dim3(256), 0, st, a);
+        const dim3 grid((unsigned)(a.grid_m * a.grid_n * a.splits)), block(256);
+        if (p.cb_log2 == 6) hipLaunchKernelGGL(conv_wgrad_f32_kernel<1>, grid, block, 0, st, a);
+        else if (p.cb_log2 == 5) hipLaunchKernelGGL(conv_wgrad_f32_kernel<2>, grid, block, 0, st, a);
+        else hipLaunchKernelGGL(conv_wgrad_f32_kernel<4>, grid, block, 0, st, a);
     }
     if (const int rc = check_launch("conv_wgrad")) return rc;
     if (a.splits > 1) {
-        const size_t count = (size_t)g.K * (g.Kg + 1);
+        const size_t count = (size_t)g.K * (a.cols + 1);
         TraceScope trace("wgrad_sum", nullptr, (long long)count, st, (long long)((a.splits + 1) * count * 4));
-        hipLaunchKernelGGL(sum_splits_kernel, dim3(blocks_for_train(count)), dim3(256), 0, st, (const float*)ws, a.splits, g.K, g.Kg, dw, db);
+        hipLaunchKernelGGL(sum_splits_kernel, dim3(blocks_for_train(count)), dim3(256), 0, st, (const float*)ws, a.splits, g.K, g.C, g.R * g.S, a.cb_log2, a.cblocks,
+                           a.cols, dw, db);
     }
     return check_launch("conv_wgrad");
 }
