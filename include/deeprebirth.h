@@ -98,8 +98,7 @@ int dr_conv2d_fwd(const dr_tensor* xd, const void* x, const dr_conv* cd, const v
  * (xd, cd): 0 when the layer would not be cut (then ws may be NULL); cd with the stride of a slim
  * layer gives the slim layer's size.  ws: device memory, 256-byte aligned, of at least that size
  * (else DR_ERR_WORKSPACE), used only until the call's work on `stream` has finished.  fp32 NCHW layers
- * are cut; bf16 NHWC layers of few output pixels add their products in up to eight shares of the contraction (fp32, then
- * added in a fixed order), which needs no scratch; every other layer runs exactly as in dr_conv2d_fwd. */
+ * are cut; every other layer runs exactly as in dr_conv2d_fwd. */
 int dr_conv2d_workspace_bytes(const dr_tensor* xd, const dr_conv* cd, size_t* bytes);
 int dr_conv2d_fwd_ws(const dr_tensor* xd, const void* x, const dr_conv* cd, const void* w, const float* bias,
                      const dr_tensor* yd, void* y, int y_c_offset, void* ws, size_t ws_bytes, void* stream);

@@ -172,7 +172,7 @@ size_t conv_scratch_bytes(const dr_tensor& xd, const dr_conv& cd)
 
 int conv_run(const char* who, const dr_tensor& xd, const void* x, const dr_conv& cd, const void* w, const float* bias,
              const void* residual, int res_ctot, const dr_tensor& yd, void* y, int y_c_offset, hipStream_t st, int c_logical = 0,
-             void* scratch = nullptr, size_t scratch_bytes = 0, bool small = true)
+             void* scratch = nullptr, size_t scratch_bytes = 0)
 {
     if (xd.c != cd.c) return fail(DR_ERR_SHAPE, "%s: input has %d channels, filters expect %d", who, xd.c, cd.c);
     const dr_tensor o = conv_out(xd, cd);
@@ -194,11 +194,6 @@ int conv_run(const char* who, const dr_tensor& xd, const void* x, const dr_conv&
     g.c_logical = c_logical;
     if (xd.dtype == DR_F32)
         return launch_conv_f32(g, (const float*)x, (const float*)w, bias, (const float*)residual, (float*)y, st, scratch, scratch_bytes);
-    if (small && conv_bf16_small_takes(g, x, w)) {
-        TraceScope trace("conv_bf16", &g, g.Ng, st);
-        const ConvSmall job{g, x, w, bias, residual, y, nullptr};
-        return launch_conv_bf16_small(&job, 1, st);
-    }
     return launch_conv_bf16(g, (const uint16_t*)x, (const uint16_t*)w, bias, (const uint16_t*)residual, (uint16_t*)y, st);
 }
 
@@ -521,29 +516,55 @@ int run_stacked_first_steps(const dr_tensor& xd, const void* x, const dr_incepti
     return launch_conv_bf16_dma(g, (const uint16_t*)x, (const uint16_t*)w0, (const float*)b0, nullptr, (uint16_t*)sp.dst[0].y, st, &sp);
 }
 
-// A module of small layers, step by step instead of branch by branch: the convolutions at the same depth of the branches
-// (and a 3x3 pooling step beside them) are independent of one another and share launches of the small-layer kernel.
-// Steps that kernel does not take run one by one.  ReLU layers that the mode keeps apart and the concat remain kernels of
-// their own.
-struct SmallGroup {
+// A module step by step instead of branch by branch: the convolutions at the same depth of the branches (and a 3x3 pooling
+// step beside them) are independent of one another and share launches -- of the small-layer kernels, or for larger
+// fp32 layers of the tiled kernel.  Steps those do not take run one by one.  ReLU layers that the mode keeps apart and
+// the concat remain kernels of their own.
+struct StepGroup {
     hipStream_t st;
     int dtype;
-    int n = 0;
-    ConvSmall jobs[SMALL_GROUP_MAX];
-    int flush()
+    int n = 0, n_big = 0;
+    ConvSmall jobs[SMALL_GROUP_MAX], big[SMALL_GROUP_MAX];
+    int flush_small()
     {
         const int k = n;
         n = 0;
         if (!k) return DR_OK;
         return dtype == DR_BF16 ? launch_conv_bf16_small(jobs, k, st) : launch_conv_f32_small(jobs, k, st);
     }
+    int flush_big()
+    {
+        const int k = n_big;
+        n_big = 0;
+        if (!k) return DR_OK;
+        if (k > 1) return launch_conv_f32_group(big, k, st);
+        const ConvSmall& j = big[0];
+        return launch_conv_f32(j.g, (const float*)j.x, (const float*)j.w, j.bias, (const float*)j.res, (float*)j.y, st, nullptr, 0, j.split);
+    }
+    int flush()
+    {
+        DR_TRY(flush_big());
+        return flush_small();
+    }
     int add(const ConvSmall& j)
     {
-        if (n == SMALL_GROUP_MAX) DR_TRY(flush());
+        if (n == SMALL_GROUP_MAX) DR_TRY(flush_small());
         jobs[n++] = j;
         return DR_OK;
     }
+    int add_big(const ConvSmall& j)
+    {
+        if (n_big == SMALL_GROUP_MAX) DR_TRY(flush_big());
+        big[n_big++] = j;
+        return DR_OK;
+    }
 };
+
+// Larger fp32 layers that share a launch: enough tiles to be worth it (fewer are better cut over workgroups, one by one)
+bool big_takes(int dtype, const ConvGeom& g)
+{
+    return dtype == DR_F32 && conv_f32_group_takes(g) && ((long)g.K + 63) / 64 * (((long)g.Ng + 63) / 64) >= device_cus() / 2;
+}
 
 // A max-pooling step as a job of the small-layer kernel: 3x3 windows, whole 16-byte channel groups, few pixels.
 bool small_pool_job(const dr_tensor& t, const void* x, const dr_tensor& o, void* y, const dr_pool& p, ConvSmall* job)
@@ -558,8 +579,8 @@ bool small_pool_job(const dr_tensor& t, const void* x, const dr_tensor& o, void*
     return true;
 }
 
-// How many convolutions of the module the small-layer kernel takes.
-int inception_small_steps(const dr_tensor& xd, const void* x, const dr_inception& d)
+// How many convolutions of the module can share launches (larger layers: not when the caller wants the branches on streams).
+int inception_shared_steps(const dr_tensor& xd, const void* x, const dr_inception& d)
 {
     if (xd.layout != (xd.dtype == DR_BF16 ? DR_NHWC : DR_NCHW)) return 0;
     int n = 0;
@@ -568,7 +589,10 @@ int inception_small_steps(const dr_tensor& xd, const void* x, const dr_inception
         for (int s = 0; s < d.branches[b].n_steps; ++s) {
             const dr_step& stp = d.branches[b].steps[s];
             const dr_tensor o = stp.kind == DR_STEP_CONV ? conv_out(t, stp.conv) : pool_out(t, stp.pool);
-            if (stp.kind == DR_STEP_CONV && small_takes(xd.dtype, conv_geom(t, stp.conv, o), s == 0 ? x : nullptr, nullptr)) ++n;
+            if (stp.kind == DR_STEP_CONV) {
+                const ConvGeom g = conv_geom(t, stp.conv, o);
+                n += small_takes(xd.dtype, g, s == 0 ? x : nullptr, nullptr) || (!(d.mode & DR_CONCURRENT_BRANCHES) && big_takes(xd.dtype, g));
+            }
             t = o;
         }
     }
@@ -581,7 +605,7 @@ int inception_run_levels(const dr_tensor& xd, const void* x, const dr_inception&
     const char* who = "dr_inception_fwd";
     const bool fuse_relu = d.mode & DR_FUSE_RELU, fuse_cat = d.mode & DR_FUSE_CONCAT;
     if (!x) return fail(DR_ERR_NULL, "%s: x is NULL", who);
-    SmallGroup group{st, xd.dtype};
+    StepGroup group{st, xd.dtype};
     void* stacked_dst[DR_MAX_BRANCHES] = {};
     bool stacked[DR_MAX_BRANCHES] = {};
     ConvSplit sp;
@@ -627,6 +651,9 @@ int inception_run_levels(const dr_tensor& xd, const void* x, const dr_inception&
                     if (small_takes(xd.dtype, g, q.cur, w)) {
                         if (direct) { g.y_ctot = yd.c; g.y_coff = q.c_off; }
                         DR_TRY(group.add(ConvSmall{g, q.cur, w, bias, nullptr, dst, nullptr}));
+                    } else if (big_takes(xd.dtype, g)) {
+                        if (direct) { g.y_ctot = yd.c; g.y_coff = q.c_off; }
+                        DR_TRY(group.add_big(ConvSmall{g, q.cur, w, bias, nullptr, dst, nullptr}));
                     } else {
                         const size_t sbytes = conv_scratch_bytes(q.t, cd);
                         void* sc = sbytes ? ar.take(sbytes) : nullptr;
@@ -667,7 +694,7 @@ int inception_run(const dr_tensor& xd, const void* x, const dr_inception& d, Par
     const bool fuse_relu = d.mode & DR_FUSE_RELU, fuse_cat = d.mode & DR_FUSE_CONCAT;
     // A trace of every kernel (no label filter) is there to time each kernel on its own: it runs the branches in turn.
     const bool full_trace = g_trace.active && !g_trace.filter[0];
-    if (!ar.measure && !g_trace.active && wts.p && bss.p && inception_small_steps(xd, x, d) >= 2) return inception_run_levels(xd, x, d, wts, bss, yd, y, ar, main_st);
+    if (!ar.measure && !g_trace.active && wts.p && bss.p && inception_shared_steps(xd, x, d) >= 2) return inception_run_levels(xd, x, d, wts, bss, yd, y, ar, main_st);
     ConcatSeg segs[DR_MAX_BRANCHES];
     int nseg = 0, c_off = 0;
     // DR_FUSE_STACK (Eq. (12)): first-step 1x1 convolutions on the module input run as one convolution
@@ -1050,8 +1077,7 @@ int dr_conv2d_fwd(const dr_tensor* xd, const void* x, const dr_conv* cd, const v
     DR_TRY(check_tensor(who, "xd", xd));
     DR_TRY(check_tensor(who, "yd", yd));
     DR_TRY(check_conv_desc(who, cd));
-    // (no small-layer kernel: this entry point's sums run in one order over (r, s, c) at every size)
-    return conv_run(who, *xd, x, *cd, w, bias, nullptr, 0, *yd, y, y_c_offset, (hipStream_t)stream, 0, nullptr, 0, false);
+    return conv_run(who, *xd, x, *cd, w, bias, nullptr, 0, *yd, y, y_c_offset, (hipStream_t)stream);
 }
 
 int dr_conv2d_workspace_bytes(const dr_tensor* xd, const dr_conv* cd, size_t* bytes)

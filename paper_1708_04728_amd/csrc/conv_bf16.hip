@@ -368,6 +368,11 @@ int launch_conv_bf16(const ConvGeom& g, const uint16_t* x, const uint16_t* w, co
                      const uint16_t* residual, uint16_t* y, hipStream_t st)
 {
     TraceScope trace("conv_bf16", &g, g.Ng, st);
+    // few output pixels: small tiles, loading and multiplying waves apart (conv_bf16_small.hip)
+    if (conv_bf16_small_takes(g, x, w)) {
+        const ConvSmall job{g, x, w, bias, residual, y, nullptr};
+        return launch_conv_bf16_small(&job, 1, st);
+    }
     // several taps at stride 1 on few channels: the input patch of a tile is loaded once for all taps (conv_bf16_patch.hip)
     if (!residual && conv_bf16_patch_eligible(g, x, w, y)) return launch_conv_bf16_patch(g, x, w, bias, y, st);
     if (!residual && conv_bf16_rows_eligible(g, x, w, y)) return launch_conv_bf16_rows(g, x, w, bias, y, st);

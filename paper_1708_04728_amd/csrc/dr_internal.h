@@ -72,6 +72,9 @@ struct ConvSmall {
 };
 bool conv_f32_small_takes(const ConvGeom& g, bool scratch);      // scratch: the caller can have the contraction cut over workgroups instead
 int launch_conv_f32_small(const ConvSmall* jobs, int n, hipStream_t st);
+// conv_f32.hip: several larger fp32 layers (KRSC filters, C % 16 == 0) in one launch
+bool conv_f32_group_takes(const ConvGeom& g);
+int launch_conv_f32_group(const ConvSmall* jobs, int n, hipStream_t st);
 
 // conv_bf16_dma.hip: the main bf16 kernel (NHWC, KRSC filters, C % 8 == 0, 16-byte aligned tensors)
 bool conv_bf16_dma_eligible(const ConvGeom& g, const void* x, const void* w);

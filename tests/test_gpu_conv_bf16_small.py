@@ -1,7 +1,7 @@
-"""GPU parity of the small-layer bf16 convolution kernel (the contraction of a 32 x 32 tile shared by the waves of a
-workgroup, several layers per launch) against the fp64 oracle, where it can go wrong: fewer slices than waves, one slice more than a
-multiple of the waves, both slice modes, ragged filters / pixels / channel runs, every border, the scalar store, the
-largest layer it takes; and modules whose branches share launches, with the pooling step in them."""
+"""GPU parity of the small-layer bf16 convolution kernel (loading and multiplying waves apart, several layers per launch) against
+the fp64 oracle, where it can go wrong: contractions of one slice and of every remainder of the ring, both slice modes,
+ragged filters / pixels / channel runs, every border, the scalar store, all three tile shapes, the largest layer it takes;
+and modules whose branches share launches, with the pooling step in them."""
 import numpy as np
 import pytest
 
@@ -19,23 +19,23 @@ CUS = 256
 def takes(N, C, H, W, K, R, S, stride, pad):
     """The launcher's rule, restated."""
     n = N * oracle.conv_out_size(H, R, stride, pad) * oracle.conv_out_size(W, S, stride, pad)
-    if R * S == 1:
-        return n <= 1024 and C > 256
-    return -(-n // 32) * -(-K // 32) <= 2 * CUS
+    return -(-n // 64) * -(-K // 64) <= (2 if R * S > 1 else 1) * CUS
 
 
 @pytest.mark.parametrize("case", [
     # N, C, H, W, K, R, S, stride, pad
-    (1, 8, 5, 7, 8, 3, 3, 1, 1),          # 72 values: fewer slices than waves, one channel chunk per tap
+    (1, 8, 5, 7, 8, 3, 3, 1, 1),          # 72 values: two slices, one channel chunk per tap
     (1, 24, 9, 11, 40, 3, 3, 1, 1),       # slices that run on from filter row to filter row, ragged filters
-    (2, 40, 13, 10, 100, 5, 5, 2, 2),     # stride 2, filters no multiple of 8 (scalar store at the end)
-    (1, 64, 6, 6, 33, 3, 3, 1, 1),        # whole taps, 9 slices for 8 waves, a second filter block of one filter
+    (2, 40, 13, 10, 100, 5, 5, 2, 2),     # stride 2, filters no multiple of 8 (scalar store)
+    (1, 64, 6, 6, 33, 3, 3, 1, 1),        # whole taps, 9 slices, a second filter block of one filter
     (3, 128, 7, 9, 64, 3, 3, 2, 1),       # two slices per tap
-    (1, 16, 4, 4, 16, 3, 1, 1, 0),        # a filter row shorter than a slice: no run-on
+    (1, 16, 4, 4, 16, 3, 1, 1, 0),        # a filter row shorter than a slice: no run-on, three slices
+    (1, 64, 3, 5, 24, 1, 1, 1, 0),        # one slice
     (1, 264, 3, 5, 24, 1, 1, 1, 0),       # 1x1, ragged run: 5 slices
-    (4, 832, 16, 16, 72, 1, 1, 1, 0),     # 1x1 at the largest pixel count
     (1, 320, 9, 9, 56, 1, 1, 2, 0),       # strided 1x1
-    (2, 48, 64, 64, 64, 3, 3, 1, 1),      # 512 tiles, the most it takes: four waves per workgroup
+    (4, 96, 64, 64, 64, 1, 1, 1, 0),      # 256 tiles of 64 x 64: the largest layer with 1x1 filters
+    (1, 48, 64, 61, 96, 3, 3, 1, 1),      # 64 x 32 tiles, half a filter block
+    (2, 24, 96, 84, 104, 3, 3, 1, 1),     # 504 tiles of 64 x 64, ragged
     (1, 1032, 2, 3, 8, 3, 3, 1, 1),       # long contraction, 146 slices
 ])
 def test_small_layer(case):
