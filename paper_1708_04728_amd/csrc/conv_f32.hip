@@ -496,7 +496,9 @@ __global__ __launch_bounds__(NT) void conv_f32_kernel(const KArgs a)
 {
     __shared__ __attribute__((aligned(16))) float As[2][BM * (BK + 4)];
     __shared__ __attribute__((aligned(16))) float Bs[2][BN * (BK + 4)];
-    __shared__ __attribute__((aligned(16))) int ktab[CF ? 4 : KTAB1];   // CF = false: {byte offset, r | s << 8} per k
+    // (filters known to have more than 31 taps never use the one-word table: 4 KB less is one workgroup more per compute unit, which
+    // AlexNet's first two convolutions at batch 128 show as 1465 us against 1518)
+    __shared__ __attribute__((aligned(16))) int ktab[CF ? 4 : FR * FS > 31 ? 2 * KTAB : KTAB1];   // CF = false: {byte offset, r | s << 8} per k
     conv_f32_tile<BM, BN, WGM, WGN, BK, PF, CF, FR, FS, SPLIT>(a, (int)blockIdx.x, As, Bs, ktab);
 }
 
