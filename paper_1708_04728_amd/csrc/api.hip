@@ -290,8 +290,7 @@ int padded_conv_run(const char* who, const dr_tensor& xd, const void* x, const d
         void* wbuf = probe.take((size_t)cd.k * 512);
         if (!xbuf || !wbuf || !conv_bf16_rows_stem_eligible(g, hp, wp, xbuf, y, &rt)) return DR_OK;
         ar = probe;
-        DR_TRY(launch_stem_pack_bf16(x, xbuf, xd.n, xd.c, xd.h, xd.w, cd.pad_h, cd.pad_w, hp, wp, st));
-        DR_TRY(launch_stem_filters_bf16(w, wbuf, cd.k, cd.c, cd.r, cd.s, g.w_krsc, st));
+        DR_TRY(launch_stem_copies_bf16(x, xbuf, xd.n, xd.c, xd.h, xd.w, cd.pad_h, cd.pad_w, hp, wp, w, wbuf, cd.k, cd.r, cd.s, g.w_krsc, st));
         DR_TRY(launch_conv_bf16_rows_stem(g, (const uint16_t*)xbuf, hp, wp, (const uint16_t*)wbuf, bias, (uint16_t*)y, st, &rt));
         if (fused) *fused = true;
         return DR_OK;
@@ -324,8 +323,7 @@ int padded_conv_run(const char* who, const dr_tensor& xd, const void* x, const d
             g.w_krsc = cd.filter_layout == DR_KRSC;
             g.nhwc = 1;
             g.c_logical = 0;
-            DR_TRY(launch_stem_pack_bf16(x, xbuf, xd.n, xd.c, xd.h, xd.w, cd.pad_h, cd.pad_w, hp, wp, st));
-            DR_TRY(launch_stem_filters_bf16(w, wbuf, cd.k, cd.c, cd.r, cd.s, g.w_krsc, st));
+            DR_TRY(launch_stem_copies_bf16(x, xbuf, xd.n, xd.c, xd.h, xd.w, cd.pad_h, cd.pad_w, hp, wp, w, wbuf, cd.k, cd.r, cd.s, g.w_krsc, st));
             if (conv_bf16_rows_stem_eligible(g, hp, wp, xbuf, y))
                 return launch_conv_bf16_rows_stem(g, (const uint16_t*)xbuf, hp, wp, (const uint16_t*)wbuf, bias, (uint16_t*)y, st);
             return launch_conv_bf16_stem(g, (const uint16_t*)xbuf, hp, wp, (const uint16_t*)wbuf, bias, (uint16_t*)y, st);
@@ -592,11 +590,12 @@ int inception_shared_steps(const dr_tensor& xd, const void* x, const dr_inceptio
             if (stp.kind == DR_STEP_CONV) {
                 const ConvGeom g = conv_geom(t, stp.conv, o);
                 n += small_takes(xd.dtype, g, s == 0 ? x : nullptr, nullptr) || (!(d.mode & DR_CONCURRENT_BRANCHES) && big_takes(xd.dtype, g));
+                ++all;
             }
             t = o;
         }
     }
-    return n;
+    return n >= 2 && (n == all || !(d.mode & DR_CONCURRENT_BRANCHES));
 }
 
 int inception_run_levels(const dr_tensor& xd, const void* x, const dr_inception& d, ParamCursor& wts, ParamCursor& bss, const dr_tensor& yd, void* y,

@@ -867,6 +867,10 @@ int launch_conv_bf16_stem(const ConvGeom& real, const uint16_t* xp, int hp, int 
     g.W = wp / 8;                 // so that one "tap row" of W * C * 2 bytes is two rows of the padded copy
     g.ph = g.pw = 0;
     g.w_krsc = 1; g.nhwc = 1;
+    if (((long)g.Ng + 63) / 64 * ((g.K + 63) / 64) <= 2 * device_cus()) {
+        const ConvSmall job{g, xp, wp8, bias, nullptr, y, nullptr, hp, wp};
+        return launch_conv_bf16_small(&job, 1, st);
+    }
     DArgs a;
     a.x = xp; a.w = wp8; a.bias = bias; a.res = nullptr; a.y = y; a.g = g;
     a.grid_m = a.grid_n = 0;

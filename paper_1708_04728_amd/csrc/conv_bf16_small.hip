@@ -42,6 +42,7 @@ struct SmallJob {
     int nsplit, res_ctot;
     int C, H, W, K, R, S, sh, sw, ph, pw, P, Q, Kg, Ng, relu;
     int x_bytes, w_bytes;
+    int stem_hp, stem_wp;                                // padded 4-channel input copy (see launch_conv_bf16_stem), 0: ordinary input
     int tap, flat, pointwise;                                       // slices: whole taps (C % 64 == 0); running on from filter row to filter row
     int c8, run_chunks, spr, slices;                     // chunks per tap, per filter row; slices per filter row, per tile
     unsigned magic_c8;
@@ -130,6 +131,11 @@ __global__ __launch_bounds__((CM * CN + 4) * 64) void conv_bf16_small_kernel(con
             } else {
                 const int nn = in ? n : 0;
                 const int img = div_small(nn, j.m_pq), pix = nn - img * j.P * j.Q, p = div_small(pix, j.m_q), q = pix - p * j.Q;
+                if (j.stem_wp) {                         // chunk lc of a slice: pixel pair lc & 3 of window row lc >> 2; nothing lies outside the copy
+                    b_base[i] = ((img * j.stem_hp + p * j.sh + (lc >> 2)) * j.stem_wp + q * j.sw + 2 * (lc & 3)) * 8;
+                    b_mask[i] = in ? 0xFFFFFEu : 0xFFFFu;
+                    continue;
+                }
                 const int ih0 = p * j.sh - j.ph, iw0 = q * j.sw - j.pw;
                 b_base[i] = (((img * j.H + ih0) * j.W + iw0) * j.C + lc * 8) * 2;
                 const unsigned wv = bit_range(max(0, -iw0), min(j.S - 1, j.W - 1 - iw0));
@@ -306,7 +312,8 @@ SmallJob small_job(const ConvSmall& c, int bm, int bn, int nth)
         j.tiles = (g.Ng * j.c8 + nth - 1) / nth;
         return j;
     }
-    j.x_bytes = (int)((size_t)g.N * g.C * g.H * g.W * 2);
+    j.stem_hp = c.stem_hp; j.stem_wp = c.stem_wp;
+    j.x_bytes = c.stem_wp ? (int)((size_t)g.N * c.stem_hp * c.stem_wp * 8) : (int)((size_t)g.N * g.C * g.H * g.W * 2);
     j.w_bytes = (int)((size_t)g.K * g.Kg * 2);
     j.tap = g.C % 64 == 0;
     j.pointwise = g.R == 1 && g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0;

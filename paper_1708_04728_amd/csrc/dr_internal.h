@@ -69,6 +69,7 @@ struct ConvSmall {
     const void* res;
     void* y;
     const ConvSplit* split;      // destinations of a stacked convolution, or NULL
+    int stem_hp, stem_wp;        // bf16: x and w are the copies launch_conv_bf16_stem takes (0: ordinary layer)
 };
 bool conv_f32_small_takes(const ConvGeom& g, bool scratch);      // scratch: the caller can have the contraction cut over workgroups instead
 int launch_conv_f32_small(const ConvSmall* jobs, int n, hipStream_t st);
@@ -165,8 +166,8 @@ int launch_bn_nhwc(const dr_tensor& d, const void* x, void* y, const float* gamm
 int launch_pad_channels_bf16(const void* x, void* y, size_t pixels, int C, int Cp, hipStream_t st);
 int launch_pad_filters_bf16(const void* w, void* y, int K, int C, int RS, int Cp, int krsc, hipStream_t st);
 // the copies launch_conv_bf16_stem takes: xp[N][hp][wp][4] and wp8[K][8][8][4]
-int launch_stem_pack_bf16(const void* x, void* xp, int N, int C, int H, int W, int pad_h, int pad_w, int hp, int wp, hipStream_t st);
-int launch_stem_filters_bf16(const void* w, void* wp8, int K, int C, int R, int S, int krsc, hipStream_t st);
+int launch_stem_copies_bf16(const void* x, void* xp, int N, int C, int H, int W, int pad_h, int pad_w, int hp, int wp, const void* w, void* wp8, int K,
+                            int R, int S, int krsc, hipStream_t st);
 int launch_fc(int dtype, const void* x, const void* w, const float* bias, void* y, int N, int I, int O, hipStream_t st);
 int launch_softmax(int dtype, const void* x, float* y, int N, int O, hipStream_t st);
 

@@ -462,10 +462,14 @@ int launch_fc(int dtype, const void* x, const void* w, const float* bias, void* 
     if (N == 0 || O == 0) return DR_OK;
     if (dtype == DR_BF16) {
         // an inner product is a 1x1 convolution over a one-pixel image: y[n][o] = sum_i w[o][i] x[n][i] runs on
-        // the matrix cores through the streaming convolution kernel when its layout conditions hold
+        // the matrix cores through the small-layer or the streaming convolution kernel when their layout conditions hold
         ConvGeom g;
         g.N = N; g.C = I; g.H = g.W = 1; g.K = O; g.R = g.S = 1; g.sh = g.sw = 1; g.ph = g.pw = 0; g.P = g.Q = 1;
         g.Kg = I; g.Ng = N; g.y_ctot = O; g.y_coff = 0; g.relu = 0; g.res_ctot = 0; g.w_krsc = 1; g.nhwc = 1; g.c_logical = 0;
+        if (conv_bf16_small_takes(g, x, w)) {
+            const ConvSmall job{g, x, w, bias, nullptr, y, nullptr};
+            return launch_conv_bf16_small(&job, 1, st);
+        }
         if (conv_bf16_dma_eligible(g, x, w))
             return launch_conv_bf16_dma(g, (const uint16_t*)x, (const uint16_t*)w, bias, nullptr, (uint16_t*)y, st);
     }

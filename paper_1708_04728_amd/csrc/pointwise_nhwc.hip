@@ -822,14 +822,36 @@ __global__ __launch_bounds__(256) void stem_pack_kernel(const uint16_t* __restri
     }
 }
 
+// wp8[k][r][s][c] (8 x 8 x 4 per filter) = w[k][c][r][s] (KCRS) or w[k][r][s][c] (KRSC) inside R x S x C, else 0
+struct StemFilters {
+    const uint16_t* w;
+    uint16_t* y;
+    int K, C, R, S, krsc;
+};
+__device__ __forceinline__ void stem_filters(const StemFilters& f, int block, int blocks)
+{
+    const int total = f.K * 256;
+    for (int i = block * 256 + (int)threadIdx.x; i < total; i += blocks * 256) {
+        const int c = i & 3, s = (i >> 2) & 7, r = (i >> 5) & 7, k = i >> 8;
+        uint16_t v = 0;
+        if (c < f.C && r < f.R && s < f.S) v = f.krsc ? f.w[((k * f.R + r) * f.S + s) * f.C + c] : f.w[((k * f.C + c) * f.R + r) * f.S + s];
+        f.y[i] = v;
+    }
+}
+__global__ __launch_bounds__(256) void stem_filters_kernel(const StemFilters f) { stem_filters(f, (int)blockIdx.x, (int)gridDim.x); }
+
 // The same copy, a workgroup per PACK_ROWS rows of xp: the input rows are fetched whole with 16-byte loads into LDS
 // (an input row of W * C bf16 values must be a multiple of 16 bytes, x 16-byte aligned) and the pixels are picked
 // out of LDS; two pixels of xp per thread and 16-byte store.  A quarter of the load instructions of the kernel above.
 constexpr int PACK_ROWS = 4;
 __global__ __launch_bounds__(256) void stem_pack_rows_kernel(const uint16_t* __restrict__ x, uint16_t* __restrict__ xp, int C, int H, int W,
-                                                             int pad_h, int pad_w, int hp, int wp)
+                                                             int pad_h, int pad_w, int hp, int wp, int copy_blocks, const StemFilters f)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char pack_lds[];
+    if ((int)blockIdx.x >= copy_blocks) {                 // the filters ride in the same launch
+        stem_filters(f, (int)blockIdx.x - copy_blocks, (int)gridDim.x - copy_blocks);
+        return;
+    }
     const int row_bytes = W * C * 2, chunks = row_bytes >> 4, pairs = wp >> 1;
     const int groups = (hp + PACK_ROWS - 1) / PACK_ROWS;
     const int n = blockIdx.x / groups, yy0 = (blockIdx.x - n * groups) * PACK_ROWS;
@@ -860,45 +882,27 @@ __global__ __launch_bounds__(256) void stem_pack_rows_kernel(const uint16_t* __r
     }
 }
 
-// wp8[k][r][s][c] (8 x 8 x 4 per filter) = w[k][c][r][s] (KCRS) or w[k][r][s][c] (KRSC) inside R x S x C, else 0
-__global__ __launch_bounds__(256) void stem_filters_kernel(const uint16_t* __restrict__ w, uint16_t* __restrict__ y, int K, int C, int R,
-                                                           int S, int krsc)
-{
-    const int total = K * 256;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
-        const int c = i & 3, s = (i >> 2) & 7, r = (i >> 5) & 7, k = i >> 8;
-        uint16_t v = 0;
-        if (c < C && r < R && s < S) v = krsc ? w[((k * R + r) * S + s) * C + c] : w[((k * C + c) * R + r) * S + s];
-        y[i] = v;
-    }
-}
-
 }  // namespace
 
-int launch_stem_pack_bf16(const void* x, void* xp, int N, int C, int H, int W, int pad_h, int pad_w, int hp, int wp, hipStream_t st)
+int launch_stem_copies_bf16(const void* x, void* xp, int N, int C, int H, int W, int pad_h, int pad_w, int hp, int wp, const void* w, void* wp8, int K,
+                            int R, int S, int krsc, hipStream_t st)
 {
     TraceScope trace("conv_pad", nullptr, (long long)((size_t)N * hp * wp * 4), st);
     const size_t total = (size_t)N * hp * wp;
-    if (total == 0) return DR_OK;
+    const StemFilters f{(const uint16_t*)w, (uint16_t*)wp8, K, C, R, S, krsc};
+    const unsigned filter_blocks = K ? blocks_for((size_t)K * 256, 256, 1024) : 0;
     const size_t row_bytes = (size_t)W * C * 2;
     const size_t groups = (size_t)N * ((hp + PACK_ROWS - 1) / PACK_ROWS);
-    if (row_bytes % 16 == 0 && PACK_ROWS * row_bytes <= 48 * 1024 && aligned16(x) && aligned16(xp) && wp % 2 == 0 && groups < (1u << 31)) {
-        hipLaunchKernelGGL(stem_pack_rows_kernel, dim3((unsigned)groups), dim3(256), PACK_ROWS * row_bytes, st, (const uint16_t*)x,
-                           (uint16_t*)xp, C, H, W, pad_h, pad_w, hp, wp);
+    if (total && row_bytes % 16 == 0 && PACK_ROWS * row_bytes <= 48 * 1024 && aligned16(x) && aligned16(xp) && wp % 2 == 0 && groups + filter_blocks < (1u << 31)) {
+        hipLaunchKernelGGL(stem_pack_rows_kernel, dim3((unsigned)groups + filter_blocks), dim3(256), PACK_ROWS * row_bytes, st, (const uint16_t*)x,
+                           (uint16_t*)xp, C, H, W, pad_h, pad_w, hp, wp, (int)groups, f);
         return check_launch("stem_pack");
     }
-    hipLaunchKernelGGL(stem_pack_kernel, dim3(blocks_for(total, 256, 256 * 64)), dim3(256), 0, st, (const uint16_t*)x, (uint16_t*)xp, C, H, W,
-                       pad_h, pad_w, hp, wp, total);
+    if (total)
+        hipLaunchKernelGGL(stem_pack_kernel, dim3(blocks_for(total, 256, 256 * 64)), dim3(256), 0, st, (const uint16_t*)x, (uint16_t*)xp, C, H, W,
+                           pad_h, pad_w, hp, wp, total);
+    if (K) hipLaunchKernelGGL(stem_filters_kernel, dim3(filter_blocks), dim3(256), 0, st, f);
     return check_launch("stem_pack");
-}
-
-int launch_stem_filters_bf16(const void* w, void* wp8, int K, int C, int R, int S, int krsc, hipStream_t st)
-{
-    TraceScope trace("conv_pad", nullptr, (long long)K * 256, st);
-    if (K == 0) return DR_OK;
-    hipLaunchKernelGGL(stem_filters_kernel, dim3(blocks_for((size_t)K * 256, 256, 1024)), dim3(256), 0, st, (const uint16_t*)w, (uint16_t*)wp8, K, C,
-                       R, S, krsc);
-    return check_launch("stem_filters");
 }
 
 int launch_pad_channels_bf16(const void* x, void* y, size_t pixels, int C, int Cp, hipStream_t st)

@@ -96,3 +96,34 @@ def test_module_whose_branches_share_launches(form, n, hw):
     net.fwd(xg, G.stack_first_steps([layer], G.flat_params(params, "bf16", pack=True)), y, ws)
     torch.cuda.synchronize()
     assert np.array_equal(G.to_host(y), plain)
+
+
+@pytest.mark.parametrize("N,K,S,stride", [(2, 64, 128, 2), (1, 20, 93, 4), (2, 64, 130, 2)])
+def test_first_layer_at_the_edge_of_the_rule(N, K, S, stride):
+    """7x7 on three channels through the padded copy: the largest layer that runs here (128 x 128 outputs of two images = 512
+    pixel tiles), a scalar store, and the first size that goes to the streaming kernel."""
+    from test_gpu_bf16_nets import run_net_bf16
+    rng = np.random.default_rng(S)
+    H = S * stride
+    x = workloads.round_to_bf16(rng.standard_normal((N, 3, H, H)).astype(np.float32))
+    w = workloads.round_to_bf16(rng.standard_normal((K, 3, 7, 7)).astype(np.float32) * np.float32(0.1))
+    b = (rng.standard_normal(K) * 0.1).astype(np.float32)
+    layers = [workloads.conv(K, 7, stride, 3), workloads.relu()]
+    got = run_net_bf16(layers, [{"w": w, "b": b}], x, fuse_relu=True)
+    ref = oracle.forward(layers, [{"w": w, "b": b}], x)
+    assert got.shape == (N, K, S, S)
+    assert close(got, oracle.round_bf16(ref), 2.0 ** -7)
+
+
+@pytest.mark.parametrize("N,I,O", [(1, 1024, 1000), (33, 72, 10), (70, 264, 200)])
+def test_inner_product(N, I, O):
+    """One-pixel images: a single row, ragged inputs, outputs that 8-byte stores do not fit."""
+    rng = np.random.default_rng(I)
+    x = workloads.round_to_bf16(rng.standard_normal((N, I)).astype(np.float32))
+    w = workloads.round_to_bf16(rng.standard_normal((O, I)).astype(np.float32) * np.float32(I ** -0.5))
+    b = rng.standard_normal(O).astype(np.float32)
+    y = torch.empty((N, O), dtype=torch.bfloat16, device="cuda")
+    B.fc_fwd(gpu(x, "bf16"), gpu(w, "bf16"), gpu(b), y)
+    torch.cuda.synchronize()
+    ref = x.astype(np.float64) @ w.astype(np.float64).T + b
+    assert close(y.float().cpu().numpy(), oracle.round_bf16(ref.astype(np.float32)), 2.0 ** -7)
