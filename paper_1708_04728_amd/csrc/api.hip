@@ -577,11 +577,13 @@ bool small_pool_job(const dr_tensor& t, const void* x, const dr_tensor& o, void*
     return true;
 }
 
-// How many convolutions of the module can share launches (larger layers: not when the caller wants the branches on streams).
-int inception_shared_steps(const dr_tensor& xd, const void* x, const dr_inception& d)
+// Whether the module runs level by level, its steps sharing launches: at least two convolutions that can.  Where the caller wants the
+// branches on streams, every convolution has to be small: a level is a barrier between the branches, and larger layers fill the
+// device better side by side (the original GoogLeNet at batch 128, half of whose 14x14 steps are small: 1605 us against 1690).
+bool inception_by_levels(const dr_tensor& xd, const void* x, const dr_inception& d)
 {
-    if (xd.layout != (xd.dtype == DR_BF16 ? DR_NHWC : DR_NCHW)) return 0;
-    int n = 0;
+    if (xd.layout != (xd.dtype == DR_BF16 ? DR_NHWC : DR_NCHW)) return false;
+    int n = 0, all = 0;
     for (int b = 0; b < d.n_branches; ++b) {
         dr_tensor t = xd;
         for (int s = 0; s < d.branches[b].n_steps; ++s) {
@@ -624,7 +626,8 @@ int inception_run_levels(const dr_tensor& xd, const void* x, const dr_inception&
         depth = std::max(depth, d.branches[b].n_steps);
     }
     for (int s = 0; s < depth; ++s) {
-        struct Relu { void* p; size_t n; } relus[DR_MAX_BRANCHES];
+        void* relu_p[DR_MAX_BRANCHES];
+        size_t relu_count[DR_MAX_BRANCHES];
         int n_relu = 0;
         for (int b = 0; b < d.n_branches; ++b) {
             if (s >= d.branches[b].n_steps) continue;
@@ -658,7 +661,10 @@ int inception_run_levels(const dr_tensor& xd, const void* x, const dr_inception&
                         void* sc = sbytes ? ar.take(sbytes) : nullptr;
                         DR_TRY(conv_run(who, q.t, q.cur, cd, w, bias, nullptr, 0, direct ? yd : o, dst, direct ? q.c_off : 0, st, 0, sc, sc ? sbytes : 0));
                     }
-                    if (relu_after && !cd.relu) relus[n_relu++] = Relu{dst, tensor_elems(o)};
+                    if (relu_after && !cd.relu) {
+                        relu_p[n_relu] = dst;
+                        relu_count[n_relu++] = tensor_elems(o);
+                    }
                 }
                 if (last && !direct) q.seg = ConcatSeg{dst, o.c, q.c_off};
             } else {
@@ -674,7 +680,7 @@ int inception_run_levels(const dr_tensor& xd, const void* x, const dr_inception&
             q.t = o;
         }
         DR_TRY(group.flush());
-        for (int i = 0; i < n_relu; ++i) DR_TRY(launch_relu(xd.dtype, relus[i].p, relus[i].p, relus[i].n, st));
+        if (n_relu) DR_TRY(launch_relu_group(xd.dtype, n_relu, relu_p, relu_count, st));
     }
     wts.i += param;
     bss.i += param;
@@ -693,7 +699,7 @@ int inception_run(const dr_tensor& xd, const void* x, const dr_inception& d, Par
     const bool fuse_relu = d.mode & DR_FUSE_RELU, fuse_cat = d.mode & DR_FUSE_CONCAT;
     // A trace of every kernel (no label filter) is there to time each kernel on its own: it runs the branches in turn.
     const bool full_trace = g_trace.active && !g_trace.filter[0];
-    if (!ar.measure && !g_trace.active && wts.p && bss.p && inception_shared_steps(xd, x, d) >= 2) return inception_run_levels(xd, x, d, wts, bss, yd, y, ar, main_st);
+    if (!ar.measure && !g_trace.active && wts.p && bss.p && inception_by_levels(xd, x, d)) return inception_run_levels(xd, x, d, wts, bss, yd, y, ar, main_st);
     ConcatSeg segs[DR_MAX_BRANCHES];
     int nseg = 0, c_off = 0;
     // DR_FUSE_STACK (Eq. (12)): first-step 1x1 convolutions on the module input run as one convolution

@@ -142,6 +142,7 @@ int launch_sgd_step(float* w, const float* dw, float lr, size_t count, hipStream
 // pointwise.hip
 int launch_pack_filters(int dtype, const void* w_kcrs, void* w_krsc, int K, int C, int RS, hipStream_t st);
 int launch_relu(int dtype, const void* x, void* y, size_t count, hipStream_t st);
+int launch_relu_group(int dtype, int n, void* const* p, const size_t* count, hipStream_t st);   // in place on up to DR_MAX_BRANCHES buffers
 int launch_lrn(const dr_tensor& d, const void* x, void* y, const dr_lrn& p, hipStream_t st);
 int launch_maxpool(const dr_tensor& xd, const void* x, const dr_tensor& yd, void* y, const dr_pool& p, hipStream_t st);
 int launch_avgpool(const dr_tensor& xd, const void* x, const dr_tensor& yd, void* y, const dr_pool& p, hipStream_t st);

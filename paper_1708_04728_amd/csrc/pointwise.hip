@@ -44,6 +44,46 @@ int relu_launch(const void* a, const void* b, void* y, size_t count, hipStream_t
     return check_launch(ADD ? "add_relu" : "relu");
 }
 
+// y = max(y, 0) on several buffers in one launch: a launch of its own costs a small buffer more than its bytes do (the
+// original GoogLeNet on 24 images: 662 us against 774).
+struct ReluGroup {
+    void* p[DR_MAX_BRANCHES];
+    size_t nvec[DR_MAX_BRANCHES], count[DR_MAX_BRANCHES];
+};
+template <typename T>
+__global__ __launch_bounds__(256) void relu_group_kernel(const ReluGroup g)
+{
+    constexpr int VN = Store<T>::VN;
+    const size_t stride = (size_t)gridDim.x * blockDim.x, first = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    T* const p = (T*)g.p[blockIdx.y];
+    const size_t nvec = g.nvec[blockIdx.y], count = g.count[blockIdx.y];
+    for (size_t i = first; i < nvec; i += stride) {
+        float v[VN];
+        Store<T>::ldv(p + i * VN, v);
+#pragma unroll
+        for (int j = 0; j < VN; ++j) v[j] = fmaxf(v[j], 0.f);
+        Store<T>::stv(p + i * VN, v);
+    }
+    for (size_t i = nvec * VN + first; i < count; i += stride) Store<T>::st(p + i, fmaxf(Store<T>::ld(p + i), 0.f));
+}
+
+template <typename T>
+int relu_group_launch(int n, void* const* p, const size_t* count, hipStream_t st)
+{
+    constexpr int VN = Store<T>::VN;
+    ReluGroup g{};
+    size_t items = 0;
+    for (int i = 0; i < n; ++i) {
+        g.p[i] = p[i];
+        g.count[i] = count[i];
+        g.nvec[i] = aligned16(p[i]) ? count[i] / VN : 0;
+        items = std::max(items, g.nvec[i] ? g.nvec[i] : count[i]);
+    }
+    if (items == 0) return DR_OK;
+    hipLaunchKernelGGL(relu_group_kernel<T>, dim3(blocks_for(items, 256, 256 * 16), (unsigned)n), dim3(256), 0, st, g);
+    return check_launch("relu");
+}
+
 // ---- LRN ---------------------------------------------------------------------------------------------
 // (s^-beta: pow_neg_beta in dr_store.h)
 
@@ -407,6 +447,14 @@ int launch_relu(int dtype, const void* x, void* y, size_t count, hipStream_t st)
     TraceScope trace("relu", nullptr, (long long)(count), st, 2ll * count * elem_size(dtype));
     return DR_BY_DTYPE(dtype, (relu_launch<float, false>(x, nullptr, y, count, st)),
                        (relu_launch<uint16_t, false>(x, nullptr, y, count, st)));
+}
+
+int launch_relu_group(int dtype, int n, void* const* p, const size_t* count, hipStream_t st)
+{
+    size_t total = 0;
+    for (int i = 0; i < n; ++i) total += count[i];
+    TraceScope trace("relu", nullptr, (long long)total, st, 2ll * total * elem_size(dtype));
+    return DR_BY_DTYPE(dtype, relu_group_launch<float>(n, p, count, st), relu_group_launch<uint16_t>(n, p, count, st));
 }
 
 int launch_add_relu(int dtype, const void* a, const void* b, void* y, size_t count, hipStream_t st)
