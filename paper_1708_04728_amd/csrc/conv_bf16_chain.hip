@@ -1,0 +1,237 @@
+// The 1x1 convolutions around the residual sum of a folded ResNet bottleneck (Sec. 4.2) in one pass over the pixels:
+//
+//   y  = max(W3 m + b3 + s, 0)                 m: the 3x3 layer's output, s: the block's input or Wp x + bp (projected shortcut)
+//   m' = max(W1' y + b1', 0)                   the first layer of the bottleneck behind it, if there is one
+//
+// What bounds these layers is HBM: 64 -> 256 with its residual moves 1.2 KB per pixel for 33 KFLOP.  As layers of their own the
+// projected shortcut is written and read once more, and y is read once more by the layer behind it.  Here both stay in registers.
+// After the lane exchange of the store a lane holds 8 consecutive filters of its pixel, rounded to bf16: that is the matrix
+// instruction's second operand for the next contraction over those filters (see pack_blocks), so m' takes y's registers as they are.
+//
+// A wave works alone: 32 pixels at a time, all filters, no barrier after the filters have reached LDS (each 1 KB fragment in the
+// order the lanes read it, so reads are free of bank conflicts).  The next 32 pixels' operands and residuals are requested while the current
+// ones are multiplied: 20 KB per wave in flight, eight waves per compute unit (one workgroup: the filters take up to 96 KB).
+// The sums run in the order of the streaming kernel and every tensor it would store is rounded where it would be: the same bits.
+#include "dr_internal.h"
+#include "dr_store.h"
+#include "conv_bf16_dev.h"
+
+namespace dr {
+namespace {
+
+constexpr int CHAIN_WAVES = 8, CHAIN_KS = CHAIN_MID / 16, CHAIN_OB = CHAIN_OUT / 32, CHAIN_FRAGS = CHAIN_OB * CHAIN_KS;
+
+struct ChainArgs {
+    ConvChain c;
+    int m_bytes, y_bytes, x_bytes, next_bytes;
+};
+
+__device__ __forceinline__ u32x4 load16(__amdgpu_buffer_rsrc_t r, int voff)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 0));
+#else
+    return u32x4{};
+#endif
+}
+__device__ __forceinline__ void store16(u32x4 v, __amdgpu_buffer_rsrc_t r, int voff)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, 0, 0);
+#endif
+}
+__device__ __forceinline__ f32x16 mfma(u32x4 a, u32x4 b, f32x16 c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+// result registers 8 qp .. 8 qp + 7 of both halves of a pixel -> 8 consecutive filters
+__device__ __forceinline__ void exchange(const f32x16& acc, int qp, float (&o)[8])
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[qp * 8 + e]), __float_as_uint(acc[qp * 8 + 4 + e]), false, false);
+        o[e] = __uint_as_float(sw[0]);
+        o[4 + e] = __uint_as_float(sw[1]);
+    }
+}
+__device__ __forceinline__ void add_bias(const float* b, float (&o)[8])
+{
+    const f32x4 lo = *reinterpret_cast<const f32x4*>(b), hi = *reinterpret_cast<const f32x4*>(b + 4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { o[e] += lo[e]; o[4 + e] += hi[e]; }
+}
+__device__ __forceinline__ void relu8(float (&o)[8])
+{
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = fmaxf(o[e], 0.f);
+}
+__device__ __forceinline__ u32x4 pack8(const float (&o)[8])
+{
+    u32x4 pk;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) pk[e] = pack_bf16x2(o[2 * e], o[2 * e + 1]);
+    return pk;
+}
+
+// PROJ: the shortcut is Wp x; NEXT: m' is computed
+template <bool PROJ, bool NEXT>
+__global__ __launch_bounds__(CHAIN_WAVES * 64) void conv_bf16_chain_kernel(const ChainArgs a)
+{
+    __shared__ u32x4 frag[(1 + PROJ + NEXT) * CHAIN_FRAGS * 64];
+    __shared__ __attribute__((aligned(16))) float bias[2 * CHAIN_OUT + CHAIN_MID];
+    const ConvChain& c = a.c;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5, l32 = lane & 31;
+    u32x4* const f_out = frag;
+    u32x4* const f_proj = frag + (PROJ ? CHAIN_FRAGS * 64 : 0);
+    u32x4* const f_next = frag + (1 + PROJ) * CHAIN_FRAGS * 64;
+
+    // ---- filters and biases, zeros beyond the layers' own: fragment (i, ks) holds filters 32 i .., channels 16 ks .. of a bank
+    auto bank = [&](u32x4* dst, const uint16_t* w, int rows, int cols, int ksteps) {
+        for (int e = tid; e < CHAIN_FRAGS * 64; e += CHAIN_WAVES * 64) {
+            const int f = e >> 6, i = f / ksteps, ks = f - i * ksteps;
+            const int row = i * 32 + (e & 31), col = ks * 16 + ((e >> 5) & 1) * 8;
+            dst[e] = row < rows && col < cols ? *reinterpret_cast<const u32x4*>(w + (size_t)row * cols + col) : u32x4{0u, 0u, 0u, 0u};
+        }
+    };
+    bank(f_out, c.w, c.out, c.mid, CHAIN_KS);
+    if constexpr (PROJ) bank(f_proj, c.w_proj, c.out, c.c_in, CHAIN_KS);
+    if constexpr (NEXT) bank(f_next, c.w_next, c.next, c.out, 2 * CHAIN_OB);
+    for (int e = tid; e < CHAIN_OUT; e += CHAIN_WAVES * 64) {
+        bias[e] = c.bias && e < c.out ? c.bias[e] : 0.f;
+        if constexpr (PROJ) bias[CHAIN_OUT + e] = c.bias_proj && e < c.out ? c.bias_proj[e] : 0.f;
+        if constexpr (NEXT)
+            if (e < CHAIN_MID) bias[2 * CHAIN_OUT + e] = c.bias_next && e < c.next ? c.bias_next[e] : 0.f;
+    }
+    __syncthreads();
+
+    const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc((void*)c.m, 0, a.m_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)c.x, 0, a.x_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void*)c.y, 0, a.y_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rn = __builtin_amdgcn_make_buffer_rsrc((void*)c.m_next, 0, a.next_bytes, 0x00020000);
+    const int blocks = (c.pixels + 31) >> 5, stride = (int)gridDim.x * CHAIN_WAVES;
+    // channels ch .. ch + 7 of pixel n of a tensor of C channels; outside it (also: no pixel) an offset the hardware answers with zeros
+    auto at = [&](int n, int C, int ch) __attribute__((always_inline)) { return n < c.pixels && ch < C ? (n * C + ch) * 2 : OOB; };
+
+    u32x4 vm[CHAIN_KS], vx[PROJ ? CHAIN_KS : 1], res[PROJ ? 1 : 2 * CHAIN_OB];
+    int blk = (int)blockIdx.x + wave * (int)gridDim.x;
+    {
+        const int n = blk * 32 + l32;
+#pragma unroll
+        for (int ks = 0; ks < CHAIN_KS; ++ks) {
+            vm[ks] = load16(rm, at(n, c.mid, ks * 16 + half * 8));
+            if constexpr (PROJ) vx[ks] = load16(rx, at(n, c.c_in, ks * 16 + half * 8));
+        }
+        if constexpr (!PROJ) {
+#pragma unroll
+            for (int q = 0; q < 2 * CHAIN_OB; ++q) res[q] = load16(rx, at(n, c.out, q * 16 + half * 8));
+        }
+    }
+    for (; blk < blocks; blk += stride) {
+        const int n = blk * 32 + l32, nn = n + stride * 32;          // this lane's pixel now and in the next round
+        u32x4 vm_n[CHAIN_KS], vx_n[PROJ ? CHAIN_KS : 1];
+#pragma unroll
+        for (int ks = 0; ks < CHAIN_KS; ++ks) {
+            vm_n[ks] = load16(rm, at(nn, c.mid, ks * 16 + half * 8));
+            if constexpr (PROJ) vx_n[ks] = load16(rx, at(nn, c.c_in, ks * 16 + half * 8));
+        }
+        // (the filters and biases read below are the same in every round: without this the compiler would fetch all of them ahead
+        // of the loop, into registers it does not have)
+        int fl = lane, bl = half * 8;
+        asm volatile("" : "+v"(fl), "+v"(bl));
+        f32x16 sum_next[2];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) sum_next[0][v] = sum_next[1][v] = 0.f;
+#pragma unroll
+        for (int i = 0; i < CHAIN_OB; ++i) {
+            f32x16 acc, accp;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[v] = accp[v] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < CHAIN_KS; ++ks) {
+                acc = mfma(f_out[(i * CHAIN_KS + ks) * 64 + fl], vm[ks], acc);
+                if constexpr (PROJ) accp = mfma(f_proj[(i * CHAIN_KS + ks) * 64 + fl], vx[ks], accp);
+            }
+#pragma unroll
+            for (int qp = 0; qp < 2; ++qp) {
+                const int ch = i * 32 + qp * 16 + half * 8;
+                float o[8];
+                exchange(acc, qp, o);
+                add_bias(bias + i * 32 + qp * 16 + bl, o);
+                u32x4 s;
+                if constexpr (PROJ) {
+                    float op[8];
+                    exchange(accp, qp, op);
+                    add_bias(bias + CHAIN_OUT + i * 32 + qp * 16 + bl, op);
+                    s = pack8(op);
+                } else {
+                    s = res[2 * i + qp];
+                    res[2 * i + qp] = load16(rx, at(nn, c.out, ch));
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    o[2 * e] += __uint_as_float(s[e] << 16);
+                    o[2 * e + 1] += __uint_as_float(s[e] & 0xFFFF0000u);
+                }
+                relu8(o);
+                const u32x4 pk = pack8(o);
+                store16(pk, ry, at(n, c.out, ch));
+                if constexpr (NEXT) {
+#pragma unroll
+                    for (int mb = 0; mb < 2; ++mb) sum_next[mb] = mfma(f_next[(mb * 2 * CHAIN_OB + 2 * i + qp) * 64 + fl], pk, sum_next[mb]);
+                }
+            }
+        }
+        if constexpr (NEXT) {
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+                for (int qp = 0; qp < 2; ++qp) {
+                    const int ch = mb * 32 + qp * 16 + half * 8;
+                    float o[8];
+                    exchange(sum_next[mb], qp, o);
+                    add_bias(bias + 2 * CHAIN_OUT + mb * 32 + qp * 16 + bl, o);
+                    relu8(o);
+                    store16(pack8(o), rn, at(n, c.next, ch));
+                }
+        }
+#pragma unroll
+        for (int ks = 0; ks < CHAIN_KS; ++ks) {
+            vm[ks] = vm_n[ks];
+            if constexpr (PROJ) vx[ks] = vx_n[ks];
+        }
+    }
+}
+
+template <bool PROJ, bool NEXT>
+int launch_chain(const ChainArgs& a, hipStream_t st)
+{
+    const int blocks = (a.c.pixels + 31) / 32, cus = device_cus();
+    hipLaunchKernelGGL((conv_bf16_chain_kernel<PROJ, NEXT>), dim3((unsigned)(blocks < cus ? blocks : cus)), dim3(CHAIN_WAVES * 64), 0, st, a);
+    return check_launch("conv_bf16_chain");
+}
+
+}  // namespace
+
+// Whole 16-byte channel groups, widths the kernel's registers hold, 32-bit offsets (also for the pixels a wave asks for past the end).
+bool conv_bf16_chain_eligible(const ConvChain& c)
+{
+    const auto width = [](int v, int most) { return v >= 8 && v % 8 == 0 && v <= most; };
+    if (!width(c.mid, CHAIN_MID) || !width(c.out, CHAIN_OUT) || !width(c.c_in, c.w_proj ? CHAIN_MID : CHAIN_OUT) || (!c.w_proj && c.c_in != c.out)) return false;
+    if (c.w_next && !width(c.next, CHAIN_MID)) return false;
+    if (!aligned16(c.m) || !aligned16(c.x) || !aligned16(c.y) || !aligned16(c.m_next) || !aligned16(c.w) || !aligned16(c.w_proj) || !aligned16(c.w_next)) return false;
+    return c.pixels > 0 && c.pixels < (1 << 24) && (double)c.pixels * c.out * 2.0 < 2147483648.0;
+}
+
+int launch_conv_bf16_chain(const ConvChain& c, hipStream_t st)
+{
+    ChainArgs a;
+    a.c = c;
+    a.m_bytes = c.pixels * c.mid * 2;
+    a.x_bytes = c.pixels * c.c_in * 2;
+    a.y_bytes = c.pixels * c.out * 2;
+    a.next_bytes = c.w_next ? c.pixels * c.next * 2 : 0;
+    if (c.w_proj) return c.w_next ? launch_chain<true, true>(a, st) : launch_chain<true, false>(a, st);
+    return c.w_next ? launch_chain<false, true>(a, st) : launch_chain<false, false>(a, st);
+}
+
+}  // namespace dr

@@ -91,6 +91,19 @@ int launch_conv_bf16_dma(const ConvGeom& g, const uint16_t* x, const uint16_t* w
 bool conv_bf16_small_takes(const ConvGeom& g, const void* x, const void* w);
 int launch_conv_bf16_small(const ConvSmall* jobs, int n, hipStream_t st);
 
+// conv_bf16_chain.hip: the expanding 1x1 convolution of a folded bottleneck with its shortcut, and the first layer of the bottleneck
+// behind it.  bf16 channels-last; filters [k][c].
+constexpr int CHAIN_MID = 64, CHAIN_OUT = 256;      // most channels of m, m_next (and of x with w_proj); of y
+struct ConvChain {
+    int pixels, mid, out, c_in, next;
+    const uint16_t *m, *x;                   // the 3x3 layer's output; the block's input
+    const uint16_t *w, *w_proj, *w_next;     // w_proj NULL: the shortcut is x itself; w_next NULL: no layer behind
+    const float *bias, *bias_proj, *bias_next;      // may be NULL
+    uint16_t *y, *m_next;
+};
+bool conv_bf16_chain_eligible(const ConvChain& c);
+int launch_conv_bf16_chain(const ConvChain& c, hipStream_t st);
+
 // conv_bf16_patch.hip: filters of several taps at stride 1, C % 64 == 0, maps at most 256 pixels wide whose patch of
 // TH + R - 1 input rows fits LDS: the tile's input patch is loaded once and every tap multiplies from there
 bool conv_bf16_patch_eligible(const ConvGeom& g, const void* x, const void* w, const void* y);

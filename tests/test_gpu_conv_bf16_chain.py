@@ -1,0 +1,71 @@
+"""GPU parity of the kernel that runs the end of a folded bottleneck (expansion, shortcut, the next block's first layer) in one pass:
+the same bits as the layers run one after the other (which is what a kernel trace makes the library do), and the oracle's
+result, at the edges of its 32-pixel blocks, its 16-channel steps and its widths."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from paper_1708_04728_amd import binding as B, graph as G
+from test_gpu_bf16_nets import folded_params
+from util import TOL_BF16, case_seed, close
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def bn(k, rng):
+    return {"gamma": rng.uniform(0.5, 1.5, k).astype(np.float32), "beta": (rng.standard_normal(k) * 0.1).astype(np.float32),
+            "mean": (rng.standard_normal(k) * 0.1).astype(np.float32), "var": rng.uniform(0.5, 1.5, k).astype(np.float32)}
+
+
+def stage(rng, c, blocks):
+    """Bottlenecks (mid, out) on c channels and their folded parameters; the shortcut is projected where the widths differ or for the first."""
+    layers, params = [], []
+    for i, (mid, out) in enumerate(blocks):
+        project = i == 0 or c != out
+        layers.append(workloads.bottleneck(mid, out, project))
+        for k, r, ci in ((mid, 1, c), (mid, 3, mid), (out, 1, mid)) + (((out, 1, c),) if project else ()):
+            w = rng.standard_normal((k, ci, r, r)).astype(np.float32) * np.float32(np.sqrt(2.0 / (ci * r * r)))
+            params += [{"w": w, "b": (rng.standard_normal(k) * 0.1).astype(np.float32)}, bn(k, rng)]
+        c = out
+    return layers, folded_params(params)
+
+
+@pytest.mark.parametrize("case", [
+    # N, C, H, W, ((mid, out), ...)
+    (1, 8, 1, 1, ((8, 8),)),                                   # one pixel, one channel group
+    (1, 64, 4, 8, ((64, 256), (64, 256))),                     # one whole block of pixels
+    (1, 64, 3, 11, ((64, 256), (64, 256), (64, 256))),         # 33 pixels
+    (2, 24, 5, 3, ((40, 72), (40, 72))),                       # ragged steps, 30 pixels
+    (3, 56, 17, 19, ((48, 200), (32, 200), (32, 248))),        # a narrower block behind, then a projected one on too many channels
+    (1, 64, 9, 9, ((32, 128), (64, 128), (64, 264))),          # a wider block behind (not joined), an output too wide for the kernel
+    (9, 64, 61, 59, ((64, 256), (64, 256))),                   # several rounds of every wave, the last one not whole
+])
+def test_chain(case):
+    n, c, h, w, blocks = case
+    rng = np.random.default_rng(case_seed(case))
+    layers, params = stage(rng, c, blocks)
+    x = workloads.round_to_bf16(np.abs(rng.standard_normal((n, c, h, w))).astype(np.float32))
+    xg = G.to_device(x, "bf16", nhwc=True)
+    net = B.Net(G.net_descs(layers, c, folded=True, pack="bf16"))
+    flat = G.flat_params(params, "bf16", pack=True)
+    ws = torch.empty(max(net.workspace_bytes(B.desc(xg)), 256), dtype=torch.uint8, device="cuda")
+    out = []
+    for traced in (False, True, False):
+        y = G.empty_like_desc(net.output_desc(B.desc(xg)))
+        y.t.fill_(float("nan"))
+        ws.fill_(255)                                          # NaN where nothing has been written
+        if traced:
+            B.trace_begin()
+        net.fwd(xg, flat, y, ws)
+        torch.cuda.synchronize()
+        if traced:
+            B.trace_end()
+        out.append(G.to_host(y))
+    assert np.isfinite(out[0]).all()
+    assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2])
+    if n * h * w < 4000:
+        ref = oracle.forward(layers, params, x, mirror_bf16=True, fold="given")
+        # two implementations that round every stored tensor to bf16: 2e-2 per rounding in quadrature, 3 per block
+        assert close(out[0], ref, TOL_BF16 * (3 * len(blocks)) ** 0.5, "oracle with bf16 storage")
