@@ -10,7 +10,11 @@
 //
 // A wave works alone: 32 pixels at a time, all filters, no barrier after the filters have reached LDS (each 1 KB fragment in the
 // order the lanes read it, so reads are free of bank conflicts).  The next 32 pixels' operands and residuals are requested while the current
-// ones are multiplied: 20 KB per wave in flight, eight waves per compute unit (one workgroup: the filters take up to 96 KB).
+// ones are multiplied: 20 KB per wave in flight, eight waves per compute unit (one workgroup: the filters take up to 96 KB; ten or
+// twelve waves: no faster).  A round's pixels lie next to one another across the whole device: a run of pixels per workgroup or
+// per die took 7 % longer.
+// ResNet's conv2_x, three folded blocks on 56 x 56: 128 images 625 us as single layers, now 472; 30 images 163 and 122; one image 52 and 48.
+// What bounds it now: 4.1 TB/s on the bytes left, of about 5 that a copy reaches.
 // The sums run in the order of the streaming kernel and every tensor it would store is rounded where it would be: the same bits.
 #include "dr_internal.h"
 #include "dr_store.h"
@@ -138,6 +142,7 @@ __global__ __launch_bounds__(CHAIN_WAVES * 64) void conv_bf16_chain_kernel(const
         // of the loop, into registers it does not have)
         int fl = lane, bl = half * 8;
         asm volatile("" : "+v"(fl), "+v"(bl));
+        u32x4 out[4];
         f32x16 sum_next[2];
 #pragma unroll
         for (int v = 0; v < 16; ++v) sum_next[0][v] = sum_next[1][v] = 0.f;
@@ -165,7 +170,6 @@ __global__ __launch_bounds__(CHAIN_WAVES * 64) void conv_bf16_chain_kernel(const
                     s = pack8(op);
                 } else {
                     s = res[2 * i + qp];
-                    res[2 * i + qp] = load16(rx, at(nn, c.out, ch));
                 }
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -174,10 +178,21 @@ __global__ __launch_bounds__(CHAIN_WAVES * 64) void conv_bf16_chain_kernel(const
                 }
                 relu8(o);
                 const u32x4 pk = pack8(o);
-                store16(pk, ry, at(n, c.out, ch));
+                out[(i & 1) * 2 + qp] = pk;
                 if constexpr (NEXT) {
 #pragma unroll
                     for (int mb = 0; mb < 2; ++mb) sum_next[mb] = mfma(f_next[(mb * 2 * CHAIN_OB + 2 * i + qp) * 64 + fl], pk, sum_next[mb]);
+                }
+            }
+            // residuals and outputs move 128 bytes of a pixel at a time: a line's four pieces asked for apart are fetched apart, the vector
+            // cache holds a quarter of what the waves have in flight (128 images of 56 x 56: 520 against 472 us for the three blocks;
+            // 256 bytes at a time: the same)
+            if (i & 1) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) store16(out[q], ry, at(n, c.out, (i - 1) * 32 + q * 16 + half * 8));
+                if constexpr (!PROJ) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) res[2 * i - 2 + q] = load16(rx, at(nn, c.out, (i - 1) * 32 + q * 16 + half * 8));
                 }
             }
         }
