@@ -232,9 +232,9 @@ typedef struct { int kind; dr_conv conv; dr_pool pool; } dr_step;
 typedef struct { int n_steps; dr_step steps[DR_MAX_STEPS]; } dr_branch;
 
 /* How the module is executed.  0 = the layer-by-layer form the paper times: every ReLU is its own
- * kernel and the branch outputs are gathered by a concat kernel.  (In every mode the bf16 NHWC convolutions at one depth of
- * the branches, and a 3x3 pooling step beside them, may share a launch where each is small; each still reads its whole
- * input and writes its whole output.)  Flags remove passes without changing the function computed: */
+ * kernel and the branch outputs are gathered by a concat kernel.  (In every mode the convolutions at one depth of the
+ * branches, a 3x3 pooling step beside them, and the ReLUs behind them may share a launch each where the layers are
+ * small; each layer still reads its whole input and writes its whole output.)  Flags remove passes without changing the function computed: */
 #define DR_FUSE_RELU   1   /* ReLU in the convolution's store */
 #define DR_FUSE_CONCAT 2   /* a branch ending in a convolution writes its channel range of y directly
                               (that convolution then also applies its ReLU in the store) */
@@ -316,12 +316,14 @@ int dr_net_workspace_bytes(const dr_net* net, const dr_tensor* xd, size_t* bytes
 /* Runs the layer list on x.  params: host array of dr_net_num_params device pointers.  The output
  * has the dtype of the input except after a softmax layer (fp32).  ws: at least
  * dr_net_workspace_bytes, 256-byte aligned.
- * Layers run one after the other with one exception, which changes no value: a bf16 NHWC
+ * Layers run one after the other with two exceptions, which change no value.  A bf16 NHWC
  * convolution on at most 4 input channels (a network's first layer) with at most 64 filters and
  * a 1x1 convolution with at most 64 filters right behind it run as ONE kernel when the first
  * layer's kernel takes the pair; the tensor between them (rounded to bf16 as it would be stored)
- * stays in registers and is never written.  Per-layer timing then books the kernel under the
- * first of the two layers; the second shows only the gap between two event records. */
+ * stays in registers and is never written.  And the last 1x1 convolution of a folded bf16 NHWC bottleneck runs with
+ * its projected shortcut and with the first 1x1 convolution of a folded bottleneck right behind it as ONE kernel
+ * (at most 64 inner and 256 outer channels, KRSC filters; not during a kernel trace).  Per-layer timing books such a
+ * kernel under the first of the two layers; the second then shows only what is left of it. */
 int dr_net_fwd(dr_net* net, const dr_tensor* xd, const void* x, const void* const* params,
                const dr_tensor* yd, void* y, void* ws, size_t ws_bytes, void* stream);
 
