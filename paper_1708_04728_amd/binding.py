@@ -203,13 +203,15 @@ def _ptr(t):
 _pack_pointers = {}                     # number of pointers -> struct.Struct("nQ").pack
 
 
-def _ptrs(ts):
-    """Host array of the tensors' device pointers (bytes, read during the call only); None -> NULL."""
-    n = len(ts)
-    pack = _pack_pointers.get(n)
+def _ptrs(ts, n=1):
+    """Host array of the tensors' device pointers (bytes, read during the call only), padded with NULL to at least n; None -> NULL."""
+    v = [0 if t is None else t.data_ptr() for t in ts]
+    if len(v) < n:
+        v += [0] * (n - len(v))
+    pack = _pack_pointers.get(len(v))
     if pack is None:
-        pack = _pack_pointers[n] = struct.Struct("%dQ" % n).pack
-    return pack(*[0 if t is None else t.data_ptr() for t in ts])
+        pack = _pack_pointers[len(v)] = struct.Struct("%dQ" % len(v)).pack
+    return pack(*v)
 
 
 def _nbytes(t):
@@ -390,7 +392,7 @@ def inception_workspace_bytes(x, idesc):
 
 
 def inception_fwd(x, idesc, weights, biases, y, ws, stream=None):
-    _check(lib().dr_inception_fwd(desc(x), _ptr(x), idesc, _ptrs(weights), _ptrs(biases), desc(y), _ptr(y), _ptr(ws), _nbytes(ws), _stream(stream)))
+    _check(lib().dr_inception_fwd(desc(x), _ptr(x), idesc, _ptrs(weights), _ptrs(biases, len(weights)), desc(y), _ptr(y), _ptr(ws), _nbytes(ws), _stream(stream)))
     return y
 
 

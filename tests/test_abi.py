@@ -202,3 +202,13 @@ def test_stack_first_steps_lays_reducers_back_to_back():
             assert w1.data_ptr() == w0.data_ptr() + w0.numel() * w0.element_size()
             assert b1.data_ptr() == b0.data_ptr() + b0.numel() * b0.element_size()
         pos = j
+
+
+def test_pointer_arrays_reach_as_far_as_the_library_reads():
+    """No parameters at all, or fewer biases than weights, are NULL pointers to the library and not whatever lies behind the array."""
+    w = np.zeros(4, np.float32)
+    tensors = [type("T", (), {"data_ptr": lambda self: w.ctypes.data})() for _ in range(3)]
+    assert B._ptrs([]) == bytes(8)
+    assert B._ptrs([], 3) == bytes(24)
+    assert B._ptrs([tensors[0], None], 3) == (w.ctypes.data).to_bytes(8, "little") + bytes(16)
+    assert B._ptrs(tensors, 3) == 3 * (w.ctypes.data).to_bytes(8, "little")
