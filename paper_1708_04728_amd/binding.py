@@ -392,6 +392,8 @@ def inception_workspace_bytes(x, idesc):
 
 
 def inception_fwd(x, idesc, weights, biases, y, ws, stream=None):
+    if len(biases) > len(weights):
+        raise IndexError("more biases than weights")
     _check(lib().dr_inception_fwd(desc(x), _ptr(x), idesc, _ptrs(weights), _ptrs(biases, len(weights)), desc(y), _ptr(y), _ptr(ws), _nbytes(ws), _stream(stream)))
     return y
 

@@ -212,3 +212,5 @@ def test_pointer_arrays_reach_as_far_as_the_library_reads():
     assert B._ptrs([], 3) == bytes(24)
     assert B._ptrs([tensors[0], None], 3) == (w.ctypes.data).to_bytes(8, "little") + bytes(16)
     assert B._ptrs(tensors, 3) == 3 * (w.ctypes.data).to_bytes(8, "little")
+    with pytest.raises(IndexError):
+        B.inception_fwd(None, None, [], [None], None, None)
