@@ -124,7 +124,9 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// TPT: taps per column tile (64 channels of one tap, 32 of two, 16 of four).  Bound by the fp32 matrix cores; what the loop adds to the
+// TPT: taps per column tile (64 channels of one tap, 32 of two, 16 of four; 8 of eight or 4 of sixteen where a layer on the
+// image would leave most of 16 channels empty: 11x11 3 -> 96 at stride 4 on 227 x 227 x 32 images 531 us with 16, 173 with 4; 7x7 3 -> 64 at
+// stride 2 453 and 184; 5x5 8 -> 64 on 56 x 56 x 32 75 and 59).  Bound by the fp32 matrix cores; what the loop adds to the
 // 16 matrix instructions of a slice is kept to a couple of instructions per loaded element: a thread's eight columns
 // belong to TPT taps, so the padding test is made TPT times per slice (with columns in (c, r, s) order it was made for every
 // element and that arithmetic took longer than the multiplications), the rest of an address is a per-thread constant, and
@@ -135,7 +137,7 @@ __global__ __launch_bounds__(256) void conv_wgrad_f32_kernel(const WArgs a)
 {
     __shared__ __attribute__((aligned(16))) float As[2][BM * LDT];
     __shared__ __attribute__((aligned(16))) float Bs[2][BN * LDT];
-    constexpr int CB = BN / TPT, IPT = 8 / TPT;            // channels per tile; a thread's columns per tap
+    constexpr int CB = BN / TPT, NT = TPT < 8 ? TPT : 8, IPT = 8 / NT;     // channels per tile; taps of a thread's columns; columns per tap
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1, half = lane >> 5, l32 = lane & 31;
     // workgroup b runs on die b & 7: a die takes a contiguous range of (split, column tile, row tile), so that the tiles of one
@@ -154,16 +156,18 @@ __global__ __launch_bounds__(256) void conv_wgrad_f32_kernel(const WArgs a)
     // does not exist has the offset OOB; whatever is then read belongs to an output that is not stored.
     const int ll = tid & 31, row0 = tid >> 5;
     const int tg = nt / a.cblocks, c0 = (nt - tg * a.cblocks) * CB;
-    int a_row[8], b_row[8], tap_r[TPT], tap_s[TPT];
+    // column row0 + 8 i: tap i / IPT and channel row0 + 8 (i % IPT) of the tile; with tiles of 4 channels tap 2 i + row0 / 4, channel row0 % 4
+    auto tap_of = [&](int t) __attribute__((always_inline)) { return tg * TPT + (TPT > 8 ? 2 * t + (row0 >> 2) : t); };
+    int a_row[8], b_row[8], tap_r[NT], tap_s[NT];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        const int m = m0 + row0 + 8 * i, c = c0 + row0 + 8 * (i % IPT);
+        const int m = m0 + row0 + 8 * i, c = c0 + (TPT > 8 ? row0 & 3 : row0 + 8 * (i % IPT));
         a_row[i] = m < a.K ? m * PQ * 4 : OOB;
-        b_row[i] = c < a.C && tg * TPT + i / IPT < RS ? c * HW * 4 : OOB;
+        b_row[i] = c < a.C && tap_of(i / IPT) < RS ? c * HW * 4 : OOB;
     }
 #pragma unroll
-    for (int t = 0; t < TPT; ++t) {
-        const int rs = tg * TPT + t, r = rs / a.S;
+    for (int t = 0; t < NT; ++t) {
+        const int rs = tap_of(t), r = rs / a.S;
         tap_r[t] = r - a.ph; tap_s[t] = rs - r * a.S - a.pw;
     }
     // the slice being fetched: image, first (p, q) run element and this thread's own
@@ -179,7 +183,7 @@ __global__ __launch_bounds__(256) void conv_wgrad_f32_kernel(const WArgs a)
 #pragma unroll
         for (int i = 0; i < 8; ++i) ra[SET][i] = buf_load(rz, a_row[i] + za, soff_a);
 #pragma unroll
-        for (int t = 0; t < TPT; ++t) {
+        for (int t = 0; t < NT; ++t) {
             const int ih = ih0 + tap_r[t], iw = iw0 + tap_s[t];
             const int xo = on && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W ? (ih * a.W + iw) * 4 : OOB;
 #pragma unroll
@@ -290,7 +294,8 @@ __global__ __launch_bounds__(256) void sgd_step_kernel(float* __restrict__ w, co
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (size_t)gridDim.x * 256) w[i] = w[i] - lr * dw[i];
 }
 
-// How the gradient's GEMM is tiled and split: column tiles of 64, 32 or 16 channels per tap (whichever gives the fewest), and as many
+// How the gradient's GEMM is tiled and split: column tiles of 64 to 4 channels per tap (whichever gives the fewest, the most channels first:
+// a tap costs a padding test), and as many
 // ranges of slices as make up to four workgroups per compute unit, of at least four slices each.
 struct WPlan { int cb_log2, cblocks, grid_m, grid_n, slices_per_img, slices, splits; };
 WPlan wgrad_plan(const ConvGeom& g)
@@ -298,7 +303,7 @@ WPlan wgrad_plan(const ConvGeom& g)
     WPlan p{};
     const int RS = g.R * g.S;
     int best = 0;
-    for (int l = 6; l >= 4; --l) {
+    for (int l = 6; l >= 2; --l) {
         const int tpt = BN >> l, cblocks = (g.C + (1 << l) - 1) >> l, n = (RS + tpt - 1) / tpt * cblocks;
         if (best && n >= best) continue;
         best = n; p.cb_log2 = l; p.cblocks = cblocks; p.grid_n = n;
@@ -351,7 +356,9 @@ int launch_conv_wgrad_f32(const ConvGeom& g, const float* x, const float* dz, fl
         const dim3 grid((unsigned)(a.grid_m * a.grid_n * a.splits)), block(256);
         if (p.cb_log2 == 6) hipLaunchKernelGGL(conv_wgrad_f32_kernel<1>, grid, block, 0, st, a);
         else if (p.cb_log2 == 5) hipLaunchKernelGGL(conv_wgrad_f32_kernel<2>, grid, block, 0, st, a);
-        else hipLaunchKernelGGL(conv_wgrad_f32_kernel<4>, grid, block, 0, st, a);
+        else if (p.cb_log2 == 4) hipLaunchKernelGGL(conv_wgrad_f32_kernel<4>, grid, block, 0, st, a);
+        else if (p.cb_log2 == 3) hipLaunchKernelGGL(conv_wgrad_f32_kernel<8>, grid, block, 0, st, a);
+        else hipLaunchKernelGGL(conv_wgrad_f32_kernel<16>, grid, block, 0, st, a);
     }
     if (const int rc = check_launch("conv_wgrad")) return rc;
     if (a.splits > 1) {

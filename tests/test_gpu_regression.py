@@ -41,6 +41,9 @@ WGRAD_CASES = [
     (5, 8, 10, 6, 64, 1, 1, 1, 0),        # 1x1
     (1, 4, 31, 29, 9, 7, 7, 4, 3),        # one image (no partial sums), 7x7 stride 4
     (40, 2, 6, 6, 3, 3, 2, (2, 1), (1, 0)),  # many images: several per workgroup, non-square filter and stride
+    (3, 8, 13, 9, 65, 3, 3, 1, 1),        # tiles of eight taps by 8 channels, one tap in the second
+    (2, 9, 12, 11, 20, 4, 4, 1, 1),       # tiles of sixteen taps by 4 channels, one channel in the third
+    (2, 3, 43, 39, 33, 11, 11, 4, 0),     # a layer on the image: eight tiles of sixteen taps, nine taps in the last
 ]
 
 
