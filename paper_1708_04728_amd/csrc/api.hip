@@ -431,7 +431,7 @@ BranchStreams* branch_streams()
 bool small_takes(int dtype, const ConvGeom& g, const void* x, const void* w)
 {
     if (g.Ng == 0) return false;
-    return dtype == DR_BF16 ? conv_bf16_small_takes(g, x, w) : conv_f32_small_takes(g, true);
+    return dtype == DR_BF16 ? conv_bf16_small_takes(g, x, w) : conv_f32_small_takes(g, w, true);
 }
 
 // The stacked first steps of a module (see inception_run).  Marks the branches it has served in `stacked`

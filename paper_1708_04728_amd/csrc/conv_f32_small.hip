@@ -224,10 +224,11 @@ long small_tiles(const ConvGeom& g) { return ((long)g.Ng + 31) / 32 * ((g.K + 31
 // has scratch for that (1x1 filters excepted, for which the line is drawn by pixels alone so that a convolution over stacked
 // filter banks keeps the sums of one convolution per bank): a tile alone on its compute unit takes 0.1 us per slice (3x3 192 -> 384 on one 7 x 7 map: 24 tiles,
 // 108 slices, 10.2 against 13.5).
-bool conv_f32_small_takes(const ConvGeom& g, bool scratch)
+// Filters are fetched 16 bytes at a time straight into LDS: they start on such a boundary.
+bool conv_f32_small_takes(const ConvGeom& g, const void* w, bool scratch)
 {
     const size_t xb = (size_t)g.N * g.C * g.H * g.W * 4, wb = (size_t)g.K * g.Kg * 4;
-    if (g.nhwc || g.C % 16 != 0 || (!g.w_krsc && g.R * g.S != 1) || xb >= (1ull << 31) || wb >= (1ull << 31)) return false;
+    if (g.nhwc || g.C % 16 != 0 || (!g.w_krsc && g.R * g.S != 1) || !aligned16(w) || xb >= (1ull << 31) || wb >= (1ull << 31)) return false;
     if (g.R * g.S == 1) return g.Ng <= 4096;
     const long tiles = small_tiles(g);
     if (scratch && tiles <= 64 && g.Kg > 1024) return false;

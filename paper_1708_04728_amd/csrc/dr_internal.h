@@ -59,7 +59,7 @@ int launch_conv_bf16(const ConvGeom& g, const uint16_t* x, const uint16_t* w, co
                      const uint16_t* residual, uint16_t* y, hipStream_t st);
 
 // conv_f32_small.hip, conv_bf16_small.hip: layers of few output pixels, several of them per launch (one data type each).  fp32: NCHW,
-// C % 16 == 0, KRSC filters or 1x1.  bf16: a convolution the streaming kernel takes or, with w = NULL, a 3x3 max-pooling
+// C % 16 == 0, KRSC filters or 1x1, 16-byte aligned.  bf16: a convolution the streaming kernel takes or, with w = NULL, a 3x3 max-pooling
 // layer of channels-last tensors with C % 8 == 0 and 16-byte aligned pointers (g: its input, output and window).
 constexpr int SMALL_GROUP_MAX = 4;
 struct ConvSmall {
@@ -71,7 +71,7 @@ struct ConvSmall {
     const ConvSplit* split;      // destinations of a stacked convolution, or NULL
     int stem_hp, stem_wp;        // bf16: x and w are the copies launch_conv_bf16_stem takes (0: ordinary layer)
 };
-bool conv_f32_small_takes(const ConvGeom& g, bool scratch);      // scratch: the caller can have the contraction cut over workgroups instead
+bool conv_f32_small_takes(const ConvGeom& g, const void* w, bool scratch);      // scratch: the caller can have the contraction cut over workgroups instead
 int launch_conv_f32_small(const ConvSmall* jobs, int n, hipStream_t st);
 // conv_f32.hip: several larger fp32 layers (KRSC filters, C % 16 == 0) in one launch
 bool conv_f32_group_takes(const ConvGeom& g);

@@ -50,6 +50,22 @@ def test_small_layer(case):
             assert close(host(y), ref, TOL_F32)
 
 
+def test_filters_on_any_word():
+    """Filters that start 4 bytes behind a 16-byte boundary (a slice of a parameter buffer): not the small-layer kernel's."""
+    rng = np.random.default_rng(5)
+    x = rng.standard_normal((1, 32, 14, 14)).astype(np.float32)
+    w = (rng.standard_normal((40, 32, 3, 3)) * np.sqrt(2.0 / (32 * 9))).astype(np.float32)
+    packed = B.pack_filters(gpu(w))
+    room = torch.empty(packed.numel() + 1, device="cuda")
+    shifted = room[1:].view(packed.shape)
+    shifted.copy_(packed)
+    assert shifted.data_ptr() % 16 == 4
+    y = torch.full((1, 40, 14, 14), float("nan"), device="cuda")
+    B.conv2d_fwd(gpu(x), B.conv_desc(40, 32, 3, 3, 1, 1, False, B.DR_KRSC), shifted, None, y)
+    torch.cuda.synchronize()
+    assert close(host(y), oracle.conv2d(x, w, None, 1, 1, False), TOL_F32)
+
+
 @pytest.mark.parametrize("form", ["original", "slim"])
 def test_module_whose_branches_share_launches(form):
     """A module on two ragged maps in every mode, packed filters, channel ranges of the output, stacked first steps."""
