@@ -224,6 +224,9 @@ long small_tiles(const ConvGeom& g) { return ((long)g.Ng + 31) / 32 * ((g.K + 31
 // has scratch for that (1x1 filters excepted, for which the line is drawn by pixels alone so that a convolution over stacked
 // filter banks keeps the sums of one convolution per bank): a tile alone on its compute unit takes 0.1 us per slice (3x3 192 -> 384 on one 7 x 7 map: 24 tiles,
 // 108 slices, 10.2 against 13.5).
+// A strided row spreads the 32 pixels of a load over more lines, and every filter block reads them again: 5x5 96 -> 256 at stride 2 on 28 x 28
+// takes 29.0 us tiled and 33.9 here on 6 images (296 tiles), 67 and 75 on 18, 98 and 113 on 28 (at stride 1 the same output: 95 and
+// 74); contractions of up to 75 slices still gain or tie (5x5 32 -> 256 on 28 images 38 -> 35, 3x3 128 -> 128 34 -> 33).
 // Filters are fetched 16 bytes at a time straight into LDS: they start on such a boundary.
 bool conv_f32_small_takes(const ConvGeom& g, const void* w, bool scratch)
 {
@@ -232,6 +235,7 @@ bool conv_f32_small_takes(const ConvGeom& g, const void* w, bool scratch)
     if (g.R * g.S == 1) return g.Ng <= 4096;
     const long tiles = small_tiles(g);
     if (scratch && tiles <= 64 && g.Kg > 1024) return false;
+    if (g.sw > 1 && g.Kg > 1200 && tiles > device_cus()) return false;
     return tiles <= 11 * device_cus() / 2;
 }
 
