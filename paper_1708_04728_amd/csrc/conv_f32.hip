@@ -30,7 +30,7 @@
 //        whole wave, so its table entry arrives by one broadcast LDS read and the lane adds its
 //        pixel's base offset; with padding it also tests the (r, s) bits of two per-lane masks of
 //        valid window rows and columns.  Filters of at most 31 taps use one word per entry (offset and tap) and one
-//        per-lane mask of taps, for contractions of up to KTAB1 elements (3x3 64 -> 192 at stride 2 on 56 x 56 x 32, which
+//        per-lane mask of taps, for contractions of up to KTAB1 elements whose offsets fit the word (3x3 64 -> 192 at stride 2 on 56 x 56 x 32, which
 //        decoded (c, r, s) element by element before: 81 -> 69 us).  Longer contractions decode (c, r, s) per element.
 //        Without padding and with a filter width S that rounds up to a multiple of 4 cheaply (11 -> 12,
 //        7 -> 8), k instead runs over (c, r, groups of 4 taps): the four activations of a group are
@@ -47,6 +47,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "conv_f32_table.h"
 #include "dr_internal.h"
 
 namespace dr {
@@ -170,19 +171,19 @@ __device__ __forceinline__ void conv_f32_tile(const KArgs a, const int block, fl
     const int S4 = (S + 3) & ~3;
     const int kg_eff = rg ? g.C * R * S4 : g.Kg;     // contraction length including the taps added by rounding S up
     const int ktab_n = (kg_eff + BK - 1) / BK * BK;
-    const bool use_tab1 = !CF && !rg && RS <= 31 && ktab_n <= KTAB1 && (long)g.C * HW < (1l << 26);
+    const bool use_tab1 = !CF && !rg && ktab_n <= KTAB1 && tab1_fits(g.C, g.H, g.W, R, S);
     const bool use_tab = !CF && !rg && !use_tab1 && ktab_n <= KTAB && R <= 31 && S <= 31;
     const bool nopad = g.ph == 0 && g.pw == 0;      // then every window lies inside the image
     unsigned rowmask = 0, colmask = 0;
     unsigned tap_out = 0xFFFFFFFFu;                  // (one-word table) bit r S + s: that tap lies outside the image; bits beyond: set
     if constexpr (!CF) {
         if (use_tab1) {
-            // one word per k: (offset of x[0][c][r][s] in elements) << 5 | tap, tap 31 beyond the contraction
+            // one word per k: offset of x[0][c][r][s] in elements, and the tap
             for (int k = tid; k < ktab_n; k += NT) {
-                int e = 31;
+                int e = tab1_entry(0, TAB1_NO_TAP);
                 if (k < g.Kg) {
                     const int c = k / RS, rs = k - c * RS, r = rs / S;
-                    e = (c * HW + r * g.W + rs - r * S) << 5 | rs;
+                    e = tab1_entry(c * HW + r * g.W + rs - r * S, rs);
                 }
                 ktab[k] = e;
             }
@@ -340,8 +341,8 @@ __device__ __forceinline__ void conv_f32_tile(const KArgs a, const int block, fl
                     f32x4 v;
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
-                        const int vo = bbase + ((int)((unsigned)e[j] >> 5) << 2);
-                        v[j] = buf_load(rx, (int)((tap_out >> (e[j] & 31)) << 31) | vo, 0);     // a tap outside: sign bit set, beyond the buffer
+                        const int vo = bbase + (tab1_offset(e[j]) << 2);
+                        v[j] = buf_load(rx, (int)((tap_out >> tab1_tap(e[j])) << 31) | vo, 0);     // a tap outside: sign bit set, beyond the buffer
                     }
                     rb[SET][i] = v;
                 }

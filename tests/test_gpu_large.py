@@ -60,3 +60,19 @@ def test_conv_bf16_input_of_more_than_2_gib():
     # 11600 x 11600 x 8 bf16 = 2.15 GB: byte offsets beyond 32 bits, in the input and in the output
     H = W = 11600
     _run(C=8, H=H, W=W, K=8, R=3, pad=1, rows=400, seed=22, marks=[(1 << 31) // 16, (1 << 32) // 16 if (1 << 32) // 16 < H * W else H * W - 2])
+
+
+def test_filter_taller_than_a_wide_flat_map():
+    """31 x 1 on one row of 9 million pixels, padded by 15: the one tap inside the map lies 15 rows, 1.35e8 elements, behind the window's first,
+    which is more than a one-word entry of the fp32 gather table holds."""
+    W = 9_000_001
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    x = torch.randn((1, 1, 1, W), device="cuda", generator=gen)
+    w = torch.randn((1, 1, 31, 1), device="cuda", generator=gen)
+    b = torch.tensor([0.25], device="cuda")
+    y = torch.full((1, 1, 1, W), float("nan"), device="cuda")
+    B.conv2d_fwd(x, B.conv_desc(1, 1, 31, 1, 1, (15, 0)), w, b, y)
+    torch.cuda.synchronize()
+    # one product and one sum per output: exact up to the rounding of each
+    ref = x.double() * w[0, 0, 15, 0].double() + 0.25
+    assert float((y.double() - ref).abs().max()) <= 2.0 ** -22 * float(ref.abs().max())
