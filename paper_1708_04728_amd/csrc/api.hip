@@ -558,10 +558,10 @@ struct StepGroup {
     }
 };
 
-// Larger fp32 layers that share a launch: enough tiles to be worth it (fewer are better cut over workgroups, one by one)
+// Larger fp32 layers that share a launch: enough tiles to be worth it, and none that would be cut over workgroups by itself.
 bool big_takes(int dtype, const ConvGeom& g)
 {
-    return dtype == DR_F32 && conv_f32_group_takes(g) && ((long)g.K + 63) / 64 * (((long)g.Ng + 63) / 64) >= device_cus() / 2;
+    return dtype == DR_F32 && conv_f32_group_takes(g) && ((long)g.K + 63) / 64 * (((long)g.Ng + 63) / 64) >= device_cus() / 2 && conv_f32_scratch_bytes(g) == 0;
 }
 
 // A max-pooling step as a job of the small-layer kernel: 3x3 windows, whole 16-byte channel groups, few pixels.

@@ -11,8 +11,10 @@
 // Both operand slices are staged in LDS with the slice's k index contiguous per row (rows padded by
 // 4 floats so that 128-bit LDS accesses of consecutive rows fall in distinct banks).
 // v_mfma_f32_32x32x2_f32 consumes two k per instruction, one from lanes 0-31 and one from lanes
-// 32-63; the kernel gives lane half g the slice's k in [g*BK/2, (g+1)*BK/2), so every lane fetches
-// its A (or B) values of a slice with BK/8 128-bit LDS reads.  Global loads run PF slices ahead of
+// 32-63; of every 16 k of a slice the kernel gives lane half g those in [8g, 8g + 8), so every lane
+// fetches its A (or B) values of a slice with BK/8 128-bit LDS reads, and the products of an output are
+// added in the same order whatever the depth of a slice (a layer's bits do not depend on whether it
+// shares a launch, where slices are 16 deep).  Global loads run PF slices ahead of
 // the MFMAs in registers (PF register sets), LDS is double buffered, one barrier per slice.  With
 // lanes running along n, both the gather from x and the store to NCHW y are coalesced.  Bias, the
 // optional residual sum and ReLU are applied in the store.
@@ -415,15 +417,15 @@ __device__ __forceinline__ void conv_f32_tile(const KArgs a, const int block, fl
         f32x4 fa[TM][HK / 4], fb[TN][HK / 4];
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-            const float* p = &As[buf][(wm * WM + i * 32 + l32) * LDT + half * HK];
+            const float* p = &As[buf][(wm * WM + i * 32 + l32) * LDT + half * 8];
 #pragma unroll
-            for (int h = 0; h < HK / 4; ++h) fa[i][h] = *reinterpret_cast<const f32x4*>(p + 4 * h);
+            for (int h = 0; h < HK / 4; ++h) fa[i][h] = *reinterpret_cast<const f32x4*>(p + (h >> 1) * 16 + (h & 1) * 4);
         }
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-            const float* p = &Bs[buf][(wn * WN + j * 32 + l32) * LDT + half * HK];
+            const float* p = &Bs[buf][(wn * WN + j * 32 + l32) * LDT + half * 8];
 #pragma unroll
-            for (int h = 0; h < HK / 4; ++h) fb[j][h] = *reinterpret_cast<const f32x4*>(p + 4 * h);
+            for (int h = 0; h < HK / 4; ++h) fb[j][h] = *reinterpret_cast<const f32x4*>(p + (h >> 1) * 16 + (h & 1) * 4);
         }
 #pragma unroll
         for (int kk = 0; kk < HK; ++kk)

@@ -256,3 +256,42 @@ def test_module_that_fails_half_way_leaves_no_loose_ends():
         c.graph.launch()
         torch.cuda.synchronize()
         assert close(host(y), ref, TOL_F32)
+
+
+def _strided_module():
+    """Two strided 5x5 layers side by side: 96 filters that have enough 64 x 64 tiles to share a launch and few enough 32 x 128 ones (which is
+    how they are tiled) to be cut over workgroups by themselves, and 64 filters that the small-layer kernel takes."""
+    return ("inception", {"branches": [[workloads.conv(96, 5, 2, 2), workloads.relu()], [workloads.conv(64, 5, 2, 2), workloads.relu()],
+                                       [workloads.maxpool(3, 2)]]})
+
+
+@pytest.mark.parametrize("case", [
+    # module, images, side, channels, stacked first steps too
+    ("3a", 32, 28, 192, True),      # 3x3 96 -> 128 in 784 tiles: slices 32 deep by itself, shares a launch with the 5x5
+    ("strided", 4, 64, 64, False),
+])
+def test_fp32_module_bits_do_not_depend_on_what_shares_a_launch(case):
+    """Every execution mode adds a layer's products in one order: step by step, branch by branch (which is how a kernel trace has a module run),
+    branches on streams of their own, first steps stacked."""
+    name, n, side, c, stack = case
+    layer = _strided_module() if name == "strided" else workloads.inception_original(name)
+    rng = np.random.default_rng(n)
+    x = np.abs(rng.standard_normal((n, c, side, side))).astype(np.float32)
+    params = []
+    workloads._walk(rng, [layer], c, "f32", params)
+    base = B.DR_FUSE_RELU | B.DR_FUSE_CONCAT
+    ref = run_net([layer], params, x)
+    assert np.isfinite(ref).all()
+    wrong = []
+    for mode in (B.DR_CONCURRENT_BRANCHES, B.DR_FUSE_RELU, base, base | B.DR_CONCURRENT_BRANCHES):
+        if not np.array_equal(run_net([layer], params, x, inception_mode=mode), ref):
+            wrong.append(mode)
+    B.trace_begin()
+    traced = run_net([layer], params, x)
+    B.trace_end()
+    if not np.array_equal(traced, ref):
+        wrong.append("traced")
+    for mode in (base | B.DR_FUSE_STACK, base | B.DR_FUSE_STACK | B.DR_CONCURRENT_BRANCHES) if stack else ():
+        if not np.array_equal(_run_stacked(layer, params, x, mode, True), ref):
+            wrong.append(mode)
+    assert not wrong, wrong
