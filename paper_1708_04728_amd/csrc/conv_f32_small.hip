@@ -5,10 +5,11 @@
 // The kernel of conv_f32.hip gives a workgroup a 64 x 64 tile and walks the whole contraction with it, a barrier per slice; a layer
 // with a tile or less per compute unit then runs at the latency of its slices (18 slices of 3x3 filters on 64 channels: 20 us
 // for 8 us of matrix work, most compute units idle).  Here a tile is one 32 x 32 block, and the NW waves of a workgroup
-// share its contraction: wave w takes the w-th share of the slices (16 channels of one tap each) with a ring of two slices of
-// its own in LDS, so that no wave waits for another; the partial sums meet in LDS once, are added in wave order (the same
-// bits from run to run) and stored with bias, residual and ReLU.  One launch takes several layers (the convolutions at
-// one depth of an inception module).
+// share its contraction.  The slices (16 channels of one tap each) are cut into SHARES runs; a wave takes one or two of them with
+// a ring of two slices of its own in LDS, so that no wave waits for another; the partial sums meet in LDS once, are added in a
+// fixed order and stored with bias, residual and ReLU.  Runs and order are the same however many waves there are, so a
+// layer's bits do not depend on what shares its launch.  One launch takes several layers (the convolutions at one depth of an
+// inception module).
 //
 // Operands.  v_mfma_f32_32x32x2_f32 takes one k from each half of the wave: half h holds the slice's channels 8 h .. 8 h + 7.  Both
 // operands are loaded into LDS directly: the filters 16 rows of 64 bytes per load (filter rows read straight into registers, 64
@@ -26,6 +27,7 @@ namespace {
 
 constexpr int BK = 16;                                   // channels per slice
 constexpr int SLICE = 2 * 32 * BK * 4;                   // bytes of one slice of both operands
+constexpr int SHARES = 8;                                // runs of slices with a partial sum each, summed in pairs
 
 struct SmallJobF {
     const float *x, *w, *bias, *res;
@@ -52,12 +54,14 @@ __device__ __forceinline__ u32x2 ds_read2_planes(unsigned addr)
     return v;
 }
 
-// NW waves (shares of the contraction), NS slices in flight per wave
+// NW waves, each with SHARES / NW runs of the contraction one after the other; NS slices in flight per wave
+// (at least two waves per SIMD: the compiler then keeps the sums in ordinary registers, without copies between loops)
 template <int NW, int NS>
-__global__ __launch_bounds__(NW * 64) void conv_f32_small_kernel(const SmallArgsF args)
+__global__ __launch_bounds__(NW * 64, 2) void conv_f32_small_kernel(const SmallArgsF args)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char ring[NW * NS * SLICE];     // filters; the partial sums at the end
-    static_assert(NS * SLICE >= 4096, "a wave's partial sums take 4 KiB");
+    constexpr int PER_WAVE = SHARES / NW;
+    static_assert((PER_WAVE == 1 || PER_WAVE == 2) && NS * SLICE >= 4096, "a wave's partial sums take 4 KiB");
 
     // the job and the tile; a die (workgroup id & 7) takes a contiguous range of tiles, filter block by filter block
     int ji = 0;
@@ -90,63 +94,80 @@ __global__ __launch_bounds__(NW * 64) void conv_f32_small_kernel(const SmallArgs
     const unsigned ring_lds = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)my_ring, a_lane = l32 * 64;
     const unsigned chunk0 = ((2 * half) ^ ((l32 >> 2) & 3)) * 16, chunk1 = ((2 * half + 1) ^ ((l32 >> 2) & 3)) * 16;
 
-    // this wave's slices and the position of the next one to load
-    const int s0 = j.slices * wave / NW, count = j.slices * (wave + 1) / NW - s0;
+    // this wave's slices, the first of its second run, and the position of the next one to load
+    const int s0 = j.slices * (wave * PER_WAVE) / SHARES, count = j.slices * ((wave + 1) * PER_WAVE) / SHARES - s0;
+    const int second = PER_WAVE == 2 ? j.slices * (wave * 2 + 1) / SHARES - s0 : count;
     int tap = s0 / j.per_tap, ld_c = s0 - tap * j.per_tap;
     int ld_r = tap / j.S, ld_s = tap - ld_r * j.S;
-    f32x16 acc;
+    f32x16 sum[PER_WAVE];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-    int stage = 0, ld_stage = 0;
-    for (int k = 1 - NS; k < count; ++k) {
-        if (k + NS - 1 < count) {
-            unsigned char* const dst = my_ring + ld_stage * SLICE;
-            const int soff_a = (tap * j.C + ld_c * BK) * 4;
+    for (int v = 0; v < 16; ++v)
 #pragma unroll
-            for (int i = 0; i < 2; ++i) load_to_lds16(rw, dst + i * 1024, a_voff[i], soff_a);
-            const bool in = (unsigned)(ih0 + ld_r) < (unsigned)j.H && (unsigned)(iw0 + ld_s) < (unsigned)j.W;
-            const int voff = in ? b_base + (ld_r * j.W + ld_s) * 4 : OOB;
-            int soff = ld_c * BK * HW4;
+        for (int i = 0; i < PER_WAVE; ++i) sum[i][v] = 0.f;
+    int stage = 0, ld_stage = 0, k = 1 - NS;
+    // (a loop and registers per run: where one loop changes from run to run the compiler copies the sums in every slice, 15 % slower, and
+    // where one set of registers is emptied in between the wave waits for its matrix instructions)
+    auto multiply = [&](f32x16& acc, int end) __attribute__((always_inline)) {
+        for (; k < end; ++k) {
+            if (k + NS - 1 < count) {
+                unsigned char* const dst = my_ring + ld_stage * SLICE;
+                const int soff_a = (tap * j.C + ld_c * BK) * 4;
 #pragma unroll
-            for (int i = 0; i < 8; ++i, soff += HW4) load_to_lds4(rx, dst + 2048 + i * 256, voff, soff);
-            ld_stage = ld_stage + 1 == NS ? 0 : ld_stage + 1;
-            if (++ld_c == j.per_tap) {
-                ld_c = 0; ++tap;
-                if (++ld_s == j.S) { ld_s = 0; ++ld_r; }
+                for (int i = 0; i < 2; ++i) load_to_lds16(rw, dst + i * 1024, a_voff[i], soff_a);
+                const bool in = (unsigned)(ih0 + ld_r) < (unsigned)j.H && (unsigned)(iw0 + ld_s) < (unsigned)j.W;
+                const int voff = in ? b_base + (ld_r * j.W + ld_s) * 4 : OOB;
+                int soff = ld_c * BK * HW4;
+#pragma unroll
+                for (int i = 0; i < 8; ++i, soff += HW4) load_to_lds4(rx, dst + 2048 + i * 256, voff, soff);
+                ld_stage = ld_stage + 1 == NS ? 0 : ld_stage + 1;
+                if (++ld_c == j.per_tap) {
+                    ld_c = 0; ++tap;
+                    if (++ld_s == j.S) { ld_s = 0; ++ld_r; }
+                }
             }
+            if (k < 0) continue;
+            const int behind = min(count - 1 - k, NS - 1);   // slice k has landed; the loads of the slices behind it may be pending
+            if (NS > 3 && behind == 3) wait_vmcnt<(NS > 3 ? 3 : 0) * 10>();
+            else if (NS > 2 && behind == 2) wait_vmcnt<(NS > 2 ? 2 : 0) * 10>();
+            else if (behind == 1) wait_vmcnt<10>();
+            else wait_vmcnt<0>();
+            const unsigned rd = ring_lds + stage * SLICE;
+            u32x4 a0 = ds_read16<0>(rd + a_lane + chunk0), a1 = ds_read16<0>(rd + a_lane + chunk1);
+            u32x2 bv[4];
+            bv[0] = ds_read2_planes<8>(rd + lane * 4);
+            bv[1] = ds_read2_planes<10>(rd + lane * 4);
+            bv[2] = ds_read2_planes<12>(rd + lane * 4);
+            bv[3] = ds_read2_planes<14>(rd + lane * 4);
+            wait_lgkm<0>();
+            touch(a0); touch(a1);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(bv[i]));
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(i < 4 ? a0[i & 3] : a1[i & 3]), __uint_as_float(bv[i >> 1][i & 1]), acc, 0, 0, 0);
+            stage = stage + 1 == NS ? 0 : stage + 1;
         }
-        if (k < 0) continue;
-        const int behind = min(count - 1 - k, NS - 1);   // slice k has landed; the loads of the slices behind it may be pending
-        if (NS > 3 && behind == 3) wait_vmcnt<(NS > 3 ? 3 : 0) * 10>();
-        else if (NS > 2 && behind == 2) wait_vmcnt<(NS > 2 ? 2 : 0) * 10>();
-        else if (behind == 1) wait_vmcnt<10>();
-        else wait_vmcnt<0>();
-        const unsigned rd = ring_lds + stage * SLICE;
-        u32x4 a0 = ds_read16<0>(rd + a_lane + chunk0), a1 = ds_read16<0>(rd + a_lane + chunk1);
-        u32x2 bv[4];
-        bv[0] = ds_read2_planes<8>(rd + lane * 4);
-        bv[1] = ds_read2_planes<10>(rd + lane * 4);
-        bv[2] = ds_read2_planes<12>(rd + lane * 4);
-        bv[3] = ds_read2_planes<14>(rd + lane * 4);
-        wait_lgkm<0>();
-        touch(a0); touch(a1);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(bv[i]));
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(i < 4 ? a0[i & 3] : a1[i & 3]), __uint_as_float(bv[i >> 1][i & 1]), acc, 0, 0, 0);
-        stage = stage + 1 == NS ? 0 : stage + 1;
-    }
+    };
+    if constexpr (PER_WAVE == 2) multiply(sum[0], second);
+    multiply(sum[PER_WAVE - 1], count);
 
-    // registers 4 g .. 4 g + 3 of a lane are filters 8 g + 4 half .. + 3 of the block
+    // the runs' sums are added pair by pair, then the pairs in order.  Registers 4 g .. 4 g + 3 of a lane are filters 8 g + 4 half .. + 3 of
+    // the block
+    f32x16 acc = sum[0];
+    if constexpr (PER_WAVE == 2) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] += sum[PER_WAVE - 1][v];
+    }
     f32x4* const mine = reinterpret_cast<f32x4*>(my_ring);
 #pragma unroll
     for (int g = 0; g < 4; ++g) mine[g * 64 + lane] = f32x4{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
     __syncthreads();
     if (wave >= 4 || !n_ok) return;
-    f32x4 o = reinterpret_cast<const f32x4*>(ring)[wave * 64 + lane];
+    auto sum_of = [&](int w) __attribute__((always_inline)) { return reinterpret_cast<const f32x4*>(ring + w * (NS * SLICE))[wave * 64 + lane]; };
+    auto pair = [&](int i) __attribute__((always_inline)) { return PER_WAVE == 2 ? sum_of(i) : sum_of(2 * i) + sum_of(2 * i + 1); };
+    f32x4 o = pair(0);
 #pragma unroll
-    for (int w = 1; w < NW; ++w) o += reinterpret_cast<const f32x4*>(ring + w * (NS * SLICE))[wave * 64 + lane];
+    for (int i = 1; i < SHARES / 2; ++i) o += pair(i);
     const int m0 = mt * 32 + wave * 8 + half * 4;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -241,7 +262,7 @@ bool conv_f32_small_takes(const ConvGeom& g, const void* w, bool scratch)
 
 int launch_conv_f32_small(const ConvSmall* jobs, int n, hipStream_t st)
 {
-    // eight shares while there are at most two tiles per compute unit, else four (more workgroups side by side)
+    // eight waves while there are at most two tiles per compute unit, else four (more workgroups side by side)
     long tiles = 0;
     for (int i = 0; i < n; ++i) tiles += small_tiles(jobs[i].g);
     return tiles <= 2 * device_cus() ? launch_group<8, 2>(jobs, n, st) : launch_group<4, 2>(jobs, n, st);

@@ -268,6 +268,9 @@ def _strided_module():
 @pytest.mark.parametrize("case", [
     # module, images, side, channels, stacked first steps too
     ("3a", 32, 28, 192, True),      # 3x3 96 -> 128 in 784 tiles: slices 32 deep by itself, shares a launch with the 5x5
+    ("4d", 9, 14, 512, True),       # first steps of 224, 280 and 56 tiles of 32 x 32: 504 as one layer, 560 as three
+    ("5a", 64, 7, 832, False),      # 784, 490 and 98
+    ("5b", 64, 7, 832, False),      # 1176, 588 and 196
     ("strided", 4, 64, 64, False),
 ])
 def test_fp32_module_bits_do_not_depend_on_what_shares_a_launch(case):
