@@ -558,10 +558,20 @@ struct StepGroup {
     }
 };
 
-// Larger fp32 layers that share a launch: enough tiles to be worth it, and none that would be cut over workgroups by itself.
+// Larger fp32 layers that share a launch: enough tiles to be worth it (fewer are better cut over workgroups, one by one)
 bool big_takes(int dtype, const ConvGeom& g)
 {
-    return dtype == DR_F32 && conv_f32_group_takes(g) && ((long)g.K + 63) / 64 * (((long)g.Ng + 63) / 64) >= device_cus() / 2 && conv_f32_scratch_bytes(g) == 0;
+    return dtype == DR_F32 && conv_f32_group_takes(g) && !conv_f32_small_takes(g, nullptr, false) &&
+           ((long)g.K + 63) / 64 * (((long)g.Ng + 63) / 64) >= device_cus() / 2;
+}
+
+// Scratch of a module's layer.  One that may share a launch is not cut over workgroups in any mode, so that its sums are the same in
+// all of them (its 32-row tiles can be few enough to be cut where the 64 x 64 ones are enough to share: 3a on 16 images, original form,
+// with three such layers, 91 us by levels and 109 with each of them cut).
+size_t module_scratch_bytes(const dr_tensor& xd, const dr_conv& cd)
+{
+    const size_t bytes = conv_scratch_bytes(xd, cd);
+    return bytes && big_takes(xd.dtype, conv_geom(xd, cd, conv_out(xd, cd))) ? 0 : bytes;
 }
 
 // A max-pooling step as a job of the small-layer kernel: 3x3 windows, whole 16-byte channel groups, few pixels.
@@ -657,7 +667,7 @@ int inception_run_levels(const dr_tensor& xd, const void* x, const dr_inception&
                         if (direct) { g.y_ctot = yd.c; g.y_coff = q.c_off; }
                         DR_TRY(group.add_big(ConvSmall{g, q.cur, w, bias, nullptr, dst, nullptr}));
                     } else {
-                        const size_t sbytes = conv_scratch_bytes(q.t, cd);
+                        const size_t sbytes = module_scratch_bytes(q.t, cd);
                         void* sc = sbytes ? ar.take(sbytes) : nullptr;
                         DR_TRY(conv_run(who, q.t, q.cur, cd, w, bias, nullptr, 0, direct ? yd : o, dst, direct ? q.c_off : 0, st, 0, sc, sc ? sbytes : 0));
                     }
@@ -757,7 +767,7 @@ int inception_run(const dr_tensor& xd, const void* x, const dr_inception& d, Par
                 if (direct) cd.relu = relu_after;
                 void* dst = direct ? y : (s == 0 && stacked[b]) ? stacked_dst[b] : ar.take(tensor_bytes(o));
                 if (!dst && !ar.measure) return fail(DR_ERR_WORKSPACE, "%s: workspace too small", who);
-                const size_t sbytes = conv_scratch_bytes(t, cd);
+                const size_t sbytes = module_scratch_bytes(t, cd);
                 void* sc = sbytes ? ar.take(sbytes) : nullptr;
                 if (!ar.measure && !(s == 0 && stacked[b])) {
                     if (!w) return fail(DR_ERR_NULL, "%s: missing weights of branch %d step %d", who, b, s);
