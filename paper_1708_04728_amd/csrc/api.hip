@@ -485,8 +485,9 @@ int run_stacked_first_steps(const dr_tensor& xd, const void* x, const dr_incepti
     g.Ng = xd.n * xd.h * xd.w;
     g.relu = 1;
     g.res_ctot = 0;
-    // a 1x1 filter bank is the same array in both orders; fp32 keeps the order the branches name, so that the stacked
-    // convolution adds its products in the same order as one convolution per branch
+    // a 1x1 filter bank is the same array in both orders; fp32 keeps the order the branches name, so that the stacked convolution
+    // adds its products in the same order as one convolution per branch wherever one kernel takes both (a bank may be small
+    // enough for the small-layer kernel, or to be cut over workgroups, where the stacked layer is not)
     g.w_krsc = f32 ? d.branches[members[0]].steps[0].conv.filter_layout == DR_KRSC : 1;
     g.nhwc = f32 ? 0 : 1;
     g.c_logical = 0;

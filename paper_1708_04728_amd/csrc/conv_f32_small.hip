@@ -240,10 +240,10 @@ long small_tiles(const ConvGeom& g) { return ((long)g.Ng + 31) / 32 * ((g.K + 31
 
 // Measured in chains of dependent launches, us, kernel of conv_f32.hip (with scratch where it cuts the contraction) -> this one: 3x3 64 -> 192
 // on one 56 x 56 map (588 tiles) 19.0 -> 14.2, at stride 2 (150) 11.6 -> 8.9; 1x1 480 -> 112 on 14 x 14 x 8 images (196)
-// 11.4 -> 7.7; 3x3 192 -> 384 on 7 x 7 x 32 (588) 47 -> 31; 3x3 96 -> 208 on 14 x 14 x 32 (1372) 44 -> 34; beyond that the larger
-// tiles gain (1764 tiles 28 -> 31).  A few tiles with a long contraction are better off cut over workgroups, when the caller
-// has scratch for that (1x1 filters excepted, for which the line is drawn by pixels alone so that a convolution over stacked
-// filter banks keeps the sums of one convolution per bank): a tile alone on its compute unit takes 0.1 us per slice (3x3 192 -> 384 on one 7 x 7 map: 24 tiles,
+// 11.4 -> 7.7; 3x3 192 -> 384 on 7 x 7 x 32 (588) 47 -> 31; 3x3 96 -> 208 on 14 x 14 x 32 (1372) 44 -> 34; 1x1 512 -> 320 on 14 x 14 x 20
+// (1230) 24.7 -> 20.7; beyond that the larger tiles gain: 1x1 512 -> 512 on the same map (1968) 24.4 -> 30.0, 832 -> 2048 (7872) 119 -> 157.
+// 1x1 filters: up to 4096 pixels.  A few tiles with a long contraction are better off cut over workgroups, when the caller
+// has scratch for that (1x1 filters excepted): a tile alone on its compute unit takes 0.1 us per slice (3x3 192 -> 384 on one 7 x 7 map: 24 tiles,
 // 108 slices, 10.2 against 13.5).
 // A strided row spreads the 32 pixels of a load over more lines, and every filter block reads them again: 5x5 96 -> 256 at stride 2 on 28 x 28
 // takes 29.0 us tiled and 33.9 here on 6 images (296 tiles), 67 and 75 on 18, 98 and 113 on 28 (at stride 1 the same output: 95 and
@@ -253,11 +253,11 @@ bool conv_f32_small_takes(const ConvGeom& g, const void* w, bool scratch)
 {
     const size_t xb = (size_t)g.N * g.C * g.H * g.W * 4, wb = (size_t)g.K * g.Kg * 4;
     if (g.nhwc || g.C % 16 != 0 || (!g.w_krsc && g.R * g.S != 1) || !aligned16(w) || xb >= (1ull << 31) || wb >= (1ull << 31)) return false;
+    const long tiles = small_tiles(g), cus = device_cus();
+    if (tiles > 11 * cus / 2) return false;
     if (g.R * g.S == 1) return g.Ng <= 4096;
-    const long tiles = small_tiles(g);
     if (scratch && tiles <= 64 && g.Kg > 1024) return false;
-    if (g.sw > 1 && g.Kg > 1200 && tiles > device_cus()) return false;
-    return tiles <= 11 * device_cus() / 2;
+    return !(g.sw > 1 && g.Kg > 1200 && tiles > cus);
 }
 
 int launch_conv_f32_small(const ConvSmall* jobs, int n, hipStream_t st)

@@ -66,6 +66,41 @@ def test_filters_on_any_word():
     assert close(host(y), oracle.conv2d(x, w, None, 1, 1, False), TOL_F32)
 
 
+def runs_small(n, c, hw, k, r, stride, scratch):
+    """Whether the small-layer kernel takes the layer, by its bits: filters 4 bytes behind a 16-byte boundary are not its, so the same
+    layer run with those gives the other kernel's sums."""
+    rng = np.random.default_rng(k + hw)
+    x = gpu(rng.standard_normal((n, c, hw, hw)).astype(np.float32))
+    w = B.pack_filters(gpu((rng.standard_normal((k, c, r, r)) * np.sqrt(2.0 / (c * r * r))).astype(np.float32)))
+    room = torch.empty(w.numel() + 1, device="cuda")
+    shifted = room[1:].view(w.shape)
+    shifted.copy_(w)
+    cd = B.conv_desc(k, c, r, r, stride, r // 2, False, B.DR_KRSC)
+    side = (hw + 2 * (r // 2) - r) // stride + 1
+    out = []
+    for f in (w, shifted):
+        y = torch.full((n, k, side, side), float("nan"), device="cuda")
+        need = B.conv2d_workspace_bytes(x, cd) if scratch else 0
+        if need:
+            B.conv2d_fwd_ws(x, cd, f, None, y, torch.empty(need, dtype=torch.uint8, device="cuda"))
+        else:
+            B.conv2d_fwd(x, cd, f, None, y)
+        out.append(y)
+    torch.cuda.synchronize()
+    assert close(host(out[0]), host(out[1]), TOL_F32)
+    return not torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("n,c,hw,k,small", [
+    (20, 192, 14, 352, True),        # 123 x 11 tiles
+    (20, 192, 14, 384, False),       # 123 x 12: more than 5.5 per compute unit
+    (83, 64, 7, 2048, False),        # 4067 pixels
+    (84, 192, 7, 32, False),         # 4116 pixels
+])
+def test_1x1_layers_by_tiles(n, c, hw, k, small):
+    assert runs_small(n, c, hw, k, 1, 1, False) == small
+
+
 @pytest.mark.parametrize("form", ["original", "slim"])
 def test_module_whose_branches_share_launches(form):
     """A module on two ragged maps in every mode, packed filters, channel ranges of the output, stacked first steps."""
