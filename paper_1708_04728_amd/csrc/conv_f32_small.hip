@@ -242,9 +242,16 @@ long small_tiles(const ConvGeom& g) { return ((long)g.Ng + 31) / 32 * ((g.K + 31
 // on one 56 x 56 map (588 tiles) 19.0 -> 14.2, at stride 2 (150) 11.6 -> 8.9; 1x1 480 -> 112 on 14 x 14 x 8 images (196)
 // 11.4 -> 7.7; 3x3 192 -> 384 on 7 x 7 x 32 (588) 47 -> 31; 3x3 96 -> 208 on 14 x 14 x 32 (1372) 44 -> 34; 1x1 512 -> 320 on 14 x 14 x 20
 // (1230) 24.7 -> 20.7; beyond that the larger tiles gain: 1x1 512 -> 512 on the same map (1968) 24.4 -> 30.0, 832 -> 2048 (7872) 119 -> 157.
-// 1x1 filters: up to 4096 pixels.  A few tiles with a long contraction are better off cut over workgroups, when the caller
-// has scratch for that (1x1 filters excepted): a tile alone on its compute unit takes 0.1 us per slice (3x3 192 -> 384 on one 7 x 7 map: 24 tiles,
-// 108 slices, 10.2 against 13.5).
+// 1x1 filters: up to 4096 pixels.
+// Long contractions are better off cut over workgroups, when the caller has scratch for that: here a round of tiles takes 0.085 us per
+// slice of 16 whether it fills the device or not, there the time goes with tiles times slices.  Up to 64 tiles (1x1: 32) beyond
+// 64 slices: 3x3 192 -> 384 on one 7 x 7 map (24 tiles, 108 slices) 10.2 cut against 13.5, 1x1 2048 -> 64 on the same map 8.9 and 13.0.
+// Above that, by what a round leaves idle, counted from the three quarters of it that cost as much when cut: 14 x 14 maps, 3x3
+// 512 -> 128 (76 tiles, 288 slices) 18.1 and 24.4, 352 -> 128 (100, 198) 18.6 and 18.4, 5x5 192 -> 160 (125, 300) 28.9 and 25.5, 352 -> 192
+// (150, 550) 38.2 and 42.5; in a second round 3x3 352 -> 256 (296, 198) 30.0 and 34.1, 192 -> 224 (259, 108) 22.9 and 20.6, 352 -> 320 (490, 198)
+// 41.4 and 37.4.  And where a strided layer's input, which every filter block reads for itself, is more than the L2 of a die holds:
+// at stride 2 3x3 512 -> 192 on 6.4 MB (150, 288) 30.5 and 40.4, 352 -> 192 on 6.6 MB (222, 198) 27.8 and 31.7; 5x5 192 -> 256 on 2.4 MB
+// (200, 300) 34.0 and 32.4.
 // A strided row spreads the 32 pixels of a load over more lines, and every filter block reads them again: 5x5 96 -> 256 at stride 2 on 28 x 28
 // takes 29.0 us tiled and 33.9 here on 6 images (296 tiles), 67 and 75 on 18, 98 and 113 on 28 (at stride 1 the same output: 95 and
 // 74); contractions of up to 75 slices still gain or tie (5x5 32 -> 256 on 28 images 38 -> 35, 3x3 128 -> 128 34 -> 33).
@@ -255,9 +262,13 @@ bool conv_f32_small_takes(const ConvGeom& g, const void* w, bool scratch)
     if (g.nhwc || g.C % 16 != 0 || (!g.w_krsc && g.R * g.S != 1) || !aligned16(w) || xb >= (1ull << 31) || wb >= (1ull << 31)) return false;
     const long tiles = small_tiles(g), cus = device_cus();
     if (tiles > 11 * cus / 2) return false;
-    if (g.R * g.S == 1) return g.Ng <= 4096;
-    if (scratch && tiles <= 64 && g.Kg > 1024) return false;
-    return !(g.sw > 1 && g.Kg > 1200 && tiles > cus);
+    if (g.R * g.S == 1 && g.Ng > 4096) return false;
+    if (g.sw > 1 && g.Kg > 1200 && tiles > cus) return false;
+    if (!scratch) return true;
+    const long rounds = (tiles + cus - 1) / cus;
+    if (tiles <= (g.R * g.S == 1 ? 32 : 64) && g.Kg > 1024) return false;
+    if (g.sw > 1 && g.Kg > 2560 && xb > (4u << 20)) return false;
+    return (3 * cus * rounds / 4 - tiles) * (g.Kg / BK) <= (rounds == 1 ? 85 : 60) * cus;
 }
 
 int launch_conv_f32_small(const ConvSmall* jobs, int n, hipStream_t st)

@@ -101,6 +101,24 @@ def test_1x1_layers_by_tiles(n, c, hw, k, small):
     assert runs_small(n, c, hw, k, 1, 1, False) == small
 
 
+@pytest.mark.parametrize("n,c,hw,k,r,stride,small", [
+    (1, 2048, 7, 64, 1, 1, False),       # 4 tiles, 128 slices: cut
+    (1, 1024, 7, 64, 1, 1, True),        # 64 slices
+    (3, 512, 14, 128, 3, 1, False),      # 76 tiles, 288 slices
+    (3, 192, 14, 128, 3, 1, True),       # 108 slices
+    (4, 352, 14, 256, 3, 1, True),       # 200 tiles: more than three quarters of a round
+    (6, 352, 14, 256, 3, 1, False),      # 296 tiles: a second round, mostly idle
+    (8, 352, 14, 320, 3, 1, True),       # 490
+    (4, 192, 14, 160, 5, 1, True),       # 125 tiles, 300 slices
+    (6, 352, 28, 192, 3, 2, False),      # 222 tiles, strided, 198 slices, 6.6 MB
+    (6, 192, 28, 192, 3, 2, True),       # 108 slices
+    (4, 192, 28, 256, 5, 2, True),       # 300 slices, 2.4 MB
+])
+def test_long_contractions_are_cut_where_there_is_scratch(n, c, hw, k, r, stride, small):
+    assert runs_small(n, c, hw, k, r, stride, True) == small
+    assert runs_small(n, c, hw, k, r, stride, False)
+
+
 @pytest.mark.parametrize("form", ["original", "slim"])
 def test_module_whose_branches_share_launches(form):
     """A module on two ragged maps in every mode, packed filters, channel ranges of the output, stacked first steps."""
