@@ -113,6 +113,8 @@ def test_inception_and_net_planning_on_host():
     assert m.value > 0 and m.value % (192 * 784 * 4) == 0
     assert B.lib().dr_conv2d_workspace_bytes(_t(128, 64, 56, 56), B.conv_desc(192, 64, 3, pad=1), C.byref(m)) == B.DR_OK and m.value == 0
     assert B.lib().dr_conv2d_workspace_bytes(_t(1, 64, 56, 56, B.DR_BF16), B.conv_desc(192, 64, 3, pad=1), C.byref(m)) == B.DR_OK and m.value == 0
+    # packed 1x1 filters on 64 channels: two slices of 32, nothing to cut (114 tiles)
+    assert B.lib().dr_conv2d_workspace_bytes(_t(37, 64, 14, 14), B.conv_desc(64, 64, 1, layout=B.DR_KRSC), C.byref(m)) == B.DR_OK and m.value == 0
     assert B.lib().dr_conv2d_workspace_bytes(_t(1, 32, 56, 56), B.conv_desc(192, 64, 3, pad=1), C.byref(m)) == B.DR_ERR_SHAPE
     assert B.lib().dr_conv2d_fwd_ws(_t(1, 64, 56, 56), C.c_void_p(4096), B.conv_desc(192, 64, 3, stride=2, pad=1), C.c_void_p(4096), None,
                                     _t(1, 192, 28, 28), C.c_void_p(4096), 0, None, 0, None) == B.DR_ERR_WORKSPACE

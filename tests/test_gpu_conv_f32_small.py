@@ -119,6 +119,28 @@ def test_long_contractions_are_cut_where_there_is_scratch(n, c, hw, k, r, stride
     assert runs_small(n, c, hw, k, r, stride, False)
 
 
+@pytest.mark.parametrize("c,k,images", [
+    (64, 64, (90, 334, 335)),            # tiles of 64 x 64: 276, 1023 (32 channels deep), 1026 (16 deep)
+    (288, 2048, (21, 22)),               # 2080 and 2176, deep because of 2.3 MB of filters
+    (96, 96, (55, 56)),                  # 255 and 258 tiles of 32 x 128
+])
+def test_1x1_layers_at_any_slice_depth(c, k, images):
+    """Both depths of a slice, on either side of the rule's lines: the images of a batch have the bits they have in the largest one."""
+    rng = np.random.default_rng(c + k)
+    n = max(images)
+    x = rng.standard_normal((n, c, 14, 14)).astype(np.float32)
+    w = (rng.standard_normal((k, c, 1, 1)) * np.sqrt(2.0 / c)).astype(np.float32)
+    xg, wg = gpu(x), B.pack_filters(gpu(w))
+    out = {}
+    for m in images:
+        out[m] = torch.full((m, k, 14, 14), float("nan"), device="cuda")
+        B.conv2d_fwd(xg[:m], B.conv_desc(k, c, 1, 1, 1, 0, False, B.DR_KRSC), wg, None, out[m])
+    torch.cuda.synchronize()
+    assert close(host(out[n][-3:]), oracle.conv2d(x[-3:], w, None, 1, 0, False), TOL_F32)
+    for m in images:
+        assert torch.equal(out[m], out[n][:m])
+
+
 @pytest.mark.parametrize("form", ["original", "slim"])
 def test_module_whose_branches_share_launches(form):
     """A module on two ragged maps in every mode, packed filters, channel ranges of the output, stacked first steps."""
