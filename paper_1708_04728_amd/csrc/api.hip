@@ -589,12 +589,14 @@ bool small_pool_job(const dr_tensor& t, const void* x, const dr_tensor& o, void*
 }
 
 // Whether the module runs level by level, its steps sharing launches: at least two convolutions that can.  Where the caller wants the
-// branches on streams, every convolution has to be small: a level is a barrier between the branches, and larger layers fill the
-// device better side by side (the original GoogLeNet at batch 128, half of whose 14x14 steps are small: 1605 us against 1690).
+// branches on streams, every convolution has to, and most of them in the small-layer kernel: a level is a barrier between the
+// branches, and larger layers fill the device better side by side (the original GoogLeNet at batch 128, half of whose 14x14 steps are
+// small: 1605 us against 1690; 4c in fp32 on 64 images, one small layer of six: 203 against 237), while a large layer among small
+// ones does not (slim 5a in fp32 on 64 images, a 5x5 of 392 tiles beside three small layers: 113 against 95, as graphs).
 bool inception_by_levels(const dr_tensor& xd, const void* x, const dr_inception& d)
 {
     if (xd.layout != (xd.dtype == DR_BF16 ? DR_NHWC : DR_NCHW)) return false;
-    int n = 0, all = 0;
+    int n_small = 0, n_big = 0, all = 0;
     for (int b = 0; b < d.n_branches; ++b) {
         dr_tensor t = xd;
         for (int s = 0; s < d.branches[b].n_steps; ++s) {
@@ -602,13 +604,15 @@ bool inception_by_levels(const dr_tensor& xd, const void* x, const dr_inception&
             const dr_tensor o = stp.kind == DR_STEP_CONV ? conv_out(t, stp.conv) : pool_out(t, stp.pool);
             if (stp.kind == DR_STEP_CONV) {
                 const ConvGeom g = conv_geom(t, stp.conv, o);
-                n += small_takes(xd.dtype, g, s == 0 ? x : nullptr, nullptr) || (!(d.mode & DR_CONCURRENT_BRANCHES) && big_takes(xd.dtype, g));
+                if (small_takes(xd.dtype, g, s == 0 ? x : nullptr, nullptr)) ++n_small;
+                else if (big_takes(xd.dtype, g)) ++n_big;
                 ++all;
             }
             t = o;
         }
     }
-    return n >= 2 && (n == all || !(d.mode & DR_CONCURRENT_BRANCHES));
+    const int n = n_small + n_big;
+    return n >= 2 && (!(d.mode & DR_CONCURRENT_BRANCHES) || (n == all && 2 * n_small > all));
 }
 
 int inception_run_levels(const dr_tensor& xd, const void* x, const dr_inception& d, ParamCursor& wts, ParamCursor& bss, const dr_tensor& yd, void* y,

@@ -271,13 +271,14 @@ def _strided_module():
     ("4d", 9, 14, 512, True),       # first steps of 224, 280 and 56 tiles of 32 x 32: 504 as one layer, 560 as three
     ("5a", 64, 7, 832, False),      # 784, 490 and 98
     ("5b", 64, 7, 832, False),      # 1176, 588 and 196
+    ("5a slim", 64, 7, 832, True),  # three small layers and one that is not: by levels also with streams asked for
     ("strided", 4, 64, 64, False),
 ])
 def test_fp32_module_bits_do_not_depend_on_what_shares_a_launch(case):
     """Every execution mode adds a layer's products in one order: step by step, branch by branch (which is how a kernel trace has a module run),
     branches on streams of their own, first steps stacked."""
     name, n, side, c, stack = case
-    layer = _strided_module() if name == "strided" else workloads.inception_original(name)
+    layer = _strided_module() if name == "strided" else workloads.inception_slim(name[:2]) if "slim" in name else workloads.inception_original(name)
     rng = np.random.default_rng(n)
     x = np.abs(rng.standard_normal((n, c, side, side))).astype(np.float32)
     params = []
