@@ -140,6 +140,12 @@ bool same_shape(const dr_tensor& a, const dr_tensor& b)
     return a.n == b.n && a.c == b.c && a.h == b.h && a.w == b.w && a.layout == b.layout;
 }
 
+// Contraction length and output pixels are counted in 32 bits from here on.
+bool conv_too_large(const dr_conv& cd, const dr_tensor& o)
+{
+    return (double)cd.c * cd.r * cd.s >= 2147483648.0 || (double)o.n * o.h * o.w >= 2147483648.0;
+}
+
 // Validated convolution launch (shared by the single-layer entry points and the composite ones).
 // Geometry of layer cd on input xd with output descriptor o (the output tensor's fields are set by the caller).
 ConvGeom conv_geom(const dr_tensor& xd, const dr_conv& cd, const dr_tensor& o)
@@ -166,7 +172,7 @@ size_t conv_scratch_bytes(const dr_tensor& xd, const dr_conv& cd)
 {
     if (xd.dtype != DR_F32 || xd.layout != DR_NCHW) return 0;
     const dr_tensor o = conv_out(xd, cd);
-    if ((double)cd.c * cd.r * cd.s >= 2147483648.0 || (double)o.n * o.h * o.w >= 2147483648.0 || tensor_elems(o) == 0) return 0;
+    if (conv_too_large(cd, o) || tensor_elems(o) == 0) return 0;
     return conv_f32_scratch_bytes(conv_geom(xd, cd, o));
 }
 
@@ -184,8 +190,7 @@ int conv_run(const char* who, const dr_tensor& xd, const void* x, const dr_conv&
     if (xd.dtype == DR_F32 && xd.layout != DR_NCHW) return fail(DR_ERR_UNSUPPORTED, "%s: fp32 convolution takes NCHW tensors", who);
     if (xd.dtype == DR_F32 && cd.filter_layout == DR_KRSC && cd.c % 16 != 0)
         return fail(DR_ERR_UNSUPPORTED, "%s: fp32 KRSC filters need a channel count that is a multiple of 16 (got %d)", who, cd.c);
-    if ((double)cd.c * cd.r * cd.s >= 2147483648.0 || (double)o.n * o.h * o.w >= 2147483648.0)
-        return fail(DR_ERR_UNSUPPORTED, "%s: problem too large", who);
+    if (conv_too_large(cd, o)) return fail(DR_ERR_UNSUPPORTED, "%s: problem too large", who);
     if ((size_t)o.n * cd.k * o.h * o.w == 0) return DR_OK;   // nothing to compute: pointers may be NULL
     if (!x || !w || !y) return fail(DR_ERR_NULL, "%s: x, w or y is NULL", who);
     ConvGeom g = conv_geom(xd, cd, o);
@@ -603,6 +608,7 @@ bool inception_by_levels(const dr_tensor& xd, const void* x, const dr_inception&
             const dr_step& stp = d.branches[b].steps[s];
             const dr_tensor o = stp.kind == DR_STEP_CONV ? conv_out(t, stp.conv) : pool_out(t, stp.pool);
             if (stp.kind == DR_STEP_CONV) {
+                if (conv_too_large(stp.conv, o)) return false;             // refused when its turn comes
                 const ConvGeom g = conv_geom(t, stp.conv, o);
                 if (small_takes(xd.dtype, g, s == 0 ? x : nullptr, nullptr)) ++n_small;
                 else if (big_takes(xd.dtype, g)) ++n_big;

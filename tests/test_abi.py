@@ -88,6 +88,29 @@ def test_sizes_beyond_the_kernels_index_range_are_refused_on_the_host():
     assert "GiB" in B.last_error()
 
 
+def test_module_with_a_layer_beyond_the_index_range_is_refused():
+    """An intermediate layer of 2^32 + 2^16 output pixels, whose number counted in 32 bits looks small enough to run, then pooled to a map of one
+    row: refused like the single layer, whatever the mode, before anything is launched."""
+    fake = C.c_void_p(1 << 20)   # never dereferenced
+    d = B.dr_inception()
+    d.n_branches = 2
+    for b in range(2):
+        d.branches[b].n_steps = 2
+        d.branches[b].steps[0].kind = B.DR_STEP_CONV
+        d.branches[b].steps[0].conv = B.conv_desc(64, 16, 1, 1, 1, (32768, 32767), True, B.DR_KRSC)      # 1 x 2 -> 65537 x 65536
+        d.branches[b].steps[1].kind = B.DR_STEP_MAXPOOL
+        d.branches[b].steps[1].pool = B.dr_pool(65537, 65536, 65537, 65536, 0, 0)
+    weights = (C.c_void_p * 2)(1 << 20, 1 << 20)
+    biases = (C.c_void_p * 2)(None, None)
+    xd = _t(1, 16, 1, 2)
+    need = C.c_size_t(0)
+    assert B.lib().dr_inception_workspace_bytes(xd, d, C.byref(need)) == B.DR_OK and need.value > 2 ** 40
+    for mode in (0, B.DR_FUSE_RELU | B.DR_FUSE_CONCAT, B.DR_FUSE_RELU | B.DR_FUSE_CONCAT | B.DR_FUSE_STACK):
+        d.mode = mode
+        rc = B.lib().dr_inception_fwd(xd, fake, d, weights, biases, _t(1, 128, 1, 1), fake, fake, need.value, None)
+        assert rc == B.DR_ERR_UNSUPPORTED and "too large" in B.last_error(), (mode, rc, B.last_error())
+
+
 def test_inception_and_net_planning_on_host():
     layers = workloads.CONFIGS[2]["original"]
     d = G.inception_desc(layers[0][1], 192, 0)
