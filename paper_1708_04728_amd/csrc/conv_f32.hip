@@ -166,7 +166,8 @@ __device__ __forceinline__ void conv_f32_tile(const KArgs a, const int block, fl
         const int p = pix / g.Q, q = pix - p * g.Q;
         ih0 = p * g.sh - g.ph;
         iw0 = q * g.sw - g.pw;
-        xoff0 = img * g.C * HW + ih0 * g.W + iw0;
+        // (a padded filter taller than a wide map: offsets of rows outside it may pass 2^31, their sum with the tap's does not)
+        xoff0 = (int)((unsigned)(img * g.C * HW) + (unsigned)ih0 * (unsigned)g.W + (unsigned)iw0);
     }
     // ---- CF = false: the k table and this lane's masks of window rows / columns inside the image
     const bool rg = !CF && a.row_groups;
@@ -200,7 +201,7 @@ __device__ __forceinline__ void conv_f32_tile(const KArgs a, const int block, fl
                 int off = OOB, rs_bits = 31;          // beyond the contraction: the load returns 0 (mask bit 31 is never set)
                 if (k < g.Kg) {
                     const int c = k / RS, rs = k - c * RS, r = rs / S, s_ = rs - r * S;
-                    off = (c * HW + r * g.W + s_) * 4;
+                    off = (int)(((unsigned)(c * HW) + (unsigned)r * (unsigned)g.W + (unsigned)s_) * 4u);
                     rs_bits = r | (s_ << 8);
                 }
                 ktab[2 * k] = off;
@@ -228,7 +229,7 @@ __device__ __forceinline__ void conv_f32_tile(const KArgs a, const int block, fl
             lds_barrier();
         }
     }
-    const int bbase = n_ok ? xoff0 * 4 : OOB;        // (table paths) byte offset of this lane's window origin
+    const int bbase = n_ok ? (int)((unsigned)xoff0 * 4u) : OOB;        // (table paths) byte offset of this lane's window origin
 
     // ---- per-thread state for A: rows f / KQ of the slice, byte offset of the row start
     const bool vecA = (g.Kg & 3) == 0;
@@ -307,7 +308,7 @@ __device__ __forceinline__ void conv_f32_tile(const KArgs a, const int block, fl
                 for (int i = 0; i < B_PER; ++i) {
                     const int gq = k0 / 4 + bkq0 + i * BKQ_STEP;              // the same for the whole wave
                     const int xo = ktab[2 * gq], nt = ktab[2 * gq + 1] >> 24;
-                    const int vo = bbase + xo;
+                    const int vo = (int)((unsigned)bbase + (unsigned)xo);
                     f32x4 v;
                     if ((unsigned)vo < (unsigned)a.x_bytes && (unsigned)vo + 16u > (unsigned)a.x_bytes) {
                         // the tensor's last few elements: one by one, each checked against the end
@@ -359,7 +360,7 @@ __device__ __forceinline__ void conv_f32_tile(const KArgs a, const int block, fl
                     f32x4 v;
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
-                        int vo = bbase + off[j];
+                        int vo = (int)((unsigned)bbase + (unsigned)off[j]);
                         if (!nopad) {
                             const bool ok = ((rowmask >> (rsb[j] & 255)) & (colmask >> (rsb[j] >> 8)) & 1u) != 0;
                             vo = ok ? vo : OOB;

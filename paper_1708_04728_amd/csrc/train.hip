@@ -25,7 +25,7 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int OOB = (int)0x80000000;
+constexpr unsigned OOB = 0x80000000u;       // an offset beyond every buffer; offsets are unsigned, so that two of these may be added
 
 // grid of a grid-stride kernel: at most 4096 workgroups (the loss kernel leaves one partial sum per workgroup)
 inline unsigned blocks_for_train(size_t count)
@@ -34,7 +34,7 @@ inline unsigned blocks_for_train(size_t count)
     return (unsigned)(b < 1 ? 1 : (b > 4096 ? 4096 : b));
 }
 
-__device__ __forceinline__ float buf_load(__amdgpu_buffer_rsrc_t r, int voff, int soff)
+__device__ __forceinline__ float buf_load(__amdgpu_buffer_rsrc_t r, unsigned voff, int soff)
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
 }
@@ -158,12 +158,13 @@ __global__ __launch_bounds__(256) void conv_wgrad_f32_kernel(const WArgs a)
     const int tg = nt / a.cblocks, c0 = (nt - tg * a.cblocks) * CB;
     // column row0 + 8 i: tap i / IPT and channel row0 + 8 (i % IPT) of the tile; with tiles of 4 channels tap 2 i + row0 / 4, channel row0 % 4
     auto tap_of = [&](int t) __attribute__((always_inline)) { return tg * TPT + (TPT > 8 ? 2 * t + (row0 >> 2) : t); };
-    int a_row[8], b_row[8], tap_r[NT], tap_s[NT];
+    unsigned a_row[8], b_row[8];
+    int tap_r[NT], tap_s[NT];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int m = m0 + row0 + 8 * i, c = c0 + (TPT > 8 ? row0 & 3 : row0 + 8 * (i % IPT));
-        a_row[i] = m < a.K ? m * PQ * 4 : OOB;
-        b_row[i] = c < a.C && tap_of(i / IPT) < RS ? c * HW * 4 : OOB;
+        a_row[i] = m < a.K ? (unsigned)(m * PQ * 4) : OOB;
+        b_row[i] = c < a.C && tap_of(i / IPT) < RS ? (unsigned)(c * HW * 4) : OOB;
     }
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
@@ -178,14 +179,15 @@ __global__ __launch_bounds__(256) void conv_wgrad_f32_kernel(const WArgs a)
     auto fetch = [&](auto set_c) __attribute__((always_inline)) {
         constexpr int SET = decltype(set_c)::value;
         const bool on = pq < PQ;
-        const int za = on ? pq * 4 : OOB, soff_a = img * a.K * PQ * 4, soff_b = img * a.C * HW * 4;
+        const unsigned za = on ? (unsigned)(pq * 4) : OOB;
+        const int soff_a = img * a.K * PQ * 4, soff_b = img * a.C * HW * 4;
         const int ih0 = p * a.sh, iw0 = q * a.sw;
 #pragma unroll
         for (int i = 0; i < 8; ++i) ra[SET][i] = buf_load(rz, a_row[i] + za, soff_a);
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const int ih = ih0 + tap_r[t], iw = iw0 + tap_s[t];
-            const int xo = on && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W ? (ih * a.W + iw) * 4 : OOB;
+            const unsigned xo = on && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W ? (unsigned)((ih * a.W + iw) * 4) : OOB;
 #pragma unroll
             for (int i = t * IPT; i < (t + 1) * IPT; ++i) rb[SET][i] = buf_load(rx, b_row[i] + xo, soff_b);
         }
