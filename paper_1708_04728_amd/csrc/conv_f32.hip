@@ -669,17 +669,18 @@ static KArgs base_args(const ConvGeom& g, const float* x, const float* w, const 
 static bool rows_of_32(const ConvGeom& g) { return (g.K + 31) / 32 * 32 < (g.K + 63) / 64 * 64; }
 
 // Depth of a slice: 32 channels where the count allows, which halves the barriers, and 16 for layers of more 64 x 64 tiles than the
-// device holds at 32 (four workgroups per compute unit, seven at 16: 3x3 64 -> 192 on 28 x 28 x 32, 1176 tiles, 65 -> 56 us).  1x1 filters
-// have few slices and go by the same line (512 -> 256 on 14 x 14 x 37 images, 456 tiles, 32 deep 25.0, 16 deep 26.0 us; 512 -> 192 on
-// 28 x 28 x 32, 1176 tiles, 58 and 49), with tiles of 32 x 128 by one per compute unit (64 -> 16 on 28 x 28 x 16, 98 tiles, 5.6 and 7.4;
-// 192 -> 32 on 28 x 28 x 32, 196 tiles, 10.7 and 11.5; 512 -> 96 there, 588 tiles, 40 and 37), unless half the L2 of a die is filters,
-// of which a shallow slice fetches half lines (512 -> 2048 on 7 x 7 x 83, 2048 tiles, 82 and 91).  The sums are in the same order either way.
+// device holds at 32 (four workgroups per compute unit, seven at 16: 3x3 64 -> 192 on 28 x 28 x 32, 1176 tiles, 65 -> 56 us) unless
+// they are few more than it holds at 16 (3x3 64 -> 320 on 14 x 14 x 128, 1960 tiles, 32 deep 89, 16 deep 97; 5x5 96 -> 256 on
+// 27 x 27 x 48, 2188 tiles, 353 and 374; 3x3 64 -> 384 on 14 x 14 x 128, 2352 tiles, 109 and 103).  1x1 filters go by the same lines
+// (512 -> 256 on 14 x 14 x 37, 456 tiles, 25.0 and 26.0; 512 -> 192 on 28 x 28 x 32, 1176, 58 and 49; 512 -> 2048 on 7 x 7 x 83, 2048,
+// 82 and 91), with tiles of 32 x 128 by one per compute unit (64 -> 16 on 28 x 28 x 16, 98 tiles, 5.6 and 7.4; 192 -> 32 on 28 x 28 x 32,
+// 196, 10.7 and 11.5; 512 -> 96 there, 588, 40 and 37).  The sums are in the same order either way.
 static bool slices_of_32(const ConvGeom& g)
 {
-    const bool one = g.R * g.S == 1;
+    const long cus = device_cus(), tiles = ((long)g.K + 63) / 64 * (((long)g.Ng + 63) / 64);
     if (!g.w_krsc || g.C % 32 != 0) return false;
-    if (rows_of_32(g)) return !one || ((long)g.K + 31) / 32 * (((long)g.Ng + 127) / 128) <= device_cus();
-    return ((long)g.K + 63) / 64 * (((long)g.Ng + 63) / 64) <= 4 * device_cus() || (one && (size_t)g.K * g.Kg * 4 > (2u << 20));
+    if (rows_of_32(g)) return g.R * g.S > 1 || ((long)g.K + 31) / 32 * (((long)g.Ng + 127) / 128) <= cus;
+    return tiles <= 4 * cus || (g.C > 32 && tiles > 7 * cus && tiles <= 9 * cus);
 }
 
 bool conv_f32_group_takes(const ConvGeom& g)
