@@ -104,12 +104,12 @@ __device__ __forceinline__ float buf_load(__amdgpu_buffer_rsrc_t r, int voff, in
 
 // BM x BN: workgroup tile; WGM x WGN: wave grid (4 waves); BK: k per LDS slice; PF: prefetch distance
 // in slices; CF: slice order (see above); FR, FS: compile-time filter size for CF = false (0 = taken
-// from the geometry at run time); SPLIT: the workgroup takes range blockIdx.y of the contraction and
+// from the geometry at run time); TAB1: the table of one-word entries; SPLIT: the workgroup takes range blockIdx.y of the contraction and
 // stores raw partial sums.
 // The tile is computed by workgroup `block` of the layer's grid_m grid_n.  The LDS arrays (two buffers of BM resp. BN rows, the
 // table of CF = false) are separate objects of the kernel: carved out of one array, the compiler orders every read of one
 // operand behind the writes of the other (20 % slower).
-template <int BM, int BN, int WGM, int WGN, int BK, int PF, bool CF, int FR, int FS, bool SPLIT>
+template <int BM, int BN, int WGM, int WGN, int BK, int PF, bool CF, int FR, int FS, bool TAB1, bool SPLIT>
 __device__ __forceinline__ void conv_f32_tile(const KArgs a, const int block, float (*const As)[BM * (BK + 4)], float (*const Bs)[BN * (BK + 4)], int* const ktab)
 {
     constexpr int WM = BM / WGM, WN = BN / WGN;   // wave tile
@@ -170,17 +170,16 @@ __device__ __forceinline__ void conv_f32_tile(const KArgs a, const int block, fl
         xoff0 = (int)((unsigned)(img * g.C * HW) + (unsigned)ih0 * (unsigned)g.W + (unsigned)iw0);
     }
     // ---- CF = false: the k table and this lane's masks of window rows / columns inside the image
-    const bool rg = !CF && a.row_groups;
+    const bool rg = !CF && !TAB1 && a.row_groups;
     const int S4 = (S + 3) & ~3;
     const int kg_eff = rg ? g.C * R * S4 : g.Kg;     // contraction length including the taps added by rounding S up
     const int ktab_n = (kg_eff + BK - 1) / BK * BK;
-    const bool use_tab1 = !CF && !rg && ktab_n <= KTAB1 && tab1_fits(g.C, g.H, g.W, R, S);
-    const bool use_tab = !CF && !rg && !use_tab1 && ktab_n <= KTAB && R <= 31 && S <= 31;
+    const bool use_tab = !CF && !TAB1 && !rg && ktab_n <= KTAB && R <= 31 && S <= 31;
     const bool nopad = g.ph == 0 && g.pw == 0;      // then every window lies inside the image
     unsigned rowmask = 0, colmask = 0;
     unsigned tap_out = 0xFFFFFFFFu;                  // (one-word table) bit r S + s: that tap lies outside the image; bits beyond: set
     if constexpr (!CF) {
-        if (use_tab1) {
+        if constexpr (TAB1) {
             // one word per k: offset of x[0][c][r][s] in elements, and the tap
             for (int k = tid; k < ktab_n; k += NT) {
                 int e = tab1_entry(0, TAB1_NO_TAP);
@@ -336,7 +335,7 @@ __device__ __forceinline__ void conv_f32_tile(const KArgs a, const int block, fl
                     ra[SET][i] = v;
                 }
             }
-            if (use_tab1) {
+            if constexpr (TAB1) {
                 typedef int i32x4 __attribute__((ext_vector_type(4)));
 #pragma unroll
                 for (int i = 0; i < B_PER; ++i) {
@@ -495,15 +494,15 @@ __device__ __forceinline__ void conv_f32_tile(const KArgs a, const int block, fl
     }
 }
 
-template <int BM, int BN, int WGM, int WGN, int BK, int PF, bool CF, int FR, int FS, bool SPLIT>
+template <int BM, int BN, int WGM, int WGN, int BK, int PF, bool CF, int FR, int FS, bool TAB1, bool SPLIT>
 __global__ __launch_bounds__(NT) void conv_f32_kernel(const KArgs a)
 {
     __shared__ __attribute__((aligned(16))) float As[2][BM * (BK + 4)];
     __shared__ __attribute__((aligned(16))) float Bs[2][BN * (BK + 4)];
-    // (filters known to have more than 31 taps never use the one-word table: 4 KB less is one workgroup more per compute unit, which
-    // AlexNet's first two convolutions at batch 128 show as 1465 us against 1518)
-    __shared__ __attribute__((aligned(16))) int ktab[CF ? 4 : FR * FS > 31 ? 2 * KTAB : KTAB1];   // CF = false: {byte offset, r | s << 8} per k
-    conv_f32_tile<BM, BN, WGM, WGN, BK, PF, CF, FR, FS, SPLIT>(a, (int)blockIdx.x, As, Bs, ktab);
+    // (the one-word table is an instantiation of its own: the longer table costs the other paths a workgroup per compute unit, which
+    // AlexNet's first two convolutions at batch 128 show as 1465 us against 1518, and its code the element-by-element path 4 to 15 %)
+    __shared__ __attribute__((aligned(16))) int ktab[CF ? 4 : TAB1 ? KTAB1 : 2 * KTAB];   // CF = false: {byte offset, r | s << 8} per k
+    conv_f32_tile<BM, BN, WGM, WGN, BK, PF, CF, FR, FS, TAB1, SPLIT>(a, (int)blockIdx.x, As, Bs, ktab);
 }
 
 // Several layers in one launch (KRSC filters or 1x1; each with the tile it would have by itself): the layers' tiles fill the device
@@ -522,8 +521,8 @@ __global__ __launch_bounds__(NT) void conv_f32_group_kernel(const GroupArgs args
     while (ji + 1 < args.n && (int)blockIdx.x >= args.first[ji + 1]) ++ji;
     const KArgs a = args.job[ji];
     const int block = (int)blockIdx.x - args.first[ji];
-    if (args.rows32[ji]) conv_f32_tile<32, 128, 1, 4, 16, 2, true, 0, 0, false>(a, block, (float (*)[32 * 20])As, (float (*)[128 * 20])Bs, nullptr);
-    else conv_f32_tile<64, 64, 2, 2, 16, 2, true, 0, 0, false>(a, block, (float (*)[64 * 20])As, (float (*)[64 * 20])Bs, nullptr);
+    if (args.rows32[ji]) conv_f32_tile<32, 128, 1, 4, 16, 2, true, 0, 0, false, false>(a, block, (float (*)[32 * 20])As, (float (*)[128 * 20])Bs, nullptr);
+    else conv_f32_tile<64, 64, 2, 2, 16, 2, true, 0, 0, false, false>(a, block, (float (*)[64 * 20])As, (float (*)[64 * 20])Bs, nullptr);
 }
 
 // y = bias + residual + sum over the ranges of a split contraction, ReLU: one thread per output element,
@@ -609,18 +608,27 @@ int launch_tile(const KArgs& base, void* ws, size_t ws_bytes, hipStream_t st)
     }
     const dim3 grid((unsigned)(a.grid_m * a.grid_n), (unsigned)a.splits), block(NT);
     const int R = a.g.R, S = a.g.S;
-#define DR_LAUNCH(CF, FR, FS)                                                                                              \
+#define DR_LAUNCH(CF, FR, FS, TAB1)                                                                                              \
     do {                                                                                                                   \
-        if (a.part) hipLaunchKernelGGL((conv_f32_kernel<BM, BN, WGM, WGN, BK, PF, CF, FR, FS, true>), grid, block, 0, st, a);   \
-        else hipLaunchKernelGGL((conv_f32_kernel<BM, BN, WGM, WGN, BK, PF, CF, FR, FS, false>), grid, block, 0, st, a);         \
+        if (a.part) hipLaunchKernelGGL((conv_f32_kernel<BM, BN, WGM, WGN, BK, PF, CF, FR, FS, TAB1, true>), grid, block, 0, st, a);   \
+        else hipLaunchKernelGGL((conv_f32_kernel<BM, BN, WGM, WGN, BK, PF, CF, FR, FS, TAB1, false>), grid, block, 0, st, a);         \
     } while (0)
-    if (a.g.C % BK == 0 && (a.w_krsc || R * S == 1)) DR_LAUNCH(true, 0, 0);      // (a 1x1 filter bank is the same array in both orders)
-    else if (R == 1 && S == 1) DR_LAUNCH(false, 1, 1);
-    else if (R == 3 && S == 3) DR_LAUNCH(false, 3, 3);
-    else if (R == 5 && S == 5) DR_LAUNCH(false, 5, 5);
-    else if (R == 7 && S == 7) DR_LAUNCH(false, 7, 7);
-    else if (R == 11 && S == 11) DR_LAUNCH(false, 11, 11);
-    else DR_LAUNCH(false, 0, 0);
+    if constexpr (BK == 32) {
+        DR_LAUNCH(true, 0, 0, false);                // (see slices_of_32)
+    } else {
+        const bool tab1 = !a.row_groups && a.g.Kg <= KTAB1 && tab1_fits(a.g.C, a.g.H, a.g.W, R, S);
+        if (a.g.C % BK == 0 && (a.w_krsc || R * S == 1)) DR_LAUNCH(true, 0, 0, false);      // (a 1x1 filter bank is the same array in both orders)
+        else if (tab1 && R == 1 && S == 1) DR_LAUNCH(false, 1, 1, true);
+        else if (tab1 && R == 3 && S == 3) DR_LAUNCH(false, 3, 3, true);
+        else if (tab1 && R == 5 && S == 5) DR_LAUNCH(false, 5, 5, true);
+        else if (tab1) DR_LAUNCH(false, 0, 0, true);
+        else if (R == 1 && S == 1) DR_LAUNCH(false, 1, 1, false);
+        else if (R == 3 && S == 3) DR_LAUNCH(false, 3, 3, false);
+        else if (R == 5 && S == 5) DR_LAUNCH(false, 5, 5, false);
+        else if (R == 7 && S == 7) DR_LAUNCH(false, 7, 7, false);
+        else if (R == 11 && S == 11) DR_LAUNCH(false, 11, 11, false);
+        else DR_LAUNCH(false, 0, 0, false);
+    }
 #undef DR_LAUNCH
     const int rc = check_launch("conv_f32");
     if (rc != DR_OK) return rc;
