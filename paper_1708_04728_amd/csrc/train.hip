@@ -297,8 +297,10 @@ __global__ __launch_bounds__(256) void sgd_step_kernel(float* __restrict__ w, co
 }
 
 // How the gradient's GEMM is tiled and split: column tiles of 64 to 4 channels per tap (whichever gives the fewest, the most channels first:
-// a tap costs a padding test), and as many
-// ranges of slices as make up to four workgroups per compute unit, of at least four slices each.
+// a tap costs a padding test), and as many ranges of slices as make up to four workgroups per compute unit, of at least four slices
+// each, but from eight slices on a range per image up to 16 (3x3 8 -> 32 at stride 4 on 15 x 18 x 10 images, ten slices: 14.0 us in two
+// ranges, 11.0 in ten); the sum of the ranges costs what more or shorter ones gain (7x7 128 -> 64 at stride 2 on 10 x 37 x 2, six
+// slices: 12.9 in one range, 15.5 in two, 19.0 in six).
 struct WPlan { int cb_log2, cblocks, grid_m, grid_n, slices_per_img, slices, splits; };
 WPlan wgrad_plan(const ConvGeom& g)
 {
@@ -314,7 +316,7 @@ WPlan wgrad_plan(const ConvGeom& g)
     p.slices_per_img = std::max(1, (g.P * g.Q + BL - 1) / BL);
     p.slices = g.P * g.Q > 0 ? g.N * p.slices_per_img : 0;
     const int tiles = p.grid_m * p.grid_n;
-    p.splits = std::max(1, std::min(4 * device_cus() / tiles, p.slices / 4));
+    p.splits = std::max(1, std::min(4 * device_cus() / tiles, std::max(p.slices / 4, p.slices >= 8 ? std::min(g.N, 16) : 1)));
     return p;
 }
 

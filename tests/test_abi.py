@@ -141,6 +141,9 @@ def test_inception_and_net_planning_on_host():
     assert B.lib().dr_conv2d_workspace_bytes(_t(1, 32, 56, 56), B.conv_desc(192, 64, 3, pad=1), C.byref(m)) == B.DR_ERR_SHAPE
     assert B.lib().dr_conv2d_fwd_ws(_t(1, 64, 56, 56), C.c_void_p(4096), B.conv_desc(192, 64, 3, stride=2, pad=1), C.c_void_p(4096), None,
                                     _t(1, 192, 28, 28), C.c_void_p(4096), 0, None, 0, None) == B.DR_ERR_WORKSPACE
+    # parameter gradient on ten small maps: ten partial sums of 32 x (2 column tiles of 64) and of the bias gradient
+    assert B.lib().dr_conv2d_bwd_params_workspace_bytes(_t(10, 8, 15, 18), B.conv_desc(32, 8, 3, stride=4, pad=1, relu=True), C.byref(m)) == B.DR_OK
+    assert m.value == 10 * 32 * (2 * 64 + 1) * 4
     bad = G.inception_desc(layers[0][1], 100, 0)
     assert B.lib().dr_inception_workspace_bytes(xd, bad, C.byref(n)) == B.DR_ERR_SHAPE
 

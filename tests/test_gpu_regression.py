@@ -44,6 +44,8 @@ WGRAD_CASES = [
     (3, 8, 13, 9, 65, 3, 3, 1, 1),        # tiles of eight taps by 8 channels, one tap in the second
     (2, 9, 12, 11, 20, 4, 4, 1, 1),       # tiles of sixteen taps by 4 channels, one channel in the third
     (2, 3, 43, 39, 33, 11, 11, 4, 0),     # a layer on the image: eight tiles of sixteen taps, nine taps in the last
+    (10, 8, 15, 18, 32, 3, 3, 4, 1),      # ten images of one slice each: a range per image
+    (20, 3, 12, 8, 40, 3, 3, 4, 1),       # twenty: sixteen ranges, some of two slices
 ]
 
 
