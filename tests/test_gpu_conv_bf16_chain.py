@@ -69,3 +69,43 @@ def test_chain(case):
         ref = oracle.forward(layers, params, x, mirror_bf16=True, fold="given")
         # two implementations that round every stored tensor to bf16: 2e-2 per rounding in quadrature, 3 per block
         assert close(out[0], ref, TOL_BF16 * (3 * len(blocks)) ** 0.5, "oracle with bf16 storage")
+
+
+@pytest.mark.parametrize("c,blocks,joined", [
+    (64, ((64, 256),), True),
+    (24, ((40, 72),), True),
+    (64, ((64, 256), (64, 256)), True),          # with the next block's first layer
+    (64, ((64, 256), (72, 256)), True),          # a next block that is too wide to be joined
+    (64, ((64, 264),), False),                   # more outputs than the kernel holds
+    (72, ((64, 256),), False),                   # a projected shortcut over more channels than it holds
+    (64, ((72, 256),), False),                   # more inner channels
+])
+def test_the_projected_shortcut_is_stored_only_where_the_kernel_does_not_run(c, blocks, joined):
+    """Which way a block went, by the scratch memory of its projected shortcut: the kernel keeps the shortcut in registers, the layers one by one
+    (also: the kernel under a trace) store it."""
+    n, h, w = 2, 7, 9
+    rng = np.random.default_rng(c + len(blocks))
+    layers, params = stage(rng, c, blocks)
+    xg = G.to_device(workloads.round_to_bf16(np.abs(rng.standard_normal((n, c, h, w))).astype(np.float32)), "bf16", nhwc=True)
+    net = B.Net(G.net_descs(layers, c, folded=True, pack="bf16"))
+    flat = G.flat_params(params, "bf16", pack=True)
+    y = G.empty_like_desc(net.output_desc(B.desc(xg)))
+    need = net.workspace_bytes(B.desc(xg))
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    # the scratch of a block: the outputs of its first and second layer and of its projection, each from a multiple of 256 bytes
+    up = lambda v: (v + 255) // 256 * 256
+    sizes = [(up(n * h * w * m * 2), n * h * w * k * 2 if i == 0 else 0) for i, (m, k) in enumerate(blocks)]
+    base = need - max(2 * mid + up(proj) for mid, proj in sizes)
+    lo, hi = base + 2 * sizes[0][0], base + 2 * sizes[0][0] + sizes[0][1]
+    for traced in (False, True):
+        ws.fill_(255)
+        if traced:
+            B.trace_begin()
+        net.fwd(xg, flat, y, ws)
+        torch.cuda.synchronize()
+        if traced:
+            B.trace_end()
+        # (a wider block behind uses the start of the same memory for its own layers)
+        part = ws[max(lo, base + 2 * max(mid for mid, _ in sizes)):hi]
+        assert part.numel() > 0
+        assert bool((part == 255).all()) == (joined and not traced), (traced, joined)

@@ -13,13 +13,10 @@ from util import TOL_BF16, case_seed, close, empty_nhwc, gpu, gpu_nhwc, host_nhw
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
-CUS = 256
-
-
 def takes(N, C, H, W, K, R, S, stride, pad):
     """The launcher's rule, restated."""
     n = N * oracle.conv_out_size(H, R, stride, pad) * oracle.conv_out_size(W, S, stride, pad)
-    return -(-n // 64) * -(-K // 64) <= (2 if R * S > 1 else 1) * CUS
+    return -(-n // 64) * -(-K // 64) <= (2 if R * S > 1 else 1) * torch.cuda.get_device_properties(0).multi_processor_count
 
 
 @pytest.mark.parametrize("case", [
@@ -54,6 +51,34 @@ def test_small_layer(case):
         got = host_nhwc(y)
         # one rounding of an fp32 sum: within one unit of the last place of the rounded exact result
         assert close(got, oracle.round_bf16(ref), 2.0 ** -7, "within one bf16 unit of the oracle")
+
+
+@pytest.mark.parametrize("case", [
+    # images within the rule and beyond it, C, H, W, K, R, stride
+    (2, 3, 24, 96, 84, 104, 3, 1),        # slices that run on from filter row to filter row; beyond: the streaming kernel
+    (8, 9, 128, 64, 64, 64, 3, 1),        # whole taps; beyond: the patch kernel
+    (8, 9, 32, 64, 64, 64, 5, 1),         # beyond: the row-stack kernel
+    (14, 15, 72, 96, 96, 64, 3, 2),       # stride 2
+    (5, 6, 200, 28, 28, 232, 1, 1),       # 1x1
+])
+def test_the_larger_kernels_bits(case):
+    """The slices are multiplied in the order of the kernels for larger layers: the images of a batch just within the rule have the bits
+    that they have in one just beyond it."""
+    few, many, C, H, W, K, R, stride = case
+    assert takes(few, C, H, W, K, R, R, stride, R // 2) and not takes(many, C, H, W, K, R, R, stride, R // 2)
+    gen = torch.Generator(device="cuda").manual_seed(C)
+    x = torch.randn((many, H, W, C), device="cuda", generator=gen).to(torch.bfloat16)
+    w = B.pack_filters((torch.randn((K, C, R, R), device="cuda", generator=gen) * (2.0 / (C * R * R)) ** 0.5).to(torch.bfloat16))
+    b = torch.randn(K, device="cuda", generator=gen) * 0.1
+    cd = B.conv_desc(K, C, R, R, stride, R // 2, True, B.DR_KRSC)
+    out = []
+    for n in (few, many):
+        y = torch.full((n, oracle.conv_out_size(H, R, stride, R // 2), oracle.conv_out_size(W, R, stride, R // 2), K), float("nan"), dtype=torch.bfloat16, device="cuda")
+        B.conv2d_fwd_ws(B.NHWC(x[:n]), cd, w, b, B.NHWC(y), None)
+        out.append(y)
+    torch.cuda.synchronize()
+    assert torch.isfinite(out[1].float()).all() and float(out[1].float().abs().max()) > 0
+    assert torch.equal(out[0], out[1][:few])
 
 
 def test_small_layer_into_an_odd_channel_range():
