@@ -194,10 +194,10 @@ def ceilings():
 
 
 def layer_trace(cfg_id):
-    """For a run under `rocprofv3 --kernel-trace`: every form's forward four times, kernel by kernel with the branches of
-    a module in turn, each forward preceded by a marker kernel (torch's cos_ on 7 floats), so that the kernels of the
-    trace between two markers can be matched, in order, with the launches the library reports for that form.  Prints
-    one JSON line: per form the launches as [label, K, C, R, S, items, algorithmic bytes]."""
+    """For a run under `rocprofv3 --kernel-trace`: every form's forward four times, layer by layer with the branches of
+    a module in turn (which is how the library runs while its own trace is on), each forward preceded by a marker kernel
+    (torch's cos_ on 7 floats), so that the kernels of the trace between two markers can be matched, in order, with the launches the
+    library reports for that form.  Prints one JSON line: per form the launches as [label, K, C, R, S, items, algorithmic bytes]."""
     import torch
     wl = Workload(cfg_id, serial_branches=True)
     for _ in range(3):
@@ -210,7 +210,7 @@ def layer_trace(cfg_id):
         for _ in range(4):
             marker.cos_()
             torch.cuda.synchronize()
-            wl.run(form)
+            wl.trace(form)
             torch.cuda.synchronize()
     marker.cos_()
     torch.cuda.synchronize()

@@ -234,7 +234,11 @@ typedef struct { int n_steps; dr_step steps[DR_MAX_STEPS]; } dr_branch;
 /* How the module is executed.  0 = the layer-by-layer form the paper times: every ReLU is its own
  * kernel and the branch outputs are gathered by a concat kernel.  (In every mode the convolutions at one depth of the
  * branches, a 3x3 pooling step beside them, and the ReLUs behind them may share a launch each where the layers are
- * small; each layer still reads its whole input and writes its whole output.)  Flags remove passes without changing the function computed: */
+ * small; each layer still reads its whole input and writes its whole output.  Not while a kernel trace runs, filtered or
+ * not: there every layer is a launch of its own.)  Flags remove passes without changing the function computed.  Bits: bf16 modules have
+ * the same in every mode; fp32 modules in every mode and under a trace except that DR_FUSE_STACK adds the products of the stacked
+ * convolutions in another order where the stacked layer is run by another kernel than its banks alone (banks small enough for the
+ * small-layer kernel, or cut over workgroups, and the stacked layer not). */
 #define DR_FUSE_RELU   1   /* ReLU in the convolution's store */
 #define DR_FUSE_CONCAT 2   /* a branch ending in a convolution writes its channel range of y directly
                               (that convolution then also applies its ReLU in the store) */

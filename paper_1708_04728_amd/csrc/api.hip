@@ -718,7 +718,8 @@ int inception_run(const dr_tensor& xd, const void* x, const dr_inception& d, Par
 {
     const char* who = "dr_inception_fwd";
     const bool fuse_relu = d.mode & DR_FUSE_RELU, fuse_cat = d.mode & DR_FUSE_CONCAT;
-    // A trace of every kernel (no label filter) is there to time each kernel on its own: it runs the branches in turn.
+    // A trace times layers, so while one runs each layer is a launch of its own; a trace of every kernel (no label filter) is there to
+    // time each kernel by itself and also runs the branches in turn.
     const bool full_trace = g_trace.active && !g_trace.filter[0];
     if (!ar.measure && !g_trace.active && wts.p && bss.p && inception_by_levels(xd, x, d)) return inception_run_levels(xd, x, d, wts, bss, yd, y, ar, main_st);
     ConcatSeg segs[DR_MAX_BRANCHES];

@@ -17,7 +17,7 @@
 //     module's pooling branch needs beside the other branches' first steps.
 // Measured in chains of dependent launches, streaming kernel -> this one: 3x3 160 -> 320 on one 14 x 14 image 12.3 -> 8.9 us (of
 // which 3.3 are the launch), 5x5 32 -> 512 9.0 -> 5.9 us, 1x1 832 -> 624 on 7 x 7 7.3 -> 5.6 us, 3x3 96 -> 128 on 28 x 28 x 8
-// 9.4 -> 8.2 us; the slim GoogLeNet on one image 272 -> 158 us.
+// 9.4 -> 8.2 us; the slim GoogLeNet on one image, wall time of a pass among others, 272 -> 151 us.
 // What bounds it now: about 0.2 us per slice -- a wave takes 300 cycles to read a slice's 8 KB of operands from LDS and a load that
 // writes LDS takes its sender about 50, so neither more slices in flight nor eight loading waves nor reads dealt out between
 // the matrix instructions made it faster.
