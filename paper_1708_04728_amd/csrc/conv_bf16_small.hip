@@ -7,20 +7,25 @@
 // slice costs it 0.4 us (its waves send the slice's loads, wait for older ones, meet, read operands and multiply one after
 // the other) while most compute units stand idle.  Here
 //   * the tile is as small as the layer leaves compute units for: 32 x 32, 64 x 32 or 64 x 64;
-//   * one wave per 32 x 32 block multiplies and does nothing else; four other waves send the loads.  They meet once per slice.
-//     The slices are multiplied in the same order as in the streaming kernel, so the results are the same bits.  (Sharing the
-//     contraction among eight waves was faster still, 6.2 against 8.9 us on the layer below, but adds the products in
-//     another order: a few outputs in ten thousand round the other way, and 25 layers later the class probabilities of
-//     GoogLeNet differ by 1 to 3 %.)
+//   * some waves multiply and do nothing else, others send the loads; they meet once per stage of two slices.  The multiplying waves
+//     use the 16 x 16 x 32 instruction, which adds in the order of the 32 x 32 x 16 one (compared bit by bit on the card), so that the
+//     results are the bits of the streaming kernel; four waves then read the operands of a 32 x 32 tile from LDS at once.  (Sharing the
+//     contraction among the waves adds the products in another order: a few outputs in ten thousand round the other way, and 25
+//     layers later the class probabilities of GoogLeNet differ by 1 to 3 %.)
+//   * where a chunk of the contraction lies is worked out once, by the multiplying waves while the loading waves decode their pixels: a
+//     table in LDS, chunk -> {offset, tap}.  A load then costs its wave half a dozen instructions.  Decoding chunk by chunk in every
+//     loading wave was what bounded the kernel before: with every load and every multiplication taken out the slice still took
+//     0.16 of its 0.2 us;
+//   * two groups of loading waves send a slice each of a stage;
 //   * one launch takes several layers (the second steps of an inception module, say): a launch costs 3 to 4 us on a
 //     stream whatever it does, as much as the layer itself.  A job may also be a 3x3 max-pooling layer, which a
 //     module's pooling branch needs beside the other branches' first steps.
-// Measured in chains of dependent launches, streaming kernel -> this one: 3x3 160 -> 320 on one 14 x 14 image 12.3 -> 8.9 us (of
-// which 3.3 are the launch), 5x5 32 -> 512 9.0 -> 5.9 us, 1x1 832 -> 624 on 7 x 7 7.3 -> 5.6 us, 3x3 96 -> 128 on 28 x 28 x 8
-// 9.4 -> 8.2 us; the slim GoogLeNet on one image, wall time of a pass among others, 272 -> 151 us.
-// What bounds it now: about 0.2 us per slice -- a wave takes 300 cycles to read a slice's 8 KB of operands from LDS and a load that
-// writes LDS takes its sender about 50, so neither more slices in flight nor eight loading waves nor reads dealt out between
-// the matrix instructions made it faster.
+// Measured in chains of dependent launches of one layer (3.1 us of which are the launch), one wave per 32 x 32 block and four loading waves that
+// decode -> this form: 3x3 160 -> 320 on one 14 x 14 image 8.5 -> 5.9 us, 5x5 32 -> 512 6.2 -> 4.9, 1x1 832 -> 624 on 7 x 7 5.4 -> 4.8,
+// 3x3 96 -> 128 on 28 x 28 x 8 (64 x 64 tiles, one per compute unit) 8.2 -> 6.7, 3x3 144 -> 288 on 14 x 14 x 19 (two per compute unit)
+// 12.8 -> 10.8; the slim GoogLeNet on one image 147 -> 121 us.
+// What bounds it now: 0.11 us per slice for tiles of 32 x 32 and, at two tiles of 64 x 64 per compute unit, the path from L2 into LDS (32 loads
+// of 1 KiB per pair of slices, about 24 cycles each).
 //
 // Operands travel as in the streaming kernel: 16-byte buffer loads that write LDS, lanes outside the tensor or in the padding at
 // an offset the hardware answers with zeros, chunk j of row r stored at chunk j ^ ((r >> 1) & 7) so that loads and operand
@@ -31,6 +36,18 @@
 
 namespace dr {
 namespace {
+
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int SMALL_TABLE = 2048;                        // chunks of 8 contraction elements that a layer may have (16 KB of LDS), 1x1 filters at stride 1 aside
+__device__ __forceinline__ void touch(u32x2& v) { asm volatile("" : "+v"(v)); }
+template <int OFF>
+__device__ __forceinline__ u32x2 ds_read8(unsigned addr)         // valid after wait_lgkm or ring_barrier, and touch
+{
+    u32x2 v;
+    asm volatile("ds_read_b64 %0, %1 offset:%2" : "=&v"(v) : "v"(addr), "n"(OFF));
+    return v;
+}
 
 struct SmallJob {
     const uint16_t* x;
@@ -43,15 +60,17 @@ struct SmallJob {
     int C, H, W, K, R, S, sh, sw, ph, pw, P, Q, Kg, Ng, relu;
     int x_bytes, w_bytes;
     int stem_hp, stem_wp;                                // padded 4-channel input copy (see launch_conv_bf16_stem), 0: ordinary input
-    int tap, flat, pointwise;                                       // slices: whole taps (C % 64 == 0); running on from filter row to filter row
-    int c8, run_chunks, spr, slices;                     // chunks per tap, per filter row; slices per filter row, per tile
-    unsigned magic_c8;
+    int pointwise;
+    int c8, run_chunks;                                  // 16-byte chunks per tap, per filter row
+    int row_chunks;                                      // chunks from filter row to filter row of the slices: run_chunks, or rounded up to whole slices
+    int slices;
+    unsigned magic_c8, magic_row;
     unsigned long long m_pq, m_q;
-    int n_tiles, tiles, first;                           // pixel tiles; tiles in all; first workgroup (a multiple of 8)
+    int n_tiles, tiles;                                  // pixel tiles; tiles in all
     int vec;                                             // whole groups of 8 filters, 16-byte accesses of output, residual and bias aligned
 };
 struct SmallArgs {
-    int n;
+    int first[SMALL_GROUP_MAX];                          // first workgroup of each job (a multiple of 8); beyond the last: INT_MAX
     SmallJob job[SMALL_GROUP_MAX];
 };
 
@@ -85,35 +104,38 @@ __device__ __forceinline__ void pool_items(const SmallJob& j, int block)
     *reinterpret_cast<u32x4*>(j.y_seg[0] + (size_t)n * j.C + cv * 8) = o;
 }
 
-// CM x CN multiplying waves with one block of 32 x 32 each, four loading waves, NS slices in LDS.
-template <int CM, int CN, int NS>
-__global__ __launch_bounds__((CM * CN + 4) * 64) void conv_bf16_small_kernel(const SmallArgs args)
+// A tile of 16 TM WM filters x 16 TN WN pixels: WM x WN multiplying waves with TM x TN blocks of 16 x 16 each, LG groups of four loading
+// waves, NS stages of G slices in LDS.
+template <int TM, int TN, int WM, int WN, int LG, int NS, int G>
+__global__ __launch_bounds__((WM * WN + 4 * LG) * 64) void conv_bf16_small_kernel(const SmallArgs args)
 {
-    constexpr int CW = CM * CN, LW = 4, BM = CM * 32, BN = CN * 32, A_PER = CM, B_PER = CN, L = A_PER + B_PER, STAGE = (BM + BN) * 128;
-    static_assert((NS - 1) * L < 63, "loads in flight");
+    constexpr int CW = WM * WN, BM = WM * TM * 16, BN = WN * TN * 16, A_PER = BM / 32, B_PER = BN / 32, SLICE = (BM + BN) * 128, STAGE = G * SLICE;
+    constexpr int SL = G / LG, L = SL * (A_PER + B_PER);                     // slices of a stage that a loading wave sends, its loads
+    static_assert(G % LG == 0 && BM % 32 == 0 && BN % 32 == 0 && (NS - 1) * L < 63, "loads in flight");
     __shared__ __attribute__((aligned(1024))) unsigned char ring[NS * STAGE];
+    __shared__ __attribute__((aligned(16))) u32x2 table[SMALL_TABLE];        // chunk of the contraction -> {byte offset in x, tap}, see below
 
     // ---- the job and the tile.  Workgroup b runs on die b & 7; a die takes a contiguous range of tiles, filter block by filter
     // block, so that the pixel tiles of one filter block read it from one L2.  (The job is copied: left in the argument
     // buffer, every field would be read again behind each wait.)
-    int ji = 0;
-    while (ji + 1 < args.n && (int)blockIdx.x >= args.job[ji + 1].first) ++ji;
+    static_assert(SMALL_GROUP_MAX == 4, "jobs");
+    const int ji = ((int)blockIdx.x >= args.first[1]) + ((int)blockIdx.x >= args.first[2]) + ((int)blockIdx.x >= args.first[3]);
     const SmallJob j = args.job[ji];
-    const int b = (int)blockIdx.x - j.first, die = b & 7, s_die = b >> 3, per = j.tiles >> 3, odd = j.tiles & 7;
+    const int b = (int)blockIdx.x - args.first[ji], die = b & 7, s_die = b >> 3, per = j.tiles >> 3, odd = j.tiles & 7;
     if (s_die >= per + (die < odd ? 1 : 0)) return;
     const int t = die * per + min(die, odd) + s_die;
     if (!j.w) { pool_items(j, t); return; }
     const int mt = t / j.n_tiles, nt = t - mt * j.n_tiles;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int slices = j.slices;
+    const int slices = j.slices, stages = (slices + G - 1) / G;
 
-    // Iteration k, for every wave: at the barrier slice k has landed and slice k - 1 has been read; behind it the multiplying waves
-    // read slice k and multiply slice k - 1, the loading waves send slice k + NS - 1 into the stage slice k - 1 has left.
+    // Iteration k, for every wave: at the barrier stage k has landed and stage k - 1 has been read; behind it the multiplying waves
+    // read stage k and multiply stage k - 1, the loading waves send stage k + NS - 1 into the LDS stage k - 1 has left.
     if (wave >= CW) {
         // ---- loading: pass i of this wave fills rows 32 i + lrow of an operand
         const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)j.x, 0, j.x_bytes, 0x00020000);
         const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)j.w, 0, j.w_bytes, 0x00020000);
-        const int lw = wave - CW, lrow = lw * 8 + (lane >> 3), lc = (lane & 7) ^ ((lrow >> 1) & 7);
+        const int lw = (wave - CW) & 3, lg = (wave - CW) >> 2, lrow = lw * 8 + (lane >> 3), lc = (lane & 7) ^ ((lrow >> 1) & 7);
         int a_voff[A_PER], b_base[B_PER];
         unsigned b_mask[B_PER];                          // bits 0..15: tap s is OUTSIDE the image row; bits 16..31: filter row r is inside
 #pragma unroll
@@ -126,7 +148,7 @@ __global__ __launch_bounds__((CM * CN + 4) * 64) void conv_bf16_small_kernel(con
             const int n = nt * BN + i * 32 + lrow;
             const bool in = n < j.Ng;
             if (j.pointwise) {                           // output pixel n reads input pixel n
-                b_base[i] = (n * j.C + lc * 8) * 2;
+                b_base[i] = n * j.C * 2;
                 b_mask[i] = in ? 0x1FFFEu : 0xFFFFu;
             } else {
                 const int nn = in ? n : 0;
@@ -137,162 +159,190 @@ __global__ __launch_bounds__((CM * CN + 4) * 64) void conv_bf16_small_kernel(con
                     continue;
                 }
                 const int ih0 = p * j.sh - j.ph, iw0 = q * j.sw - j.pw;
-                b_base[i] = (((img * j.H + ih0) * j.W + iw0) * j.C + lc * 8) * 2;
+                b_base[i] = ((img * j.H + ih0) * j.W + iw0) * j.C * 2;
                 const unsigned wv = bit_range(max(0, -iw0), min(j.S - 1, j.W - 1 - iw0));
                 const unsigned hv = in ? bit_range(max(0, -ih0), min(j.R - 1, j.H - 1 - ih0)) : 0u;
                 b_mask[i] = (~wv & 0xFFFFu) | (hv << 16);
             }
         }
-        int ld_r = 0, ld_s = 0, ld_j0 = 0, ld_stage = 0;     // filter row, tap (tap mode), first chunk of the next slice in the tap / row
-        auto issue_slice = [&]() __attribute__((always_inline)) {
-            unsigned char* sa = ring + ld_stage * STAGE + lw * 1024;
-            unsigned char* sb = sa + BM * 128;
-            ld_stage = ld_stage + 1 == NS ? 0 : ld_stage + 1;
-            if (j.tap) {
-                const int soff_a = ((ld_r * j.S + ld_s) * j.c8 + ld_j0) * 16, off = (ld_r * j.W + ld_s) * j.C * 2 + ld_j0 * 16;
-                const unsigned want = 1u << (16 + ld_r), sel = want | (1u << ld_s);
-#pragma unroll
-                for (int i = 0; i < A_PER; ++i) load_to_lds16(rw, sa + i * 4096, a_voff[i], soff_a);
-#pragma unroll
-                for (int i = 0; i < B_PER; ++i) load_to_lds16(rx, sb + i * 4096, (b_mask[i] & sel) == want ? b_base[i] + off : OOB, 0);
-                ld_j0 += 8;
-                if (ld_j0 == j.c8) {
-                    ld_j0 = 0;
-                    if (++ld_s == j.S) { ld_s = 0; ++ld_r; }
-                }
-                return;
-            }
-            // slices along a filter row's run of S C values; with `flat` they run on into the next row, whose filters follow in memory
-            const int soff_a = (ld_r * j.run_chunks + ld_j0) * 16, run_off = ld_r * j.W * j.C * 2 + ld_j0 * 16;
-            const bool more = j.flat && ld_r + 1 < j.R;
-            const int jl0 = ld_j0 + lc;
-            const bool wrap = jl0 >= j.run_chunks, ok = !wrap || more;
-            const int jl = wrap ? jl0 - j.run_chunks : jl0;
-            const int sh = 31 - (j.c8 == 1 ? jl : (int)__umulhi((unsigned)jl, j.magic_c8));     // the chunk's tap, at most 15 where it counts
-            const int off = run_off + (wrap ? (j.W * j.C - j.run_chunks * 8) * 2 : 0);
-            const int bit = (16 + ld_r + (wrap ? 1 : 0)) & 31;
-#pragma unroll
-            for (int i = 0; i < A_PER; ++i) load_to_lds16(rw, sa + i * 4096, ok ? a_voff[i] : OOB, soff_a);
-#pragma unroll
-            for (int i = 0; i < B_PER; ++i) {
-                const bool row_in = (b_mask[i] >> bit) & 1u, tap_out = (b_mask[i] << sh) & 0x80000000u;
-                load_to_lds16(rx, sb + i * 4096, ok && row_in && !tap_out ? b_base[i] + off : OOB, 0);
-            }
+        // wave-uniform position of this wave's next slice: its chunk in the row, its filters' offset, its place in the ring
+        int ld_e = lg * 8, ld_j0 = 0, soff_a = 0, ld_slot = lg;
+        auto next_slice = [&]() __attribute__((always_inline)) {
             ld_j0 += 8;
-            if (ld_j0 >= j.run_chunks) { ld_j0 = j.flat ? ld_j0 - j.run_chunks : 0; ++ld_r; }
+            soff_a += 128;
+            if (ld_j0 == j.row_chunks) { ld_j0 = 0; soff_a += (j.run_chunks - j.row_chunks) * 16; }
         };
-        // (one copy of the loader's code: a launch of this kernel finds the instruction cache cold)
-        for (int k = 1 - NS; k <= slices; ++k) {
-            if (k >= 0) {
-                const int behind = min(slices - 1 - k, NS - 2);      // slices requested behind slice k
-                if (behind == NS - 2) wait_vmcnt<(NS - 2) * L>();
-                else if (NS > 4 && behind >= NS / 2) wait_vmcnt<(NS > 4 ? NS / 2 : 0) * L>();
-                else if (NS > 3 && behind >= 2) wait_vmcnt<(NS > 3 ? 2 : 0) * L>();
-                else if (behind == 1) wait_vmcnt<L>();
-                else wait_vmcnt<0>();
-                ring_barrier();
+        if (lg) next_slice();
+        const unsigned tab_rd = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)table + lc * 8;
+        if (!j.pointwise) ring_barrier();                // the table is complete
+        // (one copy of the loading code: a launch of this kernel finds the instruction cache cold)
+        for (int k = 1 - NS; k + NS - 1 < stages; ++k) {
+            u32x2 e[SL];
+            if (!j.pointwise) {
+                e[0] = ds_read8<0>(tab_rd + ld_e * 8);
+                if constexpr (SL > 1) e[1] = ds_read8<LG * 64>(tab_rd + ld_e * 8);
+                static_assert(SL <= 2, "slices of a stage per loading wave");
             }
-            if (k + NS - 1 < slices) issue_slice();
+            if (k >= 0) {
+                wait_vmcnt<(NS - 2) * L>();
+                ring_barrier();
+            } else {
+                wait_lgkm<0>();
+            }
+#pragma unroll
+            for (int u = 0; u < SL; ++u) {
+                if (!j.pointwise) touch(e[u]);
+                else e[u] = u32x2{ld_e + u * LG * 8 + lc < j.c8 ? (unsigned)(ld_e + u * LG * 8 + lc) * 16u : (unsigned)OOB, 0x10001u};
+                unsigned char* sa = ring + ld_slot * SLICE + lw * 1024;
+                unsigned char* sb = sa + BM * 128;
+                const bool ok = (int)e[u][0] >= 0;
+                const unsigned sel = e[u][1], want = sel & 0xFFFF0000u;
+#pragma unroll
+                for (int i = 0; i < A_PER; ++i) load_to_lds16(rw, sa + i * 4096, ok ? a_voff[i] : OOB, soff_a);
+#pragma unroll
+                for (int i = 0; i < B_PER; ++i) load_to_lds16(rx, sb + i * 4096, ok && (b_mask[i] & sel) == want ? b_base[i] + (int)e[u][0] : OOB, 0);
+                ld_slot = ld_slot + LG == NS * G + lg ? lg : ld_slot + LG;
+#pragma unroll
+                for (int v = 0; v < LG; ++v) next_slice();
+            }
+            ld_e += G * 8;
         }
+        // the last stages, already on their way
+        const int left = min(stages, NS - 1);
+        if constexpr (NS > 4) { if (left > 3) { wait_vmcnt<3 * L>(); ring_barrier(); } }
+        if constexpr (NS > 3) { if (left > 2) { wait_vmcnt<2 * L>(); ring_barrier(); } }
+        if constexpr (NS > 2) { if (left > 1) { wait_vmcnt<L>(); ring_barrier(); } }
+        wait_vmcnt<0>();
+        ring_barrier();
         return;
     }
 
-    // ---- multiplying: block (cm, cn) of the tile
-    const int half = lane >> 5, l32 = lane & 31, cm = wave % CM, cn = wave / CM;
-    const int n = nt * BN + cn * 32 + l32, m_lane = mt * BM + cm * 32 + half * 8;     // after the store's lane exchange: filters m_lane + 16 qp ..
-    f32x4 bias[2][2];
-    u32x4 res[2];
+    // ---- the table: entry e = 8 slice + chunk of the slice.  A chunk is 8 channels of a tap: its offset from the window's first pixel, and the
+    // bits that a pixel's mask is tested with (16 + r set, s clear); beyond the contraction, and between a row's last chunk and the next slice: OOB.
+    if (!j.pointwise) {
+        for (int e = tid; e < stages * G * 8; e += CW * 64) {
+            const int r = (int)__umulhi((unsigned)e, j.magic_row), jl = e - r * j.row_chunks;
+            const int s = j.c8 == 1 ? jl : (int)__umulhi((unsigned)jl, j.magic_c8), cc = j.stem_wp ? 0 : jl - s * j.c8;
+            const bool ok = r < j.R && jl < j.run_chunks;
+            table[e] = u32x2{ok ? (unsigned)((r * j.W + s) * j.C * 2 + cc * 16) : (unsigned)OOB, (0x10000u << (r & 15)) | (1u << (s & 15))};
+        }
+        ring_barrier();
+    }
+
+    // ---- multiplying: blocks of 16 filters x 16 pixels, 32 elements of the contraction per instruction: lane = row lane & 15 of either operand,
+    // eight elements from 8 (lane >> 4) on; result register v = filter 4 (lane >> 4) + v of pixel lane & 15
+    const int quad = lane >> 4, l16 = lane & 15, m0 = (wave % WM) * TM * 16, n0 = (wave / WM) * TN * 16;
+    const int m_lane = mt * BM + m0 + quad * 4, n_lane = nt * BN + n0 + l16;
+    f32x4 bias[TM];
+    u32x2 res[TM][TN];
 #pragma unroll
-    for (int qp = 0; qp < 2; ++qp) {
-        const int mb = m_lane + qp * 16;
-        bias[qp][0] = bias[qp][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-        res[qp] = u32x4{0u, 0u, 0u, 0u};
-        if (j.vec && n < j.Ng && mb < j.K) {             // (vec: whole groups of 8 filters)
-            if (j.bias) {
-                bias[qp][0] = *reinterpret_cast<const f32x4*>(j.bias + mb);
-                bias[qp][1] = *reinterpret_cast<const f32x4*>(j.bias + mb + 4);
-            }
-            if (j.res) res[qp] = *reinterpret_cast<const u32x4*>(j.res + (size_t)n * j.res_ctot + mb);
+    for (int i = 0; i < TM; ++i) {
+        bias[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (j.vec && j.bias && m_lane + i * 16 < j.K) bias[i] = *reinterpret_cast<const f32x4*>(j.bias + m_lane + i * 16);       // (vec: whole groups of 8 filters)
+#pragma unroll
+        for (int jn = 0; jn < TN; ++jn) {
+            const int n = n_lane + jn * 16;
+            res[i][jn] = u32x2{0u, 0u};
+            if (j.vec && j.res && n < j.Ng && m_lane + i * 16 < j.K) res[i][jn] = *reinterpret_cast<const u32x2*>(j.res + (size_t)n * j.res_ctot + m_lane + i * 16);
         }
     }
     const unsigned ring_lds = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)ring;
-    const unsigned lane_x = (half << 4) ^ (((l32 >> 1) & 7) << 4);
-    const unsigned a_rd = ring_lds + (cm * 32 + l32) * 128 + lane_x, b_rd = ring_lds + BM * 128 + (cn * 32 + l32) * 128 + lane_x;
-    f32x16 acc;
+    const unsigned lane_x = (quad << 4) ^ (((l16 >> 1) & 7) << 4);
+    const unsigned a_rd = ring_lds + (m0 + l16) * 128 + lane_x, b_rd = ring_lds + BM * 128 + (n0 + l16) * 128 + lane_x;
+    f32x4 acc[TM][TN];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-    u32x4 fa[4], fb[4];
-    auto multiply = [&]() __attribute__((always_inline)) {
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[ks]), __builtin_bit_cast(bf16x8, fb[ks]), acc, 0, 0, 0);
+        for (int jn = 0; jn < TN; ++jn) acc[i][jn] = f32x4{0.f, 0.f, 0.f, 0.f};
+    u32x4 fa[2 * G][TM], fb[2 * G][TN], na[2 * G][TM], nb[2 * G][TN];
+    auto multiply = [&](int n) __attribute__((always_inline)) {             // the first n slices of the stage in registers
+#pragma unroll
+        for (int ks = 0; ks < 2 * G; ++ks) {
+            if (ks >= 2 && ks % 2 == 0 && ks / 2 >= n) break;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int jn = 0; jn < TN; ++jn)
+                    acc[i][jn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fa[ks][i]), __builtin_bit_cast(bf16x8, fb[ks][jn]), acc[i][jn], 0, 0, 0);
+        }
     };
     int stage = 0;
-    for (int k = 0; k < slices; ++k) {
+    for (int k = 0; k < stages; ++k) {
         ring_barrier();
-        u32x4 na[4], nb[4];
-        const unsigned pa = a_rd + stage * STAGE, pb = b_rd + stage * STAGE;
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            na[ks] = ds_read16<0>(pa ^ (ks * 32));
-            nb[ks] = ds_read16<0>(pb ^ (ks * 32));
+        for (int ks = 0; ks < 2 * G; ++ks) {
+            const unsigned at = stage * STAGE + (ks >> 1) * SLICE;
+            const unsigned pa = (a_rd + at) ^ ((ks & 1) * 64), pb = (b_rd + at) ^ ((ks & 1) * 64);
+            na[ks][0] = ds_read16<0>(pa);
+            if constexpr (TM > 1) na[ks][1] = ds_read16<2048>(pa);
+            nb[ks][0] = ds_read16<0>(pb);
+            if constexpr (TN > 1) nb[ks][1] = ds_read16<2048>(pb);
         }
-        if (k) multiply();
+        if (k) multiply(G);
         wait_lgkm<0>();
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) { touch(na[ks]); touch(nb[ks]); fa[ks] = na[ks]; fb[ks] = nb[ks]; }
+        for (int ks = 0; ks < 2 * G; ++ks) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) { touch(na[ks][i]); fa[ks][i] = na[ks][i]; }
+#pragma unroll
+            for (int jn = 0; jn < TN; ++jn) { touch(nb[ks][jn]); fb[ks][jn] = nb[ks][jn]; }
+        }
         stage = stage + 1 == NS ? 0 : stage + 1;
     }
-    ring_barrier();
-    multiply();
+    multiply(slices - (stages - 1) * G);                     // (slices beyond the last were sent as zeros)
 
-    // ---- the store: as in the streaming kernel
+    // ---- the store: a lane has four consecutive filters of a pixel
 #pragma unroll
-    for (int qp = 0; qp < 2; ++qp) {
-        float o[8];
+    for (int i = 0; i < TM; ++i) {
+        const int mb = m_lane + i * 16;
+        if (mb >= j.K) continue;
+        const bool s1 = mb >= j.split_end[0], s2 = mb >= j.split_end[1], s3 = mb >= j.split_end[2];      // (ends: multiples of 8)
+        uint16_t* const base = s3 ? j.y_seg[3] : s2 ? j.y_seg[2] : s1 ? j.y_seg[1] : j.y_seg[0];
+        const int ctot = s3 ? j.ctot_seg[3] : s2 ? j.ctot_seg[2] : s1 ? j.ctot_seg[1] : j.ctot_seg[0];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[qp * 8 + e]), __float_as_uint(acc[qp * 8 + 4 + e]), false, false);
-            o[e] = __uint_as_float(sw[0]);
-            o[4 + e] = __uint_as_float(sw[1]);
-        }
-        const int mb = m_lane + qp * 16;
-        if (n >= j.Ng || mb >= j.K) continue;
-        uint16_t* yb = j.y_seg[0] + (size_t)n * j.ctot_seg[0];
-        if (j.nsplit > 1) {
-            const bool s1 = mb >= j.split_end[0], s2 = mb >= j.split_end[1], s3 = mb >= j.split_end[2];
-            uint16_t* base = s3 ? j.y_seg[3] : s2 ? j.y_seg[2] : s1 ? j.y_seg[1] : j.y_seg[0];
-            yb = base + (size_t)n * (s3 ? j.ctot_seg[3] : s2 ? j.ctot_seg[2] : s1 ? j.ctot_seg[1] : j.ctot_seg[0]);
-        }
-        if (j.vec) {
+        for (int jn = 0; jn < TN; ++jn) {
+            const int n = n_lane + jn * 16;
+            if (n >= j.Ng) continue;
+            uint16_t* const yb = base + (size_t)n * ctot;
+            float o[4];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] += bias[qp][e >> 2][e & 3];
-            if (j.res) {
+            for (int e = 0; e < 4; ++e) o[e] = acc[i][jn][e];
+            if (j.vec) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    o[2 * e] += __uint_as_float(res[qp][e] << 16);
-                    o[2 * e + 1] += __uint_as_float(res[qp][e] & 0xFFFF0000u);
+                for (int e = 0; e < 4; ++e) o[e] += bias[i][e];
+                if (j.res) {
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        o[2 * e] += __uint_as_float(res[i][jn][e] << 16);
+                        o[2 * e + 1] += __uint_as_float(res[i][jn][e] & 0xFFFF0000u);
+                    }
                 }
+                if (j.relu) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = fmaxf(o[e], 0.f);
+                }
+                *reinterpret_cast<u32x2*>(yb + mb) = u32x2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
+                continue;
             }
-            if (j.relu) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) o[e] = fmaxf(o[e], 0.f);
+            for (int e = 0; e < 4; ++e) {
+                if (mb + e >= j.K) break;
+                float v = o[e] + (j.bias ? j.bias[mb + e] : 0.f);
+                if (j.res) v += bf16_to_f32(j.res[(size_t)n * j.res_ctot + mb + e]);
+                if (j.relu) v = fmaxf(v, 0.f);
+                yb[mb + e] = f32_to_bf16(v);
             }
-            u32x4 pk;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) pk[e] = pack_bf16x2(o[2 * e], o[2 * e + 1]);
-            *reinterpret_cast<u32x4*>(yb + mb) = pk;
-            continue;
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            if (mb + e >= j.K) break;
-            float v = o[e] + (j.bias ? j.bias[mb + e] : 0.f);
-            if (j.res) v += bf16_to_f32(j.res[(size_t)n * j.res_ctot + mb + e]);
-            if (j.relu) v = fmaxf(v, 0.f);
-            yb[mb + e] = f32_to_bf16(v);
         }
     }
+}
+
+// Slices of a tile's contraction.  They run on from filter row to filter row where that saves slices; else every row starts one.
+int small_slices(const ConvGeom& g, int* row_chunks)
+{
+    const int run = g.S * (g.C / 8), spr = (run + 7) / 8, flat = (g.R * run + 7) / 8;
+    const bool on = run >= 8 && flat < g.R * spr;
+    *row_chunks = on ? run : spr * 8;
+    return on ? flat : g.R * spr;
 }
 
 SmallJob small_job(const ConvSmall& c, int bm, int bn, int nth)
@@ -315,14 +365,11 @@ SmallJob small_job(const ConvSmall& c, int bm, int bn, int nth)
     j.stem_hp = c.stem_hp; j.stem_wp = c.stem_wp;
     j.x_bytes = c.stem_wp ? (int)((size_t)g.N * c.stem_hp * c.stem_wp * 8) : (int)((size_t)g.N * g.C * g.H * g.W * 2);
     j.w_bytes = (int)((size_t)g.K * g.Kg * 2);
-    j.tap = g.C % 64 == 0;
     j.pointwise = g.R == 1 && g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0;
     j.run_chunks = g.S * j.c8;
-    j.spr = (j.run_chunks + 7) / 8;
-    j.slices = g.R * j.spr;
-    const int flat_slices = (g.R * j.run_chunks + 7) / 8;
-    if (!j.tap && j.run_chunks >= 8 && flat_slices < j.slices) { j.flat = 1; j.slices = flat_slices; }
+    j.slices = small_slices(g, &j.row_chunks);
     j.magic_c8 = (unsigned)((0x100000000ull + j.c8 - 1) / j.c8);
+    j.magic_row = (unsigned)((0x100000000ull + j.row_chunks - 1) / j.row_chunks);
     j.n_tiles = (g.Ng + bn - 1) / bn;
     j.tiles = j.n_tiles * ((g.K + bm - 1) / bm);
     j.nsplit = c.split && c.split->n > 1 ? c.split->n : 0;
@@ -358,35 +405,41 @@ static long small_tiles(const ConvSmall* jobs, int n, int bm, int bn)
 
 // As long as the layer's 64 x 64 tiles fit the device at two workgroups per compute unit, 1x1 filters at one (their contraction is
 // short and the larger tiles then win: 480 -> 304 on 14 x 14 x 19, 295 tiles, 7.7 against 8.5 us; 3x3 144 -> 288, 295 tiles too,
-// 13.6 against 13.5).
+// 13.6 against 13.5).  A contraction has to fit the table (3x3 on 1792 channels does).
 bool conv_bf16_small_takes(const ConvGeom& g, const void* x, const void* w)
 {
     const long tiles = ((long)g.Ng + 63) / 64 * ((g.K + 63) / 64);
-    return conv_bf16_dma_eligible(g, x, w) && tiles <= (g.R * g.S > 1 ? 2 : 1) * device_cus();
+    int row_chunks;
+    const bool pointwise = g.R == 1 && g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0;
+    return conv_bf16_dma_eligible(g, x, w) && (pointwise || small_slices(g, &row_chunks) * 8 + 24 <= SMALL_TABLE) && tiles <= (g.R * g.S > 1 ? 2 : 1) * device_cus();
 }
 
-template <int CM, int CN, int NS>
+template <int TM, int TN, int WM, int WN, int LG, int NS, int G>
 static int launch_group(const ConvSmall* jobs, int n, hipStream_t st)
 {
-    constexpr int NTH = (CM * CN + 4) * 64;
+    constexpr int NTH = (WM * WN + 4 * LG) * 64;
     SmallArgs a{};
-    a.n = n;
     int blocks = 0;
-    for (int i = 0; i < n; ++i) {
-        a.job[i] = small_job(jobs[i], CM * 32, CN * 32, NTH);
-        a.job[i].first = blocks;
+    for (int i = 0; i < SMALL_GROUP_MAX; ++i) {
+        a.first[i] = i < n ? blocks : 0x7FFFFFFF;
+        if (i >= n) continue;
+        a.job[i] = small_job(jobs[i], WM * TM * 16, WN * TN * 16, NTH);
         blocks += (a.job[i].tiles + 7) / 8 * 8;
     }
-    hipLaunchKernelGGL((conv_bf16_small_kernel<CM, CN, NS>), dim3((unsigned)blocks), dim3(NTH), 0, st, a);
+    hipLaunchKernelGGL((conv_bf16_small_kernel<TM, TN, WM, WN, LG, NS, G>), dim3((unsigned)blocks), dim3(NTH), 0, st, a);
     return check_launch("conv_bf16_small");
 }
 
+// The smallest tile that leaves every compute unit at most one.  Stages of two slices, three in flight; eight loading waves.  Sixteen waves of
+// 16 x 16 and 32 x 16 for the larger tiles (64 x 32: GoogLeNet, fused, on 19 images 344 us with blocks of 32 x 16, 339 with 16 x 16).  Two 64 x 64
+// tiles to a compute unit: four waves of 32 x 32 and four loading ones, three stages of one slice (24 -> 88 5x5 on 31 x 45 x 9 7.8 us; eight
+// waves of 32 x 16 8.3; stages of two slices, two in flight 10.6: too few loads on their way).
 int launch_conv_bf16_small(const ConvSmall* jobs, int n, hipStream_t st)
 {
-    // the smallest tile that leaves every compute unit at most one
-    if (small_tiles(jobs, n, 32, 32) <= device_cus()) return launch_group<1, 1, 4>(jobs, n, st);
-    if (small_tiles(jobs, n, 64, 32) <= device_cus()) return launch_group<2, 1, 4>(jobs, n, st);
-    return launch_group<2, 2, 4>(jobs, n, st);
+    if (small_tiles(jobs, n, 32, 32) <= device_cus()) return launch_group<1, 1, 2, 2, 2, 3, 2>(jobs, n, st);
+    if (small_tiles(jobs, n, 64, 32) <= device_cus()) return launch_group<1, 1, 4, 2, 2, 3, 2>(jobs, n, st);
+    if (small_tiles(jobs, n, 64, 64) <= device_cus()) return launch_group<2, 1, 2, 4, 2, 3, 2>(jobs, n, st);
+    return launch_group<2, 2, 2, 2, 1, 3, 1>(jobs, n, st);
 }
 
 }  // namespace dr

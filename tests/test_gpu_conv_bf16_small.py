@@ -54,6 +54,29 @@ def test_small_layer(case):
 
 
 @pytest.mark.parametrize("case", [
+    # N, C, H, W, K, R, S, stride, pad
+    (1, 1792, 3, 4, 24, 3, 3, 1, 1),      # 252 slices: the longest contraction the chunk table holds
+    (1, 1856, 3, 4, 24, 3, 3, 1, 1),      # 261: beyond it, the larger kernels
+    (1, 16448, 1, 3, 24, 1, 1, 1, 0),     # 1x1 filters at stride 1 need no table
+    (1, 8, 19, 14, 16, 16, 9, 1, 4),      # the most filter rows and columns
+    (2, 16, 9, 9, 40, 4, 3, 1, 1),        # filter rows shorter than a slice, an odd and an even number of slices left over
+    (2, 88, 9, 9, 40, 2, 2, 1, 1),        # 22 chunks per filter row, two of them: six slices either way, every row starts one
+])
+def test_chunk_table(case):
+    """Where a chunk of the contraction lies, over the forms of the table, against the fp64 oracle: one rounding of an fp32 sum."""
+    N, C, H, W, K, R, S, stride, pad = case
+    rng = np.random.default_rng(case_seed(case))
+    x = workloads.round_to_bf16(rng.standard_normal((N, C, H, W)).astype(np.float32))
+    w = workloads.round_to_bf16(rng.standard_normal((K, C, R, S)).astype(np.float32) * np.float32(np.sqrt(2.0 / (C * R * S))))
+    b = (rng.standard_normal(K) * 0.1).astype(np.float32)
+    ref = oracle.conv2d(x, w, b, stride, pad, False)
+    y = empty_nhwc(ref.shape, "bf16")
+    B.conv2d_fwd_ws(gpu_nhwc(x, "bf16"), B.conv_desc(K, C, R, S, stride, pad, False, B.DR_KRSC), B.pack_filters(gpu(w, "bf16")), gpu(b), y, None)
+    torch.cuda.synchronize()
+    assert close(host_nhwc(y), oracle.round_bf16(ref), 2.0 ** -7, "within one bf16 unit of the oracle")
+
+
+@pytest.mark.parametrize("case", [
     # images within the rule and beyond it, C, H, W, K, R, stride
     (2, 3, 24, 96, 84, 104, 3, 1),        # slices that run on from filter row to filter row; beyond: the streaming kernel
     (8, 9, 128, 64, 64, 64, 3, 1),        # whole taps; beyond: the patch kernel
