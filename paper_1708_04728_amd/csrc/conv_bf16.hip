@@ -374,8 +374,11 @@ int launch_conv_bf16(const ConvGeom& g, const uint16_t* x, const uint16_t* w, co
         return launch_conv_bf16_small(&job, 1, st);
     }
     // several taps at stride 1 on few channels: the input patch of a tile is loaded once for all taps (conv_bf16_patch.hip)
-    if (!residual && conv_bf16_patch_eligible(g, x, w, y)) return launch_conv_bf16_patch(g, x, w, bias, y, st);
-    if (!residual && conv_bf16_rows_eligible(g, x, w, y)) return launch_conv_bf16_rows(g, x, w, bias, y, st);
+    // unless that leaves compute units idle that wide tiles would fill (conv_bf16_wide.hip)
+    const bool patch = !residual && conv_bf16_patch_eligible(g, x, w, y), rows = !residual && conv_bf16_rows_eligible(g, x, w, y);
+    if ((patch || rows) && !(conv_bf16_wide_fills(g) && conv_bf16_wide_takes(g, x, w, residual, y, nullptr)))
+        return patch ? launch_conv_bf16_patch(g, x, w, bias, y, st) : launch_conv_bf16_rows(g, x, w, bias, y, st);
+    // every other layer: wide tiles (conv_bf16_wide.hip) or the streaming kernel
     if (conv_bf16_dma_eligible(g, x, w)) return launch_conv_bf16_dma(g, x, w, bias, residual, y, st);
     const size_t xb = (size_t)g.N * g.C * g.H * g.W * 2, wb = (size_t)g.K * g.Kg * 2;
     if (g.nhwc && g.w_krsc && g.C % 8 == 0 && xb < (1ull << 31) && wb < (1ull << 31)) {

@@ -825,6 +825,7 @@ int launch_conv_bf16_block(const ConvGeom& g, const uint16_t* x, const uint16_t*
 int launch_conv_bf16_dma(const ConvGeom& g, const uint16_t* x, const uint16_t* w, const float* bias,
                          const uint16_t* residual, uint16_t* y, hipStream_t st, const ConvSplit* split)
 {
+    if (conv_bf16_wide_takes(g, x, w, residual, y, split)) return launch_conv_bf16_wide(g, x, w, bias, y, st, split);
     DArgs a = base_args(g, x, w, bias, residual, y);
     a.nsplit = 0;
     if (split && split->n > 1) {

@@ -439,6 +439,11 @@ int launch_conv_bf16_small(const ConvSmall* jobs, int n, hipStream_t st)
     if (small_tiles(jobs, n, 32, 32) <= device_cus()) return launch_group<1, 1, 2, 2, 2, 3, 2>(jobs, n, st);
     if (small_tiles(jobs, n, 64, 32) <= device_cus()) return launch_group<1, 1, 4, 2, 2, 3, 2>(jobs, n, st);
     if (small_tiles(jobs, n, 64, 64) <= device_cus()) return launch_group<2, 1, 2, 4, 2, 3, 2>(jobs, n, st);
+    // a layer by itself: wide tiles, which two to a compute unit beat only by sharing the launch (3x3 144 -> 288 on 14 x 14 x 19 10.8 us here, 10.4 there,
+    // 160 -> 320 on 7 x 7 x 128 13.4 and 11.3)
+    const ConvSmall& j = jobs[0];
+    if (n == 1 && j.w && !j.stem_wp && conv_bf16_wide_takes(j.g, j.x, j.w, j.res, j.y, j.split))
+        return launch_conv_bf16_wide(j.g, (const uint16_t*)j.x, (const uint16_t*)j.w, j.bias, (uint16_t*)j.y, st, j.split);
     return launch_group<2, 2, 2, 2, 1, 3, 1>(jobs, n, st);
 }
 

@@ -1,0 +1,387 @@
+// bf16 convolution of larger layers: one wide tile per compute unit, loading and multiplying waves apart.
+//
+//   D[m][n] = sum_k A[m][k] * B[k][n]     m = output channel, n = (image, p, q), k = (r, s, c)
+//
+// The streaming kernel (conv_bf16_dma.hip) gives every wave both jobs, and its tiles of 64 or 96 filters x 128 pixels ask more of the path
+// into LDS (one 1 KiB load per 16 to 19 cycles and compute unit, whatever it fetches) than of the matrix cores: 24 loads, 460 cycles, for a
+// slice of 64 x 128 that is 256 cycles of matrix work.  Here
+//   * a tile is 32 TM filters x 32 TN pixels, as much as one workgroup's LDS (three slices of 64) and registers hold: 160 x 224 has 48
+//     loads, 910 cycles, for 1120 of matrix work;
+//   * four waves multiply (one per SIMD, 16 TM x 16 TN each), four send the loads.  A k-step's operands are read from LDS between the matrix
+//     instructions of the one before it: a wave reads 16 bytes per lane in about 40 cycles, as long as two and a half instructions of 16 x 16 x 32
+//     take.  (Eight multiplying waves read faster and gained nothing.)
+//   * where a chunk of the contraction lies comes from a table in LDS, as in the kernel for small layers (conv_bf16_small.hip).
+// Workgroups are persistent: the loading waves run on into the next tile while the others store.  The order of the sums is the streaming
+// kernel's: the same bits.
+//
+// What bounds it: the matrix cores at the clock that they reach on varying operands -- 0.70 us per slice of 160 x 224 on 224 compute
+// units, 1.6 GHz -- and what a tile costs beside them: about 7 us for a layer of one round (a cold start, the store of the whole output at once),
+// 3 us for each further round.  Measured, streaming kernel -> this one, batch 128: 3x3 144 -> 288 on 14 x 14 38.4 -> 24.6 us, 160 -> 320 39.8 -> 26.4,
+// 128 -> 256 22.6 -> 18.3, 128 -> 192 on 28 x 28 57 -> 50, 192 -> 384 on 7 x 7 18.8 -> 13.1, 1x1 480 -> 304 on 14 x 14 21.3 -> 15.7; over 60 layers
+// of GoogLeNet and of sizes drawn at random 0.84 of the time.  GoogLeNet at batch 128: slim 722 -> 637 us, original 1584 -> 1499.
+#include <algorithm>
+#include <utility>
+
+#include "dr_internal.h"
+#include "dr_store.h"
+#include "conv_bf16_dev.h"
+
+namespace dr {
+namespace {
+
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int WIDE_TABLE = 1024;                         // chunks of 8 contraction elements that a layer may have (8 KB of LDS)
+__device__ __forceinline__ void touch(u32x2& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ u32x2 ds_read8(unsigned addr)         // valid after wait_lgkm or ring_barrier, and touch
+{
+    u32x2 v;
+    asm volatile("ds_read_b64 %0, %1" : "=&v"(v) : "v"(addr));
+    return v;
+}
+
+template <class F, int... I>
+__device__ __forceinline__ void each_of(std::integer_sequence<int, I...>, const F& f) { (f(IC<I>{}), ...); }
+template <int N, class F>
+__device__ __forceinline__ void each(const F& f) { each_of(std::make_integer_sequence<int, N>{}, f); }
+
+struct WideArgs {
+    const uint16_t* x;
+    const uint16_t* w;
+    const float* bias;
+    uint16_t* y_seg[4];                                  // destinations of the filter ranges (see ConvSplit), y_seg[0] alone otherwise
+    int ctot_seg[4], split_end[3], nsplit;
+    int C, H, W, K, R, S, sh, sw, ph, pw, P, Q, Kg, Ng, relu;
+    int x_bytes, w_bytes, pointwise;
+    int c8, run_chunks, row_chunks, slices;              // see conv_bf16_small.hip
+    unsigned magic_c8, magic_row;
+    unsigned long long m_pq, m_q;
+    int step_img, step_p, step_q;                        // 32 pixels as (images, rows, columns) of the output
+    WalkArgs wk;
+};
+
+// A tile of 32 TM filters x 32 TN pixels: 2 x 2 multiplying waves with TM x TN blocks of 16 x 16 each, four loading waves
+template <int TM, int TN>
+__global__ __launch_bounds__(512, 2) void conv_bf16_wide_kernel(const WideArgs a)
+{
+    constexpr int NS = 3, BM = TM * 32, BN = TN * 32, L = TM + TN, STAGE = (BM + BN) * 128;       // slices in LDS; loads of a wave per slice
+    static_assert(BM <= 256 && (NS - 1) * L < 63, "loads in flight");
+    __shared__ __attribute__((aligned(1024))) unsigned char ring[NS * STAGE];
+    __shared__ __attribute__((aligned(16))) u32x2 table[WIDE_TABLE];
+    __shared__ __attribute__((aligned(16))) float bias_lds[BM];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const TileWalk walk = tile_walk(a.wk);
+    const int mt = walk.mt, slices = a.slices, total = walk.count * slices;
+
+    if (wave >= 4) {
+        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)a.x, 0, a.x_bytes, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, a.w_bytes, 0x00020000);
+        const int lw = wave - 4, lrow = lw * 8 + (lane >> 3), lc = (lane & 7) ^ ((lrow >> 1) & 7);
+        int a_voff[TM], b_base[TN];
+        unsigned b_mask[TN];                             // tap column s (bit s), row r (bit 16 + r) lies outside; bit 15: set
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int m = mt * BM + i * 32 + lrow;
+            a_voff[i] = m < a.K ? (m * a.Kg + lc * 8) * 2 : OOB;
+        }
+        auto tile_setup = [&](int nt) __attribute__((always_inline)) {
+            const int n0 = nt * BN + lrow;
+            if (a.pointwise) {
+#pragma unroll
+                for (int i = 0; i < TN; ++i) {
+                    const int n = n0 + i * 32;
+                    b_base[i] = n * a.C * 2;
+                    b_mask[i] = n < a.Ng ? 0x8000u : 0xFFFFFFFFu;
+                }
+                return;
+            }
+            const int nn = n0 < a.Ng ? n0 : 0;
+            int img = div_small(nn, a.m_pq);
+            const int pix = nn - img * a.P * a.Q;
+            int p = div_small(pix, a.m_q), q = pix - p * a.Q;
+#pragma unroll
+            for (int i = 0; i < TN; ++i) {
+                const int ih0 = p * a.sh - a.ph, iw0 = q * a.sw - a.pw;
+                b_base[i] = ((img * a.H + ih0) * a.W + iw0) * a.C * 2;
+                const unsigned wv = bit_range(max(0, -iw0), min(a.S - 1, a.W - 1 - iw0)), hv = bit_range(max(0, -ih0), min(a.R - 1, a.H - 1 - ih0));
+                b_mask[i] = n0 + i * 32 < a.Ng ? ~(wv | (hv << 16)) : 0xFFFFFFFFu;
+                q += a.step_q;
+                if (q >= a.Q) { q -= a.Q; ++p; }
+                p += a.step_p;
+                if (p >= a.P) { p -= a.P; ++img; }
+                img += a.step_img;
+            }
+        };
+        int ld_t = 0, ld_s = 0, ld_j0 = 0, soff_a = 0, stage = 0;        // tile, slice, chunk in the row, offset in a filter, LDS stage of the next slice
+        tile_setup(walk.tile(0));
+        const unsigned tab_rd = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)table + lc * 8;
+        ring_barrier();
+        for (int k = 1 - NS; k + NS - 1 < total; ++k) {
+            u32x2 e = ds_read8(tab_rd + ld_s * 64);
+            if (k >= 0) {
+                wait_vmcnt<(NS - 2) * L>();
+                ring_barrier();
+            } else {
+                wait_lgkm<0>();
+            }
+            touch(e);
+            unsigned char* const sa = ring + stage * STAGE + lw * 1024;
+            unsigned char* const sb = sa + BM * 128;
+            const bool ok = (int)e[0] >= 0;
+#pragma unroll
+            for (int i = 0; i < TM; ++i) load_to_lds16(rw, sa + i * 4096, ok ? a_voff[i] : OOB, soff_a);
+#pragma unroll
+            for (int i = 0; i < TN; ++i) load_to_lds16(rx, sb + i * 4096, (b_mask[i] & e[1]) == 0 ? b_base[i] + (int)e[0] : OOB, 0);
+            stage = stage + 1 == NS ? 0 : stage + 1;
+            ld_j0 += 8;
+            soff_a += 128;
+            if (ld_j0 == a.row_chunks) { ld_j0 = 0; soff_a += (a.run_chunks - a.row_chunks) * 16; }
+            if (++ld_s == slices) {
+                ld_s = ld_j0 = soff_a = 0;
+                if (++ld_t < walk.count) tile_setup(walk.tile(ld_t));
+            }
+        }
+        if (total > 1) {
+            wait_vmcnt<L>();
+            ring_barrier();
+        }
+        wait_vmcnt<0>();
+        ring_barrier();
+        return;
+    }
+
+    for (int e = tid; e < slices * 8; e += 256) {
+        const int r = (int)__umulhi((unsigned)e, a.magic_row), jl = e - r * a.row_chunks;
+        const int s = a.c8 == 1 ? jl : (int)__umulhi((unsigned)jl, a.magic_c8), cc = jl - s * a.c8;
+        const bool ok = r < a.R && jl < a.run_chunks;
+        table[e] = u32x2{ok ? (unsigned)((r * a.W + s) * a.C * 2 + cc * 16) : (unsigned)OOB, ok ? (0x10000u << r) | (1u << s) : 0x8000u};
+    }
+    if (tid < BM) bias_lds[tid] = a.bias && mt * BM + tid < a.K ? a.bias[mt * BM + tid] : 0.f;
+    ring_barrier();
+
+    const int quad = lane >> 4, l16 = lane & 15, m0 = (wave & 1) * TM * 16, n0 = (wave >> 1) * TN * 16;
+    const unsigned ring_lds = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)ring;
+    const unsigned lane_x = (quad << 4) ^ (((l16 >> 1) & 7) << 4);
+    const unsigned a_rd = ring_lds + (m0 + l16) * 128 + lane_x, b_rd = ring_lds + BM * 128 + (n0 + l16) * 128 + lane_x;
+    f32x4 acc[TM][TN];
+    auto zero = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    // A k-step of 32: TM TN matrix instructions on the operands of slot KS, and between them the TM + TN reads of the other slot
+    u32x4 fa[2][TM], fb[2][TN];
+    auto read = [&](auto slot_c, auto r_c, unsigned pa, unsigned pb) __attribute__((always_inline)) {
+        constexpr int SLOT = decltype(slot_c)::value, R = decltype(r_c)::value;
+        if constexpr (R < TM) fa[SLOT][R] = ds_read16<R * 2048>(pa);
+        else fb[SLOT][R - TM] = ds_read16<(R - TM) * 2048>(pb);
+    };
+    auto fetch = [&](auto ks_c, int st) __attribute__((always_inline)) {
+        constexpr int KS = decltype(ks_c)::value;
+        const unsigned pa = (a_rd + st * STAGE) ^ (KS * 64), pb = (b_rd + st * STAGE) ^ (KS * 64);
+        each<TM + TN>([&](auto r_c) __attribute__((always_inline)) { read(IC<KS>{}, r_c, pa, pb); });
+    };
+    auto step = [&](auto ks_c, int st) __attribute__((always_inline)) {     // multiplies slot KS, fetches k-step 1 - KS of stage st
+        constexpr int KS = decltype(ks_c)::value, NEXT = 1 - KS, M = TM * TN, R = TM + TN;
+        const unsigned pa = (a_rd + st * STAGE) ^ (NEXT * 64), pb = (b_rd + st * STAGE) ^ (NEXT * 64);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) touch(fa[KS][i]);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) touch(fb[KS][j]);
+        each<M>([&](auto x_c) __attribute__((always_inline)) {
+            constexpr int X = decltype(x_c)::value, I = X / TN, J = X % TN;
+            acc[I][J] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fa[KS][I]), __builtin_bit_cast(bf16x8, fb[KS][J]), acc[I][J], 0, 0, 0);
+            each<R>([&](auto r_c) __attribute__((always_inline)) {
+                if constexpr (decltype(r_c)::value * (M * 3 / 4) / R == X) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    read(IC<NEXT>{}, r_c, pa, pb);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            });
+        });
+    };
+    auto store = [&](int nt) __attribute__((always_inline)) {
+        int quad_ = quad, n_lane = nt * BN + n0 + l16;
+        asm volatile("" : "+v"(quad_), "+v"(n_lane));    // (keeps what the store needs per lane out of the registers of the loop)
+        const int mw = mt * BM + m0;
+#pragma unroll
+        for (int i = 0; i < TM; i += 2) {
+            const bool two = i + 1 < TM;
+            const f32x4 b0 = *reinterpret_cast<const f32x4*>(&bias_lds[m0 + i * 16 + quad_ * 4]);
+            const f32x4 b1 = two ? *reinterpret_cast<const f32x4*>(&bias_lds[m0 + i * 16 + 16 + quad_ * 4]) : f32x4{0.f, 0.f, 0.f, 0.f};
+            // with two blocks, after the exchange: 8 filters of block i + (quad >> 1)
+            const int mb = two ? mw + i * 16 + quad_ * 8 : mw + i * 16 + quad_ * 4;
+            const bool s1 = mb >= a.split_end[0], s2 = mb >= a.split_end[1], s3 = mb >= a.split_end[2];
+            uint16_t* const base = (s3 ? a.y_seg[3] : s2 ? a.y_seg[2] : s1 ? a.y_seg[1] : a.y_seg[0]) + mb;
+            const int ctot = s3 ? a.ctot_seg[3] : s2 ? a.ctot_seg[2] : s1 ? a.ctot_seg[1] : a.ctot_seg[0];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int n = n_lane + j * 16;
+                unsigned p[2][2];
+#pragma unroll
+                for (int u = 0; u < (two ? 2 : 1); ++u) {
+                    f32x4 o = acc[i + u][j] + (u ? b1 : b0);
+                    if (a.relu) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) o[e] = fmaxf(o[e], 0.f);
+                    }
+                    p[u][0] = pack_bf16x2(o[0], o[1]);
+                    p[u][1] = pack_bf16x2(o[2], o[3]);
+                }
+                if (two) {
+                    // filters 4 quad .. + 3 of both blocks -> 8 consecutive ones of one block
+                    unsigned v[4];
+#pragma unroll
+                    for (int d = 0; d < 2; ++d) {
+                        const auto x32 = __builtin_amdgcn_permlane32_swap(p[0][d], p[1][d], false, false);
+                        const auto x16 = __builtin_amdgcn_permlane16_swap(x32[0], x32[1], false, false);
+                        v[d] = x16[0];
+                        v[2 + d] = x16[1];
+                    }
+                    if (n < a.Ng && mb < a.K) *reinterpret_cast<u32x4*>(base + (size_t)n * ctot) = u32x4{v[0], v[1], v[2], v[3]};
+                } else {
+                    if (n < a.Ng && mb < a.K) *reinterpret_cast<u32x2*>(base + (size_t)n * ctot) = u32x2{p[0][0], p[0][1]};
+                }
+            }
+        }
+    };
+
+    ring_barrier();                                      // slice 0
+    fetch(IC<0>{}, 0);
+    wait_lgkm<0>();
+    int stage = 0, g = 0;
+    for (int t = 0; t < walk.count; ++t) {
+        zero();
+        for (int s = 0; s < slices; ++s, ++g) {
+            step(IC<0>{}, stage);
+            stage = stage + 1 == NS ? 0 : stage + 1;
+            wait_lgkm<0>();
+            if (g + 1 < total) ring_barrier();
+            step(IC<1>{}, stage);               // (after the last slice: reads nobody uses)
+            wait_lgkm<0>();
+        }
+        store(walk.tile(t));
+    }
+}
+
+int wide_slices(const ConvGeom& g, int* row_chunks)
+{
+    const int run = g.S * (g.C / 8), spr = (run + 7) / 8, flat = (g.R * run + 7) / 8;
+    const bool on = run >= 8 && flat < g.R * spr;
+    *row_chunks = on ? run : spr * 8;
+    return on ? flat : g.R * spr;
+}
+
+template <int TM, int TN>
+int launch_tile(WideArgs a, hipStream_t st)
+{
+    constexpr int BM = TM * 32, BN = TN * 32;
+    const int grid_m = (a.K + BM - 1) / BM, grid_n = (a.Ng + BN - 1) / BN, gn = std::min(std::max(device_cus() / grid_m, 1), grid_n);
+    a.wk = make_walk(grid_m, gn, grid_n);
+    hipLaunchKernelGGL((conv_bf16_wide_kernel<TM, TN>), dim3((unsigned)(gn * grid_m)), dim3(512), 0, st, a);
+    return check_launch("conv_bf16_wide");
+}
+
+// The tile with the shortest time by a model fitted to 14 tiles x 60 layers (10 % off on average; the tile it picks takes 1.01 times as long
+// as the best one): a slice takes its matrix work or its loads, whichever is longer, a tile 0.54 us and its store besides.
+struct WideTile { int m, n, rounds; float us; };
+const int WIDE_TILES[][2] = {{5, 7}, {4, 7}, {7, 4}, {6, 5}, {3, 7}, {6, 4}, {4, 4}, {2, 7}, {2, 5}, {4, 3}};
+
+WideTile wide_tile(int K, int Ng, int slices)
+{
+    WideTile best{0, 0, 0, 1e30f};
+    const int cus = device_cus();
+    for (const auto& t : WIDE_TILES) {
+        const int bm = t[0] * 32, bn = t[1] * 32, grid_m = (K + bm - 1) / bm, grid_n = (Ng + bn - 1) / bn, gn = std::min(std::max(cus / grid_m, 1), grid_n);
+        const int rounds = (grid_n + gn - 1) / gn * ((gn * grid_m + cus - 1) / cus);
+        const float slice = std::max(0.644f * bm * bn / 32768.f, 12.85f * (bm + bn) / 8192.f);
+        const float us = rounds * (slices * slice + 0.54f + 1.2f * bm * bn / 10000.f);
+        if (us < best.us) best = WideTile{t[0], t[1], rounds, us};
+    }
+    return best;
+}
+
+}  // namespace
+
+// Stores are 16 bytes, eight filters; the contraction has to fit the table.  Layers of up to 32 filters stay with the streaming kernel's tiles of
+// 32, and so do contractions that end before the ring is filled: up to two slices, and where the tiles take more than one round up to three,
+// 1x1 filters up to four (64 -> 64 on 56 x 56 x 128, one slice, 19.2 us there, 21.9 here; 104 -> 352 on 28 x 28 x 128, two, 26.0 and 28.1;
+// 136 -> 392 on 28 x 56 x 24, three, 18.9 and 19.5; 240 -> 48 on 35 x 56 x 64, four, 15.2 and 16.5; in one round three slices of 1x1 160 -> 448 at
+// stride 2 on 7 x 28 x 128 8.0 and 6.4; 3x3 24 -> 256 on 14 x 31 x 128, four slices in two rounds, 20.0 and 16.6).
+bool conv_bf16_wide_takes(const ConvGeom& g, const void* x, const void* w, const void* residual, const void* y, const ConvSplit* split)
+{
+    int row_chunks;
+    if (residual || !conv_bf16_dma_eligible(g, x, w) || g.K % 8 != 0 || g.K <= 32) return false;
+    const int slices = wide_slices(g, &row_chunks);
+    if (slices < 3 || slices * 8 > WIDE_TABLE) return false;
+    if (slices <= (g.R * g.S > 1 ? 3 : 4) && wide_tile(g.K, g.Ng, slices).rounds > 1) return false;
+    if (split && split->n > 1) {
+        for (int d = 0; d < split->n; ++d)
+            if (split->dst[d].ctot % 8 != 0 || split->dst[d].c_offset % 8 != 0 || split->dst[d].k % 8 != 0 || !aligned16(split->dst[d].y)) return false;
+        return true;
+    }
+    return g.y_ctot % 8 == 0 && g.y_coff % 8 == 0 && aligned16(y);
+}
+
+// Where the kernels that keep an input patch in LDS (conv_bf16_patch.hip, conv_bf16_rows.hip: 96 filters x 252 pixels a workgroup, two of them
+// per compute unit) would have little more than a workgroup per compute unit, and this one has a single round: 5x5 48 -> 640 on 7 x 7 x 128
+// (175 workgroups) 18.3 us there and 11.9 here, 64 -> 424 on 14 x 14 x 64 (250) 22.8 and 19.8, 3x3 48 -> 336 on
+// 35 x 31 x 16 (276) 13.3 and 10.9; 64 -> 256 on 14 x 28 x 64 (300) 11.1 and 12.0, 5x5 16 -> 432 on 7 x 28 x 96 (375) 13.0 and 13.4.
+// Layers of half a workgroup per compute unit and fewer are few (most are small layers) and stay where they were.
+bool conv_bf16_wide_fills(const ConvGeom& g)
+{
+    int row_chunks;
+    const long groups = (long)(g.K + 95) / 96 * ((g.Ng + 251) / 252), cus = device_cus();
+    return 2 * groups > cus && 10 * groups <= 11 * cus && wide_tile(g.K, g.Ng, wide_slices(g, &row_chunks)).rounds == 1;
+}
+
+int launch_conv_bf16_wide(const ConvGeom& g, const uint16_t* x, const uint16_t* w, const float* bias, uint16_t* y, hipStream_t st, const ConvSplit* split)
+{
+    WideArgs a{};
+    a.x = x; a.w = w; a.bias = bias;
+    a.C = g.C; a.H = g.H; a.W = g.W; a.K = g.K; a.R = g.R; a.S = g.S; a.sh = g.sh; a.sw = g.sw; a.ph = g.ph; a.pw = g.pw;
+    a.P = g.P; a.Q = g.Q; a.Kg = g.Kg; a.Ng = g.Ng; a.relu = g.relu;
+    a.x_bytes = (int)((size_t)g.N * g.C * g.H * g.W * 2);
+    a.w_bytes = (int)((size_t)g.K * g.Kg * 2);
+    a.pointwise = g.R == 1 && g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0;
+    a.c8 = g.C / 8;
+    a.run_chunks = g.S * a.c8;
+    a.slices = wide_slices(g, &a.row_chunks);
+    a.magic_c8 = (unsigned)((0x100000000ull + a.c8 - 1) / a.c8);
+    a.magic_row = (unsigned)((0x100000000ull + a.row_chunks - 1) / a.row_chunks);
+    a.m_pq = ((1ull << 40) + (unsigned)(g.P * g.Q) - 1) / (unsigned)(g.P * g.Q);
+    a.m_q = ((1ull << 40) + (unsigned)g.Q - 1) / (unsigned)g.Q;
+    a.step_img = 32 / (g.P * g.Q);
+    a.step_p = 32 % (g.P * g.Q) / g.Q;
+    a.step_q = 32 % g.Q;
+    for (int d = 0; d < 3; ++d) a.split_end[d] = 0x7FFFFFFF;
+    if (split && split->n > 1) {
+        int start = 0;
+        for (int d = 0; d < split->n; ++d) {
+            a.y_seg[d] = (uint16_t*)split->dst[d].y + split->dst[d].c_offset - start;
+            a.ctot_seg[d] = split->dst[d].ctot;
+            start += split->dst[d].k;
+            if (d + 1 < split->n) a.split_end[d] = start;
+        }
+    } else {
+        a.y_seg[0] = y + g.y_coff;
+        a.ctot_seg[0] = g.y_ctot;
+    }
+    const WideTile t = wide_tile(g.K, g.Ng, a.slices);
+    switch (t.m * 10 + t.n) {
+    case 57: return launch_tile<5, 7>(a, st);
+    case 47: return launch_tile<4, 7>(a, st);
+    case 74: return launch_tile<7, 4>(a, st);
+    case 65: return launch_tile<6, 5>(a, st);
+    case 37: return launch_tile<3, 7>(a, st);
+    case 64: return launch_tile<6, 4>(a, st);
+    case 44: return launch_tile<4, 4>(a, st);
+    case 27: return launch_tile<2, 7>(a, st);
+    case 25: return launch_tile<2, 5>(a, st);
+    default: return launch_tile<4, 3>(a, st);
+    }
+}
+
+}  // namespace dr

@@ -88,6 +88,11 @@ struct ConvSplit { int n; ConvDest dst[4]; };
 int launch_conv_bf16_dma(const ConvGeom& g, const uint16_t* x, const uint16_t* w, const float* bias,
                          const uint16_t* residual, uint16_t* y, hipStream_t st, const ConvSplit* split = nullptr);
 
+// conv_bf16_wide.hip: larger layers, one wide tile per compute unit
+bool conv_bf16_wide_takes(const ConvGeom& g, const void* x, const void* w, const void* residual, const void* y, const ConvSplit* split);
+bool conv_bf16_wide_fills(const ConvGeom& g);      // rather than the kernels with an input patch
+int launch_conv_bf16_wide(const ConvGeom& g, const uint16_t* x, const uint16_t* w, const float* bias, uint16_t* y, hipStream_t st, const ConvSplit* split);
+
 bool conv_bf16_small_takes(const ConvGeom& g, const void* x, const void* w);
 int launch_conv_bf16_small(const ConvSmall* jobs, int n, hipStream_t st);
 
