@@ -734,6 +734,8 @@ int launch_conv_f32(const ConvGeom& g, const float* x, const float* w, const flo
     const size_t xb = (size_t)g.N * g.C * g.H * g.W * 4, wb = (size_t)g.K * g.Kg * 4;
     if (xb >= (1ull << 31) || wb >= (1ull << 31))
         return fail(DR_ERR_UNSUPPORTED, "conv_f32: input (%zu bytes) or filter tensor (%zu bytes) is 2 GiB or larger", xb, wb);
+    // wide filters on few channels, no padding (conv_f32_taps.hip)
+    if (conv_f32_taps_takes(g, residual, split)) return launch_conv_f32_taps(g, x, w, bias, y, st);
     const KArgs a = base_args(g, x, w, bias, residual, y, split);
     // (32-deep slices with the groups-of-4-taps order: measured 10 % slower)
     if (slices_of_32(g))

@@ -88,6 +88,10 @@ struct ConvSplit { int n; ConvDest dst[4]; };
 int launch_conv_bf16_dma(const ConvGeom& g, const uint16_t* x, const uint16_t* w, const float* bias,
                          const uint16_t* residual, uint16_t* y, hipStream_t st, const ConvSplit* split = nullptr);
 
+// conv_f32_taps.hip: fp32 first layers (few channels, filters 7, 8 or 10 to 12 taps wide, no padding)
+bool conv_f32_taps_takes(const ConvGeom& g, const void* residual, const ConvSplit* split);
+int launch_conv_f32_taps(const ConvGeom& g, const float* x, const float* w, const float* bias, float* y, hipStream_t st);
+
 // conv_bf16_wide.hip: larger layers, one wide tile per compute unit
 bool conv_bf16_wide_takes(const ConvGeom& g, const void* x, const void* w, const void* residual, const void* y, const ConvSplit* split);
 bool conv_bf16_wide_fills(const ConvGeom& g);      // rather than the kernels with an input patch

@@ -1,0 +1,58 @@
+"""GPU parity of the fp32 kernel for first layers (filters 7, 8 or 10 to 12 taps wide, no padding, KCRS) against the fp64 oracle: every
+overlap of the last group of taps, odd and even numbers of filter rows, one row, all filter block sizes, ragged filters and pixels,
+windows that end on the tensor's last element, a channel range of a wider tensor, long contractions on both sides of the rule."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1708_04728_amd import binding as B
+from util import TOL_F32, case_seed, close, gpu
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("case", [
+    # N, C, H, W, K, R, S, stride
+    (3, 3, 43, 47, 96, 11, 11, 4),        # AlexNet's filter: 33 rows, the last without a partner
+    (140, 3, 35, 35, 96, 11, 11, 4),      # blocks of 96 filters: at least half a workgroup per compute unit
+    (30, 3, 67, 67, 100, 11, 11, 4),      # ragged: blocks of 64, 28 filters over
+    (60, 2, 27, 39, 33, 8, 8, 2),         # whole groups of taps; 16 rows; a block of one filter
+    (2, 1, 7, 7, 5, 7, 7, 1),             # one pixel, which ends on the tensor's last element
+    (5, 3, 21, 30, 64, 7, 7, 2),          # overlap of one
+    (4, 2, 15, 33, 40, 3, 10, 3),         # overlap of two, window rows apart
+    (1, 1, 1, 300, 24, 1, 12, 1),         # one filter row
+    (2, 4, 19, 25, 70, 5, 12, 1),         # four channels
+    (1, 20, 15, 15, 48, 7, 7, 1),         # 140 rows on 81 pixels: stays with the tiled kernel
+    (40, 20, 30, 30, 200, 7, 7, 1),       # 140 rows, 180 x 7 workgroups
+])
+@pytest.mark.parametrize("relu", [False, True])
+def test_conv_f32_taps(case, relu):
+    N, C, H, W, K, R, S, stride = case
+    rng = np.random.default_rng(case_seed(case))
+    x = rng.standard_normal((N, C, H, W)).astype(np.float32)
+    w = (rng.standard_normal((K, C, R, S)) * np.sqrt(2.0 / (C * R * S))).astype(np.float32)
+    b = (rng.standard_normal(K) * 0.1).astype(np.float32) if relu else None
+    ref = oracle.conv2d(x, w, b, stride, 0, relu)
+    off, ctot = (3, K + 5) if case_seed(case) % 2 else (0, K)
+    y = torch.full((N, ctot, ref.shape[2], ref.shape[3]), -7.0, device="cuda")
+    B.conv2d_fwd(gpu(x), B.conv_desc(K, C, R, S, stride, 0, relu, B.DR_KCRS), gpu(w), None if b is None else gpu(b), y, y_c_offset=off)
+    torch.cuda.synchronize()
+    got = y.cpu().numpy()
+    assert (got[:, :off] == -7.0).all() and (got[:, off + K:] == -7.0).all()
+    assert close(got[:, off:off + K], ref, TOL_F32)
+
+
+def test_values_beside_the_window():
+    """Infinities right of a window, below it and in the other filters reach no other output."""
+    x = torch.randn((2, 3, 40, 47), device="cuda")
+    w = torch.randn((40, 3, 11, 11), device="cuda")
+    cd = B.conv_desc(40, 3, 11, 11, 4, 0, False, B.DR_KCRS)
+    y, z = torch.empty((2, 40, 8, 10), device="cuda"), torch.empty((2, 40, 8, 10), device="cuda")
+    B.conv2d_fwd(x, cd, w, None, y)
+    x[:, :, :, 11:15] = float("inf")              # columns 0 (0..10) has none of them, column 1 has
+    w[17] = float("nan")
+    B.conv2d_fwd(x, cd, w, None, z)
+    torch.cuda.synchronize()
+    keep = [m for m in range(40) if m != 17]
+    assert torch.equal(y[:, keep, :, 0], z[:, keep, :, 0]) and torch.isnan(z[:, 17]).all() and not torch.isfinite(z[:, keep, :, 1]).any()
