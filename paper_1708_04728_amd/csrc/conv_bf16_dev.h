@@ -7,6 +7,7 @@
 
 #include <type_traits>
 
+#include "conv_bf16_table.h"
 #include "dr_store.h"
 
 namespace dr {
@@ -16,6 +17,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void* lds_ptr;
 template <int V> using IC = std::integral_constant<int, V>;
 
@@ -69,12 +71,28 @@ __device__ __forceinline__ u32x4 ds_read16(unsigned addr)
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(v) : "v"(addr), "n"(OFF));
     return v;
 }
+__device__ __forceinline__ u32x2 ds_read8(unsigned addr)
+{
+    u32x2 v;
+    asm volatile("ds_read_b64 %0, %1" : "=&v"(v) : "v"(addr));
+    return v;
+}
 template <int N>
 __device__ __forceinline__ void wait_lgkm()
 {
     asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory");
 }
 __device__ __forceinline__ void touch(u32x4& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void touch(u32x2& v) { asm volatile("" : "+v"(v)); }
+
+// Entry e of the table of chunks (conv_bf16_table.h), row_chunks entries to a filter row: {offset, mask}.  rows_of_8: the first layer's padded copy, whose
+// slices are a chunk per pixel pair (see launch_conv_bf16_stem); a lane's place in the slice is in its window's offset there.
+__device__ __forceinline__ u32x2 chunk_entry(int e, int R, int W, int C, int c8, int run_chunks, int row_chunks, unsigned magic_row, unsigned magic_c8,
+                                             bool rows_of_8 = false)
+{
+    const int r = (int)__umulhi((unsigned)e, magic_row), jl = e - r * row_chunks, s = c8 == 1 ? jl : (int)__umulhi((unsigned)jl, magic_c8);
+    return u32x2{chunk_offset(r, rows_of_8 ? 0 : jl, W, C), chunk_mask(r < R && jl < run_chunks, r, s)};
+}
 
 // v / d for 0 <= v < 2^24 and 1 <= d <= 2^16, exact: (v * ceil(2^40 / d)) >> 40.  With m = (2^40 + e) / d,
 // 0 <= e < d, the product is v / d + v e / (d 2^40) and the second term is below 2^-16 <= 1 / d.

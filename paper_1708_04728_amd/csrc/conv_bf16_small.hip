@@ -37,17 +37,7 @@
 namespace dr {
 namespace {
 
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
 constexpr int SMALL_TABLE = 2048;                        // chunks of 8 contraction elements that a layer may have (16 KB of LDS), 1x1 filters at stride 1 aside
-__device__ __forceinline__ void touch(u32x2& v) { asm volatile("" : "+v"(v)); }
-template <int OFF>
-__device__ __forceinline__ u32x2 ds_read8(unsigned addr)         // valid after wait_lgkm or ring_barrier, and touch
-{
-    u32x2 v;
-    asm volatile("ds_read_b64 %0, %1 offset:%2" : "=&v"(v) : "v"(addr), "n"(OFF));
-    return v;
-}
 
 struct SmallJob {
     const uint16_t* x;
@@ -136,8 +126,8 @@ __global__ __launch_bounds__((WM * WN + 4 * LG) * 64) void conv_bf16_small_kerne
         const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)j.x, 0, j.x_bytes, 0x00020000);
         const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)j.w, 0, j.w_bytes, 0x00020000);
         const int lw = (wave - CW) & 3, lg = (wave - CW) >> 2, lrow = lw * 8 + (lane >> 3), lc = (lane & 7) ^ ((lrow >> 1) & 7);
-        int a_voff[A_PER], b_base[B_PER];
-        unsigned b_mask[B_PER];                          // bits 0..15: tap s is OUTSIDE the image row; bits 16..31: filter row r is inside
+        int a_voff[A_PER];
+        unsigned b_base[B_PER], b_mask[B_PER];           // windows of the pixels (conv_bf16_table.h)
 #pragma unroll
         for (int i = 0; i < A_PER; ++i) {
             const int m = mt * BM + i * 32 + lrow;
@@ -148,21 +138,19 @@ __global__ __launch_bounds__((WM * WN + 4 * LG) * 64) void conv_bf16_small_kerne
             const int n = nt * BN + i * 32 + lrow;
             const bool in = n < j.Ng;
             if (j.pointwise) {                           // output pixel n reads input pixel n
-                b_base[i] = n * j.C * 2;
-                b_mask[i] = in ? 0x1FFFEu : 0xFFFFu;
+                b_base[i] = window_offset(0, 0, n, 0, 0, j.C);
+                b_mask[i] = in ? CHUNK_NONE : WINDOW_NONE;
             } else {
                 const int nn = in ? n : 0;
                 const int img = div_small(nn, j.m_pq), pix = nn - img * j.P * j.Q, p = div_small(pix, j.m_q), q = pix - p * j.Q;
                 if (j.stem_wp) {                         // chunk lc of a slice: pixel pair lc & 3 of window row lc >> 2; nothing lies outside the copy
                     b_base[i] = ((img * j.stem_hp + p * j.sh + (lc >> 2)) * j.stem_wp + q * j.sw + 2 * (lc & 3)) * 8;
-                    b_mask[i] = in ? 0xFFFFFEu : 0xFFFFu;
+                    b_mask[i] = in ? CHUNK_NONE : WINDOW_NONE;
                     continue;
                 }
                 const int ih0 = p * j.sh - j.ph, iw0 = q * j.sw - j.pw;
-                b_base[i] = ((img * j.H + ih0) * j.W + iw0) * j.C * 2;
-                const unsigned wv = bit_range(max(0, -iw0), min(j.S - 1, j.W - 1 - iw0));
-                const unsigned hv = in ? bit_range(max(0, -ih0), min(j.R - 1, j.H - 1 - ih0)) : 0u;
-                b_mask[i] = (~wv & 0xFFFFu) | (hv << 16);
+                b_base[i] = window_offset(img, ih0, iw0, j.H, j.W, j.C);
+                b_mask[i] = in ? window_mask(ih0, iw0, j.R, j.S, j.H, j.W) : WINDOW_NONE;
             }
         }
         // wave-uniform position of this wave's next slice: its chunk in the row, its filters' offset, its place in the ring
@@ -179,9 +167,8 @@ __global__ __launch_bounds__((WM * WN + 4 * LG) * 64) void conv_bf16_small_kerne
         for (int k = 1 - NS; k + NS - 1 < stages; ++k) {
             u32x2 e[SL];
             if (!j.pointwise) {
-                e[0] = ds_read8<0>(tab_rd + ld_e * 8);
-                if constexpr (SL > 1) e[1] = ds_read8<LG * 64>(tab_rd + ld_e * 8);
-                static_assert(SL <= 2, "slices of a stage per loading wave");
+                e[0] = ds_read8(tab_rd + ld_e * 8);
+                static_assert(SL == 1, "slices of a stage per loading wave");
             }
             if (k >= 0) {
                 wait_vmcnt<(NS - 2) * L>();
@@ -192,15 +179,14 @@ __global__ __launch_bounds__((WM * WN + 4 * LG) * 64) void conv_bf16_small_kerne
 #pragma unroll
             for (int u = 0; u < SL; ++u) {
                 if (!j.pointwise) touch(e[u]);
-                else e[u] = u32x2{ld_e + u * LG * 8 + lc < j.c8 ? (unsigned)(ld_e + u * LG * 8 + lc) * 16u : (unsigned)OOB, 0x10001u};
+                else e[u] = u32x2{chunk_offset(0, ld_e + u * LG * 8 + lc, 0, 0), chunk_mask(ld_e + u * LG * 8 + lc < j.c8, 0, 0)};
                 unsigned char* sa = ring + ld_slot * SLICE + lw * 1024;
                 unsigned char* sb = sa + BM * 128;
-                const bool ok = (int)e[u][0] >= 0;
-                const unsigned sel = e[u][1], want = sel & 0xFFFF0000u;
+                const bool ok = !(e[u][1] & CHUNK_NONE);
 #pragma unroll
                 for (int i = 0; i < A_PER; ++i) load_to_lds16(rw, sa + i * 4096, ok ? a_voff[i] : OOB, soff_a);
 #pragma unroll
-                for (int i = 0; i < B_PER; ++i) load_to_lds16(rx, sb + i * 4096, ok && (b_mask[i] & sel) == want ? b_base[i] + (int)e[u][0] : OOB, 0);
+                for (int i = 0; i < B_PER; ++i) load_to_lds16(rx, sb + i * 4096, (b_mask[i] & e[u][1]) == 0 ? (int)(b_base[i] + e[u][0]) : OOB, 0);
                 ld_slot = ld_slot + LG == NS * G + lg ? lg : ld_slot + LG;
 #pragma unroll
                 for (int v = 0; v < LG; ++v) next_slice();
@@ -217,15 +203,10 @@ __global__ __launch_bounds__((WM * WN + 4 * LG) * 64) void conv_bf16_small_kerne
         return;
     }
 
-    // ---- the table: entry e = 8 slice + chunk of the slice.  A chunk is 8 channels of a tap: its offset from the window's first pixel, and the
-    // bits that a pixel's mask is tested with (16 + r set, s clear); beyond the contraction, and between a row's last chunk and the next slice: OOB.
+    // ---- the table: entry e = 8 slice + chunk of the slice
     if (!j.pointwise) {
-        for (int e = tid; e < stages * G * 8; e += CW * 64) {
-            const int r = (int)__umulhi((unsigned)e, j.magic_row), jl = e - r * j.row_chunks;
-            const int s = j.c8 == 1 ? jl : (int)__umulhi((unsigned)jl, j.magic_c8), cc = j.stem_wp ? 0 : jl - s * j.c8;
-            const bool ok = r < j.R && jl < j.run_chunks;
-            table[e] = u32x2{ok ? (unsigned)((r * j.W + s) * j.C * 2 + cc * 16) : (unsigned)OOB, (0x10000u << (r & 15)) | (1u << (s & 15))};
-        }
+        for (int e = tid; e < stages * G * 8; e += CW * 64)
+            table[e] = chunk_entry(e, j.R, j.W, j.C, j.c8, j.run_chunks, j.row_chunks, j.magic_row, j.magic_c8, j.stem_wp != 0);
         ring_barrier();
     }
 
@@ -336,15 +317,6 @@ __global__ __launch_bounds__((WM * WN + 4 * LG) * 64) void conv_bf16_small_kerne
     }
 }
 
-// Slices of a tile's contraction.  They run on from filter row to filter row where that saves slices; else every row starts one.
-int small_slices(const ConvGeom& g, int* row_chunks)
-{
-    const int run = g.S * (g.C / 8), spr = (run + 7) / 8, flat = (g.R * run + 7) / 8;
-    const bool on = run >= 8 && flat < g.R * spr;
-    *row_chunks = on ? run : spr * 8;
-    return on ? flat : g.R * spr;
-}
-
 SmallJob small_job(const ConvSmall& c, int bm, int bn, int nth)
 {
     const ConvGeom& g = c.g;
@@ -367,7 +339,7 @@ SmallJob small_job(const ConvSmall& c, int bm, int bn, int nth)
     j.w_bytes = (int)((size_t)g.K * g.Kg * 2);
     j.pointwise = g.R == 1 && g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0;
     j.run_chunks = g.S * j.c8;
-    j.slices = small_slices(g, &j.row_chunks);
+    j.slices = chunk_slices(g.R, g.S, g.C, &j.row_chunks);
     j.magic_c8 = (unsigned)((0x100000000ull + j.c8 - 1) / j.c8);
     j.magic_row = (unsigned)((0x100000000ull + j.row_chunks - 1) / j.row_chunks);
     j.n_tiles = (g.Ng + bn - 1) / bn;
@@ -411,7 +383,7 @@ bool conv_bf16_small_takes(const ConvGeom& g, const void* x, const void* w)
     const long tiles = ((long)g.Ng + 63) / 64 * ((g.K + 63) / 64);
     int row_chunks;
     const bool pointwise = g.R == 1 && g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0;
-    return conv_bf16_dma_eligible(g, x, w) && (pointwise || small_slices(g, &row_chunks) * 8 + 24 <= SMALL_TABLE) && tiles <= (g.R * g.S > 1 ? 2 : 1) * device_cus();
+    return conv_bf16_dma_eligible(g, x, w) && (pointwise || chunk_slices(g.R, g.S, g.C, &row_chunks) * 8 + 24 <= SMALL_TABLE) && tiles <= (g.R * g.S > 1 ? 2 : 1) * device_cus();
 }
 
 template <int TM, int TN, int WM, int WN, int LG, int NS, int G>

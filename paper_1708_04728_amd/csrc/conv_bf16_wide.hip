@@ -29,16 +29,7 @@
 namespace dr {
 namespace {
 
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
 constexpr int WIDE_TABLE = 1024;                         // chunks of 8 contraction elements that a layer may have (8 KB of LDS)
-__device__ __forceinline__ void touch(u32x2& v) { asm volatile("" : "+v"(v)); }
-__device__ __forceinline__ u32x2 ds_read8(unsigned addr)         // valid after wait_lgkm or ring_barrier, and touch
-{
-    u32x2 v;
-    asm volatile("ds_read_b64 %0, %1" : "=&v"(v) : "v"(addr));
-    return v;
-}
 
 template <class F, int... I>
 __device__ __forceinline__ void each_of(std::integer_sequence<int, I...>, const F& f) { (f(IC<I>{}), ...); }
@@ -78,8 +69,8 @@ __global__ __launch_bounds__(512, 2) void conv_bf16_wide_kernel(const WideArgs a
         const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)a.x, 0, a.x_bytes, 0x00020000);
         const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, a.w_bytes, 0x00020000);
         const int lw = wave - 4, lrow = lw * 8 + (lane >> 3), lc = (lane & 7) ^ ((lrow >> 1) & 7);
-        int a_voff[TM], b_base[TN];
-        unsigned b_mask[TN];                             // tap column s (bit s), row r (bit 16 + r) lies outside; bit 15: set
+        int a_voff[TM];
+        unsigned b_base[TN], b_mask[TN];                 // windows of the pixels (conv_bf16_table.h)
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             const int m = mt * BM + i * 32 + lrow;
@@ -91,8 +82,8 @@ __global__ __launch_bounds__(512, 2) void conv_bf16_wide_kernel(const WideArgs a
 #pragma unroll
                 for (int i = 0; i < TN; ++i) {
                     const int n = n0 + i * 32;
-                    b_base[i] = n * a.C * 2;
-                    b_mask[i] = n < a.Ng ? 0x8000u : 0xFFFFFFFFu;
+                    b_base[i] = window_offset(0, 0, n, 0, 0, a.C);
+                    b_mask[i] = n < a.Ng ? CHUNK_NONE : WINDOW_NONE;
                 }
                 return;
             }
@@ -103,9 +94,8 @@ __global__ __launch_bounds__(512, 2) void conv_bf16_wide_kernel(const WideArgs a
 #pragma unroll
             for (int i = 0; i < TN; ++i) {
                 const int ih0 = p * a.sh - a.ph, iw0 = q * a.sw - a.pw;
-                b_base[i] = ((img * a.H + ih0) * a.W + iw0) * a.C * 2;
-                const unsigned wv = bit_range(max(0, -iw0), min(a.S - 1, a.W - 1 - iw0)), hv = bit_range(max(0, -ih0), min(a.R - 1, a.H - 1 - ih0));
-                b_mask[i] = n0 + i * 32 < a.Ng ? ~(wv | (hv << 16)) : 0xFFFFFFFFu;
+                b_base[i] = window_offset(img, ih0, iw0, a.H, a.W, a.C);
+                b_mask[i] = n0 + i * 32 < a.Ng ? window_mask(ih0, iw0, a.R, a.S, a.H, a.W) : WINDOW_NONE;
                 q += a.step_q;
                 if (q >= a.Q) { q -= a.Q; ++p; }
                 p += a.step_p;
@@ -128,11 +118,11 @@ __global__ __launch_bounds__(512, 2) void conv_bf16_wide_kernel(const WideArgs a
             touch(e);
             unsigned char* const sa = ring + stage * STAGE + lw * 1024;
             unsigned char* const sb = sa + BM * 128;
-            const bool ok = (int)e[0] >= 0;
+            const bool ok = !(e[1] & CHUNK_NONE);
 #pragma unroll
             for (int i = 0; i < TM; ++i) load_to_lds16(rw, sa + i * 4096, ok ? a_voff[i] : OOB, soff_a);
 #pragma unroll
-            for (int i = 0; i < TN; ++i) load_to_lds16(rx, sb + i * 4096, (b_mask[i] & e[1]) == 0 ? b_base[i] + (int)e[0] : OOB, 0);
+            for (int i = 0; i < TN; ++i) load_to_lds16(rx, sb + i * 4096, (b_mask[i] & e[1]) == 0 ? (int)(b_base[i] + e[0]) : OOB, 0);
             stage = stage + 1 == NS ? 0 : stage + 1;
             ld_j0 += 8;
             soff_a += 128;
@@ -151,12 +141,7 @@ __global__ __launch_bounds__(512, 2) void conv_bf16_wide_kernel(const WideArgs a
         return;
     }
 
-    for (int e = tid; e < slices * 8; e += 256) {
-        const int r = (int)__umulhi((unsigned)e, a.magic_row), jl = e - r * a.row_chunks;
-        const int s = a.c8 == 1 ? jl : (int)__umulhi((unsigned)jl, a.magic_c8), cc = jl - s * a.c8;
-        const bool ok = r < a.R && jl < a.run_chunks;
-        table[e] = u32x2{ok ? (unsigned)((r * a.W + s) * a.C * 2 + cc * 16) : (unsigned)OOB, ok ? (0x10000u << r) | (1u << s) : 0x8000u};
-    }
+    for (int e = tid; e < slices * 8; e += 256) table[e] = chunk_entry(e, a.R, a.W, a.C, a.c8, a.run_chunks, a.row_chunks, a.magic_row, a.magic_c8);
     if (tid < BM) bias_lds[tid] = a.bias && mt * BM + tid < a.K ? a.bias[mt * BM + tid] : 0.f;
     ring_barrier();
 
@@ -266,14 +251,6 @@ __global__ __launch_bounds__(512, 2) void conv_bf16_wide_kernel(const WideArgs a
     }
 }
 
-int wide_slices(const ConvGeom& g, int* row_chunks)
-{
-    const int run = g.S * (g.C / 8), spr = (run + 7) / 8, flat = (g.R * run + 7) / 8;
-    const bool on = run >= 8 && flat < g.R * spr;
-    *row_chunks = on ? run : spr * 8;
-    return on ? flat : g.R * spr;
-}
-
 template <int TM, int TN>
 int launch_tile(WideArgs a, hipStream_t st)
 {
@@ -314,7 +291,7 @@ bool conv_bf16_wide_takes(const ConvGeom& g, const void* x, const void* w, const
 {
     int row_chunks;
     if (residual || !conv_bf16_dma_eligible(g, x, w) || g.K % 8 != 0 || g.K <= 32) return false;
-    const int slices = wide_slices(g, &row_chunks);
+    const int slices = chunk_slices(g.R, g.S, g.C, &row_chunks);
     if (slices < 3 || slices * 8 > WIDE_TABLE) return false;
     if (slices <= (g.R * g.S > 1 ? 3 : 4) && wide_tile(g.K, g.Ng, slices).rounds > 1) return false;
     if (split && split->n > 1) {
@@ -334,7 +311,7 @@ bool conv_bf16_wide_fills(const ConvGeom& g)
 {
     int row_chunks;
     const long groups = (long)(g.K + 95) / 96 * ((g.Ng + 251) / 252), cus = device_cus();
-    return 2 * groups > cus && 10 * groups <= 11 * cus && wide_tile(g.K, g.Ng, wide_slices(g, &row_chunks)).rounds == 1;
+    return 2 * groups > cus && 10 * groups <= 11 * cus && wide_tile(g.K, g.Ng, chunk_slices(g.R, g.S, g.C, &row_chunks)).rounds == 1;
 }
 
 int launch_conv_bf16_wide(const ConvGeom& g, const uint16_t* x, const uint16_t* w, const float* bias, uint16_t* y, hipStream_t st, const ConvSplit* split)
@@ -348,7 +325,7 @@ int launch_conv_bf16_wide(const ConvGeom& g, const uint16_t* x, const uint16_t* 
     a.pointwise = g.R == 1 && g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0;
     a.c8 = g.C / 8;
     a.run_chunks = g.S * a.c8;
-    a.slices = wide_slices(g, &a.row_chunks);
+    a.slices = chunk_slices(g.R, g.S, g.C, &a.row_chunks);
     a.magic_c8 = (unsigned)((0x100000000ull + a.c8 - 1) / a.c8);
     a.magic_row = (unsigned)((0x100000000ull + a.row_chunks - 1) / a.row_chunks);
     a.m_pq = ((1ull << 40) + (unsigned)(g.P * g.Q) - 1) / (unsigned)(g.P * g.Q);

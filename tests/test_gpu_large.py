@@ -62,6 +62,34 @@ def test_conv_bf16_input_of_more_than_2_gib():
     _run(C=8, H=H, W=W, K=8, R=3, pad=1, rows=400, seed=22, marks=[(1 << 31) // 16, (1 << 32) // 16 if (1 << 32) // 16 < H * W else H * W - 2])
 
 
+@pytest.mark.parametrize("C,H,W,K,pad,stride", [
+    (512, 1, 139811, 64, 15, (16, 3)),        # wide tiles: the one tap inside the map lies 2^31 bytes and more behind every window's first pixel
+    (512, 1, 139811, 60, 15, (16, 3)),        # the streaming kernel
+    (8, 1, 9_000_000, 32, 15, (16, 1000)),    # the kernel for small layers
+    (64, 3, 1_200_000, 64, 13, (4, 200)),     # three rows: taps on both sides of 2^31
+    (64, 3, 1_200_000, 32, 13, (4, 200)),
+])
+def test_filter_rows_2_gib_behind_the_window(C, H, W, K, pad, stride):
+    """16 x 1 filters on a few very long rows: with the padding above the map a window begins before the tensor, and rows of the filter that are
+    inside the map lie 2 GiB or more behind its first pixel."""
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    x = torch.randn((1, H, W, C), device="cuda", generator=gen).to(torch.bfloat16)
+    w = (torch.randn((K, C, 16, 1), device="cuda", generator=gen) * (1.0 / (C * H)) ** 0.5).to(torch.bfloat16)
+    b = torch.randn(K, device="cuda", generator=gen) * 0.1
+    P, Q = (H + 2 * pad - 16) // stride[0] + 1, (W - 1) // stride[1] + 1
+    assert (pad + H - 1) * W * C * 2 >= 1 << 31
+    y = torch.full((1, P, Q, K), float("nan"), dtype=torch.bfloat16, device="cuda")
+    B.conv2d_fwd(B.NHWC(x), B.conv_desc(K, C, 16, 1, stride, (pad, 0), False, B.DR_KRSC), B.pack_filters(w), b, B.NHWC(y))
+    torch.cuda.synchronize()
+    ref = b.double().expand(P, Q, K).clone()
+    for p in range(P):
+        for r in range(16):
+            if 0 <= p * stride[0] - pad + r < H:
+                ref[p] += x[0, p * stride[0] - pad + r, ::stride[1]].double() @ w[:, :, r, 0].double().t()
+    # one rounding of an fp32 sum: within one unit of the last place of the rounded exact result
+    assert close(y[0].double().cpu().numpy(), ref.to(torch.bfloat16).double().cpu().numpy(), 2.0 ** -7)
+
+
 def test_filter_taller_than_a_wide_flat_map():
     """31 x 1 on one row of 9 million pixels, padded by 15: the one tap inside the map lies 15 rows, 1.35e8 elements, behind the window's first,
     which is more than a one-word entry of the fp32 gather table holds."""
