@@ -183,8 +183,11 @@ __global__ __launch_bounds__((WM * WN + 4 * LG) * 64) void conv_bf16_small_kerne
                 unsigned char* sa = ring + ld_slot * SLICE + lw * 1024;
                 unsigned char* sb = sa + BM * 128;
                 const bool ok = !(e[u][1] & CHUNK_NONE);
+                // A stage's slice beyond the last one begins behind the filters, and of few filters behind the whole tensor: OOB is only sure to be
+                // out of range beside a scalar offset inside the buffer, since the hardware compares with the bytes that are left behind that.
+                const int soff = ld_e + u * LG * 8 < slices * 8 ? soff_a : 0;
 #pragma unroll
-                for (int i = 0; i < A_PER; ++i) load_to_lds16(rw, sa + i * 4096, ok ? a_voff[i] : OOB, soff_a);
+                for (int i = 0; i < A_PER; ++i) load_to_lds16(rw, sa + i * 4096, ok ? a_voff[i] : OOB, soff);
 #pragma unroll
                 for (int i = 0; i < B_PER; ++i) load_to_lds16(rx, sb + i * 4096, (b_mask[i] & e[u][1]) == 0 ? (int)(b_base[i] + e[u][0]) : OOB, 0);
                 ld_slot = ld_slot + LG == NS * G + lg ? lg : ld_slot + LG;

@@ -61,6 +61,9 @@ def test_small_layer(case):
     (1, 8, 19, 14, 16, 16, 9, 1, 4),      # the most filter rows and columns
     (2, 16, 9, 9, 40, 4, 3, 1, 1),        # filter rows shorter than a slice, an odd and an even number of slices left over
     (2, 88, 9, 9, 40, 2, 2, 1, 1),        # 22 chunks per filter row, two of them: six slices either way, every row starts one
+    (1, 8, 5, 7, 1, 1, 1, 1, 0),          # one slice: the stage's second one begins 112 bytes behind the filter tensor
+    (1, 8, 9, 7, 5, 1, 1, 2, 0),          # 48 bytes
+    (2, 72, 6, 5, 1, 3, 3, 1, 1),         # 11 slices that run on: the twelfth begins 112 bytes behind it
 ])
 def test_chunk_table(case):
     """Where a chunk of the contraction lies, over the forms of the table, against the fp64 oracle: one rounding of an fp32 sum."""
