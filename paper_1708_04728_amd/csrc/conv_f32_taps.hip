@@ -16,6 +16,7 @@
 #include "dr_internal.h"
 #include "dr_store.h"
 #include "conv_bf16_dev.h"
+#include "conv_f32_taps.h"
 
 namespace dr {
 namespace {
@@ -26,8 +27,6 @@ struct TapsArgs {
     int K, HW, W, C, R, S, rows, Kg, Ng, Q, PQ, sh, sw, y_ctot, relu;
     int x_bytes, w_bytes, grid_m;
 };
-
-constexpr int TAPS_BN = 128;                             // pixels per tile: 32 per multiplying wave
 
 template <int TM, int G, int D>
 __global__ __launch_bounds__(512, 4) void conv_f32_taps_kernel(const TapsArgs a)
@@ -179,15 +178,6 @@ int launch_tm(const TapsArgs& a, int tm, unsigned blocks, hipStream_t st)
     return check_launch("conv_f32_taps");
 }
 
-// blocks of 32 filters per workgroup: the number that pads the filter count least, the larger one of two
-int taps_tm(int K)
-{
-    int best = 1;
-    for (int tm = 2; tm <= 3; ++tm)
-        if ((K + tm * 32 - 1) / (tm * 32) * tm <= (K + best * 32 - 1) / (best * 32) * best) best = tm;
-    return best;
-}
-
 long taps_blocks(const ConvGeom& g, int tm) { return ((long)g.K + tm * 32 - 1) / (tm * 32) * (((long)g.Ng + TAPS_BN - 1) / TAPS_BN); }
 
 }  // namespace
@@ -199,8 +189,7 @@ bool conv_f32_taps_takes(const ConvGeom& g, const void* residual, const ConvSpli
     const int G = (g.S + 3) / 4, D = 4 * G - g.S;
     if (g.nhwc || g.w_krsc || residual || (split && split->n > 1) || g.ph || g.pw || !((G == 2 && D <= 1) || (G == 3 && D <= 2))) return false;
     if (g.C * g.R > 64 && taps_blocks(g, 1) < device_cus()) return false;
-    // a tile's outputs lie within 2 GiB of its first image's
-    return ((double)TAPS_BN / ((double)g.P * g.Q) + 2) * g.y_ctot * g.P * g.Q * 4.0 < 2147483648.0;
+    return taps_store_fits(g.K, g.y_ctot, g.P, g.Q);
 }
 
 int launch_conv_f32_taps(const ConvGeom& g, const float* x, const float* w, const float* bias, float* y, hipStream_t st)
