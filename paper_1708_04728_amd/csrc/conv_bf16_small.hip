@@ -64,6 +64,12 @@ struct SmallArgs {
     SmallJob job[SMALL_GROUP_MAX];
 };
 
+// How a loading wave finds a chunk: by the table; 1x1 filters at stride 1, where the chunks lie side by side
+enum { TABLE, POINTWISE };
+
+// Keeps the computation of v before what follows
+__device__ __forceinline__ void keep(int& v) { asm volatile("" : "+v"(v)); }
+
 // 3x3 max-pooling of one job: an item is one 16-byte channel group of an output pixel
 __device__ __forceinline__ void pool_items(const SmallJob& j, int block)
 {
@@ -95,15 +101,16 @@ __device__ __forceinline__ void pool_items(const SmallJob& j, int block)
 }
 
 // A tile of 16 TM WM filters x 16 TN WN pixels: WM x WN multiplying waves with TM x TN blocks of 16 x 16 each, LG groups of four loading
-// waves, NS stages of G slices in LDS.
-template <int TM, int TN, int WM, int WN, int LG, int NS, int G>
+// waves, a slice of each stage for every group, three stages in LDS.
+template <int TM, int TN, int WM, int WN, int LG>
 __global__ __launch_bounds__((WM * WN + 4 * LG) * 64) void conv_bf16_small_kernel(const SmallArgs args)
 {
+    constexpr int NS = 3, G = LG;                                            // stages in LDS; slices of a stage, one per loading group
     constexpr int CW = WM * WN, BM = WM * TM * 16, BN = WN * TN * 16, A_PER = BM / 32, B_PER = BN / 32, SLICE = (BM + BN) * 128, STAGE = G * SLICE;
-    constexpr int SL = G / LG, L = SL * (A_PER + B_PER);                     // slices of a stage that a loading wave sends, its loads
-    static_assert(G % LG == 0 && BM % 32 == 0 && BN % 32 == 0 && (NS - 1) * L < 63, "loads in flight");
+    constexpr int L = A_PER + B_PER;                                         // a wave's loads for a stage
+    static_assert(BM % 32 == 0 && BN % 32 == 0 && (NS - 1) * L < 63, "loads in flight");
     __shared__ __attribute__((aligned(1024))) unsigned char ring[NS * STAGE];
-    __shared__ __attribute__((aligned(16))) u32x2 table[SMALL_TABLE];        // chunk of the contraction -> {byte offset in x, tap}, see below
+    __shared__ __attribute__((aligned(16))) u32x2 table[SMALL_TABLE];      // chunk of the contraction -> {offset, mask}
 
     // ---- the job and the tile.  Workgroup b runs on die b & 7; a die takes a contiguous range of tiles, filter block by filter
     // block, so that the pixel tiles of one filter block read it from one L2.  (The job is copied: left in the argument
@@ -150,57 +157,63 @@ __global__ __launch_bounds__((WM * WN + 4 * LG) * 64) void conv_bf16_small_kerne
                 }
                 const int ih0 = p * j.sh - j.ph, iw0 = q * j.sw - j.pw;
                 b_base[i] = window_offset(img, ih0, iw0, j.H, j.W, j.C);
-                b_mask[i] = in ? window_mask(ih0, iw0, j.R, j.S, j.H, j.W) : WINDOW_NONE;
+                b_mask[i] = window_mask(in, ih0, iw0, j.R, j.S, j.H, j.W);
             }
         }
-        // wave-uniform position of this wave's next slice: its chunk in the row, its filters' offset, its place in the ring
-        int ld_e = lg * 8, ld_j0 = 0, soff_a = 0, ld_slot = lg;
-        auto next_slice = [&]() __attribute__((always_inline)) {
-            ld_j0 += 8;
-            soff_a += 128;
-            if (ld_j0 == j.row_chunks) { ld_j0 = 0; soff_a += (j.run_chunks - j.row_chunks) * 16; }
-        };
-        if (lg) next_slice();
-        const unsigned tab_rd = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)table + lc * 8;
-        if (!j.pointwise) ring_barrier();                // the table is complete
-        // (one copy of the loading code: a launch of this kernel finds the instruction cache cold)
-        for (int k = 1 - NS; k + NS - 1 < stages; ++k) {
-            u32x2 e[SL];
-            if (!j.pointwise) {
-                e[0] = ds_read8(tab_rd + ld_e * 8);
-                static_assert(SL == 1, "slices of a stage per loading wave");
-            }
-            if (k >= 0) {
-                wait_vmcnt<(NS - 2) * L>();
-                ring_barrier();
-            } else {
-                wait_lgkm<0>();
-            }
+        // The slices one after the other.  The loading waves are on the path of every stage, so the addresses are there before the barrier, and the
+        // next slice's are worked out behind the loads.  (A copy of the code for each way to find a chunk; within it, one: a launch of
+        // this kernel finds the instruction cache cold.)
+        auto send = [&](auto way_c) __attribute__((always_inline)) {
+            constexpr int WAY = decltype(way_c)::value;
+            // wave-uniform position of this wave's next slice: its number, its chunk in the row, its filters' offset, its place in the ring
+            int ld_s = lg, ld_j0 = 0, soff_a = 0, ld_slot = lg;
+            auto next_slice = [&]() __attribute__((always_inline)) {
+                ld_j0 += 8;
+                soff_a += 128;
+                if (WAY == POINTWISE) return;
+                if (ld_j0 == j.row_chunks) { ld_j0 = 0; soff_a += (j.run_chunks - j.row_chunks) * 16; }
+            };
+            if (lg) next_slice();
+            const unsigned tab_rd = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)table + lc * 8;
+            auto entry = [&]() __attribute__((always_inline)) {
+                if constexpr (WAY == TABLE) return ds_read8(tab_rd + ld_s * 64);
+                else return u32x2{chunk_offset(0, ld_j0 + lc, 0, 0), chunk_mask(ld_j0 + lc < j.c8, 0, 0)};
+            };
+            if (WAY == TABLE) ring_barrier();            // the table is complete
+            u32x2 e = entry();
+            for (int k = 1 - NS; k + NS - 1 < stages; ++k) {
+                if (WAY == TABLE) { wait_lgkm<0>(); touch(e); }
+                int va[A_PER], vb[B_PER];
+                const bool ok = chunk_exists(e[1]);
 #pragma unroll
-            for (int u = 0; u < SL; ++u) {
-                if (!j.pointwise) touch(e[u]);
-                else e[u] = u32x2{chunk_offset(0, ld_e + u * LG * 8 + lc, 0, 0), chunk_mask(ld_e + u * LG * 8 + lc < j.c8, 0, 0)};
-                unsigned char* sa = ring + ld_slot * SLICE + lw * 1024;
-                unsigned char* sb = sa + BM * 128;
-                const bool ok = !(e[u][1] & CHUNK_NONE);
+                for (int i = 0; i < A_PER; ++i) { va[i] = ok ? a_voff[i] : OOB; keep(va[i]); }
+#pragma unroll
+                for (int i = 0; i < B_PER; ++i) { vb[i] = (b_mask[i] & e[1]) == 0 ? (int)(b_base[i] + e[0]) : OOB; keep(vb[i]); }
                 // A stage's slice beyond the last one begins behind the filters, and of few filters behind the whole tensor: OOB is only sure to be
                 // out of range beside a scalar offset inside the buffer, since the hardware compares with the bytes that are left behind that.
-                const int soff = ld_e + u * LG * 8 < slices * 8 ? soff_a : 0;
+                const int soff = min(soff_a, j.w_bytes);
+                unsigned char* const sa = ring + ld_slot * SLICE + lw * 1024;
+                unsigned char* const sb = sa + BM * 128;
+                if (k >= 0) {
+                    wait_vmcnt<(NS - 2) * L>();
+                    ring_barrier();
+                }
 #pragma unroll
-                for (int i = 0; i < A_PER; ++i) load_to_lds16(rw, sa + i * 4096, ok ? a_voff[i] : OOB, soff);
+                for (int i = 0; i < A_PER; ++i) load_to_lds16(rw, sa + i * 4096, va[i], soff);
 #pragma unroll
-                for (int i = 0; i < B_PER; ++i) load_to_lds16(rx, sb + i * 4096, (b_mask[i] & e[u][1]) == 0 ? (int)(b_base[i] + e[u][0]) : OOB, 0);
-                ld_slot = ld_slot + LG == NS * G + lg ? lg : ld_slot + LG;
+                for (int i = 0; i < B_PER; ++i) load_to_lds16(rx, sb + i * 4096, vb[i], 0);
+                ld_s += LG;
+                if (WAY == TABLE) e = entry();           // (after the last slice: entries of the table that nobody uses)
 #pragma unroll
                 for (int v = 0; v < LG; ++v) next_slice();
+                if (WAY != TABLE) e = entry();
+                ld_slot = ld_slot + LG == NS * G + lg ? lg : ld_slot + LG;
             }
-            ld_e += G * 8;
-        }
-        // the last stages, already on their way
-        const int left = min(stages, NS - 1);
-        if constexpr (NS > 4) { if (left > 3) { wait_vmcnt<3 * L>(); ring_barrier(); } }
-        if constexpr (NS > 3) { if (left > 2) { wait_vmcnt<2 * L>(); ring_barrier(); } }
-        if constexpr (NS > 2) { if (left > 1) { wait_vmcnt<L>(); ring_barrier(); } }
+        };
+        if (j.pointwise) send(IC<POINTWISE>{});
+        else send(IC<TABLE>{});
+        // the last two stages, already on their way
+        if (stages > 1) { wait_vmcnt<L>(); ring_barrier(); }
         wait_vmcnt<0>();
         ring_barrier();
         return;
@@ -380,7 +393,7 @@ static long small_tiles(const ConvSmall* jobs, int n, int bm, int bn)
 
 // As long as the layer's 64 x 64 tiles fit the device at two workgroups per compute unit, 1x1 filters at one (their contraction is
 // short and the larger tiles then win: 480 -> 304 on 14 x 14 x 19, 295 tiles, 7.7 against 8.5 us; 3x3 144 -> 288, 295 tiles too,
-// 13.6 against 13.5).  A contraction has to fit the table (3x3 on 1792 channels does).
+// 13.6 against 13.5).  A contraction has to fit the table with the last stage's second slice and an entry read ahead by each group (3x3 on 1792 channels does).
 bool conv_bf16_small_takes(const ConvGeom& g, const void* x, const void* w)
 {
     const long tiles = ((long)g.Ng + 63) / 64 * ((g.K + 63) / 64);
@@ -389,7 +402,7 @@ bool conv_bf16_small_takes(const ConvGeom& g, const void* x, const void* w)
     return conv_bf16_dma_eligible(g, x, w) && (pointwise || chunk_slices(g.R, g.S, g.C, &row_chunks) * 8 + 24 <= SMALL_TABLE) && tiles <= (g.R * g.S > 1 ? 2 : 1) * device_cus();
 }
 
-template <int TM, int TN, int WM, int WN, int LG, int NS, int G>
+template <int TM, int TN, int WM, int WN, int LG>
 static int launch_group(const ConvSmall* jobs, int n, hipStream_t st)
 {
     constexpr int NTH = (WM * WN + 4 * LG) * 64;
@@ -401,7 +414,7 @@ static int launch_group(const ConvSmall* jobs, int n, hipStream_t st)
         a.job[i] = small_job(jobs[i], WM * TM * 16, WN * TN * 16, NTH);
         blocks += (a.job[i].tiles + 7) / 8 * 8;
     }
-    hipLaunchKernelGGL((conv_bf16_small_kernel<TM, TN, WM, WN, LG, NS, G>), dim3((unsigned)blocks), dim3(NTH), 0, st, a);
+    hipLaunchKernelGGL((conv_bf16_small_kernel<TM, TN, WM, WN, LG>), dim3((unsigned)blocks), dim3(NTH), 0, st, a);
     return check_launch("conv_bf16_small");
 }
 
@@ -411,15 +424,15 @@ static int launch_group(const ConvSmall* jobs, int n, hipStream_t st)
 // waves of 32 x 16 8.3; stages of two slices, two in flight 10.6: too few loads on their way).
 int launch_conv_bf16_small(const ConvSmall* jobs, int n, hipStream_t st)
 {
-    if (small_tiles(jobs, n, 32, 32) <= device_cus()) return launch_group<1, 1, 2, 2, 2, 3, 2>(jobs, n, st);
-    if (small_tiles(jobs, n, 64, 32) <= device_cus()) return launch_group<1, 1, 4, 2, 2, 3, 2>(jobs, n, st);
-    if (small_tiles(jobs, n, 64, 64) <= device_cus()) return launch_group<2, 1, 2, 4, 2, 3, 2>(jobs, n, st);
+    if (small_tiles(jobs, n, 32, 32) <= device_cus()) return launch_group<1, 1, 2, 2, 2>(jobs, n, st);
+    if (small_tiles(jobs, n, 64, 32) <= device_cus()) return launch_group<1, 1, 4, 2, 2>(jobs, n, st);
+    if (small_tiles(jobs, n, 64, 64) <= device_cus()) return launch_group<2, 1, 2, 4, 2>(jobs, n, st);
     // a layer by itself: wide tiles, which two to a compute unit beat only by sharing the launch (3x3 144 -> 288 on 14 x 14 x 19 10.8 us here, 10.4 there,
     // 160 -> 320 on 7 x 7 x 128 13.4 and 11.3)
     const ConvSmall& j = jobs[0];
     if (n == 1 && j.w && !j.stem_wp && conv_bf16_wide_takes(j.g, j.x, j.w, j.res, j.y, j.split))
         return launch_conv_bf16_wide(j.g, (const uint16_t*)j.x, (const uint16_t*)j.w, j.bias, (uint16_t*)j.y, st, j.split);
-    return launch_group<2, 2, 2, 2, 1, 3, 1>(jobs, n, st);
+    return launch_group<2, 2, 2, 2, 1>(jobs, n, st);
 }
 
 }  // namespace dr

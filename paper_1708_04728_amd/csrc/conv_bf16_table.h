@@ -14,14 +14,17 @@ constexpr unsigned window_offset(int img, int ih0, int iw0, int H, int W, int C)
     return (((unsigned)img * (unsigned)H + (unsigned)ih0) * (unsigned)W + (unsigned)iw0) * (unsigned)C * 2u;
 }
 
-// Bits of a chunk's mask: its tap column s (0..8), its filter row r (16 + 0..15); CHUNK_NONE alone: beyond the contraction.  Bits of a
-// window's mask: the columns and rows that lie outside the image, and CHUNK_NONE.  A chunk is read where the two have no bit in common.
-constexpr unsigned CHUNK_NONE = 0x8000u, WINDOW_NONE = 0xFFFFFFFFu;      // WINDOW_NONE: no such output
-constexpr unsigned chunk_mask(bool exists, int r, int s) { return exists ? (0x10000u << r) | (1u << s) : CHUNK_NONE; }
+// Bits of a chunk's mask: its tap column s (0..8), its filter row r (9 + 0..15); the sign bit alone: beyond the contraction.  Bits of a
+// window's mask: the columns and rows that lie outside the image, and the sign bit.  A chunk is read where the two have no bit in common.
+constexpr unsigned CHUNK_NONE = 0x80000000u, WINDOW_NONE = 0xFFFFFFFFu;      // WINDOW_NONE: no such output
+constexpr unsigned chunk_mask(bool exists, int r, int s) { return exists ? (0x200u << r) | (1u << s) : CHUNK_NONE; }
+constexpr bool chunk_exists(unsigned mask) { return (int)mask >= 0; }
 constexpr unsigned bits(int lo, int hi) { return hi >= lo ? (2u << hi) - (1u << lo) : 0u; }      // lo..hi set
-constexpr unsigned window_mask(int ih0, int iw0, int R, int S, int H, int W)
+constexpr int smaller(int a, int b) { return a < b ? a : b; }
+constexpr int larger(int a, int b) { return a > b ? a : b; }
+constexpr unsigned window_mask(bool exists, int ih0, int iw0, int R, int S, int H, int W)
 {
-    return ~(bits(iw0 < 0 ? -iw0 : 0, S - 1 < W - 1 - iw0 ? S - 1 : W - 1 - iw0) | bits(ih0 < 0 ? -ih0 : 0, R - 1 < H - 1 - ih0 ? R - 1 : H - 1 - ih0) << 16);
+    return ~(bits(larger(0, -iw0), smaller(S - 1, W - 1 - iw0)) | bits(larger(0, -ih0), smaller(R - 1, H - 1 - ih0)) << 9) | (exists ? 0u : WINDOW_NONE);
 }
 
 // Slices of 8 chunks of a contraction: row_chunks from filter row to filter row.  They run on across filter rows (row_chunks: a row's chunks)

@@ -95,7 +95,7 @@ __global__ __launch_bounds__(512, 2) void conv_bf16_wide_kernel(const WideArgs a
             for (int i = 0; i < TN; ++i) {
                 const int ih0 = p * a.sh - a.ph, iw0 = q * a.sw - a.pw;
                 b_base[i] = window_offset(img, ih0, iw0, a.H, a.W, a.C);
-                b_mask[i] = n0 + i * 32 < a.Ng ? window_mask(ih0, iw0, a.R, a.S, a.H, a.W) : WINDOW_NONE;
+                b_mask[i] = window_mask(n0 + i * 32 < a.Ng, ih0, iw0, a.R, a.S, a.H, a.W);
                 q += a.step_q;
                 if (q >= a.Q) { q -= a.Q; ++p; }
                 p += a.step_p;
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(512, 2) void conv_bf16_wide_kernel(const WideArgs a
             touch(e);
             unsigned char* const sa = ring + stage * STAGE + lw * 1024;
             unsigned char* const sb = sa + BM * 128;
-            const bool ok = !(e[1] & CHUNK_NONE);
+            const bool ok = chunk_exists(e[1]);
 #pragma unroll
             for (int i = 0; i < TM; ++i) load_to_lds16(rw, sa + i * 4096, ok ? a_voff[i] : OOB, soff_a);
 #pragma unroll

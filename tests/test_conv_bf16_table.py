@@ -17,16 +17,16 @@ int main()
     while (scanf("%d %d %d %d %d %d %d %d %d %d %d %d %d", &N, &C, &H, &W, &R, &S, &sh, &sw, &ph, &pw, &img, &p, &q) == 13) {
         int row_chunks, read = 0, wrong = 0;
         const int slices = dr::chunk_slices(R, S, C, &row_chunks), c8 = C / 8, ih0 = p * sh - ph, iw0 = q * sw - pw;
-        const unsigned base = dr::window_offset(img, ih0, iw0, H, W, C), outside = dr::window_mask(ih0, iw0, R, S, H, W);
+        const unsigned base = dr::window_offset(img, ih0, iw0, H, W, C), outside = dr::window_mask(true, ih0, iw0, R, S, H, W);
         int filters = 0;
         for (int e = 0; e < slices * 8; ++e) {
             const int r = e / row_chunks, jl = e % row_chunks, s = jl / c8, c = jl % c8;
             const bool exists = r < R && s < S, inside = exists && ih0 + r >= 0 && ih0 + r < H && iw0 + s >= 0 && iw0 + s < W;
             const unsigned mask = dr::chunk_mask(exists, r, s), at = base + dr::chunk_offset(r, jl, W, C);
             const long long true_at = ((((long long)img * H + ih0 + r) * W + iw0 + s) * C + c * 8) * 2;
-            filters += !(mask & dr::CHUNK_NONE);
+            filters += dr::chunk_exists(mask);
             read += (mask & outside) == 0;
-            wrong += ((mask & outside) == 0) != inside || (inside && at != true_at) || !(mask & dr::WINDOW_NONE) || exists != !(mask & dr::CHUNK_NONE);
+            wrong += ((mask & outside) == 0) != inside || (inside && at != true_at) || !(mask & dr::WINDOW_NONE) || exists != dr::chunk_exists(mask);
         }
         printf("%d %d %d\n", wrong, read, filters == R * S * c8);
     }
