@@ -37,7 +37,7 @@
 namespace dr {
 namespace {
 
-constexpr int SMALL_TABLE = 2048;                        // chunks of 8 contraction elements that a layer may have (16 KB of LDS), 1x1 filters at stride 1 aside
+constexpr int SMALL_TABLE = 2048;                        // chunks of 8 contraction elements that the table holds (16 KB of LDS)
 
 struct SmallJob {
     const uint16_t* x;
@@ -50,7 +50,7 @@ struct SmallJob {
     int C, H, W, K, R, S, sh, sw, ph, pw, P, Q, Kg, Ng, relu;
     int x_bytes, w_bytes;
     int stem_hp, stem_wp;                                // padded 4-channel input copy (see launch_conv_bf16_stem), 0: ordinary input
-    int pointwise;
+    int pointwise, tabled;                               // 1x1 at stride 1; the table holds the contraction
     int c8, run_chunks;                                  // 16-byte chunks per tap, per filter row
     int row_chunks;                                      // chunks from filter row to filter row of the slices: run_chunks, or rounded up to whole slices
     int slices;
@@ -64,8 +64,10 @@ struct SmallArgs {
     SmallJob job[SMALL_GROUP_MAX];
 };
 
-// How a loading wave finds a chunk: by the table; 1x1 filters at stride 1, where the chunks lie side by side
-enum { TABLE, POINTWISE };
+// How a loading wave finds a chunk: by the table; 1x1 filters at stride 1, where the chunks lie side by side; worked out chunk by chunk for a
+// contraction that the table does not hold (about 20 instructions more per slice and wave; the streaming kernel, which took these layers once,
+// needs twice as long: 7x7 512 -> 4096 on one pixel 113 us there, 56 here; 3x3 2048 -> 512 on 7 x 7 87 and 41)
+enum { TABLE, POINTWISE, LONG };
 
 // Keeps the computation of v before what follows
 __device__ __forceinline__ void keep(int& v) { asm volatile("" : "+v"(v)); }
@@ -165,19 +167,28 @@ __global__ __launch_bounds__((WM * WN + 4 * LG) * 64) void conv_bf16_small_kerne
         // this kernel finds the instruction cache cold.)
         auto send = [&](auto way_c) __attribute__((always_inline)) {
             constexpr int WAY = decltype(way_c)::value;
-            // wave-uniform position of this wave's next slice: its number, its chunk in the row, its filters' offset, its place in the ring
-            int ld_s = lg, ld_j0 = 0, soff_a = 0, ld_slot = lg;
+            // wave-uniform position of this wave's next slice: its number, its filter row (LONG) and chunk in the row, its filters' offset, its place in the ring
+            int ld_s = lg, ld_r = 0, ld_j0 = 0, soff_a = 0, ld_slot = lg;
             auto next_slice = [&]() __attribute__((always_inline)) {
                 ld_j0 += 8;
                 soff_a += 128;
                 if (WAY == POINTWISE) return;
-                if (ld_j0 == j.row_chunks) { ld_j0 = 0; soff_a += (j.run_chunks - j.row_chunks) * 16; }
+                if (WAY == LONG ? ld_j0 >= j.row_chunks : ld_j0 == j.row_chunks) {
+                    ld_j0 = WAY == LONG ? ld_j0 - j.row_chunks : 0;
+                    ++ld_r;
+                    soff_a += (j.run_chunks - j.row_chunks) * 16;
+                }
             };
             if (lg) next_slice();
             const unsigned tab_rd = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)table + lc * 8;
             auto entry = [&]() __attribute__((always_inline)) {
                 if constexpr (WAY == TABLE) return ds_read8(tab_rd + ld_s * 64);
-                else return u32x2{chunk_offset(0, ld_j0 + lc, 0, 0), chunk_mask(ld_j0 + lc < j.c8, 0, 0)};
+                else if constexpr (WAY == POINTWISE) return u32x2{chunk_offset(0, ld_j0 + lc, 0, 0), chunk_mask(ld_j0 + lc < j.c8, 0, 0)};
+                else {                                   // chunk ld_j0 + lc of row ld_r, or of the row behind it where the slices run on
+                    const int jl = ld_j0 + lc, over = jl >= j.row_chunks, jr = over ? jl - j.row_chunks : jl, r = ld_r + over;
+                    const int s = j.c8 == 1 ? jr : (int)__umulhi((unsigned)jr, j.magic_c8);
+                    return u32x2{chunk_offset(ld_r, jr, j.W, j.C) + (over ? chunk_offset(1, 0, j.W, j.C) : 0u), chunk_mask(r < j.R && jr < j.run_chunks, r, s)};
+                }
             };
             if (WAY == TABLE) ring_barrier();            // the table is complete
             u32x2 e = entry();
@@ -211,7 +222,8 @@ __global__ __launch_bounds__((WM * WN + 4 * LG) * 64) void conv_bf16_small_kerne
             }
         };
         if (j.pointwise) send(IC<POINTWISE>{});
-        else send(IC<TABLE>{});
+        else if (j.tabled) send(IC<TABLE>{});
+        else send(IC<LONG>{});
         // the last two stages, already on their way
         if (stages > 1) { wait_vmcnt<L>(); ring_barrier(); }
         wait_vmcnt<0>();
@@ -220,7 +232,7 @@ __global__ __launch_bounds__((WM * WN + 4 * LG) * 64) void conv_bf16_small_kerne
     }
 
     // ---- the table: entry e = 8 slice + chunk of the slice
-    if (!j.pointwise) {
+    if (j.tabled) {
         for (int e = tid; e < stages * G * 8; e += CW * 64)
             table[e] = chunk_entry(e, j.R, j.W, j.C, j.c8, j.run_chunks, j.row_chunks, j.magic_row, j.magic_c8, j.stem_wp != 0);
         ring_barrier();
@@ -356,6 +368,7 @@ SmallJob small_job(const ConvSmall& c, int bm, int bn, int nth)
     j.pointwise = g.R == 1 && g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0;
     j.run_chunks = g.S * j.c8;
     j.slices = chunk_slices(g.R, g.S, g.C, &j.row_chunks);
+    j.tabled = !j.pointwise && (j.slices + 3) * 8 <= SMALL_TABLE;      // (+ 3: the last stage's second slice, and one entry read ahead by each group)
     j.magic_c8 = (unsigned)((0x100000000ull + j.c8 - 1) / j.c8);
     j.magic_row = (unsigned)((0x100000000ull + j.row_chunks - 1) / j.row_chunks);
     j.n_tiles = (g.Ng + bn - 1) / bn;
@@ -393,13 +406,11 @@ static long small_tiles(const ConvSmall* jobs, int n, int bm, int bn)
 
 // As long as the layer's 64 x 64 tiles fit the device at two workgroups per compute unit, 1x1 filters at one (their contraction is
 // short and the larger tiles then win: 480 -> 304 on 14 x 14 x 19, 295 tiles, 7.7 against 8.5 us; 3x3 144 -> 288, 295 tiles too,
-// 13.6 against 13.5).  A contraction has to fit the table with the last stage's second slice and an entry read ahead by each group (3x3 on 1792 channels does).
+// 13.6 against 13.5).  Channels: as many as a tap is found exactly for by a multiplication (the kernel's LONG).
 bool conv_bf16_small_takes(const ConvGeom& g, const void* x, const void* w)
 {
     const long tiles = ((long)g.Ng + 63) / 64 * ((g.K + 63) / 64);
-    int row_chunks;
-    const bool pointwise = g.R == 1 && g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0;
-    return conv_bf16_dma_eligible(g, x, w) && (pointwise || chunk_slices(g.R, g.S, g.C, &row_chunks) * 8 + 24 <= SMALL_TABLE) && tiles <= (g.R * g.S > 1 ? 2 : 1) * device_cus();
+    return conv_bf16_dma_eligible(g, x, w) && (g.R * g.S == 1 || g.C <= 1 << 17) && tiles <= (g.R * g.S > 1 ? 2 : 1) * device_cus();
 }
 
 template <int TM, int TN, int WM, int WN, int LG>

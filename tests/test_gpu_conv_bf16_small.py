@@ -56,7 +56,14 @@ def test_small_layer(case):
 @pytest.mark.parametrize("case", [
     # N, C, H, W, K, R, S, stride, pad
     (1, 1792, 3, 4, 24, 3, 3, 1, 1),      # 252 slices: the longest contraction the chunk table holds
-    (1, 1856, 3, 4, 24, 3, 3, 1, 1),      # 261: beyond it, the larger kernels
+    (1, 1856, 3, 4, 24, 3, 3, 1, 1),      # 261: beyond it, worked out chunk by chunk; rows of whole slices
+    (1, 648, 5, 7, 24, 5, 5, 1, 2),       # 254 slices that run on; the table would hold them, but not what is read ahead
+    (2, 656, 6, 5, 40, 5, 5, 2, 2),       # 257 that run on, worked out: a row's last slice goes on into the next one
+    (1, 1832, 2, 12, 24, 1, 9, 1, 4),     # one row of 2061 chunks, filter rows outside the image
+    (1, 512, 7, 7, 200, 7, 7, 1, 0),      # a classifier's first layer: one pixel
+    (1, 1856, 64, 65, 40, 3, 3, 1, 1),    # tiles of 64 x 32
+    (1, 1856, 89, 90, 8, 3, 3, 1, 1),     # 64 x 64
+    (1, 1856, 129, 130, 8, 3, 3, 1, 1),   # 64 x 64, two to a compute unit
     (1, 16448, 1, 3, 24, 1, 1, 1, 0),     # 1x1 filters at stride 1 need no table
     (1, 8, 19, 14, 16, 16, 9, 1, 4),      # the most filter rows and columns
     (2, 16, 9, 9, 40, 4, 3, 1, 1),        # filter rows shorter than a slice, an odd and an even number of slices left over
