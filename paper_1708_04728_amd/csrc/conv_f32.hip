@@ -691,6 +691,23 @@ static bool slices_of_32(const ConvGeom& g)
     return tiles <= 4 * cus || (g.C > 32 && tiles > 7 * cus && tiles <= 9 * cus);
 }
 
+// A layer for the kernel of conv_f32_taps.hip whose contraction scratch memory lets be cut over workgroups (see launch_tile): whether that is
+// faster.  There a workgroup walks all pairs of filter rows, 0.34 us each; the cut takes a second launch, the partial sums' way through memory
+// and the slices of a range.  Fitted to 200 layers of few pixels (5 and 7 % off), and within 9 % of the better one on each of them: 11x11 on 5 channels, two
+// outputs, 6.8 us cut and 11.9 there, 12x12 on 5 channels 27 filters on 272 outputs 9.0 and 13.6; 11x11 on 3 channels 6 filters on 1575 outputs 7.5 and
+// 8.7; 8x8 on 5 channels 13 filters on 12054 outputs 11.5 and 10.2, 10x10 on 3 channels 240 filters on 1740 outputs 17.3 and 8.1.
+static bool cut_beats_taps(const ConvGeom& g, const void* ws, size_t ws_bytes)
+{
+    int row_groups, per;
+    const int nslices = contraction_slices<16>(g, &row_groups);
+    const int tiles = rows_of_32(g) ? ((g.K + 31) / 32) * ((g.Ng + 127) / 128) : ((g.K + 63) / 64) * ((g.Ng + 63) / 64);
+    const int splits = split_plan(tiles, nslices, &per);
+    const size_t bytes = (size_t)splits * g.K * g.Ng * sizeof(float);
+    if (!ws || splits <= 1 || bytes > ws_bytes || ((uintptr_t)ws & 15) != 0) return false;
+    const float taps_us = 3.0f + 0.34f * ((g.C * g.R + 1) / 2), cut_us = 6.4f + 0.84e-6f * bytes + 1.26f * (per - 2) + 0.071f * splits;
+    return cut_us < 0.95f * taps_us;
+}
+
 bool conv_f32_group_takes(const ConvGeom& g)
 {
     const size_t xb = (size_t)g.N * g.C * g.H * g.W * 4, wb = (size_t)g.K * g.Kg * 4;
@@ -735,7 +752,7 @@ int launch_conv_f32(const ConvGeom& g, const float* x, const float* w, const flo
     if (xb >= (1ull << 31) || wb >= (1ull << 31))
         return fail(DR_ERR_UNSUPPORTED, "conv_f32: input (%zu bytes) or filter tensor (%zu bytes) is 2 GiB or larger", xb, wb);
     // wide filters on few channels, no padding (conv_f32_taps.hip)
-    if (conv_f32_taps_takes(g, residual, split)) return launch_conv_f32_taps(g, x, w, bias, y, st);
+    if (conv_f32_taps_takes(g, residual, split) && !cut_beats_taps(g, ws, ws_bytes)) return launch_conv_f32_taps(g, x, w, bias, y, st);
     const KArgs a = base_args(g, x, w, bias, residual, y, split);
     // (32-deep slices with the groups-of-4-taps order: measured 10 % slower)
     if (slices_of_32(g))

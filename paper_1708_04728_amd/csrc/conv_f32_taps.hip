@@ -183,7 +183,8 @@ long taps_blocks(const ConvGeom& g, int tm) { return ((long)g.K + tm * 32 - 1) /
 }  // namespace
 
 // Filters 7, 8 or 10 to 12 taps wide (groups of 4 that overlap by at most a fifth), as conv_f32.hip's order over groups of 4 taps, which
-// this kernel takes the place of.  Contractions of more than 64 filter rows on few pixels stay there: they are cut over workgroups.
+// this kernel takes the place of.  Contractions of more than 64 filter rows on few pixels stay there, and with scratch memory shorter ones that are faster
+// cut over workgroups (cut_beats_taps in conv_f32.hip).
 bool conv_f32_taps_takes(const ConvGeom& g, const void* residual, const ConvSplit* split)
 {
     const int G = (g.S + 3) / 4, D = 4 * G - g.S;

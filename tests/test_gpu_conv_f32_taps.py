@@ -43,6 +43,51 @@ def test_conv_f32_taps(case, relu):
     assert close(got[:, off:off + K], ref, TOL_F32)
 
 
+def cut_is_faster(case):
+    """The library's rule for layers with scratch memory, restated."""
+    N, C, H, W, K, R, S, stride = case
+    ng = N * oracle.conv_out_size(H, R, stride, 0) * oracle.conv_out_size(W, S, stride, 0)
+    rows32 = -(-K // 32) * 32 < -(-K // 64) * 64
+    tiles = -(-K // 32) * -(-ng // 128) if rows32 else -(-K // 64) * -(-ng // 64)
+    slices = -(-C * R * (-(-S // 4) * 4) // 16)
+    if 2 * tiles > 256 or slices < 4:
+        return False
+    per = max(2, -(-slices // -(-512 // tiles)))
+    splits = -(-slices // per)
+    return splits > 1 and 6.4 + 0.84e-6 * splits * K * ng * 4 + 1.26 * (per - 2) + 0.071 * splits < 0.95 * (3 + 0.34 * -(-C * R // 2))
+
+
+@pytest.mark.parametrize("case,cut", [
+    ((2, 5, 12, 15, 1, 11, 11, 2), True),        # two outputs, 55 filter rows
+    ((17, 5, 27, 25, 27, 12, 12, 4), True),
+    ((7, 3, 40, 39, 6, 11, 11, 2), True),        # 33 rows: beside the line
+    ((11, 5, 40, 41, 3, 7, 7, 4), True),         # 35
+    ((2, 3, 66, 68, 240, 10, 10, 2), False),     # partial sums of 8 MB
+    ((7, 5, 90, 92, 13, 8, 8, 4), True),
+    ((7, 5, 170, 172, 13, 8, 8, 4), False),      # ... of 3 MB
+    ((26, 1, 20, 23, 115, 8, 8, 4), False),      # 8 rows
+    ((1, 3, 227, 227, 96, 11, 11, 4), False),    # AlexNet's first layer on one image
+])
+def test_cut_over_workgroups_where_that_is_faster(case, cut):
+    """With scratch memory: the partial sums are written into it exactly where the rule says, and either way gives the layer."""
+    assert cut_is_faster(case) == cut
+    N, C, H, W, K, R, S, stride = case
+    rng = np.random.default_rng(case_seed(case))
+    x = rng.standard_normal((N, C, H, W)).astype(np.float32)
+    w = (rng.standard_normal((K, C, R, S)) * np.sqrt(2.0 / (C * R * S))).astype(np.float32)
+    b = (rng.standard_normal(K) * 0.1).astype(np.float32)
+    ref = oracle.conv2d(x, w, b, stride, 0, True)
+    cd = B.conv_desc(K, C, R, S, stride, 0, True, B.DR_KCRS)
+    need = B.conv2d_workspace_bytes(gpu(x), cd)
+    assert need > 0
+    ws = torch.full((need,), 0xA5, dtype=torch.uint8, device="cuda")
+    y = torch.full(ref.shape, float("nan"), device="cuda")
+    B.conv2d_fwd_ws(gpu(x), cd, gpu(w), gpu(b), y, ws)
+    torch.cuda.synchronize()
+    assert bool((ws != 0xA5).any()) == cut
+    assert close(y.cpu().numpy(), ref, TOL_F32)
+
+
 def test_values_beside_the_window():
     """Infinities right of a window, below it and in the other filters reach no other output."""
     x = torch.randn((2, 3, 40, 47), device="cuda")
