@@ -30,6 +30,8 @@
 // Operands travel as in the streaming kernel: 16-byte buffer loads that write LDS, lanes outside the tensor or in the padding at
 // an offset the hardware answers with zeros, chunk j of row r stored at chunk j ^ ((r >> 1) & 7) so that loads and operand
 // reads are free of bank conflicts.
+#include <algorithm>
+
 #include "dr_internal.h"
 #include "dr_store.h"
 #include "conv_bf16_dev.h"
@@ -437,7 +439,13 @@ int launch_conv_bf16_small(const ConvSmall* jobs, int n, hipStream_t st)
 {
     if (small_tiles(jobs, n, 32, 32) <= device_cus()) return launch_group<1, 1, 2, 2, 2>(jobs, n, st);
     if (small_tiles(jobs, n, 64, 32) <= device_cus()) return launch_group<1, 1, 4, 2, 2>(jobs, n, st);
-    if (small_tiles(jobs, n, 64, 64) <= device_cus()) return launch_group<2, 1, 2, 4, 2>(jobs, n, st);
+    // 1, 3 or 5 slices: half of the last stage of two would be empty, and four waves start sooner than eight (one slice: 1x1 32 -> 528 on 19 x 19 x 15 at
+    // stride 2 4.3 us in stages of two, 3.95 so; three: 3x3 16 -> 344 on 41 x 44 4.5 and 4.3; 1x1 at stride 1 3.7 and 3.65; two slices 3.8 and
+    // 3.9, four 4.4 and 4.4, six and more the larger stages)
+    int most = 0, row_chunks;
+    for (int i = 0; i < n; ++i)
+        if (jobs[i].w) most = std::max(most, chunk_slices(jobs[i].g.R, jobs[i].g.S, jobs[i].g.C, &row_chunks));
+    if (small_tiles(jobs, n, 64, 64) <= device_cus()) return most % 2 && most <= 5 ? launch_group<2, 2, 2, 2, 1>(jobs, n, st) : launch_group<2, 1, 2, 4, 2>(jobs, n, st);
     // a layer by itself: wide tiles, which two to a compute unit beat only by sharing the launch (3x3 144 -> 288 on 14 x 14 x 19 10.8 us here, 10.4 there,
     // 160 -> 320 on 7 x 7 x 128 13.4 and 11.3)
     const ConvSmall& j = jobs[0];

@@ -32,6 +32,11 @@ def takes(N, C, H, W, K, R, S, stride, pad):
     (1, 320, 9, 9, 56, 1, 1, 2, 0),       # strided 1x1
     (4, 96, 64, 64, 64, 1, 1, 1, 0),      # 256 tiles of 64 x 64: the largest layer with 1x1 filters
     (1, 48, 64, 61, 96, 3, 3, 1, 1),      # 64 x 32 tiles, half a filter block
+    (2, 40, 43, 46, 200, 1, 1, 1, 0),     # 64 x 64 tiles in stages of one slice: one
+    (1, 16, 41, 44, 344, 3, 3, 1, 1),     # three
+    (5, 32, 36, 35, 72, 3, 3, 1, 1),      # five
+    (10, 24, 29, 28, 72, 3, 3, 1, 1),     # 64 x 64 tiles in stages of two: four slices
+    (12, 48, 22, 25, 96, 3, 3, 1, 1),     # seven
     (2, 24, 96, 84, 104, 3, 3, 1, 1),     # 504 tiles of 64 x 64, ragged
     (1, 1032, 2, 3, 8, 3, 3, 1, 1),       # long contraction, 146 slices
 ])
