@@ -10,6 +10,7 @@ import pytest
 
 import oracle
 import workloads
+from bf16_rules import patch_rows, route
 from paper_1708_04728_amd import binding as B
 from util import TOL_BF16, case_seed, close, empty_nhwc, gpu, gpu_nhwc, host_nhwc
 
@@ -18,14 +19,8 @@ torch = pytest.importorskip("torch")
 
 
 def rows_per_tile(C, H, W, K, R, S, stride, pad):
-    """The rule of the library's launcher, restated: output rows per tile, 0 = the layer goes to the streaming kernel."""
-    P, Q = oracle.conv_out_size(H, R, stride, pad), oracle.conv_out_size(W, S, stride, pad)
-    if C % 64 or K % 8 or stride != 1 or R * S < 2 or R > 7 or S > 7 or Q < 2 or Q > 256:
-        return 0
-    th = min(256 // Q, P)
-    while th >= 1 and (C // 64) * (((th + R - 1) * (W + 2 * pad) + 31) // 32 * 32) > 352:
-        th -= 1
-    return th if th >= 1 and th * Q * 4 >= 256 * 3 else 0
+    """Output rows per tile, 0 = not for this kernel."""
+    return patch_rows((1, C, H, W, K, R, S, stride, pad))
 
 
 def tiling(C, H, W, K, R, S, stride, pad):
@@ -60,10 +55,21 @@ CASES = [
 EXPECTED_TILING = dict(zip(CASES, [(2, 9, 13), (2, 9, 13), (2, 9, 13), (1, 9, 4), (1, 3, 10), (1, 3, 6), (2, 17, 4), (1, 4, 11), (2, 7, 9), (1, 3, 4)]))
 
 
+def batch(case):
+    """The fewest images with which the layer runs in this kernel for good."""
+    return next(n for n in range(1, 200) if all(route((m,) + case[1:], 16, 8)[0] == "patch" for m in range(n, n + 40)))
+
+
+@pytest.mark.parametrize("here", [False, True])
 @pytest.mark.parametrize("case", CASES)
 @pytest.mark.parametrize("relu", [False, True])
-def test_conv_patch(case, relu):
+def test_conv_patch(case, relu, here):
     N, C, H, W, K, R, S, stride, pad = case
+    pick = list(range(N))
+    if here:
+        N = batch(case)
+        pick = [0, N - 1]
+        assert route((N,) + case[1:], 16, 8) == ("patch", rows_per_tile(*case[1:]))
     assert rows_per_tile(C, H, W, K, R, S, stride, pad) > 0, "the case must be one the patch kernel takes"
     assert tiling(C, H, W, K, R, S, stride, pad) == EXPECTED_TILING[case], "the cases are chosen for these tilings"
     rng = np.random.default_rng(case_seed(case))
@@ -71,7 +77,7 @@ def test_conv_patch(case, relu):
     w = workloads.round_to_bf16(rng.standard_normal((K, C, R, S)).astype(np.float32) * np.float32(np.sqrt(2.0 / (C * R * S))))
     bias = case_seed(case) % 3 != 0
     b = (rng.standard_normal(K) * 0.1).astype(np.float32) if bias else None
-    ref = oracle.conv2d(x, w, b, stride, pad, relu)
+    ref = oracle.conv2d(x[pick], w, b, stride, pad, relu)
     # written at a channel offset of a wider tensor (a branch of a module writing its part of the concatenated output)
     ctot, coff = K + 24, 16
     y = B.NHWC(torch.full((N, ref.shape[2], ref.shape[3], ctot), -5.0, dtype=torch.bfloat16, device="cuda"))
@@ -81,15 +87,15 @@ def test_conv_patch(case, relu):
     got = host_nhwc(y)
     assert not np.isnan(got).any()
     assert (got[:, :coff] == -5.0).all() and (got[:, coff + K:] == -5.0).all()
-    assert close(got[:, coff:coff + K], ref, TOL_BF16)
-    assert close(got[:, coff:coff + K], oracle.round_bf16(ref), 2.0 ** -7, "within one bf16 unit of the oracle")
+    assert close(got[pick, coff:coff + K], ref, TOL_BF16)
+    assert close(got[pick, coff:coff + K], oracle.round_bf16(ref), 2.0 ** -7, "within one bf16 unit of the oracle")
 
 
 def test_conv_patch_many_tiles_per_workgroup_and_a_layer_the_rule_leaves_out():
     # 64 images of 56 x 56: 896 tiles on at most 512 workgroups per filter block, so workgroups walk several tiles
     case = (64, 64, 56, 56, 96, 3, 3, 1, 1)
     N, C, H, W, K, R, S, stride, pad = case
-    assert rows_per_tile(C, H, W, K, R, S, stride, pad) == 4
+    assert rows_per_tile(C, H, W, K, R, S, stride, pad) == 4 and route(case)[0] == "patch"
     rng = np.random.default_rng(7)
     x = workloads.round_to_bf16(rng.standard_normal((N, C, H, W)).astype(np.float32))
     w = workloads.round_to_bf16(rng.standard_normal((K, C, R, S)).astype(np.float32) * np.float32(np.sqrt(2.0 / (C * R * S))))
@@ -101,5 +107,5 @@ def test_conv_patch_many_tiles_per_workgroup_and_a_layer_the_rule_leaves_out():
     pick = [0, 17, 63]
     assert close(got[pick], oracle.conv2d(x[pick], w, b, stride, pad, True), TOL_BF16)
     assert np.isfinite(got).all() and (got >= 0).all()
-    # stride 2 is not for the patch kernel; the streaming kernel gives the same layer's strided form
+    # stride 2 is not for the patch kernel
     assert rows_per_tile(C, H, W, K, R, S, 2, pad) == 0

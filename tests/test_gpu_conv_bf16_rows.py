@@ -1,8 +1,9 @@
 """GPU parity of the row-stack patch convolution kernel (bf16 NHWC, several taps at stride 1 on maps with 16, 32, 48 or 64
 channels: a tile is a run of output rows of the whole batch's row stack -- image borders inside it allowed -- whose input
-patch is loaded into LDS once) against the fp64 oracle.  The library picks the kernel by rule, restated in `takes` below;
-every case satisfies it (and not the rule of the 64-channel patch kernel, which the library asks first), so what is
-compared is this kernel.  The cases put image borders at every position inside a tile, several images in one tile,
+patch is loaded into LDS once) against the fp64 oracle.  The library picks the kernel by rule, restated in bf16_rules.py;
+every case satisfies it (and not the rule of the 64-channel patch kernel, which the library asks first).  Some of them are small layers with the
+images they name, or layers that wide tiles spread over more compute units: each runs so, and with as many images as bring it
+here.  The cases put image borders at every position inside a tile, several images in one tile,
 tiles that end behind the last image, ragged filter blocks, filter rows whose last 64-deep slice is partly empty, and
 rectangular filters."""
 import numpy as np
@@ -10,6 +11,7 @@ import pytest
 
 import oracle
 import workloads
+from bf16_rules import CUS, route, rows_rows
 from paper_1708_04728_amd import binding as B
 from test_gpu_conv_bf16_patch import rows_per_tile as patch_kernel_rows
 from util import TOL_BF16, case_seed, close, empty_nhwc, gpu, gpu_nhwc, host_nhwc
@@ -17,27 +19,9 @@ from util import TOL_BF16, case_seed, close, empty_nhwc, gpu, gpu_nhwc, host_nhw
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
-CUS = 256
-
-
-def takes(N, C, H, W, K, R, S, stride, pad):
-    """The rule of the library's launcher, restated: stacked output rows per tile, 0 = the layer goes elsewhere."""
-    P, Q = oracle.conv_out_size(H, R, stride, pad), oracle.conv_out_size(W, S, stride, pad)
-    if C % 16 or C > 64 or K % 8 or stride != 1 or R * S < 2 or R > 7 or S > 7 or P < 2 or Q < 2 or Q > 256:
-        return 0
-    tm = 3 if (K + 95) // 96 * 96 <= (K + 63) // 64 * 64 else 2
-    budget = 80 * 1024 - (2 * tm * 32 * 128 + 512 + 1024)
-    th = min(256 // Q, N * P)
-    while th >= 1:
-        segs = min(N, (th + P - 2) // P + 1)
-        patch = ((th + (R - 1) * segs) * (W + 2 * pad) * (C // 8 + 1) * 16 + 4095) // 4096 * 4096
-        if patch <= budget:
-            break
-        th -= 1
-    if th < 1 or th * Q * 4 < 256 * 3:
-        return 0
-    tiles, blocks = (N * P + th - 1) // th, (K + tm * 32 - 1) // (tm * 32)
-    return th if tiles * blocks * 4 >= CUS else 0
+def takes(*case):
+    """Stacked output rows per tile, 0 = not for this kernel."""
+    return rows_rows(case)
 
 
 # N, C, H, W, K, R, S, stride, pad
@@ -80,9 +64,20 @@ def _check(case, relu, bias, images=None):
     assert close(got[pick, coff:coff + K], oracle.round_bf16(ref), 2.0 ** -7, "within one bf16 unit of the oracle")
 
 
+def batch(case):
+    """The fewest images with which the layer runs in this kernel for good."""
+    return next(n for n in range(1, 400) if all(route((m,) + case[1:], 16, 8)[0] == "rows" for m in range(n, n + 60)))
+
+
+@pytest.mark.parametrize("here", [False, True])
 @pytest.mark.parametrize("case", CASES)
-def test_conv_rows(case):
-    _check(case, relu=case_seed(case) % 2 == 0, bias=case_seed(case) % 3 != 0)
+def test_conv_rows(case, here):
+    images, N = None, case[0]
+    if here:
+        N = max(case[0], batch(case))
+        images = [0, N // 2, N - 1]
+        assert route((N,) + case[1:], 16, 8)[0] == "rows"
+    _check((N,) + case[1:], relu=case_seed(case) % 2 == 0, bias=case_seed(case) % 3 != 0, images=images)
 
 
 def test_conv_rows_many_tiles_per_workgroup():
@@ -93,7 +88,7 @@ def test_conv_rows_many_tiles_per_workgroup():
 
 
 def test_layers_the_rule_leaves_out_still_match():
-    # few tiles (the streaming kernel's smaller tiles fill the device better) and 24 channels (not a multiple of 16)
+    # few tiles (smaller ones fill the device better) and 24 channels (not a multiple of 16)
     for case in [(1, 16, 28, 28, 32, 5, 5, 1, 2), (4, 24, 14, 14, 64, 5, 5, 1, 2)]:
         assert takes(*case) == 0
         N, C, H, W, K, R, S, stride, pad = case

@@ -1,5 +1,5 @@
 """GPU parity of the wide-tile bf16 convolution kernel (one persistent workgroup per compute unit, loading and multiplying waves
-apart) against the fp64 oracle: every tile the library's rule picks (restated in `tile`), ragged filters and pixels, one round and
+apart) against the fp64 oracle: every tile the library's rule picks (restated in bf16_rules.py), ragged filters and pixels, one round and
 several, slices inside a tap, running on from filter row to filter row and starting one, strides, few slices; the store at channel
 offsets, stacked first steps; and, beside each line of the rule, layers that stay with the streaming kernel."""
 import numpy as np
@@ -7,49 +7,27 @@ import pytest
 
 import oracle
 import workloads
+from bf16_rules import route, wide_fills
 from paper_1708_04728_amd import binding as B
 from util import case_seed, close, gpu, gpu_nhwc, host_nhwc
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
-CUS = 256
-TILES = [(5, 7), (4, 7), (7, 4), (6, 5), (3, 7), (6, 4), (4, 4), (2, 7), (2, 5), (4, 3)]
-
-
-def slices(C, R, S):
-    run = S * (C // 8)
-    spr, flat = -(-run // 8), -(-R * run // 8)
-    return flat if run >= 8 and flat < R * spr else R * spr
-
-
 def tile(case):
-    """The library's rule, restated: (TM, TN, rounds) of a tile of 32 TM filters x 32 TN pixels, None = not this kernel."""
-    N, C, H, W, K, R, S, stride, pad = case
-    ng = N * oracle.conv_out_size(H, R, stride, pad) * oracle.conv_out_size(W, S, stride, pad)
-    t64, n = -(-ng // 64) * -(-K // 64), slices(C, R, S)
-    if t64 <= CUS or K % 8 or K <= 32 or n < 3 or n > 128:
-        return None
-    best = None
-    for tm, tn in TILES:
-        bm, bn = 32 * tm, 32 * tn
-        gm, gn_ = -(-K // bm), -(-ng // bn)
-        gn = min(max(CUS // gm, 1), gn_)
-        rounds = -(-gn_ // gn) * -(-gn * gm // CUS)
-        us = rounds * (n * max(0.644 * bm * bn / 32768, 12.85 * (bm + bn) / 8192) + 0.54 + 1.2 * bm * bn / 10000)
-        if best is None or us < best[0] * (1 - 1e-6):
-            best = (us, (tm, tn, rounds))
-    tm, tn, rounds = best[1]
-    return None if rounds > 1 and n <= (3 if R * S > 1 else 4) else best[1]
+    """(TM, TN, rounds) where the layer by itself runs in wide tiles, or None."""
+    r = route(case)
+    return r[1:] if r[0] == "wide" else None
 
 
-def run(case, relu, off=0, extra=0, bias=True):
+def run(case, relu, off=0, extra=0, bias=True, images=None):
     N, C, H, W, K, R, S, stride, pad = case
     rng = np.random.default_rng(case_seed(case))
     x = workloads.round_to_bf16(rng.standard_normal((N, C, H, W)).astype(np.float32))
     w = workloads.round_to_bf16(rng.standard_normal((K, C, R, S)).astype(np.float32) * np.float32(np.sqrt(2.0 / (C * R * S))))
     b = (rng.standard_normal(K) * 0.1).astype(np.float32) if bias else None
-    ref = oracle.conv2d(x, w, b, stride, pad, relu)
+    pick = list(range(N)) if images is None else images
+    ref = oracle.conv2d(x[pick], w, b, stride, pad, relu)
     y = B.NHWC(torch.full((N, ref.shape[2], ref.shape[3], K + off + extra), -7.0, dtype=torch.bfloat16, device="cuda"))
     B.conv2d_fwd(gpu_nhwc(x, "bf16"), B.conv_desc(K, C, R, S, stride, pad, relu, B.DR_KRSC), B.pack_filters(gpu(w, "bf16")), gpu(b) if bias else None, y,
                  y_c_offset=off)
@@ -57,7 +35,8 @@ def run(case, relu, off=0, extra=0, bias=True):
     got = host_nhwc(y)
     assert (got[:, :off] == -7.0).all() and (got[:, off + K:] == -7.0).all()
     # one rounding of an fp32 sum: within one unit of the last place of the rounded exact result
-    assert close(got[:, off:off + K], oracle.round_bf16(ref), 2.0 ** -7, "within one bf16 unit of the oracle")
+    assert not np.isnan(got).any()
+    assert close(got[pick, off:off + K], oracle.round_bf16(ref), 2.0 ** -7, "within one bf16 unit of the oracle")
 
 
 @pytest.mark.parametrize("expected,case", [
@@ -82,6 +61,9 @@ def run(case, relu, off=0, extra=0, bias=True):
     ((2, 5, 1), (33, 136, 14, 14, 288, 3, 3, 1, 1)),              # 20 slices
     ((3, 7, 1), (60, 88, 21, 30, 96, 2, 3, 1, 1)),                # 9 slices
     ((3, 7, 1), (60, 24, 56, 29, 176, 4, 3, 2, 1)),               # 5 slices
+    ((2, 5, 1), (1500, 64, 5, 5, 40, 3, 3, 1, 1)),                # maps of 25 pixels: a step of 32 leaves the image
+    ((4, 7, 1), (4000, 40, 3, 4, 104, 3, 3, 1, 1)),               # 12: two images and 8 pixels on
+    ((2, 5, 1), (22000, 24, 3, 3, 40, 3, 3, 1, 0)),               # one pixel: 32 images on
 ])
 def test_wide(expected, case):
     assert tile(case) == expected, tile(case)
@@ -89,19 +71,68 @@ def test_wide(expected, case):
     run(case, relu=seed % 2 == 0, off=8 * (seed % 3), extra=8 * (seed % 2), bias=seed % 4 != 0)
 
 
-@pytest.mark.parametrize("case,off", [
-    ((1, 16, 90, 190, 68, 3, 3, 1, 1), 0),         # filters no multiple of 8
-    ((2, 24, 140, 120, 32, 3, 3, 1, 1), 0),        # 32 filters
-    ((4, 24, 96, 84, 72, 3, 3, 1, 1), 4),          # channel offset no multiple of 8
-    ((1, 128, 180, 190, 72, 1, 1, 1, 0), 0),       # two slices
-    ((5, 256, 160, 170, 80, 1, 1, 1, 0), 0),       # 1x1, four slices, more than one round
-    ((16, 8, 120, 130, 136, 3, 3, 2, 1), 0),       # three slices in more than one round
-    ((35, 1032, 14, 14, 176, 3, 3, 1, 1), 0),      # 146 slices: beyond the table
+@pytest.mark.parametrize("case,off,images", [
+    ((1, 16, 90, 190, 68, 3, 3, 1, 1), 0, None),            # filters no multiple of 8
+    ((2, 24, 140, 120, 32, 3, 3, 1, 1), 0, None),           # 32 filters
+    ((4, 24, 96, 84, 72, 3, 3, 1, 1), 4, None),             # channel offset no multiple of 8
+    ((1, 128, 180, 190, 72, 1, 1, 1, 0), 0, None),          # two slices
+    ((5, 256, 160, 170, 80, 1, 1, 1, 0), 0, [0, 4]),        # 1x1, four slices, more than one round
+    ((16, 8, 120, 130, 136, 3, 3, 2, 1), 0, None),          # three slices in more than one round
+    ((56, 1032, 14, 14, 176, 3, 3, 1, 1), 0, [0, 31, 55]),  # 146 slices: beyond the table
 ])
-def test_streaming_kernel_beside_the_lines(case, off):
+def test_streaming_kernel_beside_the_lines(case, off, images):
     """Layers just beyond the lines of the rule keep to the streaming kernel."""
-    assert off % 8 or tile(case) is None
-    run(case, relu=True, off=off)
+    assert route(case, off)[0] == "stream", route(case, off)
+    run(case, relu=True, off=off, images=images)
+
+
+def outputs(case, offs, batches):
+    """The layer's outputs in a batch of each size, written at each channel offset."""
+    N, C, H, W, K, R, S, stride, pad = case
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    x = torch.randn((max(batches), H, W, C), device="cuda", generator=gen).to(torch.bfloat16)
+    w = B.pack_filters((torch.randn((K, C, R, S), device="cuda", generator=gen) * (2.0 / (C * R * S)) ** 0.5).to(torch.bfloat16))
+    b = torch.randn(K, device="cuda", generator=gen) * 0.1
+    cd, out = B.conv_desc(K, C, R, S, stride, pad, True, B.DR_KRSC), []
+    for off, n in zip(offs, batches):
+        y = torch.full((n, oracle.conv_out_size(H, R, stride, pad), oracle.conv_out_size(W, S, stride, pad), K + off), float("nan"), dtype=torch.bfloat16, device="cuda")
+        B.conv2d_fwd(B.NHWC(x[:n]), cd, w, b, B.NHWC(y), y_c_offset=off)
+        out.append(y[..., off:])
+    torch.cuda.synchronize()
+    assert torch.isfinite(out[0].float()).all() and float(out[0].float().abs().max()) > 0
+    return out
+
+
+@pytest.mark.parametrize("case", [
+    (12, 64, 92, 90, 128, 3, 3, 2, 1),         # whole taps
+    (8, 24, 100, 100, 104, 3, 3, 1, 1),        # slices that run on from filter row to filter row
+    (6, 88, 56, 60, 200, 3, 3, 1, 1),          # every row starts one
+    (7, 328, 55, 57, 96, 1, 1, 1, 0),
+    (20, 40, 70, 66, 72, 5, 5, 2, 2),
+])
+def test_the_streaming_kernels_bits(case):
+    """The same layer at a channel offset of 8 (wide tiles) and of 4 (streaming kernel): the order of the sums is the same."""
+    assert route(case, 8)[0] == "wide" and route(case, 4)[0] == "stream", (route(case, 8), route(case, 4))
+    a, b = outputs(case, (8, 4), (case[0], case[0]))
+    assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("layer,wide,patch,kernel", [
+    # C, H, W, K, R, S, stride, pad; images with which it runs in wide tiles, and in a kernel with an input patch, on either side of a line
+    ((64, 28, 28, 192, 3, 3, 1, 1), 21, 20, "patch"),      # half a workgroup of the other kernel per compute unit
+    ((64, 28, 28, 192, 3, 3, 1, 1), 45, 46, "patch"),      # little more than one
+    ((64, 28, 28, 64, 3, 3, 1, 1), 73, 74, "patch"),
+    ((32, 28, 28, 128, 5, 5, 1, 2), 45, 46, "rows"),
+    ((48, 14, 15, 304, 3, 3, 1, 1), 39, 38, "rows"),
+    ((48, 14, 15, 304, 3, 3, 1, 1), 84, 85, "rows"),
+])
+def test_the_patch_kernels_bits(layer, wide, patch, kernel):
+    """The images of a batch have the same bits in wide tiles and in a kernel with an input patch, one image more or fewer."""
+    assert route((wide,) + layer)[0] == "wide" and wide_fills((wide,) + layer)
+    assert route((patch,) + layer)[0] == kernel and not wide_fills((patch,) + layer)
+    a, b = outputs((wide,) + layer, (0, 0), (wide, patch))
+    n = min(wide, patch)
+    assert torch.equal(a[:n], b[:n])
 
 
 def test_stacked_first_steps():

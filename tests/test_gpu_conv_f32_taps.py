@@ -1,6 +1,7 @@
 """GPU parity of the fp32 kernel for first layers (filters 7, 8 or 10 to 12 taps wide, no padding, KCRS) against the fp64 oracle: every
-overlap of the last group of taps, odd and even numbers of filter rows, one row, all filter block sizes, ragged filters and pixels,
-windows that end on the tensor's last element, a channel range of a wider tensor, long contractions on both sides of the rule."""
+overlap of the last group of taps, odd and even numbers of filter rows, one row, all filter block sizes (`filter_blocks` restates the
+launcher's choice), ragged filters and pixels, windows that end on the tensor's last element, a channel range of a wider tensor, long contractions
+on both sides of the rule."""
 import numpy as np
 import pytest
 
@@ -12,22 +13,47 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-@pytest.mark.parametrize("case", [
+def filter_blocks(case):
+    """Blocks of 32 filters per workgroup, 0 = the tiled kernel."""
+    N, C, H, W, K, R, S, stride = case
+    tiles = -(-N * oracle.conv_out_size(H, R, stride, 0) * oracle.conv_out_size(W, S, stride, 0) // 128)
+    if C * R > 64 and -(-K // 32) * tiles < 256:
+        return 0
+    tm = 1
+    for t in (2, 3):
+        if -(-K // (32 * t)) * t <= -(-K // (32 * tm)) * tm:
+            tm = t
+    return tm if -(-K // (32 * tm)) * tiles >= 128 else 1
+
+
+@pytest.mark.parametrize("blocks,case", [
     # N, C, H, W, K, R, S, stride
-    (3, 3, 43, 47, 96, 11, 11, 4),        # AlexNet's filter: 33 rows, the last without a partner
-    (140, 3, 35, 35, 96, 11, 11, 4),      # blocks of 96 filters: at least half a workgroup per compute unit
-    (30, 3, 67, 67, 100, 11, 11, 4),      # ragged: blocks of 64, 28 filters over
-    (60, 2, 27, 39, 33, 8, 8, 2),         # whole groups of taps; 16 rows; a block of one filter
-    (2, 1, 7, 7, 5, 7, 7, 1),             # one pixel, which ends on the tensor's last element
-    (5, 3, 21, 30, 64, 7, 7, 2),          # overlap of one
-    (4, 2, 15, 33, 40, 3, 10, 3),         # overlap of two, window rows apart
-    (1, 1, 1, 300, 24, 1, 12, 1),         # one filter row
-    (2, 4, 19, 25, 70, 5, 12, 1),         # four channels
-    (1, 20, 15, 15, 48, 7, 7, 1),         # 140 rows on 81 pixels: stays with the tiled kernel
-    (40, 20, 30, 30, 200, 7, 7, 1),       # 140 rows, 180 x 7 workgroups
+    (1, (3, 3, 43, 47, 96, 11, 11, 4)),        # AlexNet's filter: 33 rows, the last without a partner
+    (1, (140, 3, 35, 35, 96, 11, 11, 4)),      # 54 workgroups of 96 filters would be less than half a device
+    (3, (340, 3, 35, 35, 96, 11, 11, 4)),      # 131
+    (1, (30, 3, 67, 67, 100, 11, 11, 4)),      # ragged: blocks of 32, 28 filters over
+    (2, (40, 3, 67, 67, 100, 11, 11, 4)),      # blocks of 64, 28 over
+    (3, (75, 3, 67, 67, 70, 11, 11, 4)),       # blocks of 96, 26 over
+    (2, (50, 3, 48, 50, 64, 7, 7, 2)),         # blocks of 64 with each width
+    (2, (24, 2, 60, 59, 104, 5, 8, 2)),
+    (2, (50, 1, 62, 63, 50, 4, 10, 2)),
+    (2, (46, 2, 64, 61, 120, 3, 12, 3)),
+    (3, (42, 3, 49, 48, 96, 7, 7, 2)),         # blocks of 96
+    (3, (30, 2, 60, 59, 80, 5, 8, 2)),
+    (3, (50, 1, 62, 63, 81, 4, 10, 2)),
+    (3, (90, 2, 64, 61, 185, 3, 12, 3)),       # two, 89 filters in the second
+    (1, (60, 2, 27, 39, 33, 8, 8, 2)),         # whole groups of taps; 16 rows; a block of one filter
+    (1, (2, 1, 7, 7, 5, 7, 7, 1)),             # one pixel, which ends on the tensor's last element
+    (1, (5, 3, 21, 30, 64, 7, 7, 2)),          # overlap of one
+    (1, (4, 2, 15, 33, 40, 3, 10, 3)),         # overlap of two, window rows apart
+    (1, (1, 1, 1, 300, 24, 1, 12, 1)),         # one filter row
+    (1, (2, 4, 19, 25, 70, 5, 12, 1)),         # four channels
+    (0, (1, 20, 15, 15, 48, 7, 7, 1)),         # 140 rows on 81 pixels: stays with the tiled kernel
+    (1, (40, 20, 30, 30, 200, 7, 7, 1)),       # 140 rows, 180 x 7 workgroups
 ])
 @pytest.mark.parametrize("relu", [False, True])
-def test_conv_f32_taps(case, relu):
+def test_conv_f32_taps(blocks, case, relu):
+    assert filter_blocks(case) == blocks
     N, C, H, W, K, R, S, stride = case
     rng = np.random.default_rng(case_seed(case))
     x = rng.standard_normal((N, C, H, W)).astype(np.float32)
