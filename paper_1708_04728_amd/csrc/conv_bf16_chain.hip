@@ -14,7 +14,7 @@
 // twelve waves: no faster).  A round's pixels lie next to one another across the whole device: a run of pixels per workgroup or
 // per die took 7 % longer.
 // ResNet's conv2_x, three folded blocks on 56 x 56: 128 images 625 us as single layers, now 472; 30 images 163 and 122; one image 52 and 48.
-// What bounds it now: 4.1 TB/s on the bytes left, of about 5 that a copy reaches.
+// What bounds it now: HBM, at 3.7 to 4.0 TB/s on the bytes left (the three launches of that stage move 514, 462 and 360 MB), of about 5 that a copy reaches.
 // The sums run in the order of the streaming kernel and every tensor it would store is rounded where it would be: the same bits.
 #include "dr_internal.h"
 #include "dr_store.h"

@@ -1,6 +1,8 @@
-// bf16 convolution forward (Eq. (7): Y_j = (W * X)_j + B_j), the main kernel: channels-last (NHWC)
+// bf16 convolution forward (Eq. (7): Y_j = (W * X)_j + B_j), the streaming kernel: channels-last (NHWC)
 // activations, KRSC filters, fp32 accumulation on the gfx950 matrix cores, operands streamed from
-// global memory straight into LDS.
+// global memory straight into LDS.  It takes what conv_bf16_small.hip, conv_bf16_patch.hip, conv_bf16_rows.hip and conv_bf16_wide.hip
+// leave: larger layers of one or two slices, of at most 32 filters, with a residual, of filter counts or stores that 16 bytes
+// do not fit, and of more than 128 slices.
 //
 //   D[m][n] = sum_k A[m][k] * B[k][n]     m = output channel, n = (image, p, q), k = (r, s, c)
 //
@@ -720,7 +722,8 @@ int launch_cfg(DArgs a, hipStream_t st)
     return check_launch("conv_bf16");
 }
 
-// Tile choice, from sweeps over the ResNet / GoogLeNet layer shapes at batch 128.  The kernel is limited by
+// Tile choice, from sweeps over the ResNet / GoogLeNet layer shapes at batch 128, when all of them came here (the header says which
+// still do; the lines have not been drawn again for those).  The kernel is limited by
 // instruction issue and by how fast a compute unit's vector memory path feeds LDS, not by the matrix
 // cores: two workgroups of 64, 96 or 128 filters x 128 pixels per compute unit beat one large tile.  Among
 // them, the cost of a tile grows with its filter count (measured: about 0.44 + filters / 32) and the
@@ -738,7 +741,7 @@ int launch_auto(DArgs a, hipStream_t st)
     const int K = a.g.K, Ng = a.g.Ng;
     // a layer whose 64 x 64 tiles all fit the device at two workgroups per compute unit: twice the
     // workgroups of the 128-pixel tiles and a ring of four stages, for layers that would leave compute
-    // units idle (the 7 x 7 maps, the narrow reducers of the 14 x 14 maps); also taken for K <= 32,
+    // units idle (1x1 layers of two slices or 32 filters: those of several taps are small layers); also taken for K <= 32,
     // where padding the filter block to 64 costs less than one more kernel variant between the others
     // (not while other streams of the same caller keep the device busy: measured slower there)
     if (!t_shared_device && ((K + 63) / 64) * ((Ng + 63) / 64) <= 2 * device_cus()) return launch_cfg<1, 1, 2, 2, 4, 2>(a, st);   // 64 x 64 tiles
@@ -749,7 +752,7 @@ int launch_auto(DArgs a, hipStream_t st)
     }
     // several taps and 97..128 filters on enough pixels for one round of 256-pixel tiles: one workgroup holds all filters of
     // its pixels (128 x 64 per wave, half-depth slices so that three stages fit), so every pixel row is fetched once per tap
-    // instead of twice (GoogLeNet 3a's 3x3 96 -> 128 on 28 x 28: 41 -> 34 us against 64 x 128 and 128 x 128 tiles)
+    // instead of twice (GoogLeNet 3a's 3x3 96 -> 128 on 28 x 28, which has since gone to wide tiles: 41 -> 34 us against 64 x 128 and 128 x 128 tiles)
     if (a.g.R * a.g.S > 1 && K > 96 && K <= 128 && (Ng + 255) / 256 >= device_cus() && (Ng + 255) / 256 <= 2 * device_cus())
         return launch_cfg<4, 2, 1, 4, 3, 2, 32>(a, st);                          // 128 x 256 tiles
     const float c64 = tile_rounds(K, Ng, 64, 128) * (0.44f + 2.f), c96 = tile_rounds(K, Ng, 96, 128) * (0.44f + 3.f);

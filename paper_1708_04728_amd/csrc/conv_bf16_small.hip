@@ -13,18 +13,19 @@
 //     contraction among the waves adds the products in another order: a few outputs in ten thousand round the other way, and 25
 //     layers later the class probabilities of GoogLeNet differ by 1 to 3 %.)
 //   * where a chunk of the contraction lies is worked out once, by the multiplying waves while the loading waves decode their pixels: a
-//     table in LDS, chunk -> {offset, tap}.  A load then costs its wave half a dozen instructions.  Decoding chunk by chunk in every
+//     table in LDS, chunk -> {offset, mask}.  A load then costs its wave half a dozen instructions.  Decoding chunk by chunk in every
 //     loading wave was what bounded the kernel before: with every load and every multiplication taken out the slice still took
-//     0.16 of its 0.2 us;
+//     0.16 of its 0.2 us.  The loading waves are still on the path of every stage: an instruction or a branch more between the barrier
+//     and the loads shows (two more: 2 to 7 %), so the addresses are worked out before it;
 //   * two groups of loading waves send a slice each of a stage;
 //   * one launch takes several layers (the second steps of an inception module, say): a launch costs 3 to 4 us on a
 //     stream whatever it does, as much as the layer itself.  A job may also be a 3x3 max-pooling layer, which a
 //     module's pooling branch needs beside the other branches' first steps.
 // Measured in chains of dependent launches of one layer (3.1 us of which are the launch), one wave per 32 x 32 block and four loading waves that
-// decode -> this form: 3x3 160 -> 320 on one 14 x 14 image 8.5 -> 5.9 us, 5x5 32 -> 512 6.2 -> 4.9, 1x1 832 -> 624 on 7 x 7 5.4 -> 4.8,
-// 3x3 96 -> 128 on 28 x 28 x 8 (64 x 64 tiles, one per compute unit) 8.2 -> 6.7, 3x3 144 -> 288 on 14 x 14 x 19 (two per compute unit)
-// 12.8 -> 10.8; the slim GoogLeNet on one image 147 -> 121 us.
-// What bounds it now: 0.11 us per slice for tiles of 32 x 32 and, at two tiles of 64 x 64 per compute unit, the path from L2 into LDS (32 loads
+// decode -> the table and two loading groups -> addresses ready before the barrier: 3x3 160 -> 320 on one 14 x 14 image 8.5 -> 5.7 -> 5.4 us,
+// 5x5 32 -> 512 6.2 -> 4.6 -> 4.4, 1x1 832 -> 624 on 7 x 7 5.4 -> 4.4 -> 3.9, 3x3 96 -> 128 on 28 x 28 x 8 (64 x 64 tiles, one per compute unit) 8.2 -> 6.8 -> 6.6;
+// the slim GoogLeNet on one image 151 -> 128 -> 124 us.
+// What bounds it now: 0.10 us per slice for tiles of 32 x 32 and, at two tiles of 64 x 64 per compute unit, the path from L2 into LDS (32 loads
 // of 1 KiB per pair of slices, about 24 cycles each).
 //
 // Operands travel as in the streaming kernel: 16-byte buffer loads that write LDS, lanes outside the tensor or in the padding at
@@ -48,7 +49,7 @@ struct SmallJob {
     const uint16_t* res;
     uint16_t* y_seg[4];                                  // destinations of the filter ranges (see ConvSplit), y_seg[0] alone otherwise
     int ctot_seg[4], split_end[3];
-    int nsplit, res_ctot;
+    int res_ctot;
     int C, H, W, K, R, S, sh, sw, ph, pw, P, Q, Kg, Ng, relu;
     int x_bytes, w_bytes;
     int stem_hp, stem_wp;                                // padded 4-channel input copy (see launch_conv_bf16_stem), 0: ordinary input
@@ -375,19 +376,18 @@ SmallJob small_job(const ConvSmall& c, int bm, int bn, int nth)
     j.magic_row = (unsigned)((0x100000000ull + j.row_chunks - 1) / j.row_chunks);
     j.n_tiles = (g.Ng + bn - 1) / bn;
     j.tiles = j.n_tiles * ((g.K + bm - 1) / bm);
-    j.nsplit = c.split && c.split->n > 1 ? c.split->n : 0;
     j.vec = g.K % 8 == 0 && aligned16(c.bias) && (!c.res || (g.res_ctot % 8 == 0 && aligned16(c.res)));
     auto dest = [&](int d, uint16_t* y, int ctot, int coff, int start) {
         j.y_seg[d] = y + coff - start;
         j.ctot_seg[d] = ctot;
         j.vec = j.vec && ctot % 8 == 0 && coff % 8 == 0 && aligned16(y);
     };
-    if (j.nsplit) {
+    if (c.split && c.split->n > 1) {
         int start = 0;
-        for (int d = 0; d < j.nsplit; ++d) {
+        for (int d = 0; d < c.split->n; ++d) {
             dest(d, (uint16_t*)c.split->dst[d].y, c.split->dst[d].ctot, c.split->dst[d].c_offset, start);
             start += c.split->dst[d].k;
-            if (d + 1 < j.nsplit) j.split_end[d] = start;
+            if (d + 1 < c.split->n) j.split_end[d] = start;
         }
     } else {
         dest(0, (uint16_t*)c.y, g.y_ctot, g.y_coff, 0);
@@ -407,8 +407,10 @@ static long small_tiles(const ConvSmall* jobs, int n, int bm, int bn)
 }
 
 // As long as the layer's 64 x 64 tiles fit the device at two workgroups per compute unit, 1x1 filters at one (their contraction is
-// short and the larger tiles then win: 480 -> 304 on 14 x 14 x 19, 295 tiles, 7.7 against 8.5 us; 3x3 144 -> 288, 295 tiles too,
-// 13.6 against 13.5).  Channels: as many as a tap is found exactly for by a multiplication (the kernel's LONG).
+// short).  Between one tile per compute unit and two, this kernel and the streaming one: 3x3 80 -> 24 on 24 x 26 x 29 6.9 and 8.7 us, 5x5 136 -> 24 on
+// 25 x 26 x 37 19.6 and 27.5, 3x3 64 -> 84 on 23 x 25 x 24 10.3 and 10.7, with three slices up to a fifth the other way (3x3 16 -> 20 on 35 x 37 x 58 at
+// stride 2 6.8 and 5.5); 1x1 96 -> 22 on 96 x 97 x 2 6.1 and 4.7, 280 -> 21 on 83 x 86 x 3 7.2 and 5.8.  Beyond two: 3x3 64 -> 23 on 34 x 36 x 29
+// 13.2 and 8.9, 3x3 104 -> 26 on 29 x 30 x 42 16.6 and 12.6.  Channels: as many as a tap is found exactly for by a multiplication (the kernel's LONG).
 bool conv_bf16_small_takes(const ConvGeom& g, const void* x, const void* w)
 {
     const long tiles = ((long)g.Ng + 63) / 64 * ((g.K + 63) / 64);
@@ -432,9 +434,9 @@ static int launch_group(const ConvSmall* jobs, int n, hipStream_t st)
 }
 
 // The smallest tile that leaves every compute unit at most one.  Stages of two slices, three in flight; eight loading waves.  Sixteen waves of
-// 16 x 16 and 32 x 16 for the larger tiles (64 x 32: GoogLeNet, fused, on 19 images 344 us with blocks of 32 x 16, 339 with 16 x 16).  Two 64 x 64
-// tiles to a compute unit: four waves of 32 x 32 and four loading ones, three stages of one slice (24 -> 88 5x5 on 31 x 45 x 9 7.8 us; eight
-// waves of 32 x 16 8.3; stages of two slices, two in flight 10.6: too few loads on their way).
+// 16 x 16 and 32 x 16 for the larger tiles (64 x 32: blocks of 32 x 16 were no faster).  Two 64 x 64 tiles to a compute unit -- layers that share the
+// launch, and by themselves those that wide tiles do not take: four waves of 32 x 32 and four loading ones, three stages of one slice
+// (24 -> 88 5x5 on 31 x 45 x 9, when it came here by itself, 7.8 us; eight waves of 32 x 16 8.3; stages of two slices, two in flight 10.6: too few loads on their way).
 int launch_conv_bf16_small(const ConvSmall* jobs, int n, hipStream_t st)
 {
     if (small_tiles(jobs, n, 32, 32) <= device_cus()) return launch_group<1, 1, 2, 2, 2>(jobs, n, st);

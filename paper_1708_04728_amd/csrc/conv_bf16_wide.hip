@@ -17,8 +17,10 @@
 // What bounds it: the matrix cores at the clock that they reach on varying operands -- 0.70 us per slice of 160 x 224 on 224 compute
 // units, 1.6 GHz -- and what a tile costs beside them: about 7 us for a layer of one round (a cold start, the store of the whole output at once),
 // 3 us for each further round.  Measured, streaming kernel -> this one, batch 128: 3x3 144 -> 288 on 14 x 14 38.4 -> 24.6 us, 160 -> 320 39.8 -> 26.4,
-// 128 -> 256 22.6 -> 18.3, 128 -> 192 on 28 x 28 57 -> 50, 192 -> 384 on 7 x 7 18.8 -> 13.1, 1x1 480 -> 304 on 14 x 14 21.3 -> 15.7; over 60 layers
-// of GoogLeNet and of sizes drawn at random 0.84 of the time.  GoogLeNet at batch 128: slim 722 -> 637 us, original 1584 -> 1499.
+// 128 -> 256 22.6 -> 18.3, 128 -> 192 on 28 x 28 57 -> 50, 192 -> 384 on 7 x 7 18.8 -> 13.1, 1x1 480 -> 304 on 14 x 14 21.3 -> 15.7; over 80 layers
+// of GoogLeNet and of sizes drawn at random 0.82 of the time, 1.02 at worst.  GoogLeNet at batch 128: slim 722 -> 637 us, original 1584 -> 1499.
+// It also runs beside other streams, where the streaming kernel keeps its larger tiles (SharedDeviceScope): the original GoogLeNet with its branches
+// on streams 1521 us, 1611 with the wide tiles left out there.
 #include <algorithm>
 #include <utility>
 
@@ -41,7 +43,7 @@ struct WideArgs {
     const uint16_t* w;
     const float* bias;
     uint16_t* y_seg[4];                                  // destinations of the filter ranges (see ConvSplit), y_seg[0] alone otherwise
-    int ctot_seg[4], split_end[3], nsplit;
+    int ctot_seg[4], split_end[3];
     int C, H, W, K, R, S, sh, sw, ph, pw, P, Q, Kg, Ng, relu;
     int x_bytes, w_bytes, pointwise;
     int c8, run_chunks, row_chunks, slices;              // see conv_bf16_small.hip
@@ -261,8 +263,9 @@ int launch_tile(WideArgs a, hipStream_t st)
     return check_launch("conv_bf16_wide");
 }
 
-// The tile with the shortest time by a model fitted to 14 tiles x 60 layers (10 % off on average; the tile it picks takes 1.01 times as long
-// as the best one): a slice takes its matrix work or its loads, whichever is longer, a tile 0.54 us and its store besides.
+// The tile with the shortest time by a model: a slice takes its matrix work or its loads, whichever is longer, a tile 0.54 us and its store
+// besides.  Fitted to 14 tiles on 60 layers; over these 10 tiles on 80 layers the time is the model's + 1.9 us, 6 % off on average, and
+// the tile that it picks takes 1.01 times as long as the best one on average, 1.25 at worst (3x3 512 -> 40 on 43 x 40 x 103: 64 x 160 209 us, 128 x 128 167).
 struct WideTile { int m, n, rounds; float us; };
 const int WIDE_TILES[][2] = {{5, 7}, {4, 7}, {7, 4}, {6, 5}, {3, 7}, {6, 4}, {4, 4}, {2, 7}, {2, 5}, {4, 3}};
 

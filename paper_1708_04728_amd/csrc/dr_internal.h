@@ -77,7 +77,8 @@ int launch_conv_f32_small(const ConvSmall* jobs, int n, hipStream_t st);
 bool conv_f32_group_takes(const ConvGeom& g);
 int launch_conv_f32_group(const ConvSmall* jobs, int n, hipStream_t st);
 
-// conv_bf16_dma.hip: the main bf16 kernel (NHWC, KRSC filters, C % 8 == 0, 16-byte aligned tensors)
+// conv_bf16_dma.hip: the streaming bf16 kernel (NHWC, KRSC filters, C % 8 == 0, 16-byte aligned tensors); the kernels for small layers, patches and
+// wide tiles take the same layers or some of them
 bool conv_bf16_dma_eligible(const ConvGeom& g, const void* x, const void* w);
 // Destinations of a stacked convolution (Eq. (12)): the first k filters write channels [c_offset, c_offset + k)
 // of tensor y (ctot channels per pixel), the next destination takes the following filters, and so on.
