@@ -359,7 +359,6 @@ SmallJob small_job(const ConvSmall& c, int bm, int bn, int nth)
     j.c8 = g.C / 8;
     j.m_pq = ((1ull << 40) + (unsigned)(g.P * g.Q) - 1) / (unsigned)(g.P * g.Q);
     j.m_q = ((1ull << 40) + (unsigned)g.Q - 1) / (unsigned)g.Q;
-    for (int d = 0; d < 3; ++d) j.split_end[d] = 0x7FFFFFFF;
     if (!c.w) {                                          // max-pooling
         j.y_seg[0] = (uint16_t*)c.y;
         j.tiles = (g.Ng * j.c8 + nth - 1) / nth;
@@ -377,20 +376,11 @@ SmallJob small_job(const ConvSmall& c, int bm, int bn, int nth)
     j.n_tiles = (g.Ng + bn - 1) / bn;
     j.tiles = j.n_tiles * ((g.K + bm - 1) / bm);
     j.vec = g.K % 8 == 0 && aligned16(c.bias) && (!c.res || (g.res_ctot % 8 == 0 && aligned16(c.res)));
-    auto dest = [&](int d, uint16_t* y, int ctot, int coff, int start) {
-        j.y_seg[d] = y + coff - start;
-        j.ctot_seg[d] = ctot;
-        j.vec = j.vec && ctot % 8 == 0 && coff % 8 == 0 && aligned16(y);
-    };
+    set_destinations(j, c.split, (uint16_t*)c.y, g.y_ctot, g.y_coff);
     if (c.split && c.split->n > 1) {
-        int start = 0;
-        for (int d = 0; d < c.split->n; ++d) {
-            dest(d, (uint16_t*)c.split->dst[d].y, c.split->dst[d].ctot, c.split->dst[d].c_offset, start);
-            start += c.split->dst[d].k;
-            if (d + 1 < c.split->n) j.split_end[d] = start;
-        }
+        for (int d = 0; d < c.split->n; ++d) j.vec = j.vec && c.split->dst[d].ctot % 8 == 0 && c.split->dst[d].c_offset % 8 == 0 && aligned16(c.split->dst[d].y);
     } else {
-        dest(0, (uint16_t*)c.y, g.y_ctot, g.y_coff, 0);
+        j.vec = j.vec && g.y_ctot % 8 == 0 && g.y_coff % 8 == 0 && aligned16(c.y);
     }
     return j;
 }

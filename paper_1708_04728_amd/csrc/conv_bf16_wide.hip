@@ -336,19 +336,7 @@ int launch_conv_bf16_wide(const ConvGeom& g, const uint16_t* x, const uint16_t* 
     a.step_img = 32 / (g.P * g.Q);
     a.step_p = 32 % (g.P * g.Q) / g.Q;
     a.step_q = 32 % g.Q;
-    for (int d = 0; d < 3; ++d) a.split_end[d] = 0x7FFFFFFF;
-    if (split && split->n > 1) {
-        int start = 0;
-        for (int d = 0; d < split->n; ++d) {
-            a.y_seg[d] = (uint16_t*)split->dst[d].y + split->dst[d].c_offset - start;
-            a.ctot_seg[d] = split->dst[d].ctot;
-            start += split->dst[d].k;
-            if (d + 1 < split->n) a.split_end[d] = start;
-        }
-    } else {
-        a.y_seg[0] = y + g.y_coff;
-        a.ctot_seg[0] = g.y_ctot;
-    }
+    set_destinations(a, split, y, g.y_ctot, g.y_coff);
     const WideTile t = wide_tile(g.K, g.Ng, a.slices);
     switch (t.m * 10 + t.n) {
     case 57: return launch_tile<5, 7>(a, st);

@@ -86,6 +86,22 @@ bool conv_bf16_dma_eligible(const ConvGeom& g, const void* x, const void* w);
 // n <= 1: the ordinary single destination (y, g.y_ctot, g.y_coff).
 struct ConvDest { void* y; int ctot, c_offset, k; };
 struct ConvSplit { int n; ConvDest dst[4]; };
+// The destinations as the bf16 kernels take them: filter m < split_end[0] goes to y_seg[0], m < split_end[1] to y_seg[1], ... at [pixel * ctot_seg[d] + m]
+// (the host has taken a range's first filter off y_seg); ends beyond the last are INT_MAX.
+template <class A>
+void set_destinations(A& a, const ConvSplit* split, uint16_t* y, int y_ctot, int y_coff)
+{
+    for (int d = 0; d < 3; ++d) a.split_end[d] = 0x7FFFFFFF;
+    a.y_seg[0] = y + y_coff;
+    a.ctot_seg[0] = y_ctot;
+    int start = 0;
+    for (int d = 0; split && split->n > 1 && d < split->n; ++d) {
+        a.y_seg[d] = (uint16_t*)split->dst[d].y + split->dst[d].c_offset - start;
+        a.ctot_seg[d] = split->dst[d].ctot;
+        start += split->dst[d].k;
+        if (d + 1 < split->n) a.split_end[d] = start;
+    }
+}
 int launch_conv_bf16_dma(const ConvGeom& g, const uint16_t* x, const uint16_t* w, const float* bias,
                          const uint16_t* residual, uint16_t* y, hipStream_t st, const ConvSplit* split = nullptr);
 
