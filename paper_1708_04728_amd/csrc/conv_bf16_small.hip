@@ -223,6 +223,7 @@ __global__ __launch_bounds__((WM * WN + 4 * LG) * 64) void conv_bf16_small_kerne
                 if (WAY != TABLE) e = entry();
                 ld_slot = ld_slot + LG == NS * G + lg ? lg : ld_slot + LG;
             }
+            if (WAY == TABLE) { wait_lgkm<0>(); touch(e); }      // (the registers of the entry read ahead stay its own until it has arrived)
         };
         if (j.pointwise) send(IC<POINTWISE>{});
         else if (j.tabled) send(IC<TABLE>{});
