@@ -13,8 +13,12 @@
 // ones are multiplied: 20 KB per wave in flight, eight waves per compute unit (one workgroup: the filters take up to 96 KB; ten or
 // twelve waves: no faster).  A round's pixels lie next to one another across the whole device: a run of pixels per workgroup or
 // per die took 7 % longer.
-// ResNet's conv2_x, three folded blocks on 56 x 56: 128 images 625 us as single layers, now 472; 30 images 163 and 122; one image 52 and 48.
-// What bounds it now: HBM, at 3.7 to 4.0 TB/s on the bytes left (the three launches of that stage move 514, 462 and 360 MB), of about 5 that a copy reaches.
+// What a lane holds of a tensor is 16 bytes of a pixel, half a line's quarter: an instruction that moves them as they are touches 32 lines for 1 KB,
+// and the address path then takes longer than memory.  Where there are enough blocks to hide it every piece goes through LDS and an
+// instruction moves eight whole lines: with the residual, 128 images of 56 x 56, 139 -> 101 us (117 -> 90 without a next layer); addresses that run on
+// without a gap (in a working copy) 98 and 86.
+// ResNet's conv2_x, three folded blocks on 56 x 56: 128 images 625 us as single layers, 392 in chains; 30 images 163 and 114; one image 52 and 42.
+// What bounds it now: HBM, at 5.1 TB/s on the bytes left (514, 462 and 360 MB in the three launches of that stage), as much as a copy reaches.
 // The sums run in the order of the streaming kernel and every tensor it would store is rounded where it would be: the same bits.
 #include "dr_internal.h"
 #include "dr_store.h"
@@ -24,6 +28,7 @@ namespace dr {
 namespace {
 
 constexpr int CHAIN_WAVES = 8, CHAIN_KS = CHAIN_MID / 16, CHAIN_OB = CHAIN_OUT / 32, CHAIN_FRAGS = CHAIN_OB * CHAIN_KS;
+constexpr int PART = 32 * 8;      // 16-byte chunks of 64 channels of 32 pixels: what moves between memory and LDS at a time
 
 struct ChainArgs {
     ConvChain c;
@@ -77,11 +82,13 @@ __device__ __forceinline__ u32x4 pack8(const float (&o)[8])
     return pk;
 }
 
-// PROJ: the shortcut is Wp x; NEXT: m' is computed
-template <bool PROJ, bool NEXT>
+// PROJ: the shortcut is Wp x; NEXT: m' is computed; LINES: memory is read and written by whole lines, through LDS
+template <bool PROJ, bool NEXT, bool LINES>
 __global__ __launch_bounds__(CHAIN_WAVES * 64) void conv_bf16_chain_kernel(const ChainArgs a)
 {
     __shared__ u32x4 frag[(1 + PROJ + NEXT) * CHAIN_FRAGS * 64];
+    __shared__ u32x4 stage_out[LINES ? CHAIN_WAVES * PART : 1], stage_res[LINES && !PROJ ? CHAIN_WAVES * PART : 1];
+    u32x4* const stage_in = PROJ ? stage_out : stage_res;
     __shared__ __attribute__((aligned(16))) float bias[2 * CHAIN_OUT + CHAIN_MID];
     const ConvChain& c = a.c;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5, l32 = lane & 31;
@@ -113,41 +120,72 @@ __global__ __launch_bounds__(CHAIN_WAVES * 64) void conv_bf16_chain_kernel(const
     const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void*)c.y, 0, a.y_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rn = __builtin_amdgcn_make_buffer_rsrc((void*)c.m_next, 0, a.next_bytes, 0x00020000);
     const int blocks = (c.pixels + 31) >> 5, stride = (int)gridDim.x * CHAIN_WAVES;
-    // channels ch .. ch + 7 of pixel n of a tensor of C channels; outside it (also: no pixel) an offset the hardware answers with zeros
-    auto at = [&](int n, int C, int ch) __attribute__((always_inline)) { return n < c.pixels && ch < C ? (n * C + ch) * 2 : OOB; };
+    // The matrix instructions want chunk 2 q + half (8 channels) of pixel l & 31 of 64 channels.  LINES: a lane moves chunk l & 7 of pixel l >> 3 of
+    // each eight instead, and `stage`, the wave's own, turns one into the other; chunk c of pixel p lies at c ^ (p & 7).
+    const int line = wave * PART + (lane & 56) + ((lane & 7) ^ (lane >> 3)), op = wave * PART + l32 * 8, sw = l32 & 7;
+    auto at = [&](int blk, int j, int C, int ch) __attribute__((always_inline)) {      // zeros are read, nothing written outside the tensor
+        const int n = blk * 32 + (LINES ? j * 8 + (lane >> 3) : l32), c0 = ch + (LINES ? lane & 7 : 2 * j + half) * 8;
+        return n < c.pixels && c0 < C ? (n * C + c0) * 2 : OOB;
+    };
+    auto fetch = [&](u32x4* v, __amdgpu_buffer_rsrc_t r, int blk, int C, int ch) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = load16(r, at(blk, j, C, ch));
+    };
+    auto to_operands = [&](const u32x4* v, u32x4* o) __attribute__((always_inline)) {
+        if constexpr (LINES) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) stage_in[line + j * 64] = v[j];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) o[q] = stage_in[op + ((2 * q + half) ^ sw)];
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) o[q] = v[q];
+        }
+    };
+    auto store = [&](const u32x4* o, __amdgpu_buffer_rsrc_t r, int blk, int C, int ch) __attribute__((always_inline)) {
+        if constexpr (LINES) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) stage_out[op + ((2 * q + half) ^ sw)] = o[q];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) store16(LINES ? stage_out[line + j * 64] : o[j], r, at(blk, j, C, ch));
+    };
 
-    u32x4 vm[CHAIN_KS], vx[PROJ ? CHAIN_KS : 1], res[PROJ ? 1 : 2 * CHAIN_OB];
+    u32x4 mem_m[CHAIN_KS], mem_x[PROJ ? CHAIN_KS : 1], res[PROJ ? 1 : 2 * CHAIN_OB];      // as fetched
     int blk = (int)blockIdx.x + wave * (int)gridDim.x;
-    {
-        const int n = blk * 32 + l32;
+    fetch(mem_m, rm, blk, c.mid, 0);
+    if constexpr (PROJ) {
+        fetch(mem_x, rx, blk, c.c_in, 0);
+    } else {
 #pragma unroll
-        for (int ks = 0; ks < CHAIN_KS; ++ks) {
-            vm[ks] = load16(rm, at(n, c.mid, ks * 16 + half * 8));
-            if constexpr (PROJ) vx[ks] = load16(rx, at(n, c.c_in, ks * 16 + half * 8));
-        }
-        if constexpr (!PROJ) {
-#pragma unroll
-            for (int q = 0; q < 2 * CHAIN_OB; ++q) res[q] = load16(rx, at(n, c.out, q * 16 + half * 8));
-        }
+        for (int p = 0; p < CHAIN_OB / 2; ++p) fetch(res + 4 * p, rx, blk, c.out, 64 * p);
     }
     for (; blk < blocks; blk += stride) {
-        const int n = blk * 32 + l32, nn = n + stride * 32;          // this lane's pixel now and in the next round
-        u32x4 vm_n[CHAIN_KS], vx_n[PROJ ? CHAIN_KS : 1];
-#pragma unroll
-        for (int ks = 0; ks < CHAIN_KS; ++ks) {
-            vm_n[ks] = load16(rm, at(nn, c.mid, ks * 16 + half * 8));
-            if constexpr (PROJ) vx_n[ks] = load16(rx, at(nn, c.c_in, ks * 16 + half * 8));
+        u32x4 vm[CHAIN_KS], vx[PROJ ? CHAIN_KS : 1];
+        to_operands(mem_m, vm);
+        fetch(mem_m, rm, blk + stride, c.mid, 0);
+        if constexpr (PROJ) {
+            to_operands(mem_x, vx);
+            fetch(mem_x, rx, blk + stride, c.c_in, 0);
         }
         // (the filters and biases read below are the same in every round: without this the compiler would fetch all of them ahead
         // of the loop, into registers it does not have)
         int fl = lane, bl = half * 8;
         asm volatile("" : "+v"(fl), "+v"(bl));
-        u32x4 out[4];
+        u32x4 out[4], sc[2][4];
+        auto next_res = [&](int p) __attribute__((always_inline)) {
+            to_operands(res + 4 * p, sc[p & 1]);
+            fetch(res + 4 * p, rx, blk + stride, c.out, p * 64);
+        };
         f32x16 sum_next[2];
 #pragma unroll
         for (int v = 0; v < 16; ++v) sum_next[0][v] = sum_next[1][v] = 0.f;
 #pragma unroll
         for (int i = 0; i < CHAIN_OB; ++i) {
+            if constexpr (!PROJ) {
+                if (i == 0) next_res(0);
+                if (!(i & 1) && i + 2 < CHAIN_OB) next_res(i / 2 + 1);
+            }
             f32x16 acc, accp;
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[v] = accp[v] = 0.f;
@@ -158,7 +196,6 @@ __global__ __launch_bounds__(CHAIN_WAVES * 64) void conv_bf16_chain_kernel(const
             }
 #pragma unroll
             for (int qp = 0; qp < 2; ++qp) {
-                const int ch = i * 32 + qp * 16 + half * 8;
                 float o[8];
                 exchange(acc, qp, o);
                 add_bias(bias + i * 32 + qp * 16 + bl, o);
@@ -169,7 +206,7 @@ __global__ __launch_bounds__(CHAIN_WAVES * 64) void conv_bf16_chain_kernel(const
                     add_bias(bias + CHAIN_OUT + i * 32 + qp * 16 + bl, op);
                     s = pack8(op);
                 } else {
-                    s = res[2 * i + qp];
+                    s = sc[i >> 1 & 1][(i & 1) * 2 + qp];
                 }
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -184,44 +221,35 @@ __global__ __launch_bounds__(CHAIN_WAVES * 64) void conv_bf16_chain_kernel(const
                     for (int mb = 0; mb < 2; ++mb) sum_next[mb] = mfma(f_next[(mb * 2 * CHAIN_OB + 2 * i + qp) * 64 + fl], pk, sum_next[mb]);
                 }
             }
-            // residuals and outputs move 128 bytes of a pixel at a time: a line's four pieces asked for apart are fetched apart, the vector
-            // cache holds a quarter of what the waves have in flight (128 images of 56 x 56: 520 against 472 us for the three blocks;
-            // 256 bytes at a time: the same)
-            if (i & 1) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) store16(out[q], ry, at(n, c.out, (i - 1) * 32 + q * 16 + half * 8));
-                if constexpr (!PROJ) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) res[2 * i - 2 + q] = load16(rx, at(nn, c.out, (i - 1) * 32 + q * 16 + half * 8));
-                }
-            }
+            if (i & 1) store(out, ry, blk, c.out, (i - 1) * 32);
         }
         if constexpr (NEXT) {
 #pragma unroll
             for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
                 for (int qp = 0; qp < 2; ++qp) {
-                    const int ch = mb * 32 + qp * 16 + half * 8;
                     float o[8];
                     exchange(sum_next[mb], qp, o);
                     add_bias(bias + 2 * CHAIN_OUT + mb * 32 + qp * 16 + bl, o);
                     relu8(o);
-                    store16(pack8(o), rn, at(n, c.next, ch));
+                    out[2 * mb + qp] = pack8(o);
                 }
-        }
-#pragma unroll
-        for (int ks = 0; ks < CHAIN_KS; ++ks) {
-            vm[ks] = vm_n[ks];
-            if constexpr (PROJ) vx[ks] = vx_n[ks];
+            store(out, rn, blk, c.next, 0);
         }
     }
 }
 
+// Lines from 1024 blocks of 32 pixels on, half of what the waves hold at a time: 16 images of 56 x 56 (1568) 93.2 us without, 90.9 with, eight (784)
+// 69.7 and 69.7.  With fewer a wave has one block and the way through LDS only adds to its latency: four images 52.1 and 52.7, one 41.9 and 43.2.
 template <bool PROJ, bool NEXT>
 int launch_chain(const ChainArgs& a, hipStream_t st)
 {
     const int blocks = (a.c.pixels + 31) / 32, cus = device_cus();
-    hipLaunchKernelGGL((conv_bf16_chain_kernel<PROJ, NEXT>), dim3((unsigned)(blocks < cus ? blocks : cus)), dim3(CHAIN_WAVES * 64), 0, st, a);
+    const dim3 grid((unsigned)(blocks < cus ? blocks : cus)), block(CHAIN_WAVES * 64);
+    if (blocks >= 4 * cus)
+        hipLaunchKernelGGL((conv_bf16_chain_kernel<PROJ, NEXT, true>), grid, block, 0, st, a);
+    else
+        hipLaunchKernelGGL((conv_bf16_chain_kernel<PROJ, NEXT, false>), grid, block, 0, st, a);
     return check_launch("conv_bf16_chain");
 }
 

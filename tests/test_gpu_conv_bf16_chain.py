@@ -40,7 +40,10 @@ def stage(rng, c, blocks):
     (2, 24, 5, 3, ((40, 72), (40, 72))),                       # ragged steps, 30 pixels
     (3, 56, 17, 19, ((48, 200), (32, 200), (32, 248))),        # a narrower block behind, then a projected one on too many channels
     (1, 64, 9, 9, ((32, 128), (64, 128), (64, 264))),          # a wider block behind (not joined), an output too wide for the kernel
-    (9, 64, 61, 59, ((64, 256), (64, 256))),                   # several rounds of every wave, the last one not whole
+    (9, 64, 61, 59, ((64, 256), (64, 256))),                   # 1013 blocks: the most that move as the lanes hold them
+    (11, 64, 61, 59, ((64, 256), (64, 256), (64, 256))),       # 1238 blocks, the last one not whole: by lines, through LDS
+    (10, 24, 55, 61, ((40, 72), (24, 72), (24, 200), (8, 200))),        # ... with ragged channel groups
+    (23, 56, 61, 59, ((64, 248), (64, 248))),                  # ... several rounds of every wave
 ])
 def test_chain(case):
     n, c, h, w, blocks = case
