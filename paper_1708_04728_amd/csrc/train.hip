@@ -130,9 +130,12 @@ __device__ __forceinline__ void lds_barrier()
 // 16 matrix instructions of a slice is kept to a couple of instructions per loaded element: a thread's eight columns
 // belong to TPT taps, so the padding test is made TPT times per slice (with columns in (c, r, s) order it was made for every
 // element and that arithmetic took longer than the multiplications), the rest of an address is a per-thread constant, and
-// (p, q) advances by addition.  Two LDS buffers, one barrier per slice, loads two slices ahead.  3x3 64 -> 192 at stride 2 on
-// 56 x 56 x 32 images: 118 -> 71 us (78 TFLOP/s).
-template <int TPT>
+// (p, q) advances by addition.  Two LDS buffers, one barrier per slice, loads two slices ahead; the next slice goes to LDS in the middle of the
+// products, which 64 cycles each leave time for.  3x3 64 -> 192 at stride 2 on 56 x 56 x 32 images: 118 -> 71 us (78 TFLOP/s); with that order and EIGHTS
+// the fitting step as a whole, kernels of other sizes before and behind it, another 4 to 8 us less (without EIGHTS 80 us for this kernel, 72 with).
+// EIGHTS: filters and channels come in eights, so that a row or column exists for all threads of its group of eight or for none: its offset is then the
+// load's scalar offset, and a slice takes an address for the gradient and one per tap instead of one per element.
+template <int TPT, bool EIGHTS>
 __global__ __launch_bounds__(256) void conv_wgrad_f32_kernel(const WArgs a)
 {
     __shared__ __attribute__((aligned(16))) float As[2][BM * LDT];
@@ -158,13 +161,26 @@ __global__ __launch_bounds__(256) void conv_wgrad_f32_kernel(const WArgs a)
     const int tg = nt / a.cblocks, c0 = (nt - tg * a.cblocks) * CB;
     // column row0 + 8 i: tap i / IPT and channel row0 + 8 (i % IPT) of the tile; with tiles of 4 channels tap 2 i + row0 / 4, channel row0 % 4
     auto tap_of = [&](int t) __attribute__((always_inline)) { return tg * TPT + (TPT > 8 ? 2 * t + (row0 >> 2) : t); };
-    unsigned a_row[8], b_row[8];
+    static_assert(!EIGHTS || TPT < 16, "a column tile of four channels");
+    unsigned a_row[EIGHTS ? 1 : 8], b_row[EIGHTS ? 1 : 8];      // EIGHTS: of row, of column row0; the others' distance from it is wave-uniform
+    int a_off[8], b_off[8];                                     // (0: of an eight that does not exist, whose outputs are not stored)
     int tap_r[NT], tap_s[NT];
+    if constexpr (EIGHTS) {
+        a_row[0] = (unsigned)((m0 + row0) * PQ * 4);
+        b_row[0] = (unsigned)((c0 + row0) * HW * 4);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int m = m0 + row0 + 8 * i, c = c0 + (TPT > 8 ? row0 & 3 : row0 + 8 * (i % IPT));
-        a_row[i] = m < a.K ? (unsigned)(m * PQ * 4) : OOB;
-        b_row[i] = c < a.C && tap_of(i / IPT) < RS ? (unsigned)(c * HW * 4) : OOB;
+        for (int i = 0; i < 8; ++i) {
+            a_off[i] = m0 + 8 * i < a.K ? 8 * i * PQ * 4 : 0;
+            b_off[i] = c0 + 8 * (i % IPT) < a.C ? 8 * (i % IPT) * HW * 4 : 0;
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int m = m0 + row0 + 8 * i, c = c0 + (TPT > 8 ? row0 & 3 : row0 + 8 * (i % IPT));
+            a_row[i] = m < a.K ? (unsigned)(m * PQ * 4) : OOB;
+            b_row[i] = c < a.C && tap_of(i / IPT) < RS ? (unsigned)(c * HW * 4) : OOB;
+            a_off[i] = b_off[i] = 0;
+        }
     }
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
@@ -183,13 +199,14 @@ __global__ __launch_bounds__(256) void conv_wgrad_f32_kernel(const WArgs a)
         const int soff_a = img * a.K * PQ * 4, soff_b = img * a.C * HW * 4;
         const int ih0 = p * a.sh, iw0 = q * a.sw;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) ra[SET][i] = buf_load(rz, a_row[i] + za, soff_a);
+        for (int i = 0; i < 8; ++i) ra[SET][i] = buf_load(rz, a_row[EIGHTS ? 0 : i] + za, soff_a + a_off[i]);
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const int ih = ih0 + tap_r[t], iw = iw0 + tap_s[t];
-            const unsigned xo = on && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W ? (unsigned)((ih * a.W + iw) * 4) : OOB;
+            const bool in = on & ((unsigned)ih < (unsigned)a.H) & ((unsigned)iw < (unsigned)a.W) & (!EIGHTS || tap_of(t) < RS);
+            const unsigned xo = in ? (unsigned)((ih * a.W + iw) * 4) : OOB;
 #pragma unroll
-            for (int i = t * IPT; i < (t + 1) * IPT; ++i) rb[SET][i] = buf_load(rx, b_row[i] + xo, soff_b);
+            for (int i = t * IPT; i < (t + 1) * IPT; ++i) rb[SET][i] = buf_load(rx, b_row[EIGHTS ? 0 : i] + xo, soff_b + b_off[i]);
         }
         if (--left == 0) {
             ++img; left = a.slices_per_img;
@@ -228,11 +245,15 @@ __global__ __launch_bounds__(256) void conv_wgrad_f32_kernel(const WArgs a)
             bv[j] = *reinterpret_cast<const f32x4*>(bp + 4 * j);
         }
 #pragma unroll
-        for (int j = 0; j < 16; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[j >> 2][j & 3], bv[j >> 2][j & 3], acc, 0, 0, 0);
+        for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[j >> 2][j & 3], bv[j >> 2][j & 3], acc, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
         if (sl + 1 < total) {
             put(buf ^ 1, set_c);
             if (sl + 3 < total) fetch(set_c);
         }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 8; j < 16; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[j >> 2][j & 3], bv[j >> 2][j & 3], acc, 0, 0, 0);
         lds_barrier();
     };
     using S0 = std::integral_constant<int, 0>;
@@ -358,11 +379,16 @@ int launch_conv_wgrad_f32(const ConvGeom& g, const float* x, const float* dz, fl
         ConvGeom t = g;
         TraceScope trace("conv_wgrad_f32", &t, g.Ng, st);
         const dim3 grid((unsigned)(a.grid_m * a.grid_n * a.splits)), block(256);
-        if (p.cb_log2 == 6) hipLaunchKernelGGL(conv_wgrad_f32_kernel<1>, grid, block, 0, st, a);
-        else if (p.cb_log2 == 5) hipLaunchKernelGGL(conv_wgrad_f32_kernel<2>, grid, block, 0, st, a);
-        else if (p.cb_log2 == 4) hipLaunchKernelGGL(conv_wgrad_f32_kernel<4>, grid, block, 0, st, a);
-        else if (p.cb_log2 == 3) hipLaunchKernelGGL(conv_wgrad_f32_kernel<8>, grid, block, 0, st, a);
-        else hipLaunchKernelGGL(conv_wgrad_f32_kernel<16>, grid, block, 0, st, a);
+        if (g.K % 8 == 0 && g.C % 8 == 0 && p.cb_log2 >= 3) {
+            if (p.cb_log2 == 6) hipLaunchKernelGGL((conv_wgrad_f32_kernel<1, true>), grid, block, 0, st, a);
+            else if (p.cb_log2 == 5) hipLaunchKernelGGL((conv_wgrad_f32_kernel<2, true>), grid, block, 0, st, a);
+            else if (p.cb_log2 == 4) hipLaunchKernelGGL((conv_wgrad_f32_kernel<4, true>), grid, block, 0, st, a);
+            else hipLaunchKernelGGL((conv_wgrad_f32_kernel<8, true>), grid, block, 0, st, a);
+        } else if (p.cb_log2 == 6) hipLaunchKernelGGL((conv_wgrad_f32_kernel<1, false>), grid, block, 0, st, a);
+        else if (p.cb_log2 == 5) hipLaunchKernelGGL((conv_wgrad_f32_kernel<2, false>), grid, block, 0, st, a);
+        else if (p.cb_log2 == 4) hipLaunchKernelGGL((conv_wgrad_f32_kernel<4, false>), grid, block, 0, st, a);
+        else if (p.cb_log2 == 3) hipLaunchKernelGGL((conv_wgrad_f32_kernel<8, false>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((conv_wgrad_f32_kernel<16, false>), grid, block, 0, st, a);
     }
     if (const int rc = check_launch("conv_wgrad")) return rc;
     if (a.splits > 1) {

@@ -46,6 +46,10 @@ WGRAD_CASES = [
     (2, 3, 43, 39, 33, 11, 11, 4, 0),     # a layer on the image: eight tiles of sixteen taps, nine taps in the last
     (10, 8, 15, 18, 32, 3, 3, 4, 1),      # ten images of one slice each: a range per image
     (20, 3, 12, 8, 40, 3, 3, 4, 1),       # twenty: sixteen ranges, some of two slices
+    (2, 72, 9, 11, 72, 3, 3, 1, 1),       # filters and channels in eights, one of them in the second tile
+    (3, 24, 10, 13, 40, 3, 3, 2, 1),      # ... on tiles of two taps by 32 channels, a tap in the fifth that does not exist
+    (2, 16, 7, 9, 8, 5, 5, 1, 2),         # ... four taps by 16
+    (2, 24, 8, 8, 65, 3, 3, 1, 1),        # channels in eights, filters not
 ]
 
 
