@@ -132,6 +132,79 @@ __device__ __forceinline__ void store_far(const KArgs& a, const f32x16& acc, int
     }
 }
 
+// The sums of a wave's TM x TN blocks of 32x32, rows from mw and columns from nw on; n0: the tile's first column
+template <int TM, int TN, bool SPLIT>
+__device__ __forceinline__ void store_tile(const KArgs& a, const f32x16 (&acc)[TM][TN], int mw, int nw, int n0)
+{
+    constexpr int OOB = (int)0x80000000;
+    const ConvGeom& g = a.g;
+    const int PQ = g.P * g.Q, half = (threadIdx.x >> 5) & 1, l32 = threadIdx.x & 31;
+    // Accumulator register v of a 32x32 tile holds row 8*(v/4) + 4*half + v%4, column l32.  Addresses are a descriptor that starts at
+    // the tile's first image, a per-lane offset and the row as scalar offset; lanes without an output, and rows beyond the last filter, store
+    // outside the descriptor.  Nothing per element but the bias, the ReLU and the store: with a branch each for bias, residual and destination
+    // (16 dependent loads, some 50 instructions per element, which fp32 matrix instructions of other waves do not overlap with) the store took as
+    // long as six to eight slices.  GoogLeNet's 3a on 32 images, slim: its first level 24.3 -> 20.2 us, the module 99.7 -> 92.9; 4c on 64 images
+    // 166 -> 158.5; 3x3 32 -> 256 on 30 x 45 x 9 with what follows it 44.1 -> 42.1; AlexNet's 5x5, 150 slices, 1 % or less.
+    const int img0 = n0 / PQ;
+    const __amdgpu_buffer_rsrc_t rbias = __builtin_amdgcn_make_buffer_rsrc((void*)a.bias, 0, a.bias ? g.K * 4 : 0, 0x00020000);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int n = nw + j * 32 + l32;
+        const int img = n / PQ, pix = n - img * PQ;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int mb = __builtin_amdgcn_readfirstlane(mw + i * 32), mh = mb + half * 4;
+            const bool whole = mb + 32 <= g.K;                // (wave-uniform)
+            if constexpr (SPLIT) {
+                const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc((void*)(a.part + (size_t)blockIdx.y * g.K * g.Ng), 0, 0x7FFFFFFF, 0x00020000);
+                const int vp = n < g.Ng ? (mh * g.Ng + n) * 4 : OOB;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int row = (v >> 2) * 8 + (v & 3);
+                    buf_store(acc[i][j][v], rp, whole || mh + row < g.K ? vp : OOB, row * g.Ng * 4);
+                }
+                continue;
+            }
+            if (a.far_store) {
+                if (n < g.Ng) store_far(a, acc[i][j], mh, img, pix);
+                continue;
+            }
+            f32x4 o[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) o[q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rbias, (mh + q * 8) * 4, 0, 0));
+#pragma unroll
+            for (int v = 0; v < 16; ++v) o[v >> 2][v & 3] += acc[i][j][v];
+            if (a.res) {
+                const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc((void*)(a.res + (size_t)img0 * g.res_ctot * PQ), 0, 0x7FFFFFFF, 0x00020000);
+                const int vr = n < g.Ng ? (((img - img0) * g.res_ctot + mh) * PQ + pix) * 4 : OOB;
+                float res[16];
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int row = (v >> 2) * 8 + (v & 3);
+                    res[v] = buf_load(rr, whole || mh + row < g.K ? vr : OOB, row * PQ * 4);
+                }
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[v >> 2][v & 3] += res[v];
+            }
+            if (g.relu) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[v >> 2][v & 3] = fmaxf(o[v >> 2][v & 3], 0.f);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                // rows mb + 8 q .. + 7 have one destination (wave-uniform)
+                const int m8 = mb + q * 8, d = (m8 >= a.split_end[0]) + (m8 >= a.split_end[1]) + (m8 >= a.split_end[2]);
+                const int ct = d == 0 ? a.ctot_seg[0] : d == 1 ? a.ctot_seg[1] : d == 2 ? a.ctot_seg[2] : a.ctot_seg[3];
+                float* const yd = d == 0 ? a.y_seg[0] : d == 1 ? a.y_seg[1] : d == 2 ? a.y_seg[2] : a.y_seg[3];
+                const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void*)(yd + (size_t)img0 * ct * PQ + (size_t)m8 * PQ), 0, 0x7FFFFFFF, 0x00020000);
+                const int vy = n < g.Ng ? (((img - img0) * ct + half * 4) * PQ + pix) * 4 : OOB;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) buf_store(o[q][e], ry, whole || mh + q * 8 + e < g.K ? vy : OOB, e * PQ * 4);
+            }
+        }
+    }
+}
+
 // BM x BN: workgroup tile; WGM x WGN: wave grid (4 waves); BK: k per LDS slice; PF: prefetch distance
 // in slices; CF: slice order (see above); FR, FS: compile-time filter size for CF = false (0 = taken
 // from the geometry at run time); TAB1: the table of one-word entries; SPLIT: the workgroup takes range blockIdx.y of the contraction and
@@ -457,18 +530,28 @@ __device__ __forceinline__ void conv_f32_tile(const KArgs a, const int block, fl
 #pragma unroll
             for (int h = 0; h < HK / 4; ++h) fb[j][h] = *reinterpret_cast<const f32x4*>(p + (h >> 1) * 16 + (h & 1) * 4);
         }
+        auto products = [&](auto from_c, auto to_c) {
 #pragma unroll
-        for (int kk = 0; kk < HK; ++kk)
+            for (int kk = decltype(from_c)::value; kk < decltype(to_c)::value; ++kk)
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+                for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][kk >> 2][kk & 3], fb[j][kk >> 2][kk & 3],
-                                                                     acc[i][j], 0, 0, 0);
+                    for (int j = 0; j < TN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][kk >> 2][kk & 3], fb[j][kk >> 2][kk & 3],
+                                                                         acc[i][j], 0, 0, 0);
+        };
+        // The next slice goes to LDS and the one behind it is asked for in the middle of the products: a matrix instruction takes 64 cycles and whatever
+        // does not need the vector ALU is issued meanwhile.  (Behind the products it was a wave's own time: 3a slim on 64 images 165 us and 159,
+        // 3x3 32 -> 256 on 30 x 45 x 9 52 and 48; loads that are always made, past the end from an empty buffer, so that the wait for a slice is not one
+        // for the next slice too: 4 % slower, here and in the parameter gradient.)
+        products(IC<0>{}, IC<4>{});
+        __builtin_amdgcn_sched_barrier(0);
         if (it + 1 < nslices) {
             store_slice(buf ^ 1, set_c);
             if (it + 1 + PF < nslices) load_slice(it + 1 + PF, set_c);
         }
+        __builtin_amdgcn_sched_barrier(0);
+        products(IC<4>{}, IC<HK>{});
         lds_barrier();
     };
 
@@ -483,70 +566,7 @@ __device__ __forceinline__ void conv_f32_tile(const KArgs a, const int block, fl
         if (PF == 2 && it + 1 < nslices) slice_step(it + 1, IC<PF - 1>{});
     }
 
-    // ---- store: accumulator register v of a 32x32 tile holds row 8*(v/4) + 4*half + v%4, column l32.  Addresses are a descriptor that starts at
-    // the tile's first image, a per-lane offset and the row as scalar offset; lanes without an output, and rows beyond the last filter, store
-    // outside the descriptor.  Nothing per element but the bias, the ReLU and the store: with a branch each for bias, residual and destination
-    // (16 dependent loads, some 50 instructions per element, which fp32 matrix instructions of other waves do not overlap with) the store took as
-    // long as six to eight slices.  GoogLeNet's 3a on 32 images, slim: its first level 24.3 -> 20.2 us, the module 99.7 -> 92.9; 4c on 64 images
-    // 166 -> 158.5; 3x3 32 -> 256 on 30 x 45 x 9 with what follows it 44.1 -> 42.1; AlexNet's 5x5, 150 slices, 1 % or less.
-    const int img0 = n0 / PQ;
-    const __amdgpu_buffer_rsrc_t rbias = __builtin_amdgcn_make_buffer_rsrc((void*)a.bias, 0, a.bias ? g.K * 4 : 0, 0x00020000);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int n = n0 + wn * WN + j * 32 + l32;
-        const int img = n / PQ, pix = n - img * PQ;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int mb = __builtin_amdgcn_readfirstlane(m0 + wm * WM + i * 32), mh = mb + half * 4;
-            const bool whole = mb + 32 <= g.K;                // (wave-uniform)
-            if constexpr (SPLIT) {
-                const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc((void*)(a.part + (size_t)blockIdx.y * g.K * g.Ng), 0, 0x7FFFFFFF, 0x00020000);
-                const int vp = n < g.Ng ? (mh * g.Ng + n) * 4 : OOB;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int row = (v >> 2) * 8 + (v & 3);
-                    buf_store(acc[i][j][v], rp, whole || mh + row < g.K ? vp : OOB, row * g.Ng * 4);
-                }
-                continue;
-            }
-            if (a.far_store) {
-                if (n < g.Ng) store_far(a, acc[i][j], mh, img, pix);
-                continue;
-            }
-            f32x4 o[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) o[q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rbias, (mh + q * 8) * 4, 0, 0));
-#pragma unroll
-            for (int v = 0; v < 16; ++v) o[v >> 2][v & 3] += acc[i][j][v];
-            if (a.res) {
-                const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc((void*)(a.res + (size_t)img0 * g.res_ctot * PQ), 0, 0x7FFFFFFF, 0x00020000);
-                const int vr = n < g.Ng ? (((img - img0) * g.res_ctot + mh) * PQ + pix) * 4 : OOB;
-                float res[16];
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int row = (v >> 2) * 8 + (v & 3);
-                    res[v] = buf_load(rr, whole || mh + row < g.K ? vr : OOB, row * PQ * 4);
-                }
-#pragma unroll
-                for (int v = 0; v < 16; ++v) o[v >> 2][v & 3] += res[v];
-            }
-            if (g.relu) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) o[v >> 2][v & 3] = fmaxf(o[v >> 2][v & 3], 0.f);
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                // rows mb + 8 q .. + 7 have one destination (wave-uniform)
-                const int m8 = mb + q * 8, d = (m8 >= a.split_end[0]) + (m8 >= a.split_end[1]) + (m8 >= a.split_end[2]);
-                const int ct = d == 0 ? a.ctot_seg[0] : d == 1 ? a.ctot_seg[1] : d == 2 ? a.ctot_seg[2] : a.ctot_seg[3];
-                float* const yd = d == 0 ? a.y_seg[0] : d == 1 ? a.y_seg[1] : d == 2 ? a.y_seg[2] : a.y_seg[3];
-                const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void*)(yd + (size_t)img0 * ct * PQ + (size_t)m8 * PQ), 0, 0x7FFFFFFF, 0x00020000);
-                const int vy = n < g.Ng ? (((img - img0) * ct + half * 4) * PQ + pix) * 4 : OOB;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) buf_store(o[q][e], ry, whole || mh + q * 8 + e < g.K ? vy : OOB, e * PQ * 4);
-            }
-        }
-    }
+    store_tile<TM, TN, SPLIT>(a, acc, m0 + wm * WM, n0 + wn * WN, n0);
 }
 
 template <int BM, int BN, int WGM, int WGN, int BK, int PF, bool CF, int FR, int FS, bool TAB1, bool SPLIT>
@@ -558,6 +578,143 @@ __global__ __launch_bounds__(NT) void conv_f32_kernel(const KArgs a)
     // AlexNet's first two convolutions at batch 128 show as 1465 us against 1518, and its code the element-by-element path 4 to 15 %)
     __shared__ __attribute__((aligned(16))) int ktab[CF ? 4 : TAB1 ? KTAB1 : 2 * KTAB];   // CF = false: {byte offset, r | s << 8} per k
     conv_f32_tile<BM, BN, WGM, WGN, BK, PF, CF, FR, FS, TAB1, SPLIT>(a, (int)blockIdx.x, As, Bs, ktab);
+}
+
+// 3x3 filters in KCRS order on a multiple of 16 channels: filters that change from call to call, as while a layer is being fitted, and are not worth
+// packing.  In the order of the general path every activation costs a table entry, a shift, a mask and an add, 24 vector instructions a slice, which fp32
+// matrix instructions do not overlap with.  Here the nine taps of 8 channels, 72 consecutive floats of a filter row, come to LDS as they are with 16-byte
+// loads, and a slice is one filter row of those 8 channels: 24 k, of which lane half h takes channels 4 h .. 4 h + 3.  An activation's
+// place is one of nine per-lane offsets (the padding is in them) and a channel, which is the load's scalar offset: no vector arithmetic in the loop.
+// Filter rows lie 74 floats apart: two lanes to a bank both where a row is written, by 8 bytes, and where it is read (73, one lane to a bank in the reads
+// and eight in the writes, 66 us instead of 63); an activation row is 24 floats, its 16-byte pieces in an order that bit 2 of the pixel turns
+// round: 31 KB, five workgroups per compute unit (four: the same time).
+// 3x3 64 -> 192 at stride 2 on 56 x 56 x 32, 1176 tiles in one round, 71 -> 60 us (92 TFLOP/s); on one image, with the parameter gradient and all that a
+// step of the fitting takes, 44.7 -> 37.9.  What is left: the matrix cores are busy three quarters of the time, least when one or two workgroups
+// remain on a compute unit.
+template <int BM, int BN>
+__global__ __launch_bounds__(NT, BM == 64 ? 5 : 4) void conv_f32_kcrs33_kernel(const KArgs a)
+{
+    constexpr int CB = 8, ROW = CB * 9, LDA = ROW + 2, WGN = BN / 32, OOB = (int)0x80000000;
+    constexpr int A_F4 = BM * ROW / 4, A_PER = (A_F4 + NT - 1) / NT, CPT = CB * BN / NT;       // 16-byte loads of a block; channels of an activation a thread fetches
+    static_assert(BM / 32 * WGN == 4 && (CPT == 2 || CPT == 4), "four waves");
+    __shared__ __attribute__((aligned(16))) float As[BM * LDA];
+    __shared__ __attribute__((aligned(16))) float Bs[2][BN * 24];
+    const ConvGeom& g = a.g;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
+    const int wm = wave / WGN, wn = wave % WGN;
+    int bid = (int)blockIdx.x;
+    const int nblk = a.grid_m * a.grid_n;
+    if (nblk % 8 == 0) bid = (bid & 7) * (nblk >> 3) + (bid >> 3);      // (a range of tiles per die, as above)
+    const int m0 = (bid % a.grid_m) * BM, n0 = (bid / a.grid_m) * BN, HW = g.H * g.W, PQ = g.P * g.Q, blocks = g.C / CB;
+
+    int va[A_PER], vb[3][3];
+#pragma unroll
+    for (int i = 0; i < A_PER; ++i) {
+        const int f = tid + i * NT, row = f / (ROW / 4);
+        va[i] = f < A_F4 && m0 + row < g.K ? ((m0 + row) * g.Kg + (f - row * (ROW / 4)) * 4) * 4 : OOB;
+    }
+    const int px = tid % BN, grp = tid / BN, n = n0 + px;
+    {
+        const int nn = n < g.Ng ? n : 0, img = nn / PQ, pix = nn - img * PQ, p = pix / g.Q, q = pix - p * g.Q, ih0 = p * g.sh - g.ph, iw0 = q * g.sw - g.pw;
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+                const bool in = (n < g.Ng) & ((unsigned)(ih0 + r) < (unsigned)g.H) & ((unsigned)(iw0 + t) < (unsigned)g.W);
+                vb[r][t] = in ? ((img * g.C + grp * CPT) * HW + (ih0 + r) * g.W + iw0 + t) * 4 : OOB;
+            }
+    }
+    f32x4 ra[A_PER];
+    float rb[3][CPT];
+    auto load_a = [&](int blk) __attribute__((always_inline)) {
+        const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, blk < blocks ? a.w_bytes : 0, 0x00020000);
+#pragma unroll
+        for (int i = 0; i < A_PER; ++i) ra[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rw, va[i], blk * ROW * 4, 0));
+    };
+    auto load_b = [&](int blk, auto r_c) __attribute__((always_inline)) {     // (beyond the last block: a descriptor of size 0)
+        constexpr int R = decltype(r_c)::value;
+        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)a.x, 0, blk < blocks ? a.x_bytes : 0, 0x00020000);
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+#pragma unroll
+            for (int j = 0; j < CPT; ++j) rb[t][j] = buf_load(rx, vb[R][t], (blk * CB + j) * HW * 4);
+    };
+    auto put_a = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < A_PER; ++i) {
+            const int f = tid + i * NT, row = f / (ROW / 4);
+            if (A_F4 % NT == 0 || f < A_F4) {
+                typedef float f32x2 __attribute__((ext_vector_type(2)));
+                float* const d = As + f * 4 + 2 * row;
+                *reinterpret_cast<f32x2*>(d) = f32x2{ra[i][0], ra[i][1]};
+                *reinterpret_cast<f32x2*>(d + 2) = f32x2{ra[i][2], ra[i][3]};
+            }
+        }
+    };
+    auto put_b = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            const int h = CPT == 4 ? grp : grp >> 1;
+            float* const d = &Bs[buf][px * 24 + (2 * t + (h ^ (px >> 2 & 1))) * 4 + (CPT == 4 ? 0 : (grp & 1) * 2)];
+            if constexpr (CPT == 4) {
+                *reinterpret_cast<f32x4*>(d) = f32x4{rb[t][0], rb[t][1], rb[t][2], rb[t][3]};
+            } else {
+                typedef float f32x2 __attribute__((ext_vector_type(2)));
+                *reinterpret_cast<f32x2*>(d) = f32x2{rb[t][0], rb[t][1]};
+            }
+        }
+    };
+    f32x16 acc[1][1];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[0][0][v] = 0.f;
+    const float* const a_rd = As + (wm * 32 + l32) * LDA + half * 36;
+    const int b_px = wn * 32 + l32, b_rd = b_px * 24 + (half ^ (b_px >> 2 & 1)) * 4;
+    auto multiply = [&](int buf, auto r_c, auto between) __attribute__((always_inline)) {
+        constexpr int R = decltype(r_c)::value;
+        float fa[3][4];
+        f32x4 fb[3];
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            fb[t] = *reinterpret_cast<const f32x4*>(&Bs[buf][b_rd + t * 8]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) fa[t][j] = a_rd[j * 9 + R * 3 + t];
+        }
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[t][j], fb[t][j], acc[0][0], 0, 0, 0);
+            if (t == 1) {
+                __builtin_amdgcn_sched_barrier(0);
+                between();
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+    // a block of 8 channels whose first slice is in buffer B0, its filters in LDS, its second slice and the next block's filters under way
+    auto block = [&](int blk, auto b_c) __attribute__((always_inline)) {
+        constexpr int B0 = decltype(b_c)::value;
+        multiply(B0, IC<0>{}, [&]() __attribute__((always_inline)) { put_b(B0 ^ 1); load_b(blk, IC<2>{}); });
+        lds_barrier();
+        multiply(B0 ^ 1, IC<1>{}, [&]() __attribute__((always_inline)) { put_b(B0); load_b(blk + 1, IC<0>{}); });
+        lds_barrier();
+        multiply(B0, IC<2>{}, [&]() __attribute__((always_inline)) { put_b(B0 ^ 1); load_b(blk + 1, IC<1>{}); });
+        lds_barrier();                                // every wave has read the filters
+        put_a();
+        load_a(blk + 2);
+        lds_barrier();
+    };
+    load_a(0);
+    load_b(0, IC<0>{});
+    put_a();
+    put_b(0);
+    load_a(1);
+    load_b(0, IC<1>{});
+    lds_barrier();
+    for (int blk = 0; blk < blocks; blk += 2) {
+        block(blk, IC<0>{});
+        block(blk + 1, IC<1>{});
+    }
+    store_tile<1, 1, false>(a, acc, m0 + wm * 32, n0 + wn * 32, n0);
 }
 
 // Several layers in one launch (KRSC filters or 1x1; each with the tile it would have by itself): the layers' tiles fill the device
@@ -777,6 +934,14 @@ static bool cut_beats_taps(const ConvGeom& g, const void* ws, size_t ws_bytes)
     return cut_us < 0.95f * taps_us;
 }
 
+// 3x3 filters in KCRS order that the general path does not cut over workgroups; they are read 16 bytes at a time
+static bool kcrs33_takes(const ConvGeom& g, const void* w, const void* ws, size_t ws_bytes, int nsplit)
+{
+    if (g.w_krsc || g.R != 3 || g.S != 3 || g.C % 16 != 0 || ((uintptr_t)w & 15) != 0) return false;
+    const size_t cut = conv_f32_scratch_bytes(g);
+    return !(ws && nsplit <= 1 && cut && cut <= ws_bytes && ((uintptr_t)ws & 15) == 0);
+}
+
 bool conv_f32_group_takes(const ConvGeom& g)
 {
     const size_t xb = (size_t)g.N * g.C * g.H * g.W * 4, wb = (size_t)g.K * g.Kg * 4;
@@ -822,7 +987,16 @@ int launch_conv_f32(const ConvGeom& g, const float* x, const float* w, const flo
         return fail(DR_ERR_UNSUPPORTED, "conv_f32: input (%zu bytes) or filter tensor (%zu bytes) is 2 GiB or larger", xb, wb);
     // wide filters on few channels, no padding (conv_f32_taps.hip)
     if (conv_f32_taps_takes(g, residual, split) && !cut_beats_taps(g, ws, ws_bytes)) return launch_conv_f32_taps(g, x, w, bias, y, st);
-    const KArgs a = base_args(g, x, w, bias, residual, y, split);
+    KArgs a = base_args(g, x, w, bias, residual, y, split);
+    if (kcrs33_takes(g, w, ws, ws_bytes, a.nsplit)) {
+        const bool rows32 = rows_of_32(g);
+        a.grid_m = rows32 ? (g.K + 31) / 32 : (g.K + 63) / 64;
+        a.grid_n = rows32 ? (g.Ng + 127) / 128 : (g.Ng + 63) / 64;
+        const dim3 grid((unsigned)(a.grid_m * a.grid_n)), block(NT);
+        if (rows32) hipLaunchKernelGGL((conv_f32_kcrs33_kernel<32, 128>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((conv_f32_kcrs33_kernel<64, 64>), grid, block, 0, st, a);
+        return check_launch("conv_f32 (3x3, KCRS)");
+    }
     // (32-deep slices with the groups-of-4-taps order: measured 10 % slower)
     if (slices_of_32(g))
         return rows_of_32(g) ? launch_tile<32, 128, 1, 4, 32, 2>(a, ws, ws_bytes, st) : launch_tile<64, 64, 2, 2, 32, 2>(a, ws, ws_bytes, st);
