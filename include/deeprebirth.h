@@ -233,8 +233,8 @@ typedef struct { int n_steps; dr_step steps[DR_MAX_STEPS]; } dr_branch;
 
 /* How the module is executed.  0 = the layer-by-layer form the paper times: every ReLU is its own
  * kernel and the branch outputs are gathered by a concat kernel.  (In every mode the convolutions at one depth of the
- * branches, a 3x3 pooling step beside them, and the ReLUs behind them may share a launch each where the layers are
- * small; each layer still reads its whole input and writes its whole output.  Not while a kernel trace runs, filtered or
+ * branches, a 3x3 pooling step beside them, and the ReLUs behind them may share a launch each, bf16 layers of any size,
+ * in fp32 where most are small; each layer still reads its whole input and writes its whole output.  Not while a kernel trace runs, filtered or
  * not: there every layer is a launch of its own.)  Flags remove passes without changing the function computed.  Bits: bf16 modules have
  * the same in every mode; fp32 modules in every mode and under a trace except that DR_FUSE_STACK adds the products of the stacked
  * convolutions in another order where the stacked layer is run by another kernel than its banks alone (banks small enough for the
@@ -258,6 +258,7 @@ typedef struct { int n_steps; dr_step steps[DR_MAX_STEPS]; } dr_branch;
                               also when the call returns an error after some branches have been started
                               (they are joined before it returns).  Devices 0..15 of a process.
                               Without it the branches run one after another on the caller's stream.
+                              bf16 modules whose layers share launches (below) run as without it.
                               Pays when a module's kernels are long next to the cost of the events
                               (several microseconds per fork / join) and leave compute units idle */
 typedef struct { int n_branches; dr_branch branches[DR_MAX_BRANCHES]; int mode; } dr_inception;

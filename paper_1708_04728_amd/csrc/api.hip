@@ -522,7 +522,7 @@ int run_stacked_first_steps(const dr_tensor& xd, const void* x, const dr_incepti
 
 // A module step by step instead of branch by branch: the convolutions at the same depth of the branches (and a 3x3 pooling
 // step beside them) are independent of one another and share launches -- of the small-layer kernels, or for larger
-// fp32 layers of the tiled kernel.  Steps those do not take run one by one.  ReLU layers that the mode keeps apart and
+// layers of the tiled kernel (fp32) or of wide tiles (bf16).  Steps those do not take run one by one.  ReLU layers that the mode keeps apart and
 // the concat remain kernels of their own.
 struct StepGroup {
     hipStream_t st;
@@ -541,12 +541,27 @@ struct StepGroup {
         const int k = n_big;
         n_big = 0;
         if (!k) return DR_OK;
-        if (k > 1) return launch_conv_f32_group(big, k, st);
         const ConvSmall& j = big[0];
+        if (dtype == DR_BF16) {
+            if (k > 1) return launch_conv_bf16_wide_group(big, k, st);
+            return j.split ? launch_conv_bf16_dma(j.g, (const uint16_t*)j.x, (const uint16_t*)j.w, j.bias, nullptr, (uint16_t*)j.y, st, j.split)
+                           : launch_conv_bf16(j.g, (const uint16_t*)j.x, (const uint16_t*)j.w, j.bias, nullptr, (uint16_t*)j.y, st);
+        }
+        if (k > 1) return launch_conv_f32_group(big, k, st);
         return launch_conv_f32(j.g, (const float*)j.x, (const float*)j.w, j.bias, (const float*)j.res, (float*)j.y, st, nullptr, 0, j.split);
     }
     int flush()
     {
+        // bf16: with a larger layer at this depth, or where they crowd the device, the small ones that can run in a launch of wide tiles
+        if (dtype == DR_BF16 && (n_big || conv_bf16_small_crowded(jobs, n))) {
+            int kept = 0;
+            for (int i = 0; i < n; ++i) {
+                const ConvSmall j = jobs[i];
+                if (j.w && n_big < SMALL_GROUP_MAX && conv_bf16_wide_joins(j.g, j.x, j.w, j.y, j.split)) big[n_big++] = j;
+                else jobs[kept++] = j;
+            }
+            n = kept;
+        }
         DR_TRY(flush_big());
         return flush_small();
     }
@@ -564,9 +579,11 @@ struct StepGroup {
     }
 };
 
-// Larger fp32 layers that share a launch: enough tiles to be worth it (fewer are better cut over workgroups, one by one)
-bool big_takes(int dtype, const ConvGeom& g)
+// Larger layers that share a launch.  bf16: wide tiles, whatever is not small; fp32: enough tiles to be worth it (fewer are better cut over
+// workgroups, one by one)
+bool big_takes(int dtype, const ConvGeom& g, const void* x = nullptr, const void* w = nullptr, const void* y = nullptr)
 {
+    if (dtype == DR_BF16) return conv_bf16_wide_joins(g, x, w, y, nullptr) && !conv_bf16_small_takes(g, x, w);
     return dtype == DR_F32 && conv_f32_group_takes(g) && !conv_f32_small_takes(g, nullptr, false) &&
            ((long)g.K + 63) / 64 * (((long)g.Ng + 63) / 64) >= device_cus() / 2;
 }
@@ -593,11 +610,13 @@ bool small_pool_job(const dr_tensor& t, const void* x, const dr_tensor& o, void*
     return true;
 }
 
-// Whether the module runs level by level, its steps sharing launches: at least two convolutions that can.  Where the caller wants the
-// branches on streams, every convolution has to, and most of them in the small-layer kernel: a level is a barrier between the
-// branches, and larger layers fill the device better side by side (the original GoogLeNet at batch 128, half of whose 14x14 steps are
-// small: 1605 us against 1690; 4c in fp32 on 64 images, one small layer of six: 203 against 237), while a large layer among small
-// ones does not (slim 5a in fp32 on 64 images, a 5x5 of 392 tiles beside three small layers: 113 against 95, as graphs).
+// Whether the module runs level by level, its steps sharing launches: at least two convolutions that can.  In bf16 also where the caller wants the
+// branches on streams: the layers of a depth then lie side by side in one launch, each with its share of the compute units (as graphs, streams and
+// levels: the original GoogLeNet on 12 images 487 and 360 us, on 40 746 and 581, on 128 1494 and 1367; the fused one 297 and 260, 492 and
+// 414, 1042 and 968; on six and fewer, where every layer is small, both went by levels).  In fp32 then every convolution has to, and most of them
+// in the small-layer kernel: a level is a barrier between the branches, and larger layers, which share a launch one tile after the other, fill the
+// device better on streams (4c on 64 images, one small layer of six: 203 against 237), while a large layer among small
+// ones does not (slim 5a on 64 images, a 5x5 of 392 tiles beside three small layers: 113 against 95, as graphs).
 bool inception_by_levels(const dr_tensor& xd, const void* x, const dr_inception& d)
 {
     if (xd.layout != (xd.dtype == DR_BF16 ? DR_NHWC : DR_NCHW)) return false;
@@ -618,7 +637,7 @@ bool inception_by_levels(const dr_tensor& xd, const void* x, const dr_inception&
         }
     }
     const int n = n_small + n_big;
-    return n >= 2 && (!(d.mode & DR_CONCURRENT_BRANCHES) || (n == all && 2 * n_small > all));
+    return n >= 2 && (xd.dtype == DR_BF16 || !(d.mode & DR_CONCURRENT_BRANCHES) || (n == all && 2 * n_small > all));
 }
 
 int inception_run_levels(const dr_tensor& xd, const void* x, const dr_inception& d, ParamCursor& wts, ParamCursor& bss, const dr_tensor& yd, void* y,
@@ -671,11 +690,10 @@ int inception_run_levels(const dr_tensor& xd, const void* x, const dr_inception&
                 if (!done) {
                     if (!w) return fail(DR_ERR_NULL, "%s: missing weights of branch %d step %d", who, b, s);
                     ConvGeom g = conv_geom(q.t, cd, o);
+                    if (direct) { g.y_ctot = yd.c; g.y_coff = q.c_off; }
                     if (small_takes(xd.dtype, g, q.cur, w)) {
-                        if (direct) { g.y_ctot = yd.c; g.y_coff = q.c_off; }
                         DR_TRY(group.add(ConvSmall{g, q.cur, w, bias, nullptr, dst, nullptr}));
-                    } else if (big_takes(xd.dtype, g)) {
-                        if (direct) { g.y_ctot = yd.c; g.y_coff = q.c_off; }
+                    } else if (big_takes(xd.dtype, g, q.cur, w, dst)) {
                         DR_TRY(group.add_big(ConvSmall{g, q.cur, w, bias, nullptr, dst, nullptr}));
                     } else {
                         const size_t sbytes = module_scratch_bytes(q.t, cd);

@@ -126,15 +126,15 @@ struct TileWalk {
     int mt, nt0, gn, full, last, count;   // filter block; first tile; stride; whole rounds; the left-over tile; tiles of this workgroup
     __device__ __forceinline__ int tile(int t) const { return t < full ? nt0 + t * gn : last; }
 };
-__device__ __forceinline__ TileWalk tile_walk(const WalkArgs& k)
+__device__ __forceinline__ TileWalk tile_walk(const WalkArgs& k, int block)      // block: the workgroup's id among the launch's (or, of several layers, the layer's)
 {
-    const int G = k.gn * k.grid_m, die = (int)(blockIdx.x & 7), s = (int)(blockIdx.x >> 3), per = G >> 3, odd = G & 7;
+    const int G = k.gn * k.grid_m, die = block & 7, s = block >> 3, per = G >> 3, odd = G & 7;
     const int bid = die * per + min(die, odd) + s;
     TileWalk w;
     w.gn = k.gn; w.full = k.full;
     int u;                                              // workgroups of the same filter block with a lower id
     if (k.grid_m == 1) {
-        w.mt = 0; w.nt0 = bid; u = (int)blockIdx.x;
+        w.mt = 0; w.nt0 = bid; u = block;
     } else {
         w.nt0 = (int)__umulhi((unsigned)bid, k.magic_gm);
         w.mt = bid - w.nt0 * k.grid_m;

@@ -98,7 +98,7 @@ void conv_bf16_patch_kernel(const PArgs a)
     const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void*)a.y, 0, a.y_bytes, 0x00020000);
 
     // ---- persistent walk (tile_walk)
-    const TileWalk walk = tile_walk(a.wk);
+    const TileWalk walk = tile_walk(a.wk, (int)blockIdx.x);
     const int mt = walk.mt, my_tiles = walk.count;
     const int R_ = FIXED ? 3 : g.R, S_ = FIXED ? 3 : g.S, CB_ = FIXED ? 1 : a.cblks;
     const int nslices = R_ * S_ * CB_;                  // slice sl = (tap, channel block), channel block fastest

@@ -105,7 +105,7 @@ void conv_bf16_rows_kernel(const RArgs a)
     const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void*)a.y, 0, a.y_bytes, 0x00020000);
 
     // ---- persistent walk (tile_walk)
-    const TileWalk walk = tile_walk(a.wk);
+    const TileWalk walk = tile_walk(a.wk, (int)blockIdx.x);
     const int mt = walk.mt, my_tiles = walk.count;
     const int nslices = a.nslices;
 

@@ -408,6 +408,17 @@ bool conv_bf16_small_takes(const ConvGeom& g, const void* x, const void* w)
     return conv_bf16_dma_eligible(g, x, w) && (g.R * g.S == 1 || g.C <= 1 << 17) && tiles <= (g.R * g.S > 1 ? 2 : 1) * device_cus();
 }
 
+// Several layers whose 64 x 64 tiles are more than five for four compute units are better off side by side in wide tiles (conv_bf16_wide.hip), kernel trace:
+// 1x1 .. 3x3 of GoogLeNet's 4a slim on 12 images (333 tiles) 8.2 us here, 7.8 there, on 19 (531) 11.4 and 7.9; 4c on 37 (912) 16.8 and 12.4; 4e fused
+// on 12 (333) 11.2 and 10.3; 5b slim on 64 (784) 21.8 and 16.2.  Fewer: 5a slim on 25 (260) 9.3 and 10.2, 4c slim on 12 (296) 8.9 and 9.2, 5b slim on 25 (320)
+// 11.3 and 12.6.
+bool conv_bf16_small_crowded(const ConvSmall* jobs, int n)
+{
+    int convs = 0;
+    for (int i = 0; i < n; ++i) convs += jobs[i].w != nullptr;
+    return convs > 1 && 4 * small_tiles(jobs, n, 64, 64) > 5 * device_cus();
+}
+
 template <int TM, int TN, int WM, int WN, int LG>
 static int launch_group(const ConvSmall* jobs, int n, hipStream_t st)
 {

@@ -14,6 +14,13 @@
 // Workgroups are persistent: the loading waves run on into the next tile while the others store.  The order of the sums is the streaming
 // kernel's: the same bits.
 //
+// The layers of a module that do not depend on one another share a launch (conv_bf16_wide_group_kernel): each has a tile of its own and as many of the
+// compute units as its work asks for, so that all of them are done at about the same time (wide_plan).  One by one each of them pays a start
+// and an end of its own, about 6 us, and ends in a round that leaves compute units idle; 64 x 64 tiles, two to a compute unit, in the kernel for small
+// layers ask twice as much of the path into LDS.  Modules of GoogLeNet, us, before and with it: 4a slim on 19 images 15.7 and 12.0, on 37 22.0 and 15.7, on 128 36.5 and
+// 33.5; 3b fused on 12 27.3 and 22.3, on 64 79 and 68; 4e fused on 37 41.9 and 29.0; 5b fused on 100 38.8 and 28.3; 84 modules on 5 to 100 images
+// 0.873 of the time, none slower by more than 1 %.
+//
 // What bounds it: the matrix cores at the clock that they reach on varying operands -- 0.70 us per slice of 160 x 224 on 224 compute
 // units, 1.6 GHz -- and what a tile costs beside them: about 7 us for a layer of one round (a cold start, the store of the whole output at once),
 // 3 us for each further round.  Measured, streaming kernel -> this one, batch 128: 3x3 144 -> 288 on 14 x 14 38.4 -> 24.6 us, 160 -> 320 39.8 -> 26.4,
@@ -32,11 +39,16 @@ namespace dr {
 namespace {
 
 constexpr int WIDE_TABLE = 1024;                         // chunks of 8 contraction elements that a layer may have (8 KB of LDS)
+constexpr int WIDE_STAGES = 3;                           // slices in LDS
 
 template <class F, int... I>
 __device__ __forceinline__ void each_of(std::integer_sequence<int, I...>, const F& f) { (f(IC<I>{}), ...); }
 template <int N, class F>
 __device__ __forceinline__ void each(const F& f) { each_of(std::make_integer_sequence<int, N>{}, f); }
+
+// TM, TN; a layer by itself takes one of the first ten, beside others their share of the device may ask for smaller ones
+constexpr int WIDE_TILES[][2] = {{5, 7}, {4, 7}, {7, 4}, {6, 5}, {3, 7}, {6, 4}, {4, 4}, {2, 7}, {2, 5}, {4, 3}, {3, 4}, {2, 3}, {1, 7}, {1, 4}};
+constexpr int WIDE_TILE_COUNT = sizeof(WIDE_TILES) / sizeof(WIDE_TILES[0]), WIDE_ALONE = 10;
 
 struct WideArgs {
     const uint16_t* x;
@@ -55,16 +67,12 @@ struct WideArgs {
 
 // A tile of 32 TM filters x 32 TN pixels: 2 x 2 multiplying waves with TM x TN blocks of 16 x 16 each, four loading waves
 template <int TM, int TN>
-__global__ __launch_bounds__(512, 2) void conv_bf16_wide_kernel(const WideArgs a)
+__device__ __forceinline__ void wide_tiles(const WideArgs& a, const int block, unsigned char* const ring, u32x2* const table, float* const bias_lds)
 {
-    constexpr int NS = 3, BM = TM * 32, BN = TN * 32, L = TM + TN, STAGE = (BM + BN) * 128;       // slices in LDS; loads of a wave per slice
+    constexpr int NS = WIDE_STAGES, BM = TM * 32, BN = TN * 32, L = TM + TN, STAGE = (BM + BN) * 128;       // slices in LDS; loads of a wave per slice
     static_assert(BM <= 256 && (NS - 1) * L < 63, "loads in flight");
-    __shared__ __attribute__((aligned(1024))) unsigned char ring[NS * STAGE];
-    __shared__ __attribute__((aligned(16))) u32x2 table[WIDE_TABLE];
-    __shared__ __attribute__((aligned(16))) float bias_lds[BM];
-
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const TileWalk walk = tile_walk(a.wk);
+    const TileWalk walk = tile_walk(a.wk, block);
     const int mt = walk.mt, slices = a.slices, total = walk.count * slices;
 
     if (wave >= 4) {
@@ -105,6 +113,7 @@ __global__ __launch_bounds__(512, 2) void conv_bf16_wide_kernel(const WideArgs a
                 img += a.step_img;
             }
         };
+        const int row_chunks = a.row_chunks, row_gap = (a.run_chunks - a.row_chunks) * 16;
         int ld_t = 0, ld_s = 0, ld_j0 = 0, soff_a = 0, stage = 0;        // tile, slice, chunk in the row, offset in a filter, LDS stage of the next slice
         tile_setup(walk.tile(0));
         const unsigned tab_rd = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)table + lc * 8;
@@ -128,7 +137,7 @@ __global__ __launch_bounds__(512, 2) void conv_bf16_wide_kernel(const WideArgs a
             stage = stage + 1 == NS ? 0 : stage + 1;
             ld_j0 += 8;
             soff_a += 128;
-            if (ld_j0 == a.row_chunks) { ld_j0 = 0; soff_a += (a.run_chunks - a.row_chunks) * 16; }
+            if (ld_j0 == row_chunks) { ld_j0 = 0; soff_a += row_gap; }
             if (++ld_s == slices) {
                 ld_s = ld_j0 = soff_a = 0;
                 if (++ld_t < walk.count) tile_setup(walk.tile(ld_t));
@@ -193,6 +202,8 @@ __global__ __launch_bounds__(512, 2) void conv_bf16_wide_kernel(const WideArgs a
         int quad_ = quad, n_lane = nt * BN + n0 + l16;
         asm volatile("" : "+v"(quad_), "+v"(n_lane));    // (keeps what the store needs per lane out of the registers of the loop)
         const int mw = mt * BM + m0;
+        uint16_t* const y0 = a.y_seg[0], * const y1 = a.y_seg[1], * const y2 = a.y_seg[2], * const y3 = a.y_seg[3];
+        const int c0 = a.ctot_seg[0], c1 = a.ctot_seg[1], c2 = a.ctot_seg[2], c3 = a.ctot_seg[3];
 #pragma unroll
         for (int i = 0; i < TM; i += 2) {
             const bool two = i + 1 < TM;
@@ -201,8 +212,8 @@ __global__ __launch_bounds__(512, 2) void conv_bf16_wide_kernel(const WideArgs a
             // with two blocks, after the exchange: 8 filters of block i + (quad >> 1)
             const int mb = two ? mw + i * 16 + quad_ * 8 : mw + i * 16 + quad_ * 4;
             const bool s1 = mb >= a.split_end[0], s2 = mb >= a.split_end[1], s3 = mb >= a.split_end[2];
-            uint16_t* const base = (s3 ? a.y_seg[3] : s2 ? a.y_seg[2] : s1 ? a.y_seg[1] : a.y_seg[0]) + mb;
-            const int ctot = s3 ? a.ctot_seg[3] : s2 ? a.ctot_seg[2] : s1 ? a.ctot_seg[1] : a.ctot_seg[0];
+            uint16_t* const base = (s3 ? y3 : s2 ? y2 : s1 ? y1 : y0) + mb;
+            const int ctot = s3 ? c3 : s2 ? c2 : s1 ? c1 : c0;
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
                 const int n = n_lane + j * 16;
@@ -254,6 +265,38 @@ __global__ __launch_bounds__(512, 2) void conv_bf16_wide_kernel(const WideArgs a
 }
 
 template <int TM, int TN>
+__global__ __launch_bounds__(512, 2) void conv_bf16_wide_kernel(const WideArgs a)
+{
+    __shared__ __attribute__((aligned(1024))) unsigned char ring[WIDE_STAGES * (TM + TN) * 4096];
+    __shared__ __attribute__((aligned(16))) u32x2 table[WIDE_TABLE];
+    __shared__ __attribute__((aligned(16))) float bias_lds[TM * 32];
+    wide_tiles<TM, TN>(a, (int)blockIdx.x, ring, table, bias_lds);
+}
+
+// Several layers side by side, each with a tile of its own and its share of the compute units.  (The job is copied, as in conv_bf16_small.hip.)
+struct WideGroupArgs {
+    int first[SMALL_GROUP_MAX];                          // first workgroup of each layer, a multiple of 8; beyond the last: INT_MAX
+    int tile[SMALL_GROUP_MAX];                           // its place in WIDE_TILES
+    WideArgs job[SMALL_GROUP_MAX];
+};
+__global__ __launch_bounds__(512, 2) void conv_bf16_wide_group_kernel(const WideGroupArgs args)
+{
+    __shared__ __attribute__((aligned(1024))) unsigned char ring[WIDE_STAGES * 12 * 4096];
+    __shared__ __attribute__((aligned(16))) u32x2 table[WIDE_TABLE];
+    __shared__ __attribute__((aligned(16))) float bias_lds[7 * 32];
+    static_assert(SMALL_GROUP_MAX == 4, "jobs");
+    const int ji = ((int)blockIdx.x >= args.first[1]) + ((int)blockIdx.x >= args.first[2]) + ((int)blockIdx.x >= args.first[3]);
+    const WideArgs a = args.job[ji];
+    const int block = (int)blockIdx.x - args.first[ji];
+    if (block >= a.wk.gn * a.wk.grid_m) return;
+#define DR_TILE(T) case T: wide_tiles<WIDE_TILES[T][0], WIDE_TILES[T][1]>(a, block, ring, table, bias_lds); break
+    switch (args.tile[ji]) {
+    DR_TILE(0); DR_TILE(1); DR_TILE(2); DR_TILE(3); DR_TILE(4); DR_TILE(5); DR_TILE(6); DR_TILE(7); DR_TILE(8); DR_TILE(9); DR_TILE(10); DR_TILE(11); DR_TILE(12); DR_TILE(13);
+    }
+#undef DR_TILE
+}
+
+template <int TM, int TN>
 int launch_tile(WideArgs a, hipStream_t st)
 {
     constexpr int BM = TM * 32, BN = TN * 32;
@@ -267,17 +310,22 @@ int launch_tile(WideArgs a, hipStream_t st)
 // besides.  Fitted to 14 tiles on 60 layers; over these 10 tiles on 80 layers the time is the model's + 1.9 us, 6 % off on average, and
 // the tile that it picks takes 1.01 times as long as the best one on average, 1.25 at worst (3x3 512 -> 40 on 43 x 40 x 103: 64 x 160 209 us, 128 x 128 167).
 struct WideTile { int m, n, rounds; float us; };
-const int WIDE_TILES[][2] = {{5, 7}, {4, 7}, {7, 4}, {6, 5}, {3, 7}, {6, 4}, {4, 4}, {2, 7}, {2, 5}, {4, 3}};
+
+float tile_us(int tm, int tn, int slices)
+{
+    const float mn = (float)(tm * tn * 1024);
+    return slices * std::max(0.644f * mn / 32768.f, 12.85f * (tm + tn) / 256.f) + 0.54f + 1.2f * mn / 10000.f;
+}
 
 WideTile wide_tile(int K, int Ng, int slices)
 {
     WideTile best{0, 0, 0, 1e30f};
     const int cus = device_cus();
-    for (const auto& t : WIDE_TILES) {
+    for (int i = 0; i < WIDE_ALONE; ++i) {
+        const int* const t = WIDE_TILES[i];
         const int bm = t[0] * 32, bn = t[1] * 32, grid_m = (K + bm - 1) / bm, grid_n = (Ng + bn - 1) / bn, gn = std::min(std::max(cus / grid_m, 1), grid_n);
         const int rounds = (grid_n + gn - 1) / gn * ((gn * grid_m + cus - 1) / cus);
-        const float slice = std::max(0.644f * bm * bn / 32768.f, 12.85f * (bm + bn) / 8192.f);
-        const float us = rounds * (slices * slice + 0.54f + 1.2f * bm * bn / 10000.f);
+        const float us = rounds * tile_us(t[0], t[1], slices);
         if (us < best.us) best = WideTile{t[0], t[1], rounds, us};
     }
     return best;
@@ -317,7 +365,7 @@ bool conv_bf16_wide_fills(const ConvGeom& g)
     return 2 * groups > cus && 10 * groups <= 11 * cus && wide_tile(g.K, g.Ng, chunk_slices(g.R, g.S, g.C, &row_chunks)).rounds == 1;
 }
 
-int launch_conv_bf16_wide(const ConvGeom& g, const uint16_t* x, const uint16_t* w, const float* bias, uint16_t* y, hipStream_t st, const ConvSplit* split)
+static WideArgs wide_args(const ConvGeom& g, const uint16_t* x, const uint16_t* w, const float* bias, uint16_t* y, const ConvSplit* split)
 {
     WideArgs a{};
     a.x = x; a.w = w; a.bias = bias;
@@ -337,6 +385,90 @@ int launch_conv_bf16_wide(const ConvGeom& g, const uint16_t* x, const uint16_t* 
     a.step_p = 32 % (g.P * g.Q) / g.Q;
     a.step_q = 32 % g.Q;
     set_destinations(a, split, y, g.y_ctot, g.y_coff);
+    return a;
+}
+
+// A layer that may share a launch of wide tiles: what conv_bf16_wide_takes asks of the addresses, any filter count and contraction that fits the table
+bool conv_bf16_wide_joins(const ConvGeom& g, const void* x, const void* w, const void* y, const ConvSplit* split)
+{
+    int row_chunks;
+    if (!conv_bf16_dma_eligible(g, x, w) || g.K % 8 != 0 || g.Ng == 0 || chunk_slices(g.R, g.S, g.C, &row_chunks) * 8 > WIDE_TABLE) return false;
+    if (split && split->n > 1) {
+        for (int d = 0; d < split->n; ++d)
+            if (split->dst[d].ctot % 8 != 0 || split->dst[d].c_offset % 8 != 0 || split->dst[d].k % 8 != 0 || !aligned16(split->dst[d].y)) return false;
+        return true;
+    }
+    return g.y_ctot % 8 == 0 && g.y_coff % 8 == 0 && aligned16(y);
+}
+
+// Every layer's tile and workgroups so that the slowest layer is done as soon as possible: the shortest time T, by halving (to 1/256 of where it starts:
+// closer than the model is), at which the layers' least numbers of workgroups -- rounds of each tile that fit T -- add up to at most the compute units.
+// What is added to T by a launch is 2.5 to 4.5 us (kernel trace of 112 modules).  About 2 us on the host for three layers.
+static void wide_plan(const ConvSmall* jobs, int n, int* tile, int* gn)
+{
+    const int cus = device_cus();
+    struct Option { int grid_m, grid_n; float us; } opt[SMALL_GROUP_MAX][WIDE_TILE_COUNT];
+    float lo = 0.f, hi = 0.f;
+    for (int i = 0; i < n; ++i) {
+        const ConvGeom& g = jobs[i].g;
+        int row_chunks;
+        const int slices = chunk_slices(g.R, g.S, g.C, &row_chunks);
+        float least = 1e30f, longest = 0.f;
+        for (int t = 0; t < WIDE_TILE_COUNT; ++t) {
+            const int bm = WIDE_TILES[t][0] * 32, bn = WIDE_TILES[t][1] * 32;
+            Option& o = opt[i][t];
+            o = Option{(g.K + bm - 1) / bm, (g.Ng + bn - 1) / bn, tile_us(WIDE_TILES[t][0], WIDE_TILES[t][1], slices)};
+            least = std::min(least, o.us * o.grid_m * o.grid_n);
+            longest = std::max(longest, o.us);
+        }
+        lo += least / cus;
+        hi += 2.f * least / cus + longest;
+    }
+    auto fits = [&](float T) {
+        int sum = 0, tl[SMALL_GROUP_MAX], gw[SMALL_GROUP_MAX];
+        for (int i = 0; i < n; ++i) {
+            int best = cus + 1;
+            for (int t = 0; t < WIDE_TILE_COUNT; ++t) {
+                const Option& o = opt[i][t];
+                if (o.us > T) continue;
+                const int rounds = (int)(T / o.us), w = (o.grid_n + rounds - 1) / rounds, blocks = (w * o.grid_m + 7) / 8 * 8;
+                if (blocks < best) { best = blocks; tl[i] = t; gw[i] = w; }
+            }
+            sum += best;
+        }
+        if (sum > cus) return false;
+        for (int i = 0; i < n; ++i) { tile[i] = tl[i]; gn[i] = gw[i]; }
+        return true;
+    };
+    while (!fits(hi)) hi *= 2.f;
+    for (int k = 0; k < 8; ++k) {
+        const float T = 0.5f * (lo + hi);
+        (fits(T) ? hi : lo) = T;
+    }
+}
+
+int launch_conv_bf16_wide_group(const ConvSmall* jobs, int n, hipStream_t st)
+{
+    WideGroupArgs a{};
+    int tile[SMALL_GROUP_MAX], gn[SMALL_GROUP_MAX], blocks = 0;
+    wide_plan(jobs, n, tile, gn);
+    for (int i = 0; i < SMALL_GROUP_MAX; ++i) {
+        a.first[i] = i < n ? blocks : 0x7FFFFFFF;
+        if (i >= n) continue;
+        const ConvSmall& c = jobs[i];
+        const int bm = WIDE_TILES[tile[i]][0] * 32, bn = WIDE_TILES[tile[i]][1] * 32, grid_m = (c.g.K + bm - 1) / bm;
+        a.tile[i] = tile[i];
+        a.job[i] = wide_args(c.g, (const uint16_t*)c.x, (const uint16_t*)c.w, c.bias, (uint16_t*)c.y, c.split);
+        a.job[i].wk = make_walk(grid_m, gn[i], (c.g.Ng + bn - 1) / bn);
+        blocks += (gn[i] * grid_m + 7) / 8 * 8;
+    }
+    hipLaunchKernelGGL(conv_bf16_wide_group_kernel, dim3((unsigned)blocks), dim3(512), 0, st, a);
+    return check_launch("conv_bf16_wide_group");
+}
+
+int launch_conv_bf16_wide(const ConvGeom& g, const uint16_t* x, const uint16_t* w, const float* bias, uint16_t* y, hipStream_t st, const ConvSplit* split)
+{
+    const WideArgs a = wide_args(g, x, w, bias, y, split);
     const WideTile t = wide_tile(g.K, g.Ng, a.slices);
     switch (t.m * 10 + t.n) {
     case 57: return launch_tile<5, 7>(a, st);

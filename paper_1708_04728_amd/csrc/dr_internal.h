@@ -114,8 +114,13 @@ bool conv_bf16_wide_takes(const ConvGeom& g, const void* x, const void* w, const
 bool conv_bf16_wide_fills(const ConvGeom& g);      // rather than the kernels with an input patch
 int launch_conv_bf16_wide(const ConvGeom& g, const uint16_t* x, const uint16_t* w, const float* bias, uint16_t* y, hipStream_t st, const ConvSplit* split);
 
+// several layers in one launch of wide tiles
+bool conv_bf16_wide_joins(const ConvGeom& g, const void* x, const void* w, const void* y, const ConvSplit* split);
+int launch_conv_bf16_wide_group(const ConvSmall* jobs, int n, hipStream_t st);
+
 bool conv_bf16_small_takes(const ConvGeom& g, const void* x, const void* w);
 int launch_conv_bf16_small(const ConvSmall* jobs, int n, hipStream_t st);
+bool conv_bf16_small_crowded(const ConvSmall* jobs, int n);      // several layers, more than a 64 x 64 tile per compute unit
 
 // conv_bf16_chain.hip: the expanding 1x1 convolution of a folded bottleneck with its shortcut, and the first layer of the bottleneck
 // behind it.  bf16 channels-last; filters [k][c].

@@ -163,3 +163,34 @@ def test_stacked_first_steps():
     torch.cuda.synchronize()
     assert torch.isfinite(out[0].float()).all() and float(out[0].float().abs().max()) > 0
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("n,c,h,w,widths", [
+    # 1x1 | reduce, 3x3 | reduce, 5x5 | pool projection
+    (40, 64, 14, 14, (64, 96, 208, 16, 48, 64)),            # small layers that crowd the device
+    (3, 24, 61, 67, (8, 40, 232, 24, 32, 8)),               # eight filters, eight filters more than a block of 224, a pixel tile that is not whole
+    (90, 32, 13, 15, (256, 160, 320, 32, 128, 128)),        # several rounds
+    (25, 200, 15, 13, (72, 56, 104, 8, 16, 20)),            # a projection of 20 filters, which stays out
+    (17, 40, 28, 28, (24, 360, 48, 344, 40, 48)),           # 5x5 on 344 channels: more chunks than the table holds
+    (128, 16, 7, 7, (384, 24, 384, 48, 128, 128)),
+])
+def test_layers_of_a_depth_share_a_launch(n, c, h, w, widths):
+    """A module whose layers at one depth share a launch of wide tiles, in every mode: the bits of one launch per layer (which is what a
+    kernel trace makes the library do), and the oracle's result on its first and last image."""
+    from test_gpu_bf16_nets import run_net_bf16
+    a, b3, k3, b5, k5, pp = widths
+    conv, relu = workloads.conv, workloads.relu
+    layer = ("inception", {"branches": [[conv(a, 1), relu()], [conv(b3, 1), relu(), conv(k3, 3, 1, 1), relu()], [conv(b5, 1), relu(), conv(k5, 5, 1, 2), relu()],
+                                        [workloads.maxpool(3, 1, 1), conv(pp, 1), relu()]]})
+    rng = np.random.default_rng(case_seed((n, c, h, w, widths)))
+    x = workloads.round_to_bf16(np.abs(rng.standard_normal((n, c, h, w))).astype(np.float32))
+    params = []
+    workloads._walk(rng, [layer], c, "bf16", params)
+    base = B.DR_FUSE_RELU | B.DR_FUSE_CONCAT
+    B.trace_begin()
+    plain = run_net_bf16([layer], params, x, inception_mode=base)
+    B.trace_end()
+    for mode in (0, B.DR_CONCURRENT_BRANCHES, B.DR_FUSE_RELU, base, base | B.DR_CONCURRENT_BRANCHES):
+        assert np.array_equal(run_net_bf16([layer], params, x, inception_mode=mode), plain), mode
+    pick = [0, n - 1]
+    assert close(plain[pick], oracle.forward([layer], params, x[pick], mirror_bf16=True), 2e-2)
