@@ -851,13 +851,13 @@ int param_count(const dr_layer_desc& L)
 
 // ResNet bottleneck.  Original form: conv, BatchNorm(+Scale) and ReLU are separate passes and the
 // residual sum is its own kernel; folded (slim) form: three or four convolutions with folded
-// parameters, ReLU and the residual sum applied in the convolutions' stores -- in bf16 the last one, the projected shortcut and
-// the first layer of a folded bottleneck behind this one as one kernel where that takes them (not while a trace times every layer).
-// next, next_prm (may be NULL): that bottleneck and its parameters; its first output is then left at the start of the scratch
-// memory, where the next call (first_done) finds it, and *next_done set.
+// parameters, ReLU and the residual sum applied in the convolutions' stores -- in bf16 the last one, the projected shortcut or the
+// 3x3 layer, and the first layer of a folded bottleneck behind this one as one kernel where that takes them (not while a trace times every layer).
+// next, next_prm (may be NULL): that bottleneck and its parameters; *next_first is then where in the scratch memory its first layer's output is,
+// and the next call gets it as first (NULL: that layer has not run).
 int bottleneck_run(const dr_tensor& xd, const void* x, const dr_bottleneck& bd, const void* const* prm, const dr_tensor& yd,
-                   void* y, Arena& ar, hipStream_t st, const dr_bottleneck* next = nullptr, const void* const* next_prm = nullptr, bool first_done = false,
-                   bool* next_done = nullptr)
+                   void* y, Arena& ar, hipStream_t st, const dr_bottleneck* next = nullptr, const void* const* next_prm = nullptr, void* first = nullptr,
+                   void** next_first = nullptr)
 {
     const char* who = "dr_net_fwd(bottleneck)";
     const bool run = !ar.measure;
@@ -878,32 +878,45 @@ int bottleneck_run(const dr_tensor& xd, const void* x, const dr_bottleneck& bd, 
     auto P = [&](int group, int j) { return prm[group * per + j]; };
     auto F = [&](int group, int j) { return (const float*)prm[group * per + j]; };
     if (bd.folded) {
-        if (!first_done) DR_TRY(conv_run(who, xd, x, ca, P(0, 0), F(0, 1), nullptr, 0, ta, sa, 0, st));
-        DR_TRY(conv_run(who, ta, sa, cb, P(1, 0), F(1, 1), nullptr, 0, tb, sb, 0, st));
+        // m: the 3x3 layer's input, in one of the scratch buffers; other: memory of at least that size that does not overlap it (the blocks of a
+        // chain are never wider than the one in front, so a buffer that one left m in starts no earlier than sb)
+        void* const m = first ? first : sa;
+        void* const other = m == sa ? sb : sa;
+        if (!first) DR_TRY(conv_run(who, xd, x, ca, P(0, 0), F(0, 1), nullptr, 0, ta, m, 0, st));
         if (xd.dtype == DR_BF16 && xd.layout == DR_NHWC && bd.filter_layout == DR_KRSC && !g_trace.active) {
             ConvChain c{};
             c.pixels = tb.n * tb.h * tb.w; c.mid = bd.mid; c.out = bd.out; c.c_in = xd.c;
-            c.m = (const uint16_t*)sb; c.x = (const uint16_t*)x; c.y = (uint16_t*)y;
+            c.m = (const uint16_t*)other; c.x = (const uint16_t*)x; c.y = (uint16_t*)y;
             c.w = (const uint16_t*)P(2, 0); c.bias = F(2, 1);
             if (bd.project) { c.w_proj = (const uint16_t*)P(3, 0); c.bias_proj = F(3, 1); }
-            ConvChain both = c;
-            // (the 3x3 layer has read sa, so m_next may take its place)
-            if (next && next->folded && next->filter_layout == DR_KRSC && next->mid <= bd.mid) {
-                both.w_next = (const uint16_t*)next_prm[0]; both.bias_next = (const float*)next_prm[1];
-                both.next = next->mid; both.m_next = (uint16_t*)sa;
+            // with the 3x3 layer: it reads m, so what the next block starts from goes to the other buffer; behind it: to m's place
+            for (const bool mid : {true, false}) {
+                ConvChain one = c;
+                void* free = m;
+                if (mid) {
+                    one.m = (const uint16_t*)m; one.h_map = tb.h; one.w_map = tb.w;
+                    one.w_mid = (const uint16_t*)P(1, 0); one.bias_mid = F(1, 1);
+                    free = other;
+                }
+                ConvChain both = one;
+                if (next && next->folded && next->filter_layout == DR_KRSC && next->mid <= bd.mid) {
+                    both.w_next = (const uint16_t*)next_prm[0]; both.bias_next = (const float*)next_prm[1];
+                    both.next = next->mid; both.m_next = (uint16_t*)free;
+                }
+                const bool joined = both.w_next && conv_bf16_chain_eligible(both);
+                if (!joined && !conv_bf16_chain_eligible(one)) continue;
+                if (!mid) DR_TRY(conv_run(who, ta, m, cb, P(1, 0), F(1, 1), nullptr, 0, tb, other, 0, st));
+                if (joined) *next_first = free;
+                return launch_conv_bf16_chain(joined ? both : one, st);
             }
-            if (both.w_next && conv_bf16_chain_eligible(both)) {
-                *next_done = true;
-                return launch_conv_bf16_chain(both, st);
-            }
-            if (conv_bf16_chain_eligible(c)) return launch_conv_bf16_chain(c, st);
         }
+        DR_TRY(conv_run(who, ta, m, cb, P(1, 0), F(1, 1), nullptr, 0, tb, other, 0, st));
         const void* shortcut = x;
         if (bd.project) {
             DR_TRY(conv_run(who, xd, x, cp, P(3, 0), F(3, 1), nullptr, 0, tc, sp, 0, st));
             shortcut = sp;
         }
-        return conv_run(who, tb, sb, cc, P(2, 0), F(2, 1), shortcut, tc.c, yd, y, 0, st);
+        return conv_run(who, tb, other, cc, P(2, 0), F(2, 1), shortcut, tc.c, yd, y, 0, st);
     }
     auto conv_bn = [&](const dr_tensor& in, const void* src, const dr_conv& c, int grp, const dr_tensor& o, void* dst, bool relu) -> int {
         DR_TRY(conv_run(who, in, src, c, P(grp, 0), F(grp, 1), nullptr, 0, o, dst, 0, st));
@@ -1610,7 +1623,7 @@ int dr_net_fwd(dr_net* net, const dr_tensor* xd, const void* x, const void* cons
     int cur_buf = -1;   // -1: the caller's input (read only)
     dr_tensor t = *xd;
     int pi = 0;
-    bool first_done = false;           // the previous bottleneck's last kernel ran this one's first layer too
+    void* first = nullptr;             // the output of this bottleneck's first layer, where the previous one's last kernel ran that too
     const size_t nl = net->layers.size();
     net->timed_valid = false;
     if (net->timing && hipEventRecord(net->events[0], st) != hipSuccess) return fail(DR_ERR_HIP, "%s: hipEventRecord failed", who);
@@ -1673,10 +1686,11 @@ int dr_net_fwd(dr_net* net, const dr_tensor* xd, const void* x, const void* cons
             break;
         }
         case DR_LAYER_BOTTLENECK: {
-            const bool pair = !last && net->layers[i + 1].kind == DR_LAYER_BOTTLENECK, done = first_done;
-            first_done = false;
+            const bool pair = !last && net->layers[i + 1].kind == DR_LAYER_BOTTLENECK;
+            void* const here = first;
+            first = nullptr;
             DR_TRY(bottleneck_run(t, cur, L.bottleneck, params + pi, od, dst, ar, st, pair ? &net->layers[i + 1].bottleneck : nullptr,
-                                  params + pi + param_count(L), done, &first_done));
+                                  params + pi + param_count(L), here, &first));
             break;
         }
         case DR_LAYER_FC:

@@ -127,7 +127,10 @@ bool conv_bf16_small_crowded(const ConvSmall* jobs, int n);      // several laye
 constexpr int CHAIN_MID = 64, CHAIN_OUT = 256;      // most channels of m, m_next (and of x with w_proj); of y
 struct ConvChain {
     int pixels, mid, out, c_in, next;
-    const uint16_t *m, *x;                   // the 3x3 layer's output; the block's input
+    int h_map, w_map;                        // the map's size (read with w_mid)
+    const uint16_t *m, *x;                   // the 3x3 layer's output (with w_mid: its input); the block's input
+    const uint16_t* w_mid;                   // the 3x3 layer, computed here too; NULL: it has run
+    const float* bias_mid;
     const uint16_t *w, *w_proj, *w_next;     // w_proj NULL: the shortcut is x itself; w_next NULL: no layer behind
     const float *bias, *bias_proj, *bias_next;      // may be NULL
     uint16_t *y, *m_next;

@@ -44,6 +44,11 @@ def stage(rng, c, blocks):
     (11, 64, 61, 59, ((64, 256), (64, 256), (64, 256))),       # 1238 blocks, the last one not whole: by lines, through LDS
     (10, 24, 55, 61, ((40, 72), (24, 72), (24, 200), (8, 200))),        # ... with ragged channel groups
     (23, 56, 61, 59, ((64, 248), (64, 248))),                  # ... several rounds of every wave
+    (5, 64, 7, 63, ((64, 256), (64, 256), (64, 256))),         # the widest map whose 3x3 layers are joined too
+    (2, 64, 33, 64, ((64, 256), (64, 256))),                   # ... and the first one on which they are not
+    (1, 64, 300, 1, ((64, 200), (64, 200))),                   # rows of one pixel, ragged output groups
+    (3, 64, 1, 57, ((64, 72), (64, 72), (32, 72), (32, 72))),  # images of one row; narrower blocks behind
+    (19, 64, 30, 58, ((64, 256), (64, 256), (32, 256))),       # 259 tiles of 128 pixels: a second round for three workgroups
 ])
 def test_chain(case):
     n, c, h, w, blocks = case
@@ -112,3 +117,32 @@ def test_the_projected_shortcut_is_stored_only_where_the_kernel_does_not_run(c, 
         part = ws[max(lo, base + 2 * max(mid for mid, _ in sizes)):hi]
         assert part.numel() > 0
         assert bool((part == 255).all()) == (joined and not traced), (traced, joined)
+
+
+@pytest.mark.parametrize("mid,w,joined", [(64, 1, True), (64, 63, True), (64, 64, False), (56, 63, False)])
+def test_the_middle_layer_is_stored_only_where_the_kernel_does_not_run_it(mid, w, joined):
+    """Which way the 3x3 layer of a block without a projection went, by the scratch memory of its output."""
+    n, h, c = 2, 5, 256
+    rng = np.random.default_rng(mid + w)
+    params = []
+    for k, r, ci in ((mid, 1, c), (mid, 3, mid), (c, 1, mid)):
+        wt = rng.standard_normal((k, ci, r, r)).astype(np.float32) * np.float32(np.sqrt(2.0 / (ci * r * r)))
+        params += [{"w": wt, "b": (rng.standard_normal(k) * 0.1).astype(np.float32)}, bn(k, rng)]
+    params = folded_params(params)
+    layers = [workloads.bottleneck(mid, c, False)]
+    x = workloads.round_to_bf16(np.abs(rng.standard_normal((n, c, h, w))).astype(np.float32))
+    xg = G.to_device(x, "bf16", nhwc=True)
+    net = B.Net(G.net_descs(layers, c, folded=True, pack="bf16"))
+    flat = G.flat_params(params, "bf16", pack=True)
+    y = G.empty_like_desc(net.output_desc(B.desc(xg)))
+    # the scratch of a block: the outputs of its first and second layer, each from a multiple of 256 bytes
+    size = n * h * w * mid * 2
+    step = (size + 255) // 256 * 256
+    ws = torch.full((net.workspace_bytes(B.desc(xg)),), 255, dtype=torch.uint8, device="cuda")
+    net.fwd(xg, flat, y, ws)
+    torch.cuda.synchronize()
+    base = ws.numel() - 2 * step
+    assert not bool((ws[base:base + size] == 255).all())
+    assert bool((ws[base + step:base + step + size] == 255).all()) == joined
+    ref = oracle.forward(layers, params, x, mirror_bf16=True, fold="given")
+    assert close(G.to_host(y), ref, TOL_BF16 * 3 ** 0.5, "oracle with bf16 storage")      # as above, one block
