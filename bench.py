@@ -450,7 +450,7 @@ class Workload:
             # The same forward as a HIP graph (dr_net_capture): one launch per forward.  Inside a graph the branches of
             # a module run side by side without the events between queues that this costs kernel by kernel, so the
             # forms that keep all four branches (original, fused) are captured in that mode; the slim form's two
-            # branches gain nothing from it.
+            # branches gain nothing from it.  (bf16 modules run level by level in either mode.)
             gnet = net
             if fused and any(kind == "inception" for kind, _ in layers):
                 gnet = B.Net(G.net_descs(layers, c_in, inception_mode=B.DR_FUSE_RELU | B.DR_FUSE_CONCAT | B.DR_FUSE_STACK | B.DR_CONCURRENT_BRANCHES,
