@@ -442,7 +442,7 @@ bool small_takes(int dtype, const ConvGeom& g, const void* x, const void* w)
 // The stacked first steps of a module (see inception_run).  Marks the branches it has served in `stacked`
 // and leaves their step-0 outputs in `dst` (workspace buffers; NULL for a one-step branch that wrote y).
 // Serves nothing, without error, when the parameters are not laid out for it.  sp: destinations of the stacked layer; job
-// (may be NULL): a layer that the small-layer kernel takes is not launched but left there for the caller (job->w set).
+// (may be NULL): a layer that the small-layer kernel or, in bf16, wide tiles take is not launched but left there for the caller (job->w set).
 int run_stacked_first_steps(const dr_tensor& xd, const void* x, const dr_inception& d, const ParamCursor& wts, const ParamCursor& bss,
                             const dr_tensor& yd, void* y, Arena& ar, hipStream_t st, bool* stacked, void** dst, ConvSplit& sp, ConvSmall* job)
 {
@@ -512,12 +512,31 @@ int run_stacked_first_steps(const dr_tensor& xd, const void* x, const dr_incepti
     }
     g.y_ctot = sp.dst[0].ctot; g.y_coff = sp.dst[0].c_offset;
     const ConvSmall small{g, x, w0, (const float*)b0, nullptr, sp.dst[0].y, &sp};
-    if (job && small_takes(f32 ? DR_F32 : DR_BF16, g, x, w0)) { *job = small; return DR_OK; }
+    if (job && (small_takes(f32 ? DR_F32 : DR_BF16, g, x, w0) || (!f32 && conv_bf16_wide_takes(g, x, w0, nullptr, sp.dst[0].y, &sp)))) { *job = small; return DR_OK; }
     if (f32)
         return launch_conv_f32(g, (const float*)x, (const float*)w0, (const float*)b0, nullptr, (float*)sp.dst[0].y, st, nullptr, 0, &sp);
     TraceScope trace("conv_bf16", &g, g.Ng, st);
     if (conv_bf16_small_takes(g, x, w0)) return launch_conv_bf16_small(&small, 1, st);
     return launch_conv_bf16_dma(g, (const uint16_t*)x, (const uint16_t*)w0, (const float*)b0, nullptr, (uint16_t*)sp.dst[0].y, st, &sp);
+}
+
+// A 3x3 pooling step's sizes as a convolution kernel's
+ConvGeom pool_geom(const dr_tensor& t, const dr_tensor& o, const dr_pool& p)
+{
+    ConvGeom g{};
+    g.N = t.n; g.C = g.K = t.c; g.H = t.h; g.W = t.w;
+    g.R = g.S = 3; g.sh = p.stride_h; g.sw = p.stride_w; g.ph = p.pad_h; g.pw = p.pad_w;
+    g.P = o.h; g.Q = o.w; g.Ng = (int)((long)o.n * o.h * o.w);
+    return g;
+}
+
+// A max-pooling step as a job of the small-layer kernel: 3x3 windows, whole 16-byte channel groups, few pixels.
+bool small_pool_job(const dr_tensor& t, const void* x, const dr_tensor& o, void* y, const dr_pool& p, ConvSmall* job)
+{
+    const long ng = (long)o.n * o.h * o.w;
+    if (t.dtype != DR_BF16 || p.kh != 3 || p.kw != 3 || t.c % 8 != 0 || (((uintptr_t)x | (uintptr_t)y) & 15) != 0 || ng == 0 || ng > 4096 || (long)o.h * o.w > 65536) return false;
+    *job = ConvSmall{pool_geom(t, o, p), x, nullptr, nullptr, nullptr, y, nullptr};
+    return true;
 }
 
 // A module step by step instead of branch by branch: the convolutions at the same depth of the branches (and a 3x3 pooling
@@ -529,6 +548,7 @@ struct StepGroup {
     int dtype;
     int n = 0, n_big = 0;
     ConvSmall jobs[SMALL_GROUP_MAX], big[SMALL_GROUP_MAX];
+    struct { bool set = false; dr_tensor t, o; const void* x; void* y; dr_pool p; ConvSmall job; } pool;     // a pooling step that waits for the depth's layers
     int flush_small()
     {
         const int k = n;
@@ -562,8 +582,36 @@ struct StepGroup {
             }
             n = kept;
         }
+        if (pool.set) {
+            pool.set = false;
+            const bool wide = n_big > 1 || (n_big == 1 && conv_bf16_wide_takes(big[0].g, big[0].x, big[0].w, nullptr, big[0].y, big[0].split));
+            ConvSmall job{};
+            if (wide) {
+                const int k = n_big;
+                n_big = 0;
+                DR_TRY(launch_conv_bf16_wide_group(big, k, st, &pool.job));
+            } else if (small_pool_job(pool.t, pool.x, pool.o, pool.y, pool.p, &job)) {
+                DR_TRY(add(job));
+            } else {
+                DR_TRY(launch_maxpool(pool.t, pool.x, pool.o, pool.y, pool.p, st));
+            }
+        }
         DR_TRY(flush_big());
         return flush_small();
+    }
+    int add_pool(const dr_tensor& t, const void* x, const dr_tensor& o, void* y, const dr_pool& p)
+    {
+        if (dtype == DR_BF16 && !pool.set && p.kh == 3 && p.kw == 3 && (long)o.n * o.h * o.w < (1l << 31)) {
+            pool.job = ConvSmall{pool_geom(t, o, p), x, nullptr, nullptr, nullptr, y, nullptr};
+            if (conv_bf16_wide_pools(pool.job)) {
+                pool.t = t; pool.o = o; pool.x = x; pool.y = y; pool.p = p;
+                pool.set = true;
+                return DR_OK;
+            }
+        }
+        ConvSmall job{};
+        if (small_pool_job(t, x, o, y, p, &job)) return add(job);
+        return launch_maxpool(t, x, o, y, p, st);
     }
     int add(const ConvSmall& j)
     {
@@ -595,19 +643,6 @@ size_t module_scratch_bytes(const dr_tensor& xd, const dr_conv& cd)
 {
     const size_t bytes = conv_scratch_bytes(xd, cd);
     return bytes && big_takes(xd.dtype, conv_geom(xd, cd, conv_out(xd, cd))) ? 0 : bytes;
-}
-
-// A max-pooling step as a job of the small-layer kernel: 3x3 windows, whole 16-byte channel groups, few pixels.
-bool small_pool_job(const dr_tensor& t, const void* x, const dr_tensor& o, void* y, const dr_pool& p, ConvSmall* job)
-{
-    const long ng = (long)o.n * o.h * o.w;
-    if (t.dtype != DR_BF16 || p.kh != 3 || p.kw != 3 || t.c % 8 != 0 || (((uintptr_t)x | (uintptr_t)y) & 15) != 0 || ng == 0 || ng > 4096 || (long)o.h * o.w > 65536) return false;
-    ConvGeom g{};
-    g.N = t.n; g.C = g.K = t.c; g.H = t.h; g.W = t.w;
-    g.R = g.S = 3; g.sh = p.stride_h; g.sw = p.stride_w; g.ph = p.pad_h; g.pw = p.pad_w;
-    g.P = o.h; g.Q = o.w; g.Ng = (int)ng;
-    *job = ConvSmall{g, x, nullptr, nullptr, nullptr, y, nullptr};
-    return true;
 }
 
 // Whether the module runs level by level, its steps sharing launches: at least two convolutions that can.  In bf16 also where the caller wants the
@@ -653,7 +688,7 @@ int inception_run_levels(const dr_tensor& xd, const void* x, const dr_inception&
     if (d.mode & DR_FUSE_STACK) {
         ConvSmall job{};
         DR_TRY(run_stacked_first_steps(xd, x, d, wts, bss, yd, y, ar, st, stacked, stacked_dst, sp, &job));
-        if (job.w) DR_TRY(group.add(job));
+        if (job.w) DR_TRY(small_takes(xd.dtype, job.g, job.x, job.w) ? group.add(job) : group.add_big(job));
     }
     struct Branch { dr_tensor t; const void* cur; int c_off, param; ConcatSeg seg; } br[DR_MAX_BRANCHES];
     int c_off = 0, param = 0, depth = 0;
@@ -710,9 +745,7 @@ int inception_run_levels(const dr_tensor& xd, const void* x, const dr_inception&
                 o = pool_out(q.t, stp.pool);
                 dst = ar.take(tensor_bytes(o));
                 if (!dst) return fail(DR_ERR_WORKSPACE, "%s: workspace too small", who);
-                ConvSmall job{};
-                if (small_pool_job(q.t, q.cur, o, dst, stp.pool, &job)) DR_TRY(group.add(job));
-                else DR_TRY(launch_maxpool(q.t, q.cur, o, dst, stp.pool, st));
+                DR_TRY(group.add_pool(q.t, q.cur, o, dst, stp.pool));
                 if (last) q.seg = ConcatSeg{dst, o.c, q.c_off};
             }
             q.cur = dst;

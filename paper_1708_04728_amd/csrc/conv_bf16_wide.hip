@@ -291,8 +291,64 @@ __global__ __launch_bounds__(512, 2) void conv_bf16_wide_kernel(const WideArgs a
     wide_tiles<TM, TN>(a, (int)blockIdx.x, ring, table, bias_lds);
 }
 
+// 3x3 max-pooling at stride 1 beside the layers: an item is a strip of POOL_ROWS rows of an output column and 8 channels, whose loads are all on their way
+// before any is used; an image's items are dealt to the lanes in memory order, 512 at a time, and an eighth of them to every die.  Launched before or behind
+// the layers it took 4 to 6 us in which the matrix cores stood still; its share of the compute units is as many as let it end with them, 2.2 us (loads of eight
+// waves and their latency) for each 512 items.  Modules, us, before and with it: 4c fused on 37 images 22.1 and 20.3, on 19 19.8 and 15.7; 4e fused on 19 24.1 and
+// 19.6; 5b fused on 64 26.7 and 22.3; fused GoogLeNet on 19 images 306 and 279.
+constexpr int POOL_ROWS = 4, POOL_ITEMS = 512;
+struct WidePool {
+    const uint16_t* x;
+    uint16_t* y;
+    int C, H, W, P, Q, ph, pw, per_image, groups;        // items and groups of 512 of an image
+    int blocks, per_die, share;                          // groups of 512 of all images; of a die; workgroups of this launch
+    unsigned magic_cv, magic_qcv;
+};
+__device__ __forceinline__ void wide_pool(const WidePool& a, const int block)
+{
+    constexpr int NR = POOL_ROWS + 2;
+    const int cv_n = a.C / 8, qcv = a.Q * cv_n;
+    for (int i = block >> 3; i < a.per_die; i += a.share >> 3) {
+        const int b = (block & 7) * a.per_die + i;
+        if (b >= a.blocks) return;
+        const int img = b / a.groups, item = (b - img * a.groups) * POOL_ITEMS + (int)threadIdx.x;
+        if (item >= a.per_image) continue;
+        const int strip = qcv == 1 ? item : (int)__umulhi((unsigned)item, a.magic_qcv), pair = item - strip * qcv;
+        const int q = cv_n == 1 ? pair : (int)__umulhi((unsigned)pair, a.magic_cv), cv = pair - q * cv_n;
+        const int p0 = strip * POOL_ROWS, h0 = p0 - a.ph, w0 = q - a.pw;
+        const uint16_t* const xb = a.x + (size_t)img * a.H * a.W * a.C + cv * 8;
+        u32x4 raw[NR][3];
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                raw[r][c] = u32x4{0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u};      // -inf
+                if ((unsigned)(h0 + r) < (unsigned)a.H && (unsigned)(w0 + c) < (unsigned)a.W)
+                    raw[r][c] = *reinterpret_cast<const u32x4*>(xb + ((size_t)(h0 + r) * a.W + (w0 + c)) * a.C);
+            }
+        u32x4 o[POOL_ROWS];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float lo[NR], hi[NR];
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                lo[r] = fmaxf(fmaxf(__uint_as_float(raw[r][0][e] << 16), __uint_as_float(raw[r][1][e] << 16)), __uint_as_float(raw[r][2][e] << 16));
+                hi[r] = fmaxf(fmaxf(__uint_as_float(raw[r][0][e] & 0xFFFF0000u), __uint_as_float(raw[r][1][e] & 0xFFFF0000u)), __uint_as_float(raw[r][2][e] & 0xFFFF0000u));
+            }
+#pragma unroll
+            for (int r = 0; r < POOL_ROWS; ++r)
+                o[r][e] = pack_bf16x2(fmaxf(fmaxf(lo[r], lo[r + 1]), lo[r + 2]), fmaxf(fmaxf(hi[r], hi[r + 1]), hi[r + 2]));
+        }
+#pragma unroll
+        for (int r = 0; r < POOL_ROWS; ++r)
+            if (p0 + r < a.P) *reinterpret_cast<u32x4*>(a.y + (((size_t)img * a.P + p0 + r) * a.Q + q) * a.C + cv * 8) = o[r];
+    }
+}
+
 // Several layers side by side, each with a tile of its own and its share of the compute units.  (The job is copied, as in conv_bf16_small.hip.)
 struct WideGroupArgs {
+    int first_pool;                                      // first workgroup of the pooling layer; INT_MAX: none
+    WidePool pool;
     int first[SMALL_GROUP_MAX];                          // first workgroup of each layer, a multiple of 8; beyond the last: INT_MAX
     int tile[SMALL_GROUP_MAX];                           // its place in WIDE_TILES
     WideArgs job[SMALL_GROUP_MAX];
@@ -303,6 +359,11 @@ __global__ __launch_bounds__(512, 2) void conv_bf16_wide_group_kernel(const Wide
     __shared__ __attribute__((aligned(16))) u32x2 table[WIDE_TABLE];
     __shared__ __attribute__((aligned(16))) float bias_lds[7 * 32];
     static_assert(SMALL_GROUP_MAX == 4, "jobs");
+    if ((int)blockIdx.x >= args.first_pool) {
+        const WidePool p = args.pool;
+        wide_pool(p, (int)blockIdx.x - args.first_pool);
+        return;
+    }
     const int ji = ((int)blockIdx.x >= args.first[1]) + ((int)blockIdx.x >= args.first[2]) + ((int)blockIdx.x >= args.first[3]);
     const WideArgs a = args.job[ji];
     const int block = (int)blockIdx.x - args.first[ji];
@@ -422,7 +483,9 @@ bool conv_bf16_wide_joins(const ConvGeom& g, const void* x, const void* w, const
 // Every layer's tile and workgroups so that the slowest layer is done as soon as possible: the shortest time T, by halving (to 1/256 of where it starts:
 // closer than the model is), at which the layers' least numbers of workgroups -- rounds of each tile that fit T -- add up to at most the compute units.
 // What is added to T by a launch is 2.5 to 4.5 us (kernel trace of 112 modules).  About 2 us on the host for three layers.
-static void wide_plan(const ConvSmall* jobs, int n, int* tile, int* gn)
+// pool_blocks: groups of 512 items of a pooling layer beside them (0: none), POOL_US each; *pool_share: its workgroups.
+constexpr float POOL_US = 2.2f;
+static void wide_plan(const ConvSmall* jobs, int n, int* tile, int* gn, int pool_blocks, int* pool_share)
 {
     const int cus = device_cus();
     struct Option { int grid_m, grid_n; float us; } opt[SMALL_GROUP_MAX][WIDE_TILE_COUNT];
@@ -442,8 +505,16 @@ static void wide_plan(const ConvSmall* jobs, int n, int* tile, int* gn)
         lo += least / cus;
         hi += 2.f * least / cus + longest;
     }
+    lo += POOL_US * pool_blocks / cus;
+    hi += 2.f * POOL_US * pool_blocks / cus + POOL_US;
     auto fits = [&](float T) {
-        int sum = 0, tl[SMALL_GROUP_MAX], gw[SMALL_GROUP_MAX];
+        int sum = 0, share = 0, tl[SMALL_GROUP_MAX], gw[SMALL_GROUP_MAX];
+        if (pool_blocks) {
+            if (T < POOL_US) return false;
+            const int rounds = (int)std::min(T / POOL_US, 1e6f);
+            share = ((pool_blocks + rounds - 1) / rounds + 7) / 8 * 8;
+            sum = share;
+        }
         for (int i = 0; i < n; ++i) {
             int best = cus + 1;
             for (int t = 0; t < WIDE_TILE_COUNT; ++t) {
@@ -456,6 +527,7 @@ static void wide_plan(const ConvSmall* jobs, int n, int* tile, int* gn)
         }
         if (sum > cus) return false;
         for (int i = 0; i < n; ++i) { tile[i] = tl[i]; gn[i] = gw[i]; }
+        *pool_share = share;
         return true;
     };
     while (!fits(hi)) hi *= 2.f;
@@ -465,11 +537,31 @@ static void wide_plan(const ConvSmall* jobs, int n, int* tile, int* gn)
     }
 }
 
-int launch_conv_bf16_wide_group(const ConvSmall* jobs, int n, hipStream_t st)
+static int pool_groups(const ConvGeom& g) { return ((g.P + POOL_ROWS - 1) / POOL_ROWS * g.Q * (g.C / 8) + POOL_ITEMS - 1) / POOL_ITEMS; }
+
+// Up to 7/4 groups of 512 items per compute unit: a larger pooling layer fills the device by itself and, bound by memory, takes longer on a share of it
+// (module in original form: 512 channels of 14 x 14 on 64 images, 448 groups, 47.0 us with a launch of its own and 44.0; 28 x 28 x 256 on 37 images, 481, 67.5 and
+// 69.4, on 100, 1300, 142 and 150; fused 3b on 19, 247, 28.3 and 25.5).  The kernel's divisions are exact where an image's items are that few.
+bool conv_bf16_wide_pools(const ConvSmall& c)
+{
+    const ConvGeom& g = c.g;
+    const double qcv = (double)g.Q * (g.C / 8);
+    return !c.w && g.R == 3 && g.S == 3 && g.sh == 1 && g.sw == 1 && g.C % 8 == 0 && g.Ng > 0 && aligned16(c.x) && aligned16(c.y) &&
+           qcv * qcv * (g.P + POOL_ROWS) < 4294967296.0 && 4l * g.N * pool_groups(g) <= 7l * device_cus();
+}
+
+int launch_conv_bf16_wide_group(const ConvSmall* jobs, int n, hipStream_t st, const ConvSmall* pool)
 {
     WideGroupArgs a{};
     int tile[SMALL_GROUP_MAX], gn[SMALL_GROUP_MAX], blocks = 0;
-    wide_plan(jobs, n, tile, gn);
+    a.first_pool = 0x7FFFFFFF;
+    if (pool) {
+        const ConvGeom& g = pool->g;
+        const int cv = g.C / 8, qcv = g.Q * cv, strips = (g.P + POOL_ROWS - 1) / POOL_ROWS, groups = pool_groups(g);
+        a.pool = WidePool{(const uint16_t*)pool->x, (uint16_t*)pool->y, g.C, g.H, g.W, g.P, g.Q, g.ph, g.pw, strips * qcv, groups,
+                          g.N * groups, (g.N * groups + 7) / 8, 0, (unsigned)((0x100000000ull + cv - 1) / cv), (unsigned)((0x100000000ull + qcv - 1) / qcv)};
+    }
+    wide_plan(jobs, n, tile, gn, a.pool.blocks, &a.pool.share);
     for (int i = 0; i < SMALL_GROUP_MAX; ++i) {
         a.first[i] = i < n ? blocks : 0x7FFFFFFF;
         if (i >= n) continue;
@@ -479,6 +571,10 @@ int launch_conv_bf16_wide_group(const ConvSmall* jobs, int n, hipStream_t st)
         a.job[i] = wide_args(c.g, (const uint16_t*)c.x, (const uint16_t*)c.w, c.bias, (uint16_t*)c.y, c.split);
         a.job[i].wk = make_walk(grid_m, gn[i], (c.g.Ng + bn - 1) / bn);
         blocks += (gn[i] * grid_m + 7) / 8 * 8;
+    }
+    if (pool) {
+        a.first_pool = blocks;
+        blocks += a.pool.share;
     }
     hipLaunchKernelGGL(conv_bf16_wide_group_kernel, dim3((unsigned)blocks), dim3(512), 0, st, a);
     return check_launch("conv_bf16_wide_group");

@@ -116,7 +116,8 @@ int launch_conv_bf16_wide(const ConvGeom& g, const uint16_t* x, const uint16_t* 
 
 // several layers in one launch of wide tiles
 bool conv_bf16_wide_joins(const ConvGeom& g, const void* x, const void* w, const void* y, const ConvSplit* split);
-int launch_conv_bf16_wide_group(const ConvSmall* jobs, int n, hipStream_t st);
+bool conv_bf16_wide_pools(const ConvSmall& pool);                // a max-pooling layer (w NULL) that may lie beside them
+int launch_conv_bf16_wide_group(const ConvSmall* jobs, int n, hipStream_t st, const ConvSmall* pool = nullptr);
 
 bool conv_bf16_small_takes(const ConvGeom& g, const void* x, const void* w);
 int launch_conv_bf16_small(const ConvSmall* jobs, int n, hipStream_t st);

@@ -194,3 +194,30 @@ def test_layers_of_a_depth_share_a_launch(n, c, h, w, widths):
         assert np.array_equal(run_net_bf16([layer], params, x, inception_mode=mode), plain), mode
     pick = [0, n - 1]
     assert close(plain[pick], oracle.forward([layer], params, x[pick], mirror_bf16=True), 2e-2)
+
+
+@pytest.mark.parametrize("n,c,h,w,pool", [
+    (400, 8, 21, 1, (3, 1, 1)),              # one column, one channel group: an item per strip; a strip of one row at the end
+    (448, 16, 3, 6, (3, 1, 1)),              # as many groups of items as may lie beside the layers on 256 compute units
+    (449, 16, 3, 6, (3, 1, 1)),              # ... and one more: a launch of its own
+    (60, 520, 13, 11, (3, 1, 1)),            # six groups an image, the last one not whole
+    (8, 40, 1, 1000, (3, 1, 1)),             # rows of which a strip has one
+    (5, 64, 40, 41, (3, 1, 1)),              # a share of few workgroups
+])
+def test_a_pooling_step_beside_the_layers(n, c, h, w, pool):
+    """A module's pooling step in the launch of its first layers: the bits of a launch for each, also of negative values and where windows are cut off."""
+    from test_gpu_bf16_nets import run_net_bf16
+    conv, relu = workloads.conv, workloads.relu
+    layer = ("inception", {"branches": [[conv(256, 1), relu()], [conv(128, 1), relu(), conv(64, 3, 1, 1), relu()], [workloads.maxpool(*pool), conv(64, 1), relu()]]})
+    rng = np.random.default_rng(case_seed((n, c, h, w)))
+    x = workloads.round_to_bf16(rng.standard_normal((n, c, h, w)).astype(np.float32) - 2)
+    params = []
+    workloads._walk(rng, [layer], c, "bf16", params)
+    base = B.DR_FUSE_RELU | B.DR_FUSE_CONCAT
+    B.trace_begin()
+    plain = run_net_bf16([layer], params, x, inception_mode=base)
+    B.trace_end()
+    for mode in (0, base, base | B.DR_CONCURRENT_BRANCHES):
+        assert np.array_equal(run_net_bf16([layer], params, x, inception_mode=mode), plain), mode
+    pick = [0, n - 1]
+    assert close(plain[pick], oracle.forward([layer], params, x[pick], mirror_bf16=True), 2e-2)
