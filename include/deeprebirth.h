@@ -241,7 +241,8 @@ typedef struct { int n_steps; dr_step steps[DR_MAX_STEPS]; } dr_branch;
  * small-layer kernel, or cut over workgroups, and the stacked layer not). */
 #define DR_FUSE_RELU   1   /* ReLU in the convolution's store */
 #define DR_FUSE_CONCAT 2   /* a branch ending in a convolution writes its channel range of y directly
-                              (that convolution then also applies its ReLU in the store) */
+                              (that convolution then also applies its ReLU in the store); channels-last not in
+                              a module one of whose branches ends in a pooling step */
 #define DR_FUSE_STACK  4   /* Eq. (12): first-step 1x1 convolutions (stride 1, no padding, followed by ReLU)
                               that read the module input run as one convolution with stacked filters, each
                               writing its own destination (needs DR_FUSE_RELU).  Taken for bf16 NHWC and

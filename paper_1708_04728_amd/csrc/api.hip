@@ -439,6 +439,16 @@ bool small_takes(int dtype, const ConvGeom& g, const void* x, const void* w)
     return dtype == DR_BF16 ? conv_bf16_small_takes(g, x, w) : conv_f32_small_takes(g, w, true);
 }
 
+// Whether branches that end in a convolution write their channels of y themselves.  Channels-last the concat kernel writes whole pixels, so that not where a
+// branch ends with a pooling step, whose channels it would have to place among the others'.
+bool fuses_concat(const dr_tensor& xd, const dr_inception& d)
+{
+    if (!(d.mode & DR_FUSE_CONCAT)) return false;
+    for (int b = 0; xd.layout == DR_NHWC && b < d.n_branches; ++b)
+        if (d.branches[b].n_steps > 0 && d.branches[b].steps[d.branches[b].n_steps - 1].kind != DR_STEP_CONV) return false;
+    return true;
+}
+
 // The stacked first steps of a module (see inception_run).  Marks the branches it has served in `stacked`
 // and leaves their step-0 outputs in `dst` (workspace buffers; NULL for a one-step branch that wrote y).
 // Serves nothing, without error, when the parameters are not laid out for it.  sp: destinations of the stacked layer; job
@@ -447,7 +457,7 @@ int run_stacked_first_steps(const dr_tensor& xd, const void* x, const dr_incepti
                             const dr_tensor& yd, void* y, Arena& ar, hipStream_t st, bool* stacked, void** dst, ConvSplit& sp, ConvSmall* job)
 {
     const char* who = "dr_inception_fwd";
-    const bool fuse_cat = d.mode & DR_FUSE_CONCAT;
+    const bool fuse_cat = fuses_concat(xd, d);
     int pidx = wts.i, c_off = 0, nb = 0, members[DR_MAX_BRANCHES], coffs[DR_MAX_BRANCHES], pidxs[DR_MAX_BRANCHES];
     for (int b = 0; b < d.n_branches; ++b) {
         const dr_branch& br = d.branches[b];
@@ -679,7 +689,7 @@ int inception_run_levels(const dr_tensor& xd, const void* x, const dr_inception&
                          Arena& ar, hipStream_t st)
 {
     const char* who = "dr_inception_fwd";
-    const bool fuse_relu = d.mode & DR_FUSE_RELU, fuse_cat = d.mode & DR_FUSE_CONCAT;
+    const bool fuse_relu = d.mode & DR_FUSE_RELU, fuse_cat = fuses_concat(xd, d);
     if (!x) return fail(DR_ERR_NULL, "%s: x is NULL", who);
     StepGroup group{st, xd.dtype};
     void* stacked_dst[DR_MAX_BRANCHES] = {};
@@ -768,7 +778,7 @@ int inception_run(const dr_tensor& xd, const void* x, const dr_inception& d, Par
                   const dr_tensor& yd, void* y, Arena& ar, hipStream_t main_st)
 {
     const char* who = "dr_inception_fwd";
-    const bool fuse_relu = d.mode & DR_FUSE_RELU, fuse_cat = d.mode & DR_FUSE_CONCAT;
+    const bool fuse_relu = d.mode & DR_FUSE_RELU, fuse_cat = fuses_concat(xd, d);
     // A trace times layers, so while one runs each layer is a launch of its own; a trace of every kernel (no label filter) is there to
     // time each kernel by itself and also runs the branches in turn.
     const bool full_trace = g_trace.active && !g_trace.filter[0];

@@ -25,7 +25,7 @@ import pytest
 import oracle
 import workloads
 from paper_1708_04728_amd import binding as B, graph as G
-from util import TOL_BF16, close, note, oracle_in_chunks, rel_err, rms_err
+from util import TOL_BF16, case_seed, close, note, oracle_in_chunks, rel_err, rms_err
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -383,3 +383,21 @@ def test_small_channel_first_layer_through_net(case):
     assert close(got, ref, TOL_BF16)
     got2 = run_net_bf16(layers, params, x, fuse_relu=False)
     assert np.array_equal(got, got2)
+
+
+@pytest.mark.parametrize("n,c,h,w", [(2, 24, 7, 5), (60, 520, 13, 11)])
+def test_a_branch_that_ends_with_pooling(n, c, h, w):
+    """Its channels and the other branches' in every mode: the concat of the modes that fuse it must not write over those."""
+    conv, relu = workloads.conv, workloads.relu
+    layer = ("inception", {"branches": [[conv(64, 1), relu()], [workloads.maxpool(3, 1, 1)], [conv(32, 1), relu(), conv(48, 3, 1, 1), relu()]]})
+    rng = np.random.default_rng(case_seed((n, c, h, w)))
+    x = workloads.round_to_bf16(rng.standard_normal((n, c, h, w)).astype(np.float32) - 2)
+    params = []
+    workloads._walk(rng, [layer], c, "bf16", params)
+    pick = [0, n - 1]
+    ref = oracle.forward([layer], params, x[pick], mirror_bf16=True)
+    plain = run_net_bf16([layer], params, x)
+    assert close(plain[pick], ref, 2e-2)
+    assert np.array_equal(plain[pick][:, 64:64 + c], ref[:, 64:64 + c])
+    for mode in (B.DR_FUSE_RELU, B.DR_FUSE_CONCAT, B.DR_FUSE_RELU | B.DR_FUSE_CONCAT, B.DR_FUSE_RELU | B.DR_FUSE_CONCAT | B.DR_CONCURRENT_BRANCHES):
+        assert np.array_equal(run_net_bf16([layer], params, x, inception_mode=mode), plain), mode
