@@ -570,41 +570,51 @@ struct StepGroup {
     {
         const int k = n_big;
         n_big = 0;
-        if (!k) return DR_OK;
-        const ConvSmall& j = big[0];
-        if (dtype == DR_BF16) {
-            if (k > 1) return launch_conv_bf16_wide_group(big, k, st);
-            return j.split ? launch_conv_bf16_dma(j.g, (const uint16_t*)j.x, (const uint16_t*)j.w, j.bias, nullptr, (uint16_t*)j.y, st, j.split)
-                           : launch_conv_bf16(j.g, (const uint16_t*)j.x, (const uint16_t*)j.w, j.bias, nullptr, (uint16_t*)j.y, st);
+        if (k > 1) {
+            if (dtype != DR_BF16) return launch_conv_f32_group(big, k, st);
+            bool launched;
+            DR_TRY(launch_conv_bf16_wide_group(big, k, st, nullptr, &launched));
+            if (launched) return DR_OK;
         }
-        if (k > 1) return launch_conv_f32_group(big, k, st);
-        return launch_conv_f32(j.g, (const float*)j.x, (const float*)j.w, j.bias, (const float*)j.res, (float*)j.y, st, nullptr, 0, j.split);
+        for (int i = 0; i < k; ++i) {
+            const ConvSmall& j = big[i];
+            if (dtype != DR_BF16) DR_TRY(launch_conv_f32(j.g, (const float*)j.x, (const float*)j.w, j.bias, (const float*)j.res, (float*)j.y, st, nullptr, 0, j.split));
+            else if (j.split) DR_TRY(launch_conv_bf16_dma(j.g, (const uint16_t*)j.x, (const uint16_t*)j.w, j.bias, nullptr, (uint16_t*)j.y, st, j.split));
+            else DR_TRY(launch_conv_bf16(j.g, (const uint16_t*)j.x, (const uint16_t*)j.w, j.bias, nullptr, (uint16_t*)j.y, st));
+        }
+        return DR_OK;
+    }
+    // bf16: the larger layers of a depth, the small ones that can run in wide tiles -- with a larger one there, or where they crowd the device -- and the
+    // pooling step in one launch.  Where there are too few of them or of the compute units, nothing: everything stays with its own kernel.
+    int flush_wide()
+    {
+        ConvSmall wide[SMALL_GROUP_MAX], rest[SMALL_GROUP_MAX];
+        int k = 0, kept = 0;
+        for (int i = 0; i < n_big; ++i) wide[k++] = big[i];
+        const bool join = n_big || conv_bf16_small_crowded(jobs, n);
+        for (int i = 0; i < n; ++i) {
+            const ConvSmall& j = jobs[i];
+            if (join && j.w && k < SMALL_GROUP_MAX && conv_bf16_wide_joins(j.g, j.x, j.w, j.y, j.split)) wide[k++] = j;
+            else rest[kept++] = j;
+        }
+        if (!(k > 1 || (k == 1 && pool.set && conv_bf16_wide_takes(wide[0].g, wide[0].x, wide[0].w, nullptr, wide[0].y, wide[0].split)))) return DR_OK;
+        bool launched;
+        DR_TRY(launch_conv_bf16_wide_group(wide, k, st, pool.set ? &pool.job : nullptr, &launched));
+        if (!launched) return DR_OK;
+        for (int i = 0; i < kept; ++i) jobs[i] = rest[i];
+        n = kept;
+        n_big = 0;
+        pool.set = false;
+        return DR_OK;
     }
     int flush()
     {
-        // bf16: with a larger layer at this depth, or where they crowd the device, the small ones that can run in a launch of wide tiles
-        if (dtype == DR_BF16 && (n_big || conv_bf16_small_crowded(jobs, n))) {
-            int kept = 0;
-            for (int i = 0; i < n; ++i) {
-                const ConvSmall j = jobs[i];
-                if (j.w && n_big < SMALL_GROUP_MAX && conv_bf16_wide_joins(j.g, j.x, j.w, j.y, j.split)) big[n_big++] = j;
-                else jobs[kept++] = j;
-            }
-            n = kept;
-        }
+        if (dtype == DR_BF16) DR_TRY(flush_wide());
         if (pool.set) {
             pool.set = false;
-            const bool wide = n_big > 1 || (n_big == 1 && conv_bf16_wide_takes(big[0].g, big[0].x, big[0].w, nullptr, big[0].y, big[0].split));
             ConvSmall job{};
-            if (wide) {
-                const int k = n_big;
-                n_big = 0;
-                DR_TRY(launch_conv_bf16_wide_group(big, k, st, &pool.job));
-            } else if (small_pool_job(pool.t, pool.x, pool.o, pool.y, pool.p, &job)) {
-                DR_TRY(add(job));
-            } else {
-                DR_TRY(launch_maxpool(pool.t, pool.x, pool.o, pool.y, pool.p, st));
-            }
+            if (small_pool_job(pool.t, pool.x, pool.o, pool.y, pool.p, &job)) DR_TRY(add(job));
+            else DR_TRY(launch_maxpool(pool.t, pool.x, pool.o, pool.y, pool.p, st));
         }
         DR_TRY(flush_big());
         return flush_small();

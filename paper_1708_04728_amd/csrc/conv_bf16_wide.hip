@@ -34,6 +34,7 @@
 #include "dr_internal.h"
 #include "dr_store.h"
 #include "conv_bf16_dev.h"
+#include "conv_bf16_wide_plan.h"
 
 namespace dr {
 namespace {
@@ -45,10 +46,6 @@ template <class F, int... I>
 __device__ __forceinline__ void each_of(std::integer_sequence<int, I...>, const F& f) { (f(IC<I>{}), ...); }
 template <int N, class F>
 __device__ __forceinline__ void each(const F& f) { each_of(std::make_integer_sequence<int, N>{}, f); }
-
-// TM, TN; a layer by itself takes one of the first ten, beside others their share of the device may ask for smaller ones
-constexpr int WIDE_TILES[][2] = {{5, 7}, {4, 7}, {7, 4}, {6, 5}, {3, 7}, {6, 4}, {4, 4}, {2, 7}, {2, 5}, {4, 3}, {3, 4}, {2, 3}, {1, 7}, {1, 4}};
-constexpr int WIDE_TILE_COUNT = sizeof(WIDE_TILES) / sizeof(WIDE_TILES[0]), WIDE_ALONE = 10;
 
 struct WideArgs {
     const uint16_t* x;
@@ -385,16 +382,9 @@ int launch_tile(WideArgs a, hipStream_t st)
     return check_launch("conv_bf16_wide");
 }
 
-// The tile with the shortest time by a model: a slice takes its matrix work or its loads, whichever is longer, a tile 0.54 us and its store
-// besides.  Fitted to 14 tiles on 60 layers; over these 10 tiles on 80 layers the time is the model's + 1.9 us, 6 % off on average, and
+// The tile with the shortest time by the model (wide_tile_us).  Over these 10 tiles on 80 layers the time is the model's + 1.9 us, 6 % off on average, and
 // the tile that it picks takes 1.01 times as long as the best one on average, 1.25 at worst (3x3 512 -> 40 on 43 x 40 x 103: 64 x 160 209 us, 128 x 128 167).
 struct WideTile { int m, n, rounds; float us; };
-
-float tile_us(int tm, int tn, int slices)
-{
-    const float mn = (float)(tm * tn * 1024);
-    return slices * std::max(0.644f * mn / 32768.f, 12.85f * (tm + tn) / 256.f) + 0.54f + 1.2f * mn / 10000.f;
-}
 
 WideTile wide_tile(int K, int Ng, int slices)
 {
@@ -404,7 +394,7 @@ WideTile wide_tile(int K, int Ng, int slices)
         const int* const t = WIDE_TILES[i];
         const int bm = t[0] * 32, bn = t[1] * 32, grid_m = (K + bm - 1) / bm, grid_n = (Ng + bn - 1) / bn, gn = std::min(std::max(cus / grid_m, 1), grid_n);
         const int rounds = (grid_n + gn - 1) / gn * ((gn * grid_m + cus - 1) / cus);
-        const float us = rounds * tile_us(t[0], t[1], slices);
+        const float us = rounds * wide_tile_us(t[0], t[1], slices);
         if (us < best.us) best = WideTile{t[0], t[1], rounds, us};
     }
     return best;
@@ -480,63 +470,6 @@ bool conv_bf16_wide_joins(const ConvGeom& g, const void* x, const void* w, const
     return g.y_ctot % 8 == 0 && g.y_coff % 8 == 0 && aligned16(y);
 }
 
-// Every layer's tile and workgroups so that the slowest layer is done as soon as possible: the shortest time T, by halving (to 1/256 of where it starts:
-// closer than the model is), at which the layers' least numbers of workgroups -- rounds of each tile that fit T -- add up to at most the compute units.
-// What is added to T by a launch is 2.5 to 4.5 us (kernel trace of 112 modules).  About 2 us on the host for three layers.
-// pool_blocks: groups of 512 items of a pooling layer beside them (0: none), POOL_US each; *pool_share: its workgroups.
-constexpr float POOL_US = 2.2f;
-static void wide_plan(const ConvSmall* jobs, int n, int* tile, int* gn, int pool_blocks, int* pool_share)
-{
-    const int cus = device_cus();
-    struct Option { int grid_m, grid_n; float us; } opt[SMALL_GROUP_MAX][WIDE_TILE_COUNT];
-    float lo = 0.f, hi = 0.f;
-    for (int i = 0; i < n; ++i) {
-        const ConvGeom& g = jobs[i].g;
-        int row_chunks;
-        const int slices = chunk_slices(g.R, g.S, g.C, &row_chunks);
-        float least = 1e30f, longest = 0.f;
-        for (int t = 0; t < WIDE_TILE_COUNT; ++t) {
-            const int bm = WIDE_TILES[t][0] * 32, bn = WIDE_TILES[t][1] * 32;
-            Option& o = opt[i][t];
-            o = Option{(g.K + bm - 1) / bm, (g.Ng + bn - 1) / bn, tile_us(WIDE_TILES[t][0], WIDE_TILES[t][1], slices)};
-            least = std::min(least, o.us * o.grid_m * o.grid_n);
-            longest = std::max(longest, o.us);
-        }
-        lo += least / cus;
-        hi += 2.f * least / cus + longest;
-    }
-    lo += POOL_US * pool_blocks / cus;
-    hi += 2.f * POOL_US * pool_blocks / cus + POOL_US;
-    auto fits = [&](float T) {
-        int sum = 0, share = 0, tl[SMALL_GROUP_MAX], gw[SMALL_GROUP_MAX];
-        if (pool_blocks) {
-            if (T < POOL_US) return false;
-            const int rounds = (int)std::min(T / POOL_US, 1e6f);
-            share = ((pool_blocks + rounds - 1) / rounds + 7) / 8 * 8;
-            sum = share;
-        }
-        for (int i = 0; i < n; ++i) {
-            int best = cus + 1;
-            for (int t = 0; t < WIDE_TILE_COUNT; ++t) {
-                const Option& o = opt[i][t];
-                if (o.us > T) continue;
-                const int rounds = (int)(T / o.us), w = (o.grid_n + rounds - 1) / rounds, blocks = (w * o.grid_m + 7) / 8 * 8;
-                if (blocks < best) { best = blocks; tl[i] = t; gw[i] = w; }
-            }
-            sum += best;
-        }
-        if (sum > cus) return false;
-        for (int i = 0; i < n; ++i) { tile[i] = tl[i]; gn[i] = gw[i]; }
-        *pool_share = share;
-        return true;
-    };
-    while (!fits(hi)) hi *= 2.f;
-    for (int k = 0; k < 8; ++k) {
-        const float T = 0.5f * (lo + hi);
-        (fits(T) ? hi : lo) = T;
-    }
-}
-
 static int pool_groups(const ConvGeom& g) { return ((g.P + POOL_ROWS - 1) / POOL_ROWS * g.Q * (g.C / 8) + POOL_ITEMS - 1) / POOL_ITEMS; }
 
 // Up to 7/4 groups of 512 items per compute unit: a larger pooling layer fills the device by itself and, bound by memory, takes longer on a share of it
@@ -550,10 +483,12 @@ bool conv_bf16_wide_pools(const ConvSmall& c)
            qcv * qcv * (g.P + POOL_ROWS) < 4294967296.0 && 4l * g.N * pool_groups(g) <= 7l * device_cus();
 }
 
-int launch_conv_bf16_wide_group(const ConvSmall* jobs, int n, hipStream_t st, const ConvSmall* pool)
+static_assert(SMALL_GROUP_MAX <= WIDE_LAYERS, "layers of a plan");
+
+int launch_conv_bf16_wide_group(const ConvSmall* jobs, int n, hipStream_t st, const ConvSmall* pool, bool* launched)
 {
     WideGroupArgs a{};
-    int tile[SMALL_GROUP_MAX], gn[SMALL_GROUP_MAX], blocks = 0;
+    int blocks = 0;
     a.first_pool = 0x7FFFFFFF;
     if (pool) {
         const ConvGeom& g = pool->g;
@@ -561,16 +496,25 @@ int launch_conv_bf16_wide_group(const ConvSmall* jobs, int n, hipStream_t st, co
         a.pool = WidePool{(const uint16_t*)pool->x, (uint16_t*)pool->y, g.C, g.H, g.W, g.P, g.Q, g.ph, g.pw, strips * qcv, groups,
                           g.N * groups, (g.N * groups + 7) / 8, 0, (unsigned)((0x100000000ull + cv - 1) / cv), (unsigned)((0x100000000ull + qcv - 1) / qcv)};
     }
-    wide_plan(jobs, n, tile, gn, a.pool.blocks, &a.pool.share);
+    WideLayer layers[SMALL_GROUP_MAX];
+    WidePlan plan;
+    for (int i = 0; i < n; ++i) {
+        const ConvGeom& g = jobs[i].g;
+        int row_chunks;
+        layers[i] = WideLayer{g.K, g.Ng, chunk_slices(g.R, g.S, g.C, &row_chunks)};
+    }
+    *launched = wide_plan(layers, n, a.pool.blocks, device_cus(), &plan);
+    if (!*launched) return DR_OK;
+    a.pool.share = plan.pool_share;
     for (int i = 0; i < SMALL_GROUP_MAX; ++i) {
         a.first[i] = i < n ? blocks : 0x7FFFFFFF;
         if (i >= n) continue;
         const ConvSmall& c = jobs[i];
-        const int bm = WIDE_TILES[tile[i]][0] * 32, bn = WIDE_TILES[tile[i]][1] * 32, grid_m = (c.g.K + bm - 1) / bm;
-        a.tile[i] = tile[i];
+        const int bm = WIDE_TILES[plan.tile[i]][0] * 32, bn = WIDE_TILES[plan.tile[i]][1] * 32, grid_m = (c.g.K + bm - 1) / bm;
+        a.tile[i] = plan.tile[i];
         a.job[i] = wide_args(c.g, (const uint16_t*)c.x, (const uint16_t*)c.w, c.bias, (uint16_t*)c.y, c.split);
-        a.job[i].wk = make_walk(grid_m, gn[i], (c.g.Ng + bn - 1) / bn);
-        blocks += (gn[i] * grid_m + 7) / 8 * 8;
+        a.job[i].wk = make_walk(grid_m, plan.gn[i], (c.g.Ng + bn - 1) / bn);
+        blocks += (plan.gn[i] * grid_m + 7) / 8 * 8;
     }
     if (pool) {
         a.first_pool = blocks;

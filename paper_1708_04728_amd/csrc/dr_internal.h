@@ -117,7 +117,8 @@ int launch_conv_bf16_wide(const ConvGeom& g, const uint16_t* x, const uint16_t* 
 // several layers in one launch of wide tiles
 bool conv_bf16_wide_joins(const ConvGeom& g, const void* x, const void* w, const void* y, const ConvSplit* split);
 bool conv_bf16_wide_pools(const ConvSmall& pool);                // a max-pooling layer (w NULL) that may lie beside them
-int launch_conv_bf16_wide_group(const ConvSmall* jobs, int n, hipStream_t st, const ConvSmall* pool = nullptr);
+// *launched: whether the compute units suffice for them side by side; if not nothing has been launched
+int launch_conv_bf16_wide_group(const ConvSmall* jobs, int n, hipStream_t st, const ConvSmall* pool, bool* launched);
 
 bool conv_bf16_small_takes(const ConvGeom& g, const void* x, const void* w);
 int launch_conv_bf16_small(const ConvSmall* jobs, int n, hipStream_t st);

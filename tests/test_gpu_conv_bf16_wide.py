@@ -221,3 +221,27 @@ def test_a_pooling_step_beside_the_layers(n, c, h, w, pool):
         assert np.array_equal(run_net_bf16([layer], params, x, inception_mode=mode), plain), mode
     pick = [0, n - 1]
     assert close(plain[pick], oracle.forward([layer], params, x[pick], mirror_bf16=True), 2e-2)
+
+
+@pytest.mark.parametrize("branches,c,h,w", [
+    ([[("conv", 30000)], [("conv", 30000)]], 8, 14, 14),             # more blocks of filters than compute units to run them side by side
+    ([[("conv", 30000)], [("conv", 30000)]], 8, 7, 7),
+    ([[("conv", 57400)], [("maxpool", 0), ("conv", 16)]], 264, 7, 7),       # a single one with the pooling step
+    ([[("conv", 14400)], [("conv", 14400)], [("conv", 14400)], [("conv", 14400)]], 8, 7, 9),      # small layers that would crowd the device
+])
+def test_layers_too_wide_to_share_a_launch(branches, c, h, w):
+    """A module whose layers have more filters than fit the compute units side by side runs them one by one."""
+    from test_gpu_bf16_nets import run_net_bf16
+    layer = ("inception", {"branches": [[s for kind, k in branch for s in ([workloads.conv(k, 1), workloads.relu()] if kind == "conv" else [workloads.maxpool(3, 1, 1)])]
+                                        for branch in branches]})
+    rng = np.random.default_rng(case_seed((branches, c, h, w)))
+    x = workloads.round_to_bf16(rng.standard_normal((1, c, h, w)).astype(np.float32))
+    params = []
+    workloads._walk(rng, [layer], c, "bf16", params)
+    base = B.DR_FUSE_RELU | B.DR_FUSE_CONCAT
+    B.trace_begin()
+    plain = run_net_bf16([layer], params, x, inception_mode=base)
+    B.trace_end()
+    for mode in (0, base, base | B.DR_FUSE_STACK, base | B.DR_CONCURRENT_BRANCHES):
+        assert np.array_equal(run_net_bf16([layer], params, x, inception_mode=mode), plain), mode
+    assert close(plain, oracle.forward([layer], params, x, mirror_bf16=True), 2e-2)
