@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "dr_internal.h"
+#include "inception_levels.h"
 
 namespace dr {
 
@@ -665,34 +666,33 @@ size_t module_scratch_bytes(const dr_tensor& xd, const dr_conv& cd)
     return bytes && big_takes(xd.dtype, conv_geom(xd, cd, conv_out(xd, cd))) ? 0 : bytes;
 }
 
-// Whether the module runs level by level, its steps sharing launches: at least two convolutions that can.  In bf16 also where the caller wants the
-// branches on streams: the layers of a depth then lie side by side in one launch, each with its share of the compute units (as graphs, streams and
-// levels: the original GoogLeNet on 12 images 487 and 360 us, on 40 746 and 581, on 128 1494 and 1367; the fused one 297 and 260, 492 and
-// 414, 1042 and 968; on six and fewer, where every layer is small, both went by levels).  In fp32 then every convolution has to, and most of them
-// in the small-layer kernel: a level is a barrier between the branches, and larger layers, which share a launch one tile after the other, fill the
-// device better on streams (4c on 64 images, one small layer of six: 203 against 237), while a large layer among small
-// ones does not (slim 5a on 64 images, a 5x5 of 392 tiles beside three small layers: 113 against 95, as graphs).
+// Whether the module runs level by level, its steps sharing launches (the rule and its reasons: inception_levels.h)
 bool inception_by_levels(const dr_tensor& xd, const void* x, const dr_inception& d)
 {
-    if (xd.layout != (xd.dtype == DR_BF16 ? DR_NHWC : DR_NCHW)) return false;
-    int n_small = 0, n_big = 0, all = 0;
+    const bool bf16 = xd.dtype == DR_BF16;
+    if (xd.layout != (bf16 ? DR_NHWC : DR_NCHW)) return false;
+    ModuleLayers m{};
     for (int b = 0; b < d.n_branches; ++b) {
         dr_tensor t = xd;
+        long alone = 0;
         for (int s = 0; s < d.branches[b].n_steps; ++s) {
             const dr_step& stp = d.branches[b].steps[s];
             const dr_tensor o = stp.kind == DR_STEP_CONV ? conv_out(t, stp.conv) : pool_out(t, stp.pool);
             if (stp.kind == DR_STEP_CONV) {
                 if (conv_too_large(stp.conv, o)) return false;             // refused when its turn comes
                 const ConvGeom g = conv_geom(t, stp.conv, o);
-                if (small_takes(xd.dtype, g, s == 0 ? x : nullptr, nullptr)) ++n_small;
-                else if (big_takes(xd.dtype, g)) ++n_big;
-                ++all;
+                const void* const xs = s == 0 ? x : nullptr;
+                if (small_takes(xd.dtype, g, xs, nullptr)) ++m.small;
+                else if (big_takes(xd.dtype, g)) ++m.big;
+                else if (bf16 && !conv_bf16_dma_eligible(g, xs, nullptr)) alone += g.Kg;
+                ++m.all;
             }
             t = o;
         }
+        if (alone > m.longest) { m.second = m.longest; m.longest = alone; }
+        else if (alone > m.second) m.second = alone;
     }
-    const int n = n_small + n_big;
-    return n >= 2 && (xd.dtype == DR_BF16 || !(d.mode & DR_CONCURRENT_BRANCHES) || (n == all && 2 * n_small > all));
+    return module_by_levels(m, bf16, d.mode & DR_CONCURRENT_BRANCHES);
 }
 
 int inception_run_levels(const dr_tensor& xd, const void* x, const dr_inception& d, ParamCursor& wts, ParamCursor& bss, const dr_tensor& yd, void* y,

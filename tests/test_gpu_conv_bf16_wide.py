@@ -172,6 +172,7 @@ def test_stacked_first_steps():
     (90, 32, 13, 15, (256, 160, 320, 32, 128, 128)),        # several rounds
     (25, 200, 15, 13, (72, 56, 104, 8, 16, 20)),            # a projection of 20 filters, which stays out
     (17, 40, 28, 28, (24, 360, 48, 344, 40, 48)),           # 5x5 on 344 channels: more chunks than the table holds
+    (13, 64, 14, 15, (192, 92, 208, 44, 48, 64)),           # 3x3 on 92 channels, 5x5 on 44: on streams of their own where the caller wants that
     (128, 16, 7, 7, (384, 24, 384, 48, 128, 128)),
 ])
 def test_layers_of_a_depth_share_a_launch(n, c, h, w, widths):
