@@ -131,12 +131,14 @@ __device__ __forceinline__ void lds_barrier()
 // belong to TPT taps, so the padding test is made TPT times per slice (with columns in (c, r, s) order it was made for every
 // element and that arithmetic took longer than the multiplications), the rest of an address is a per-thread constant, and
 // (p, q) advances by addition.  Two LDS buffers, one barrier per slice, loads two slices ahead; the next slice goes to LDS in the middle of the
-// products, which 64 cycles each leave time for.  3x3 64 -> 192 at stride 2 on 56 x 56 x 32 images: 118 -> 71 us (78 TFLOP/s); with that order and EIGHTS
-// the fitting step as a whole, kernels of other sizes before and behind it, another 4 to 8 us less (without EIGHTS 80 us for this kernel, 72 with).
+// products, which 64 cycles each leave time for.  3x3 64 -> 192 at stride 2 on 56 x 56 x 32 images, the call with the sum of its ranges (5.6 us): 118 us
+// with columns in (c, r, s) order, 74.4 with these, 71.5 with that order and EIGHTS; 43 drawn layers 1.040 more, 43 that EIGHTS does not take 1.034.
 // EIGHTS: filters and channels come in eights, so that a row or column exists for all threads of its group of eight or for none: its offset is then the
 // load's scalar offset, and a slice takes an address for the gradient and one per tap instead of one per element.
+// Four workgroups per compute unit, for which the registers are bounded: left to itself the compiler takes a few more without EIGHTS and three fit
+// (3x3 68 -> 68 at stride 2 on 23 x 56 x 32 51.4 us and 43.1, 20 -> 50 on 56 x 56 x 32 37.7 and 33.7; 43 such layers 1.2 % together).
 template <int TPT, bool EIGHTS>
-__global__ __launch_bounds__(256) void conv_wgrad_f32_kernel(const WArgs a)
+__global__ __launch_bounds__(256, 4) void conv_wgrad_f32_kernel(const WArgs a)
 {
     __shared__ __attribute__((aligned(16))) float As[2][BM * LDT];
     __shared__ __attribute__((aligned(16))) float Bs[2][BN * LDT];
