@@ -261,7 +261,7 @@ typedef struct { int n_steps; dr_step steps[DR_MAX_STEPS]; } dr_branch;
                               Without it the branches run one after another on the caller's stream.
                               bf16 modules two or more of whose layers share launches (above) run as without it,
                               unless two branches have layers that cannot (channels not in eights, ...),
-                              one's at least a third as long as the other's.
+                              one's at least two fifths as long as the other's.
                               Pays when a module's kernels are long next to the cost of the events
                               (several microseconds per fork / join) and leave compute units idle */
 typedef struct { int n_branches; dr_branch branches[DR_MAX_BRANCHES]; int mode; } dr_inception;

@@ -33,9 +33,9 @@ def by_levels(tmp_path_factory):
     (6, 6, 0, 0, 0, True, True),
     (6, 3, 2, 0, 0, True, True),             # one that shares nothing but has a kernel of its own beside the others
     (6, 4, 1, 300, 0, True, True),           # a 5x5 on 12 channels
-    (6, 2, 2, 828, 300, True, False),        # 3x3 on 92 and 5x5 on 12
-    (6, 2, 2, 828, 276, True, False),
-    (6, 2, 2, 828, 275, True, True),
+    (6, 2, 2, 828, 300, True, True),         # 3x3 on 92 and 5x5 on 12
+    (6, 2, 2, 1000, 399, True, True),
+    (6, 2, 2, 1000, 400, True, False),
     (6, 2, 2, 1692, 1100, True, False),      # 3x3 on 188 and 5x5 on 44
     (6, 2, 0, 484, 484, True, False),
     (6, 2, 2, 1692, 1100, False, True),      # branches in turn
