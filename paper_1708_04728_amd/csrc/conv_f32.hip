@@ -49,6 +49,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "conv_f32_kcrs33.h"
 #include "conv_f32_table.h"
 #include "dr_internal.h"
 
@@ -594,7 +595,7 @@ __global__ __launch_bounds__(NT) void conv_f32_kernel(const KArgs a)
 template <int BM, int BN>
 __global__ __launch_bounds__(NT, BM == 64 ? 5 : 4) void conv_f32_kcrs33_kernel(const KArgs a)
 {
-    constexpr int CB = 8, ROW = CB * 9, LDA = ROW + 2, WGN = BN / 32, OOB = (int)0x80000000;
+    constexpr int CB = KCRS33_CB, ROW = KCRS33_ROW, LDA = ROW + 2, WGN = BN / 32, OOB = (int)0x80000000;
     constexpr int A_F4 = BM * ROW / 4, A_PER = (A_F4 + NT - 1) / NT, CPT = CB * BN / NT;       // 16-byte loads of a block; channels of an activation a thread fetches
     static_assert(BM / 32 * WGN == 4 && (CPT == 2 || CPT == 4), "four waves");
     __shared__ __attribute__((aligned(16))) float As[BM * LDA];
@@ -627,17 +628,18 @@ __global__ __launch_bounds__(NT, BM == 64 ? 5 : 4) void conv_f32_kcrs33_kernel(c
     f32x4 ra[A_PER];
     float rb[3][CPT];
     auto load_a = [&](int blk) __attribute__((always_inline)) {
-        const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, blk < blocks ? a.w_bytes : 0, 0x00020000);
+        const LoadRange l = kcrs33_filters(blk, blocks, a.w_bytes);
+        const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, l.bytes, 0x00020000);
 #pragma unroll
-        for (int i = 0; i < A_PER; ++i) ra[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rw, va[i], blk * ROW * 4, 0));
+        for (int i = 0; i < A_PER; ++i) ra[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rw, va[i], l.scalar, 0));
     };
-    auto load_b = [&](int blk, auto r_c) __attribute__((always_inline)) {     // (beyond the last block: a descriptor of size 0)
+    auto load_b = [&](int blk, auto r_c) __attribute__((always_inline)) {
         constexpr int R = decltype(r_c)::value;
-        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)a.x, 0, blk < blocks ? a.x_bytes : 0, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)a.x, 0, kcrs33_plane(blk, blocks, 0, HW, a.x_bytes).bytes, 0x00020000);
 #pragma unroll
         for (int t = 0; t < 3; ++t)
 #pragma unroll
-            for (int j = 0; j < CPT; ++j) rb[t][j] = buf_load(rx, vb[R][t], (blk * CB + j) * HW * 4);
+            for (int j = 0; j < CPT; ++j) rb[t][j] = buf_load(rx, vb[R][t], kcrs33_plane(blk, blocks, j, HW, a.x_bytes).scalar);
     };
     auto put_a = [&]() __attribute__((always_inline)) {
 #pragma unroll
