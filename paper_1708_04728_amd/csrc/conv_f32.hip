@@ -50,6 +50,7 @@
 #include <type_traits>
 
 #include "conv_f32_kcrs33.h"
+#include "conv_f32_store.h"
 #include "conv_f32_table.h"
 #include "dr_internal.h"
 
@@ -858,15 +859,15 @@ int launch_tile(const KArgs& base, void* ws, size_t ws_bytes, hipStream_t st)
 
 }  // namespace
 
-// The store's offsets are counted from a tile's first image: its images, of up to 128 pixels' worth, times their channels below 2 GiB.  Ranges of filters
-// with a destination each start at multiples of 8 (a lane's half holds four filters of every eight).
+// The short form of the store: offsets that fit (conv_f32_store.h), and ranges of filters with a destination each that start at multiples of 8 (a lane's half
+// holds four filters of every eight).
 static bool store_fits(const KArgs& a)
 {
-    long ctot = a.g.res_ctot;
-    for (int d = 0; d < 4; ++d) ctot = std::max<long>(ctot, a.ctot_seg[d]);
+    int ctot = a.g.res_ctot;
+    for (int d = 0; d < 4; ++d) ctot = std::max(ctot, a.ctot_seg[d]);
     for (int d = 0; d < 3; ++d)
         if (a.split_end[d] != 0x7FFFFFFF && a.split_end[d] % 8 != 0) return false;
-    return (128.0 + 2.0 * a.g.P * a.g.Q) * (double)ctot * 4.0 < 2147483648.0;
+    return store_tile_fits(ctot, a.g.P, a.g.Q, a.res != nullptr);
 }
 
 // Destinations of a (stacked) layer, tensor sizes.

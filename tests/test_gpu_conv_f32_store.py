@@ -80,3 +80,39 @@ def test_channels_2_gib_apart(bias):
     assert bool((y[:, ctot - k - 1] == 7.0).all())
     del y
     assert close(got, oracle.conv2d(x, w, b if bias else np.zeros(k, np.float32), 1, 0, True), TOL_F32)
+
+
+def test_planes_of_a_gigabyte():
+    """One filter on 13400 x 13400: three planes, the rows that an eight is rounded up to, are 2.15e9 bytes, beyond the short form's buffer."""
+    side = 13400
+    x = torch.rand((1, 1, side, side), device="cuda")
+    w, b = torch.full((1, 1, 1, 1), 0.75, device="cuda"), torch.full((1,), -0.25, device="cuda")
+    y = torch.full((1, 1, side, side), float("nan"), device="cuda")
+    B.conv2d_fwd(x, B.conv_desc(1, 1, 1, 1, 1, 0, True, B.DR_KCRS), w, b, y)
+    torch.cuda.synchronize()
+    assert float((y - (x * 0.75 - 0.25).clamp(min=0)).abs().max()) <= 2.0 ** -22      # a product and a sum of values below 1, each rounded once
+
+
+@pytest.mark.parametrize("side", [4400, 4608])
+def test_residual_of_large_planes(side):
+    """The residual sum on 8 filters of a map whose 27 planes, the rows that a block of 32 is rounded up to, end just below and beyond 2 GiB.  The 3x3 layer has
+    its middle tap alone, so that the block is a sum per pixel."""
+    rng = np.random.default_rng(side)
+    c = 8
+    params = [{"w": rng.standard_normal((1, c, 1, 1)).astype(np.float32) * np.float32(0.5), "b": np.full(1, 0.1, np.float32)},
+              {"w": np.zeros((1, 1, 3, 3), np.float32), "b": np.full(1, 0.2, np.float32)},
+              {"w": rng.standard_normal((c, 1, 1, 1)).astype(np.float32), "b": (rng.standard_normal(c) * 0.1).astype(np.float32)}]
+    params[1]["w"][0, 0, 1, 1] = 0.75
+    net = B.Net(G.net_descs([workloads.bottleneck(1, c, False)], c, folded=True))
+    x = torch.rand((1, c, side, side), device="cuda")
+    y = torch.full((1, c, side, side), float("nan"), device="cuda")
+    ws = torch.empty(max(net.workspace_bytes(B.desc(x)), 256), dtype=torch.uint8, device="cuda")
+    net.fwd(x, [gpu(p[k]) for p in params for k in ("w", "b")], y, ws)
+    torch.cuda.synchronize()
+    m = torch.zeros((side, side), device="cuda", dtype=torch.float64)
+    for i in range(c):
+        m += x[0, i].double() * float(params[0]["w"][0, i, 0, 0])
+    m = ((m + float(params[0]["b"][0])).clamp(min=0) * 0.75 + float(params[1]["b"][0])).clamp(min=0)
+    for i in range(c):
+        ref = (m * float(params[2]["w"][i, 0, 0, 0]) + float(params[2]["b"][i]) + x[0, i].double()).clamp(min=0)
+        assert float((y[0, i].double() - ref).abs().max()) < 2e-5       # some 15 roundings of values below 10
