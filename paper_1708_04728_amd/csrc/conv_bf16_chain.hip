@@ -84,6 +84,16 @@ __device__ __forceinline__ u32x4 pack8(const float (&o)[8])
     return pk;
 }
 
+// A value of which the compiler knows nothing.  Lanes read in `stage` what other lanes of their wave have written, and a wave's LDS instructions run in order:
+// what has to be kept is the order of the program.  The compiler keeps it where one lane's write and read may be the same place, which with an index that
+// comes from here they may, whatever it finds out about the others.  (A fence at wavefront scope in each place keeps more than that: one to eight images of
+// 56 x 56 2 % longer in the kernel with the 3x3 layer, spills in the other.)
+__device__ __forceinline__ int unknown(int v)
+{
+    asm("" : "+v"(v));
+    return v;
+}
+
 // PROJ: the shortcut is Wp x; NEXT: m' is computed; LINES: memory is read and written by whole lines, through LDS
 template <bool PROJ, bool NEXT, bool LINES>
 __global__ __launch_bounds__(CHAIN_WAVES * 64) void conv_bf16_chain_kernel(const ChainArgs a)
@@ -124,7 +134,7 @@ __global__ __launch_bounds__(CHAIN_WAVES * 64) void conv_bf16_chain_kernel(const
     const int blocks = (c.pixels + 31) >> 5, stride = (int)gridDim.x * CHAIN_WAVES;
     // The matrix instructions want chunk 2 q + half (8 channels) of pixel l & 31 of 64 channels.  LINES: a lane moves chunk l & 7 of pixel l >> 3 of
     // each eight instead, and `stage`, the wave's own, turns one into the other; chunk c of pixel p lies at c ^ (p & 7).
-    const int line = wave * PART + (lane & 56) + ((lane & 7) ^ (lane >> 3)), op = wave * PART + l32 * 8, sw = l32 & 7;
+    const int line = wave * PART + (lane & 56) + ((lane & 7) ^ (lane >> 3)), op = unknown(wave * PART + l32 * 8), sw = l32 & 7;
     auto at = [&](int blk, int j, int C, int ch) __attribute__((always_inline)) {      // zeros are read, nothing written outside the tensor
         const int n = blk * 32 + (LINES ? j * 8 + (lane >> 3) : l32), c0 = ch + (LINES ? lane & 7 : 2 * j + half) * 8;
         return n < c.pixels && c0 < C ? (n * C + c0) * 2 : OOB;
@@ -332,7 +342,7 @@ __global__ __launch_bounds__(512, 2) void conv_bf16_chain_mid_kernel(const Chain
     const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void*)c.y, 0, a.y_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rn = __builtin_amdgcn_make_buffer_rsrc((void*)c.m_next, 0, a.next_bytes, 0x00020000);
     // memory by whole lines, as in the kernel above
-    const int line = wave * PART + (lane & 56) + ((lane & 7) ^ (lane >> 3)), op = wave * PART + l32 * 8, sw = l32 & 7;
+    const int line = wave * PART + (lane & 56) + ((lane & 7) ^ (lane >> 3)), op = unknown(wave * PART + l32 * 8), sw = l32 & 7;
     auto at = [&](int n0, int j, int C, int ch) __attribute__((always_inline)) {
         const int n = n0 + j * 8 + (lane >> 3), c0 = ch + (lane & 7) * 8;
         return n < c.pixels && c0 < C ? (n * C + c0) * 2 : OOB;
