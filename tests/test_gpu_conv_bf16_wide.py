@@ -9,7 +9,7 @@ import oracle
 import workloads
 from bf16_rules import route, wide_fills
 from paper_1708_04728_amd import binding as B
-from util import case_seed, close, gpu, gpu_nhwc, host_nhwc
+from util import case_seed, close, gpu, gpu_nhwc, host_nhwc, kernel_launches
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -246,3 +246,36 @@ def test_layers_too_wide_to_share_a_launch(branches, c, h, w):
     for mode in (0, base, base | B.DR_FUSE_STACK, base | B.DR_CONCURRENT_BRANCHES):
         assert np.array_equal(run_net_bf16([layer], params, x, inception_mode=mode), plain), mode
     assert close(plain, oracle.forward([layer], params, x, mirror_bf16=True), 2e-2)
+
+
+@pytest.mark.parametrize("n,c,h,w,branches,launches", [
+    # branches: widths of a 1x1, of a 1x1 and what follows it, ("pool", width of the projection); kernels with ReLU and concat in the stores
+    (448, 16, 3, 6, [(256,), (128, (3, 64)), ("pool", 64)], 2),            # as many groups of pooling items as may lie beside the layers of a depth
+    (449, 16, 3, 6, [(256,), (128, (3, 64)), ("pool", 64)], 3),            # ... and one more: a launch of its own
+    (40, 64, 14, 14, [(64,), (96, (3, 208)), (16, (5, 48)), ("pool", 64)], 2),      # small layers that crowd the device
+    (4, 64, 14, 14, [(64,), (96, (3, 208)), (16, (5, 48)), ("pool", 64)], 2),       # ... and that do not: the kernel for small layers
+    (25, 200, 15, 13, [(72,), (56, (3, 104)), (8, (5, 16)), ("pool", 20)], 3),      # a projection of 20 filters stays out
+    (1, 8, 14, 14, [(30000,), (30000,)], 2),                                         # too wide to lie side by side
+])
+def test_launches_of_a_module(n, c, h, w, branches, launches):
+    """How many kernels a module takes: which of its layers share a launch."""
+    from paper_1708_04728_amd import graph as G
+    conv, relu, layers, shapes = workloads.conv, workloads.relu, [], []
+    for first, *rest in branches:
+        steps, ci = ([workloads.maxpool(3, 1, 1)], c) if first == "pool" else ([conv(first, 1), relu()], first)
+        if first != "pool":
+            shapes.append((first, c, 1))
+        for r in rest:
+            r, k = r if isinstance(r, tuple) else (1, r)
+            steps += [conv(k, r, 1, r // 2), relu()]
+            shapes.append((k, ci, r))
+            ci = k
+        layers.append(steps)
+    x = B.NHWC(torch.zeros((n, h, w, c), dtype=torch.bfloat16, device="cuda"))
+    weights = [B.pack_filters(torch.zeros((k, ci, r, r), dtype=torch.bfloat16, device="cuda")) for k, ci, r in shapes]
+    biases = [torch.zeros(k, device="cuda") for k, _, _ in shapes]
+    d = G.inception_desc({"branches": layers}, c, B.DR_FUSE_RELU | B.DR_FUSE_CONCAT, "bf16")
+    y = B.NHWC(torch.zeros((n, h, w, sum((b[-1][1] if isinstance(b[-1], tuple) else b[-1]) for b in branches)), dtype=torch.bfloat16, device="cuda"))
+    ws = torch.empty(max(B.inception_workspace_bytes(x, d), 256), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    assert kernel_launches(lambda: B.inception_fwd(x, d, weights, biases, y, ws)) == launches

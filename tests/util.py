@@ -92,3 +92,22 @@ def empty_nhwc(shape_nchw, dtype="f32"):
     n, c, h, w = shape_nchw
     return B.NHWC(torch.full((n, h, w, c), float("nan"), dtype=torch.bfloat16 if dtype == "bf16" else torch.float32,
                              device="cuda"))
+
+
+def kernel_launches(fn):
+    """Kernels that fn launches on the current stream: recorded into a graph on a stream of its own, whose kernel nodes are counted (never launched)."""
+    import ctypes
+    import torch
+    hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+    graph, side = torch.cuda.CUDAGraph(keep_graph=True), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(graph, stream=side):
+        fn()
+    raw, n, kind, kernels = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0), ctypes.c_int(-1), 0
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * max(n.value, 1))()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(n)) == 0
+    for i in range(n.value):
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(nodes[i]), ctypes.byref(kind)) == 0
+        kernels += kind.value == 0                 # hipGraphNodeTypeKernel
+    return kernels
