@@ -17,8 +17,8 @@
 // and the address path then takes longer than memory.  Where there are enough blocks to hide it every piece goes through LDS and an
 // instruction moves eight whole lines: with the residual, 128 images of 56 x 56, 139 -> 101 us (117 -> 90 without a next layer); addresses that run on
 // without a gap (in a working copy) 98 and 86.
-// ResNet's conv2_x, three folded blocks on 56 x 56: 128 images 625 us as single layers, 402 in chains without and 383 with their 3x3 layers; 30 images
-// 163, 122 and 107; one image 52, 42 and 39.
+// ResNet's conv2_x, three folded blocks on 56 x 56: 128 images 625 us as single layers, 402 in chains without and 380 with their 3x3 layers; 30 images
+// 163, 122 and 106; one image 52, 42 and 39.
 // What bounds the kernel that reads m: HBM, at 5.1 TB/s on the bytes left (360 MB in the first launch of that stage), as much as a copy reaches.
 // The sums run in the order of the streaming kernel and every tensor it would store is rounded where it would be: the same bits.
 #include "dr_internal.h"
@@ -256,8 +256,8 @@ __global__ __launch_bounds__(CHAIN_WAVES * 64) void conv_bf16_chain_kernel(const
 // pixels are numbered through rows and images; a tap outside the image reads a row of zeros -- and its filters by taps, through a ring of three.  Loads
 // of the multiplying waves (residuals, a tile ahead) and of the loading ones are then waited for apart, which one memory counter for both would not
 // allow.  The waves meet at every tap and once behind the last, from where on the loading waves bring the next tile's patch.
-// What it is worth, layer and chain kernel -> this one, conv2_x of 1, 8, 30, 64 and 128 images: 42 -> 39, 70 -> 56, 122 -> 107, 241 -> 208 and 469 -> 380 us
-// (the last two with the chain kernel's lines in both figures: 402 -> 380); 90 maps of 33 x 51 186 -> 163.  W > 63 does not fit the patch, a projected block
+// What it is worth, layer and chain kernel -> this one, conv2_x of 1, 8, 30 and 128 images: 42 -> 39, 70 -> 57, 122 -> 106 and 402 -> 380 us; 90 maps of
+// 33 x 51 186 -> 163.  W > 63 does not fit the patch, a projected block
 // not the filters: those keep the layer of their own.
 // What bounds it: a tile takes a multiplying wave about 24000 cycles, its bytes' share of HBM 17000; one such wave per SIMD, so that its LDS reads, stores
 // and vector work (a lane exchange and a conversion for every result) are not hidden by another.  Tried: eight multiplying waves, which leaves

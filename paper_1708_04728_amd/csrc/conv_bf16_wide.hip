@@ -26,8 +26,8 @@
 // 3 us for each further round.  Measured, streaming kernel -> this one, batch 128: 3x3 144 -> 288 on 14 x 14 38.4 -> 24.6 us, 160 -> 320 39.8 -> 26.4,
 // 128 -> 256 22.6 -> 18.3, 128 -> 192 on 28 x 28 57 -> 50, 192 -> 384 on 7 x 7 18.8 -> 13.1, 1x1 480 -> 304 on 14 x 14 21.3 -> 15.7; over 80 layers
 // of GoogLeNet and of sizes drawn at random 0.83 of the time, 1.02 at worst.  GoogLeNet at batch 128: slim 722 -> 637 us, original 1584 -> 1499.
-// It also runs beside other streams, where the streaming kernel keeps its larger tiles (SharedDeviceScope): the original GoogLeNet with its branches
-// on streams 1521 us, 1611 with the wide tiles left out there.
+// It also runs beside other streams, where the streaming kernel keeps its larger tiles (SharedDeviceScope): modules that do not run by levels although
+// their branches are wanted on streams (inception_levels.h), or while a trace of some layers runs.
 #include <algorithm>
 #include <utility>
 

@@ -122,7 +122,7 @@ int launch_conv_bf16_wide_group(const ConvSmall* jobs, int n, hipStream_t st, co
 
 bool conv_bf16_small_takes(const ConvGeom& g, const void* x, const void* w);
 int launch_conv_bf16_small(const ConvSmall* jobs, int n, hipStream_t st);
-bool conv_bf16_small_crowded(const ConvSmall* jobs, int n);      // several layers, more than a 64 x 64 tile per compute unit
+bool conv_bf16_small_crowded(const ConvSmall* jobs, int n);      // several layers, more than five 64 x 64 tiles for four compute units
 
 // conv_bf16_chain.hip: the expanding 1x1 convolution of a folded bottleneck with its shortcut, and the first layer of the bottleneck
 // behind it.  bf16 channels-last; filters [k][c].
