@@ -654,7 +654,7 @@ bool big_takes(int dtype, const ConvGeom& g, const void* x = nullptr, const void
 {
     if (dtype == DR_BF16) return conv_bf16_wide_joins(g, x, w, y, nullptr) && !conv_bf16_small_takes(g, x, w);
     return dtype == DR_F32 && conv_f32_group_takes(g) && !conv_f32_small_takes(g, nullptr, false) &&
-           ((long)g.K + 63) / 64 * (((long)g.Ng + 63) / 64) >= device_cus() / 2;
+           (((long)g.K + 63) / 64 * (((long)g.Ng + 63) / 64) >= device_cus() / 2 || conv_f32_pieces_takes(g));
 }
 
 // Scratch of a module's layer.  One that may share a launch is not cut over workgroups in any mode, so that its sums are the same in

@@ -49,46 +49,16 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "conv_f32_dev.h"
 #include "conv_f32_kcrs33.h"
-#include "conv_f32_store.h"
 #include "conv_f32_table.h"
-#include "dr_internal.h"
 
 namespace dr {
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
 constexpr int NT = 256;       // threads per workgroup
 constexpr int KTAB = 512;     // CF = false: contraction elements (or groups of 4 taps) whose two-word table entries are used
 constexpr int KTAB1 = 2048;   // CF = false, at most 31 taps: elements whose one-word entries fit the LDS table (8 KB)
-
-struct KArgs {
-    const float* x;
-    const float* w;
-    const float* bias;
-    const float* res;
-    float* y;
-    ConvGeom g;
-    int grid_m, grid_n;
-    int x_bytes, w_bytes;   // sizes of the x and w tensors (both < 2 GiB, checked by the launcher)
-    int w_krsc;             // filters are in KRSC order (else KCRS)
-    int row_groups;         // CF = false: k runs over (c, r, groups of 4 taps), see the header
-    // Stacked convolution (Eq. (12): several filter banks on one input) whose filter ranges go to different tensors:
-    // filter m < split_end[0] goes to destination 0, m < split_end[1] to destination 1, ... (unused ends hold INT_MAX).
-    // Element (img, m, pix) of destination d lies at y_seg[d][(img * ctot_seg[d] + m) * P * Q + pix] (the host has
-    // folded the destination's channel offset and the range's first filter into y_seg).  nsplit <= 1: everything to destination 0.
-    int nsplit;
-    int far_store;          // destinations or offsets that the short form of the store does not take (see store_fits)
-    int split_end[3];
-    float* y_seg[4];
-    int ctot_seg[4];
-    float* part;            // partial sums [splits][K][Ng] of a split contraction, or NULL
-    int splits, slices_per_split;
-};
-
-template <int V> using IC = std::integral_constant<int, V>;
 
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also waits for every outstanding
 // global load (its fence covers all address spaces), which would serialise the register prefetch
@@ -98,113 +68,6 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-__device__ __forceinline__ float buf_load(__amdgpu_buffer_rsrc_t r, int voff, int soff)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
-}
-
-__device__ __forceinline__ void buf_store(float v, __amdgpu_buffer_rsrc_t r, int voff, int soff)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, voff, soff, 0);
-#endif
-}
-
-// The store of one column of a 32x32 block, element by element: any destinations, any size
-__device__ __forceinline__ void store_far(const KArgs& a, const f32x16& acc, int mh, int img, int pix)
-{
-    const ConvGeom& g = a.g;
-    const size_t PQ = (size_t)g.P * g.Q;
-#pragma unroll 1
-    for (int v = 0; v < 16; ++v) {
-        const int m = mh + (v >> 2) * 8 + (v & 3);
-        if (m >= g.K) continue;
-        float o = acc[0];
-#pragma unroll
-        for (int u = 1; u < 16; ++u) o = v == u ? acc[u] : o;
-        if (a.bias) o += a.bias[m];
-        if (a.res) o += a.res[((size_t)img * g.res_ctot + m) * PQ + pix];
-        if (g.relu) o = fmaxf(o, 0.f);
-        const int d = (m >= a.split_end[0]) + (m >= a.split_end[1]) + (m >= a.split_end[2]);
-        float* const yd = d == 0 ? a.y_seg[0] : d == 1 ? a.y_seg[1] : d == 2 ? a.y_seg[2] : a.y_seg[3];
-        const int ct = d == 0 ? a.ctot_seg[0] : d == 1 ? a.ctot_seg[1] : d == 2 ? a.ctot_seg[2] : a.ctot_seg[3];
-        yd[((size_t)img * ct + m) * PQ + pix] = o;
-    }
-}
-
-// The sums of a wave's TM x TN blocks of 32x32, rows from mw and columns from nw on; n0: the tile's first column
-template <int TM, int TN, bool SPLIT>
-__device__ __forceinline__ void store_tile(const KArgs& a, const f32x16 (&acc)[TM][TN], int mw, int nw, int n0)
-{
-    constexpr int OOB = (int)0x80000000;
-    const ConvGeom& g = a.g;
-    const int PQ = g.P * g.Q, half = (threadIdx.x >> 5) & 1, l32 = threadIdx.x & 31;
-    // Accumulator register v of a 32x32 tile holds row 8*(v/4) + 4*half + v%4, column l32.  Addresses are a descriptor that starts at
-    // the tile's first image, a per-lane offset and the row as scalar offset; lanes without an output, and rows beyond the last filter, store
-    // outside the descriptor.  Nothing per element but the bias, the ReLU and the store: with a branch each for bias, residual and destination
-    // (16 dependent loads, some 50 instructions per element, which fp32 matrix instructions of other waves do not overlap with) the store took as
-    // long as six to eight slices.  GoogLeNet's 3a on 32 images, slim: its first level 24.3 -> 20.2 us, the module 99.7 -> 92.9; 4c on 64 images
-    // 166 -> 158.5; 3x3 32 -> 256 on 30 x 45 x 9 with what follows it 44.1 -> 42.1; AlexNet's 5x5, 150 slices, 1 % or less.
-    const int img0 = n0 / PQ;
-    const __amdgpu_buffer_rsrc_t rbias = __builtin_amdgcn_make_buffer_rsrc((void*)a.bias, 0, a.bias ? g.K * 4 : 0, 0x00020000);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int n = nw + j * 32 + l32;
-        const int img = n / PQ, pix = n - img * PQ;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int mb = __builtin_amdgcn_readfirstlane(mw + i * 32), mh = mb + half * 4;
-            const bool whole = mb + 32 <= g.K;                // (wave-uniform)
-            if constexpr (SPLIT) {
-                const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc((void*)(a.part + (size_t)blockIdx.y * g.K * g.Ng), 0, 0x7FFFFFFF, 0x00020000);
-                const int vp = n < g.Ng ? (mh * g.Ng + n) * 4 : OOB;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int row = (v >> 2) * 8 + (v & 3);
-                    buf_store(acc[i][j][v], rp, whole || mh + row < g.K ? vp : OOB, row * g.Ng * 4);
-                }
-                continue;
-            }
-            if (a.far_store) {
-                if (n < g.Ng) store_far(a, acc[i][j], mh, img, pix);
-                continue;
-            }
-            f32x4 o[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) o[q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rbias, (mh + q * 8) * 4, 0, 0));
-#pragma unroll
-            for (int v = 0; v < 16; ++v) o[v >> 2][v & 3] += acc[i][j][v];
-            if (a.res) {
-                const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc((void*)(a.res + (size_t)img0 * g.res_ctot * PQ), 0, 0x7FFFFFFF, 0x00020000);
-                const int vr = n < g.Ng ? (((img - img0) * g.res_ctot + mh) * PQ + pix) * 4 : OOB;
-                float res[16];
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int row = (v >> 2) * 8 + (v & 3);
-                    res[v] = buf_load(rr, whole || mh + row < g.K ? vr : OOB, row * PQ * 4);
-                }
-#pragma unroll
-                for (int v = 0; v < 16; ++v) o[v >> 2][v & 3] += res[v];
-            }
-            if (g.relu) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) o[v >> 2][v & 3] = fmaxf(o[v >> 2][v & 3], 0.f);
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                // rows mb + 8 q .. + 7 have one destination (wave-uniform)
-                const int m8 = mb + q * 8, d = (m8 >= a.split_end[0]) + (m8 >= a.split_end[1]) + (m8 >= a.split_end[2]);
-                const int ct = d == 0 ? a.ctot_seg[0] : d == 1 ? a.ctot_seg[1] : d == 2 ? a.ctot_seg[2] : a.ctot_seg[3];
-                float* const yd = d == 0 ? a.y_seg[0] : d == 1 ? a.y_seg[1] : d == 2 ? a.y_seg[2] : a.y_seg[3];
-                const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void*)(yd + (size_t)img0 * ct * PQ + (size_t)m8 * PQ), 0, 0x7FFFFFFF, 0x00020000);
-                const int vy = n < g.Ng ? (((img - img0) * ct + half * 4) * PQ + pix) * 4 : OOB;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) buf_store(o[q][e], ry, whole || mh + q * 8 + e < g.K ? vy : OOB, e * PQ * 4);
-            }
-        }
-    }
 }
 
 // BM x BN: workgroup tile; WGM x WGN: wave grid (4 waves); BK: k per LDS slice; PF: prefetch distance
@@ -859,49 +722,6 @@ int launch_tile(const KArgs& base, void* ws, size_t ws_bytes, hipStream_t st)
 
 }  // namespace
 
-// The short form of the store: offsets that fit (conv_f32_store.h), and ranges of filters with a destination each that start at multiples of 8 (a lane's half
-// holds four filters of every eight).
-static bool store_fits(const KArgs& a)
-{
-    int ctot = a.g.res_ctot;
-    for (int d = 0; d < 4; ++d) ctot = std::max(ctot, a.ctot_seg[d]);
-    for (int d = 0; d < 3; ++d)
-        if (a.split_end[d] != 0x7FFFFFFF && a.split_end[d] % 8 != 0) return false;
-    return store_tile_fits(ctot, a.g.P, a.g.Q, a.res != nullptr);
-}
-
-// Destinations of a (stacked) layer, tensor sizes.
-static KArgs base_args(const ConvGeom& g, const float* x, const float* w, const float* bias, const float* residual, float* y, const ConvSplit* split)
-{
-    KArgs a;
-    a.x = x; a.w = w; a.bias = bias; a.res = residual; a.y = y; a.g = g;
-    a.grid_m = a.grid_n = 0;
-    a.row_groups = 0;
-    a.part = nullptr;
-    a.splits = a.slices_per_split = 0;
-    a.nsplit = 0;
-    for (int d = 0; d < 4; ++d) { a.y_seg[d] = nullptr; a.ctot_seg[d] = 0; if (d < 3) a.split_end[d] = 0x7FFFFFFF; }
-    a.y_seg[0] = y + (size_t)g.y_coff * g.P * g.Q;
-    a.ctot_seg[0] = g.y_ctot;
-    if (split && split->n > 1) {
-        a.nsplit = split->n;
-        const long PQ = (long)g.P * g.Q;
-        int start = 0;
-        for (int d = 0; d < split->n && d < 4; ++d) {
-            const ConvDest& s = split->dst[d];
-            a.y_seg[d] = (float*)s.y + ((long)s.c_offset - start) * PQ;
-            a.ctot_seg[d] = s.ctot;
-            start += s.k;
-            if (d < 3 && d + 1 < split->n) a.split_end[d] = start;
-        }
-    }
-    a.x_bytes = (int)((size_t)g.N * g.C * g.H * g.W * 4);
-    a.w_bytes = (int)((size_t)g.K * g.Kg * 4);
-    a.w_krsc = g.w_krsc;
-    a.far_store = !store_fits(a);
-    return a;
-}
-
 // 32-row tiles when they pad the filter count less than 64-row tiles (16, 32, 96 filters ...), else 64 x 64 tiles
 static bool rows_of_32(const ConvGeom& g) { return (g.K + 31) / 32 * 32 < (g.K + 63) / 64 * 64; }
 
@@ -954,8 +774,16 @@ bool conv_f32_group_takes(const ConvGeom& g)
     return !g.nhwc && g.w_krsc && g.C % 16 == 0 && xb < (1ull << 31) && wb < (1ull << 31) && g.Ng > 0;
 }
 
-int launch_conv_f32_group(const ConvSmall* jobs, int n, hipStream_t st)
+int launch_conv_f32_group(const ConvSmall* all, int n_all, hipStream_t st)
 {
+    ConvSmall jobs[SMALL_GROUP_MAX], pieces[SMALL_GROUP_MAX];
+    int n = 0, n_pieces = 0;
+    for (int i = 0; i < n_all; ++i) (conv_f32_pieces_takes(all[i].g) ? pieces[n_pieces++] : jobs[n++]) = all[i];
+    if (n_pieces) {
+        const int rc = launch_conv_f32_pieces(pieces, n_pieces, st);
+        if (rc != DR_OK) return rc;
+    }
+    if (!n) return DR_OK;
     GroupArgs a{};
     a.n = n;
     int order[SMALL_GROUP_MAX], blocks = 0;
@@ -963,7 +791,7 @@ int launch_conv_f32_group(const ConvSmall* jobs, int n, hipStream_t st)
     std::sort(order, order + n, [&](int p, int q) { return jobs[p].g.Kg > jobs[q].g.Kg; });      // the longest tiles first
     for (int i = 0; i < n; ++i) {
         const ConvSmall& c = jobs[order[i]];
-        a.job[i] = base_args(c.g, (const float*)c.x, (const float*)c.w, c.bias, (const float*)c.res, (float*)c.y, c.split);
+        a.job[i] = conv_f32_args(c.g, (const float*)c.x, (const float*)c.w, c.bias, (const float*)c.res, (float*)c.y, c.split);
         a.rows32[i] = rows_of_32(c.g);
         a.job[i].grid_m = a.rows32[i] ? (c.g.K + 31) / 32 : (c.g.K + 63) / 64;
         a.job[i].grid_n = a.rows32[i] ? (c.g.Ng + 127) / 128 : (c.g.Ng + 63) / 64;
@@ -976,6 +804,7 @@ int launch_conv_f32_group(const ConvSmall* jobs, int n, hipStream_t st)
 
 size_t conv_f32_scratch_bytes(const ConvGeom& g)
 {
+    if (conv_f32_pieces_takes(g)) return 0;
     if (slices_of_32(g)) return rows_of_32(g) ? split_bytes<32, 128, 32>(g) : split_bytes<64, 64, 32>(g);
     return rows_of_32(g) ? split_bytes<32, 128, 16>(g) : split_bytes<64, 64, 16>(g);
 }
@@ -984,6 +813,10 @@ int launch_conv_f32(const ConvGeom& g, const float* x, const float* w, const flo
                     float* y, hipStream_t st, void* ws, size_t ws_bytes, const ConvSplit* split)
 {
     TraceScope trace("conv_f32", &g, g.Ng, st);
+    if (conv_f32_pieces_takes(g)) {
+        const ConvSmall job{g, x, w, bias, residual, y, split};
+        return launch_conv_f32_pieces(&job, 1, st);
+    }
     if (conv_f32_small_takes(g, w, ws != nullptr)) {
         const ConvSmall job{g, x, w, bias, residual, y, split};
         return launch_conv_f32_small(&job, 1, st);
@@ -993,7 +826,7 @@ int launch_conv_f32(const ConvGeom& g, const float* x, const float* w, const flo
         return fail(DR_ERR_UNSUPPORTED, "conv_f32: input (%zu bytes) or filter tensor (%zu bytes) is 2 GiB or larger", xb, wb);
     // wide filters on few channels, no padding (conv_f32_taps.hip)
     if (conv_f32_taps_takes(g, residual, split) && !cut_beats_taps(g, ws, ws_bytes)) return launch_conv_f32_taps(g, x, w, bias, y, st);
-    KArgs a = base_args(g, x, w, bias, residual, y, split);
+    KArgs a = conv_f32_args(g, x, w, bias, residual, y, split);
     if (kcrs33_takes(g, w, ws, ws_bytes, a.nsplit)) {
         const bool rows32 = rows_of_32(g);
         a.grid_m = rows32 ? (g.K + 31) / 32 : (g.K + 63) / 64;

@@ -1,0 +1,133 @@
+"""Which layers the fp32 kernel on bf16 pieces takes and how its workgroups share the tiles (csrc/conv_f32_pieces_plan.h), compiled for the host: where a tile fits,
+no run of its outputs lies over more input pixels than LDS has places for; a plan gives every tile of every layer to exactly one workgroup."""
+import os
+import random
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1708_04728_amd", "csrc")
+
+PROGRAM = r"""
+#include <cstdio>
+#include <cstring>
+#include "conv_f32_pieces_plan.h"
+int main(int argc, char** argv)
+{
+    if (argc > 1 && !strcmp(argv[1], "plan")) {
+        int n, cus;
+        while (scanf("%d %d", &n, &cus) == 2) {
+            long tiles[dr::PIECES_LAYERS];
+            double cost[dr::PIECES_LAYERS];
+            for (int i = 0; i < n; ++i)
+                if (scanf("%ld %lf", &tiles[i], &cost[i]) != 2) return 1;
+            dr::PiecesPlan p;
+            const bool found = dr::pieces_plan(n, tiles, cost, cus, &p);
+            printf("%d %d %.6f", found, p.workgroups, p.us);
+            for (int i = 0; found && i < n; ++i) {
+                printf(" %d", p.layer[i].n);
+                for (int k = 0; k < p.layer[i].n; ++k) printf(" %d %d %d %d", p.layer[i].first[k], p.layer[i].first[k + 1], p.layer[i].per[k], p.layer[i].tile[k]);
+            }
+            printf("\n");
+        }
+        return 0;
+    }
+    dr::PiecesLayer l;
+    int ph, pw;
+    while (scanf("%d %d %d %d %d %d %d %d %d %d %d", &l.N, &l.C, &l.H, &l.W, &l.K, &l.R, &l.S, &l.sh, &l.sw, &ph, &pw) == 11) {
+        l.P = (l.H + 2 * ph - l.R) / l.sh + 1;
+        l.Q = (l.W + 2 * pw - l.S) / l.sw + 1;
+        double us = 0;
+        printf("%d %d", dr::pieces_pays(l, 256), dr::pieces_best(l, 256, &us));
+        for (const dr::PiecesTile& t : dr::pieces_tiles) printf(" %d", dr::pieces_fits(l, t) ? t.patch : 0);
+        printf("\n");
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    d = tmp_path_factory.mktemp("pieces")
+    (d / "plan.cpp").write_text(PROGRAM)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=undefined", "-I", CSRC, str(d / "plan.cpp"), "-o", str(d / "plan")])
+
+    def ask(lines, *args):
+        out = subprocess.run([str(d / "plan"), *args], input="\n".join(lines), capture_output=True, text=True, check=True, timeout=60).stdout.splitlines()
+        assert len(out) == len(lines)
+        return [line.split() for line in out]
+    return ask
+
+
+def patch_pixels(P, Q, R, S, first, last):
+    """Input pixels under the outputs first .. last of a stack of P x Q maps: per image the rows under its rows, Q + S - 1 wide."""
+    rows = 0
+    for img in range(first // (P * Q), last // (P * Q) + 1):
+        a, b = max(first, img * P * Q) - img * P * Q, min(last, (img + 1) * P * Q - 1) - img * P * Q
+        # the first image from its first row of the tile on, the others from their first row on
+        rows += (b // Q if img == last // (P * Q) else P - 1) - (a // Q if img == first // (P * Q) else 0) + R
+    return rows * (Q + S - 1)
+
+
+def test_a_tile_that_fits_has_room_for_every_patch(program):
+    rng = random.Random(4)
+    layers = []
+    while len(layers) < 400:
+        R, S = rng.choice(((3, 3), (5, 5), (2, 4), (4, 2), (1, 9), (9, 1), (7, 7), (3, 5)))
+        H, W = rng.choice((rng.randint(1, 12), rng.randint(5, 80))), rng.choice((rng.randint(1, 12), rng.randint(5, 80)))
+        ph, pw = rng.randint(0, R), rng.randint(0, S)
+        if H + 2 * ph >= R and W + 2 * pw >= S:
+            layers.append((rng.randint(1, 40), 16, H, W, 64, R, S, 1, 1, ph, pw))
+    fitting = 0
+    for (N, _, H, W, _, R, S, _, _, ph, pw), (_, _, *caps) in zip(layers, program([" ".join(map(str, l)) for l in layers])):
+        P, Q = H + 2 * ph - R + 1, W + 2 * pw - S + 1
+        for pixels, cap in zip((128, 128, 128, 256), map(int, caps)):
+            if not cap:
+                continue
+            fitting += 1
+            most = max(patch_pixels(P, Q, R, S, n, min(n + pixels, N * P * Q) - 1) for n in range(0, N * P * Q, pixels))
+            assert most <= cap and most <= R * S // 2 * 128, (N, H, W, R, S, ph, pw, pixels)
+    assert fitting > 500
+
+
+def test_what_stays_with_the_other_kernels(program):
+    taken = (32, 96, 28, 28, 128, 3, 3, 1, 1, 1, 1)
+    beside = [(32, 96, 28, 28, 128, 1, 1, 1, 1, 0, 0),       # one tap
+              (32, 96, 28, 28, 128, 3, 3, 2, 1, 1, 1),       # a stride
+              (32, 24, 28, 28, 128, 3, 3, 1, 1, 1, 1),       # channels not in sixteens
+              (32, 96, 28, 28, 128, 1, 7, 1, 1, 0, 3),       # seven taps
+              (1, 96, 28, 28, 128, 3, 3, 1, 1, 1, 1),        # one image: few tiles
+              (2, 16, 28, 300, 128, 3, 3, 1, 1, 1, 1),       # a row of 300 pixels
+              (4, 16, 1200, 60, 64, 3, 3, 1, 1, 1, 1)]       # 72000 pixels
+    got = [int(v[0]) for v in program([" ".join(map(str, l)) for l in [taken] + beside])]
+    assert got == [1] + [0] * len(beside)
+
+
+def test_every_tile_has_one_workgroup(program):
+    rng = random.Random(5)
+    cases = [(1, 256, [(1, 10.0)]), (1, 256, [(256, 10.0)]), (1, 256, [(257, 10.0)]), (2, 256, [(196, 27.0), (196, 12.5)]), (4, 256, [(1, 9.0), (1, 8.0), (1, 7.0), (1, 6.0)]),
+             (1, 1, [(7, 3.0)]), (3, 256, [(100000, 50.0), (3, 1.0), (70000, 1.0)])]
+    while len(cases) < 3000:
+        n = rng.randint(1, 4)
+        cases.append((n, rng.choice((1, 2, 8, 64, 256, 304)), sorted([(int(10 ** rng.uniform(0, 4)), rng.uniform(3, 100)) for _ in range(n)], key=lambda v: -v[1])))
+    for (n, cus, layers), out in zip(cases, program(["%d %d " % (n, cus) + " ".join("%d %.6f" % v for v in layers) for n, cus, layers in cases], "plan")):
+        assert out[0] == "1", (n, cus, layers)
+        workgroups, us, v = int(out[1]), float(out[2]), [int(x) for x in out[3:]]
+        assert 1 <= workgroups <= cus
+        load = [0.0] * cus
+        for tiles, cost in layers:
+            ranges, v = v[0], v[1:]
+            at, wg = 0, 0
+            for _ in range(ranges):
+                (first, end, per, tile), v = v[:4], v[4:]
+                assert first == wg and end > first
+                wg = end
+                if per:
+                    assert tile == at and end <= workgroups
+                    at += per * (end - first)
+                    for w in range(first, end):
+                        load[w] += per * cost
+            assert wg == cus and at == tiles, (n, cus, layers)
+        assert max(load) == pytest.approx(us, rel=1e-6)
+        # no longer than the work spread evenly and one more tile of each layer
+        assert us <= sum(t * c for t, c in layers) / cus + sum(c for _, c in layers) + 1e-6
