@@ -771,7 +771,7 @@ static bool kcrs33_takes(const ConvGeom& g, const void* w, const void* ws, size_
 bool conv_f32_group_takes(const ConvGeom& g)
 {
     const size_t xb = (size_t)g.N * g.C * g.H * g.W * 4, wb = (size_t)g.K * g.Kg * 4;
-    return !g.nhwc && g.w_krsc && g.C % 16 == 0 && xb < (1ull << 31) && wb < (1ull << 31) && g.Ng > 0;
+    return !g.nhwc && g.w_krsc && g.C % 16 == 0 && xb < (1ull << 31) && wb < (1ull << 31) && g.Ng > 0 && !conv_f32_direct_takes(g);
 }
 
 int launch_conv_f32_group(const ConvSmall* all, int n_all, hipStream_t st)
@@ -804,7 +804,7 @@ int launch_conv_f32_group(const ConvSmall* all, int n_all, hipStream_t st)
 
 size_t conv_f32_scratch_bytes(const ConvGeom& g)
 {
-    if (conv_f32_pieces_takes(g)) return 0;
+    if (conv_f32_pieces_takes(g) || conv_f32_direct_takes(g)) return 0;
     if (slices_of_32(g)) return rows_of_32(g) ? split_bytes<32, 128, 32>(g) : split_bytes<64, 64, 32>(g);
     return rows_of_32(g) ? split_bytes<32, 128, 16>(g) : split_bytes<64, 64, 16>(g);
 }
@@ -813,10 +813,11 @@ int launch_conv_f32(const ConvGeom& g, const float* x, const float* w, const flo
                     float* y, hipStream_t st, void* ws, size_t ws_bytes, const ConvSplit* split)
 {
     TraceScope trace("conv_f32", &g, g.Ng, st);
-    if (conv_f32_pieces_takes(g)) {
+    if (!residual && conv_f32_pieces_takes(g)) {
         const ConvSmall job{g, x, w, bias, residual, y, split};
         return launch_conv_f32_pieces(&job, 1, st);
     }
+    if (!residual && conv_f32_direct_takes(g)) return launch_conv_f32_direct(ConvSmall{g, x, w, bias, nullptr, y, split}, st);
     if (conv_f32_small_takes(g, w, ws != nullptr)) {
         const ConvSmall job{g, x, w, bias, residual, y, split};
         return launch_conv_f32_small(&job, 1, st);

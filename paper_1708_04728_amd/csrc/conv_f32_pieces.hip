@@ -23,31 +23,11 @@
 // 28 x 28 x 32 59 -> 37, 64 -> 192 on 56 x 56 x 32 178 -> 138; 64 -> 128 5x5 on 29 x 25 x 120 285 -> 174.  In the loop the matrix cores are busy 75 to 85 %.
 #include <algorithm>
 
-#include "conv_f32_dev.h"
+#include "conv_f32_cut.h"
 #include "conv_f32_pieces_plan.h"
 
 namespace dr {
 namespace {
-
-// Eight operands as three vectors of bf16: high + middle + low == v, exactly (8 bits of the significand each, the lower ones with a sign of their own).
-__device__ __forceinline__ void split8(const float (&v)[8], u32x4& high, u32x4& middle, u32x4& low)
-{
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const unsigned h = pack_bf16x2(v[2 * i], v[2 * i + 1]);
-        const float ra = v[2 * i] - __uint_as_float(h << 16), rb = v[2 * i + 1] - __uint_as_float(h & 0xFFFF0000u);
-        const unsigned m = pack_bf16x2(ra, rb);
-        const float la = ra - __uint_as_float(m << 16), lb = rb - __uint_as_float(m & 0xFFFF0000u);
-        high[i] = h;
-        middle[i] = m;
-        low[i] = __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), 0x07060302u);
-    }
-}
-
-__device__ __forceinline__ f32x16 mfma(u32x4 a, u32x4 b, f32x16 c)
-{
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
 
 // LDS: for each piece and each 8 of a slice's k a run of rows (filters or pixels), 16 bytes each
 template <int ROWS> constexpr int chunk_stride() { return ROWS * 16 + 64; }
@@ -60,38 +40,6 @@ constexpr int pieces_lds()
     int most = 0;
     for (const PiecesTile& t : pieces_tiles) most = std::max(most, filter_bytes(t) + 2 * patch_bytes(t) + t.patch * 8);
     return most;
-}
-
-// One block of 32 x 32 outputs by fp32 matrix instructions, straight from memory: for operands that three bf16 pieces do not hold
-__device__ __forceinline__ f32x16 exact_block(const KArgs& a, int m, int n, int half)
-{
-    const ConvGeom& g = a.g;
-    const int HW = g.H * g.W, PQ = g.P * g.Q;
-    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)a.x, 0, a.x_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, a.w_bytes, 0x00020000);
-    const int nn = n < g.Ng ? n : 0, img = nn / PQ, pix = nn - img * PQ, p = pix / g.Q, q = pix - p * g.Q, ih0 = p * g.sh - g.ph, iw0 = q * g.sw - g.pw;
-    const int arow = m < g.K ? m * g.Kg * 4 + half * 32 : OOB;
-    f32x16 acc;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-    for (int r = 0; r < g.R; ++r)
-        for (int s = 0; s < g.S; ++s) {
-            const bool ok = (n < g.Ng) & ((unsigned)(ih0 + r) < (unsigned)g.H) & ((unsigned)(iw0 + s) < (unsigned)g.W);
-            const int base = ok ? ((img * g.C + half * 8) * HW + (ih0 + r) * g.W + iw0 + s) * 4 : OOB;
-#pragma unroll 1
-            for (int c = 0; c < g.C; c += 16) {
-                const int sa = ((r * g.S + s) * g.C + c) * 4;
-                f32x4 fa[2];
-                float fb[8];
-#pragma unroll
-                for (int i = 0; i < 2; ++i) fa[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rw, arow, sa + i * 16, 0));
-#pragma unroll
-                for (int j = 0; j < 8; ++j) fb[j] = buf_load(rx, base, (c + j) * HW * 4);
-#pragma unroll
-                for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[j >> 2][j & 3], fb[j], acc, 0, 0, 0);
-            }
-        }
-    return acc;
 }
 
 struct PatchArgs {
@@ -160,18 +108,6 @@ __device__ __forceinline__ void patch_tiles(const int job, const int tile0, cons
         const float *const w = a.w, *const x = a.x;
         float ra[2][AU][8], rb[8];
         unsigned least = 0xFFFFFFFFu;            // of the largest values of eight, as bits, less one: zeros count as large
-        auto put = [&](const float (&v)[8], unsigned char* d, int ps) __attribute__((always_inline)) {
-            u32x4 p3[3];
-            split8(v, p3[0], p3[1], p3[2]);
-#pragma unroll
-            for (int e = 0; e < 3; ++e) *reinterpret_cast<u32x4*>(d + e * ps) = p3[e];
-            float m = fmaxf(fabsf(v[0]), fabsf(v[1]));
-#pragma unroll
-            for (int e = 2; e < 8; e += 2) m = fmaxf(fmaxf(m, fabsf(v[e])), fabsf(v[e + 1]));
-            least = min(least, __float_as_uint(m) - 1);
-            asm volatile("" : "+v"(least));      // (here: later it would keep v from being loaded again into the same registers)
-        };
-
         // A: the filters, a walk over (tile, 16 channels, tap) that runs three slices ahead
         int a_tile = tile0, a_step = 0, a_tap = 0, a_blk = 0, a_m = Patch(pa, tile0, BM, BN).m0 * g.Kg * 4;
         const int a_end = tile0 + count;
@@ -208,7 +144,7 @@ __device__ __forceinline__ void patch_tiles(const int job, const int tile0, cons
             constexpr int SET = decltype(set_c)::value;
 #pragma unroll
             for (int i = 0; i < AU; ++i)
-                if (BM * 4 % 256 == 0 || a_ks[i] < 2) put(ra[SET][i], lds + SET * STAGE + a_lds[i], PSA);
+                if (BM * 4 % 256 == 0 || a_ks[i] < 2) put_pieces(ra[SET][i], lds + SET * STAGE + a_lds[i], PSA, least);
         };
 
         // B: the patches, a walk over (tile, 16 channels, unit)
@@ -268,7 +204,7 @@ __device__ __forceinline__ void patch_tiles(const int job, const int tile0, cons
             load_a(IC<0>{});
 #pragma unroll
             for (int i = 0; i < PATCH_UNITS; ++i)
-                if (i < b_units) put(first[i], patch + place(i), PATCH_PIECE);
+                if (i < b_units) put_pieces(first[i], patch + place(i), PATCH_PIECE, least);
             b_unit = b_units - 1;
             b_next();
         }
@@ -283,12 +219,12 @@ __device__ __forceinline__ void patch_tiles(const int job, const int tile0, cons
             load_a(set_c);
             if (k >= next_start) { ++m_blk; ++m_serial; next_start = ((m_blk + 1) * T + 1) >> 1; }
             if (b_serial == m_serial + 1) {
-                put(rb, patch + (b_serial & 1) * PATCH_BYTES + b_at, PATCH_PIECE);
+                put_pieces(rb, patch + (b_serial & 1) * PATCH_BYTES + b_at, PATCH_PIECE, least);
                 __builtin_amdgcn_sched_barrier(0);
                 b_next();
             }
             if (++k == slices) { k = 0; m_blk = 0; ++m_serial; next_start = (T + 1) >> 1; }
-            if (__any(least < __float_as_uint(0x1p-100f) - 1)) *tiny = 1;      // (for the rest of the workgroup's tiles)
+            if (too_small(least)) *tiny = 1;      // (for the rest of the workgroup's tiles)
             ring_barrier();
         };
         for (int at = 0; at < total; at += 2) {
@@ -384,53 +320,7 @@ __device__ __forceinline__ void patch_tiles(const int job, const int tile0, cons
         }
         const KArgs& a = fresh_args(job).k;
         const Patch t(fresh_args(job), tile, BM, BN);
-        f32x4 bias[TM][4];
-        const __amdgpu_buffer_rsrc_t rbias = __builtin_amdgcn_make_buffer_rsrc((void*)a.bias, 0, a.bias ? a.g.K * 4 : 0, 0x00020000);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                bias[i][q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rbias, (half * 4 + q * 8) * 4, (t.m0 + (wm * TM + i) * 32) * 4, 0));
-        const bool all = __builtin_amdgcn_readfirstlane(*reinterpret_cast<volatile int*>(tiny)) != 0;
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                float z = 0.f;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    acc[i][j][v] += small[i][j][v];
-                    z = __builtin_fmaf(acc[i][j][v], 0.f, z);
-                }
-                if (all || __any(z != 0.f)) acc[i][j] = exact_block(a, t.m0 + (wm * TM + i) * 32 + l32, t.n0 + (wn * TN + j) * 32 + l32, half);
-            }
-        const int mw = t.m0 + wm * TM * 32;
-        if (a.res || a.nsplit > 1 || a.far_store || mw + TM * 32 > a.g.K) {
-            store_tile<TM, TN, false>(a, acc, mw, t.n0 + wn * TN * 32, t.n0);
-        } else {
-            // one destination, whole blocks: a store per element whose filter is the scalar offset
-            const int PQ = a.g.P * a.g.Q, plane = PQ * 4, ct = a.ctot_seg[0];
-            const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void*)(a.y_seg[0] + ((size_t)t.img0 * ct + mw) * PQ), 0, 0x7FFFFFFF, 0x00020000);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int n = t.n0 + (wn * TN + j) * 32 + l32, o = n - t.img0 * PQ, img = div_small(o, fresh_args(job).by_pq);
-                const int vy = n < a.g.Ng ? ((img * ct + half * 4) * PQ + o - img * PQ) * 4 : OOB;
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        f32x4 v = bias[i][q];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) v[e] += acc[i][j][q * 4 + e];
-                        if (a.g.relu) {
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
-                        }
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) buf_store(v[e], ry, vy, (i * 32 + q * 8 + e) * plane);
-                    }
-            }
-        }
+        finish_tile<TM, TN>(a, acc, small, t.m0 + wm * TM * 32, t.n0 + wn * TN * 32, t.n0, t.img0, fresh_args(job).by_pq, tiny);
         t_buf = PATCH_BYTES - t_buf;
     }
     if (count * slices & 1) ring_barrier();      // (the loading waves go in pairs of slices)

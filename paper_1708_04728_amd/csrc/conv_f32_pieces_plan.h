@@ -48,11 +48,15 @@ inline int pieces_best(const PiecesLayer& l, int cus, double* us)
 // small-layer kernel takes (6 % off), and larger ones in tiles of 64 x 64 or 32 x 128 (7 %).  Of 133 layers drawn around the line none is slower than before
 // with the margin of a tenth, the choice takes 1.007 times the best one's time on average, and they gain a factor of 1.23; the line in figures: 3x3 96 -> 96 on
 // 28 x 28 x 12 29.2 us there and 32.0 here, 32 -> 96 on 28 x 28 x 16 14.3 and 14.1, 160 -> 128 on 28 x 28 x 11 43.6 and 36.4, 32 -> 128 on 27 x 27 x 15 17.4 and 12.8;
-// 32 filters use half of a tile here: 3x3 192 -> 32 on 68 x 70 x 30 196 and 238.  Up to two blocks of 32 x 32 per compute unit the others are at least twice as
-// fast (tiles here leave most compute units idle).
+// of 70 more, on rectified operands, one is slower (3x3 64 -> 40 on 18 x 68 x 119 91.2 and 94.3).
+// Contractions of up to nine slices, whose tiles are mostly start and end, have a wider margin (3x3 16 -> 360 on 5 x 13 x 63 10.4 and 12.0, 32 -> 232 on 12 x 67 x 22 29.7 and 31.5); eight taps (2x4 16 -> 43
+// on 21 x 21 x 75 9.1 and 10.6, 144 -> 69 on 32 x 25 x 12 27.7 and 30.5) stay there, and 32 filters use half of a tile here: 3x3 192 -> 32 on 68 x 70 x 30 196 and 238.
+// Fewer tiles than three for four compute units leave room that the layers of a module's depth would fill in one launch of the other kernels: the fused form of 5a on 64
+// images, with a 3x3 160 -> 320 of 125 tiles, 132 us there and 142 here, so they have a wider margin too.  Up to two blocks of 32 x 32 per compute unit the others are at
+// least twice as fast (tiles here leave most compute units idle).
 inline bool pieces_pays(const PiecesLayer& l, int cus)
 {
-    if (l.sh != 1 || l.sw != 1 || l.C % 16 != 0 || l.R * l.S < 8 || (long)l.P * l.Q > 65536 || (long)l.P + l.R > 65536) return false;
+    if (l.sh != 1 || l.sw != 1 || l.C % 16 != 0 || l.R * l.S < 9 || (long)l.P * l.Q > 65536 || (long)l.P + l.R > 65536) return false;
     const double Ng = (double)l.N * l.P * l.Q, slices = (double)l.R * l.S * (l.C / 16);
     const double small = ceil(Ng / 32) * ((l.K + 31) / 32) / cus;
     if (small <= 2) return false;
@@ -63,7 +67,9 @@ inline bool pieces_pays(const PiecesLayer& l, int cus)
         other = 5.6 + 0.61 * tiles + 0.277 * tiles * slices + 0.282 * (ceil(tiles) - tiles) * slices;
     }
     double us = 0;
-    return pieces_best(l, cus, &us) >= 0 && us < 0.9 * other;
+    const int best = pieces_best(l, cus, &us);
+    if (best < 0) return false;
+    return us < (4 * pieces_count(l, pieces_tiles[best]) < 3 * cus ? 0.7 : pieces_slices(l) <= 9 ? 0.75 : 0.9) * other;
 }
 
 // How the workgroups share the tiles of up to 4 layers: for each layer ranges of workgroups with the same number of tiles each

@@ -261,7 +261,7 @@ bool conv_f32_small_takes(const ConvGeom& g, const void* w, bool scratch)
     const size_t xb = (size_t)g.N * g.C * g.H * g.W * 4, wb = (size_t)g.K * g.Kg * 4;
     if (g.nhwc || g.C % 16 != 0 || (!g.w_krsc && g.R * g.S != 1) || !aligned16(w) || xb >= (1ull << 31) || wb >= (1ull << 31)) return false;
     const long tiles = small_tiles(g), cus = device_cus();
-    if (tiles > 11 * cus / 2 || conv_f32_pieces_takes(g)) return false;
+    if (tiles > 11 * cus / 2 || conv_f32_pieces_takes(g) || conv_f32_direct_takes(g)) return false;
     if (g.R * g.S == 1 && g.Ng > 4096) return false;
     if (g.sw > 1 && g.Kg > 1200 && tiles > cus) return false;
     if (!scratch) return true;

@@ -79,6 +79,9 @@ int launch_conv_f32_group(const ConvSmall* jobs, int n, hipStream_t st);
 // conv_f32_pieces.hip: layers of several taps at stride 1 on the bf16 matrix cores, with fp32 operands in three pieces; up to SMALL_GROUP_MAX in one launch
 bool conv_f32_pieces_takes(const ConvGeom& g);
 int launch_conv_f32_pieces(const ConvSmall* jobs, int n, hipStream_t st);
+// conv_f32_direct.hip: strided layers of several taps so
+bool conv_f32_direct_takes(const ConvGeom& g);
+int launch_conv_f32_direct(const ConvSmall& job, hipStream_t st);
 
 // conv_bf16_dma.hip: the streaming bf16 kernel (NHWC, KRSC filters, C % 8 == 0, 16-byte aligned tensors); the kernels for small layers, patches and
 // wide tiles take the same layers or some of them

@@ -1,4 +1,4 @@
-"""Which layers the fp32 kernel on bf16 pieces takes and how its workgroups share the tiles (csrc/conv_f32_pieces_plan.h), compiled for the host: where a tile fits,
+"""Which layers the fp32 kernels on bf16 pieces take and how their workgroups share the tiles (csrc/conv_f32_pieces_plan.h, conv_f32_direct_plan.h), compiled for the host: where a tile fits,
 no run of its outputs lies over more input pixels than LDS has places for; a plan gives every tile of every layer to exactly one workgroup."""
 import os
 import random
@@ -11,7 +11,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 PROGRAM = r"""
 #include <cstdio>
 #include <cstring>
-#include "conv_f32_pieces_plan.h"
+#include "conv_f32_direct_plan.h"
 int main(int argc, char** argv)
 {
     if (argc > 1 && !strcmp(argv[1], "plan")) {
@@ -38,7 +38,7 @@ int main(int argc, char** argv)
         l.P = (l.H + 2 * ph - l.R) / l.sh + 1;
         l.Q = (l.W + 2 * pw - l.S) / l.sw + 1;
         double us = 0;
-        printf("%d %d", dr::pieces_pays(l, 256), dr::pieces_best(l, 256, &us));
+        printf("%d %d %d", dr::pieces_pays(l, 256), dr::direct_pays(l, 256), l.sh * l.sw > 1 ? dr::direct_best(l, 256, &us) : dr::pieces_best(l, 256, &us));
         for (const dr::PiecesTile& t : dr::pieces_tiles) printf(" %d", dr::pieces_fits(l, t) ? t.patch : 0);
         printf("\n");
     }
@@ -79,7 +79,7 @@ def test_a_tile_that_fits_has_room_for_every_patch(program):
         if H + 2 * ph >= R and W + 2 * pw >= S:
             layers.append((rng.randint(1, 40), 16, H, W, 64, R, S, 1, 1, ph, pw))
     fitting = 0
-    for (N, _, H, W, _, R, S, _, _, ph, pw), (_, _, *caps) in zip(layers, program([" ".join(map(str, l)) for l in layers])):
+    for (N, _, H, W, _, R, S, _, _, ph, pw), (_, _, _, *caps) in zip(layers, program([" ".join(map(str, l)) for l in layers])):
         P, Q = H + 2 * ph - R + 1, W + 2 * pw - S + 1
         for pixels, cap in zip((128, 128, 128, 256), map(int, caps)):
             if not cap:
@@ -90,17 +90,29 @@ def test_a_tile_that_fits_has_room_for_every_patch(program):
     assert fitting > 500
 
 
+def test_the_kernel_and_tile_of_the_gpu_cases(program):
+    from test_gpu_conv_f32_pieces import CASES, STRIDED
+    got = program([" ".join(map(str, c[:7] + (1, 1) + c[7])) for c, _ in CASES] + [" ".join(map(str, c[:7] + c[7] + c[8])) for c, _ in STRIDED])
+    assert [tuple(map(int, v[:3])) for v in got] == [(1, 0, t) for _, t in CASES] + [(0, 1, t) for _, t in STRIDED]
+    # the layers with operands that pieces cannot hold
+    assert [v[:2] for v in program(["28 32 30 30 96 3 3 1 1 1 1", "28 32 30 30 96 3 3 1 1 0 0", "40 32 41 33 200 3 3 2 2 1 1", "40 32 41 33 200 3 3 2 2 0 0"])] == [["1", "0"]] * 2 + [["0", "1"]] * 2
+
+
 def test_what_stays_with_the_other_kernels(program):
-    taken = (32, 96, 28, 28, 128, 3, 3, 1, 1, 1, 1)
+    taken = ((32, 96, 28, 28, 128, 3, 3, 1, 1, 1, 1), (52, 160, 28, 28, 288, 3, 3, 2, 2, 1, 1))
     beside = [(32, 96, 28, 28, 128, 1, 1, 1, 1, 0, 0),       # one tap
-              (32, 96, 28, 28, 128, 3, 3, 2, 1, 1, 1),       # a stride
+              (32, 96, 28, 28, 128, 3, 3, 2, 1, 1, 1),       # a stride in one direction
               (32, 24, 28, 28, 128, 3, 3, 1, 1, 1, 1),       # channels not in sixteens
-              (32, 96, 28, 28, 128, 1, 7, 1, 1, 0, 3),       # seven taps
+              (32, 96, 28, 28, 128, 2, 4, 1, 1, 0, 3),       # eight taps
               (1, 96, 28, 28, 128, 3, 3, 1, 1, 1, 1),        # one image: few tiles
               (2, 16, 28, 300, 128, 3, 3, 1, 1, 1, 1),       # a row of 300 pixels
-              (4, 16, 1200, 60, 64, 3, 3, 1, 1, 1, 1)]       # 72000 pixels
-    got = [int(v[0]) for v in program([" ".join(map(str, l)) for l in [taken] + beside])]
-    assert got == [1] + [0] * len(beside)
+              (4, 16, 1200, 60, 64, 3, 3, 1, 1, 1, 1),       # 72000 pixels
+              (64, 160, 7, 7, 320, 3, 3, 1, 1, 1, 1),        # tiles for half of the compute units
+              (128, 96, 28, 28, 256, 5, 5, 2, 2, 2, 2),      # strided, whole tiles of 64 filters
+              (5, 64, 56, 56, 96, 3, 3, 2, 2, 1, 1),         # strided: not enough faster
+              (97, 128, 35, 34, 40, 5, 5, 2, 2, 2, 2)]       # strided, 40 filters
+    got = [v[:2] for v in program([" ".join(map(str, l)) for l in [*taken] + beside])]
+    assert got == [["1", "0"], ["0", "1"]] + [["0", "0"]] * len(beside)
 
 
 def test_every_tile_has_one_workgroup(program):

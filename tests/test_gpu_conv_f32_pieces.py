@@ -1,5 +1,5 @@
-"""GPU parity of the fp32 kernel on three bf16 pieces against the oracle: at the edges of its tiles (128 x 128, 96 x 128, 64 x 128 and 64 x 256 filters x pixels), its
-slices and its patches, which cross rows and images; and operands that bf16 pieces cannot hold."""
+"""GPU parity of the fp32 kernels on three bf16 pieces against the oracle: at the edges of their tiles (128 x 128, 96 x 128, 64 x 128 and 64 x 256 filters x pixels),
+slices and patches, which cross rows and images, and at strides; and operands that bf16 pieces cannot hold."""
 import numpy as np
 import pytest
 
@@ -11,11 +11,11 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-def run(x, w, b, pad, relu, k_off=0):
+def run(x, w, b, pad, relu, stride=(1, 1)):
     K, C, R, S = w.shape
-    (N, _, H, W), (ph, pw) = x.shape, pad
-    P, Q = H + 2 * ph - R + 1, W + 2 * pw - S + 1
-    cd = B.conv_desc(K, C, R, S, 1, pad, relu, B.DR_KRSC)
+    N, _, H, W = x.shape
+    P, Q = (oracle.conv_out_size(*v) for v in ((H, R, stride[0], pad[0]), (W, S, stride[1], pad[1])))
+    cd = B.conv_desc(K, C, R, S, stride, pad, relu, B.DR_KRSC)
     y = torch.full((N, K + 3, P, Q), float("nan"), device="cuda")
     B.conv2d_fwd(gpu(x), cd, B.pack_filters(gpu(w)), None if b is None else gpu(b), y, 2)
     torch.cuda.synchronize()
@@ -23,76 +23,91 @@ def run(x, w, b, pad, relu, k_off=0):
     return host(y[:, 2:K + 2])
 
 
-@pytest.mark.parametrize("case", [
-    # N, C, H, W, K, R, S, pad: with 256 compute units the tile that the comment names
-    (70, 16, 7, 43, 250, 3, 3, (0, 0)),     # 128 x 128, the last block of filters not whole; one block of channels
-    (9, 32, 39, 46, 97, 3, 3, (2, 1)),      # ... more padding than the taps need
-    (19, 32, 25, 41, 127, 4, 2, (0, 0)),    # ... eight taps: a block is four slices
-    (150, 16, 46, 12, 128, 1, 9, (1, 0)),   # ... one row of taps
-    (37, 32, 31, 17, 97, 9, 1, (2, 1)),     # ... one column
-    (19, 48, 20, 55, 65, 3, 3, (0, 1)),     # 96 x 128, three blocks of channels: blocks start in the middle of a slice
-    (5, 16, 86, 35, 129, 3, 3, (2, 2)),     # ... one filter in the last block
-    (19, 16, 40, 27, 65, 5, 5, (1, 0)),     # ... 25 taps
-    (9, 32, 43, 50, 64, 3, 3, (0, 0)),      # 64 x 128
-    (300, 16, 7, 7, 65, 3, 3, (1, 1)),      # ... several images under a tile
-    (700, 16, 5, 4, 72, 3, 3, (1, 1)),      # ... seven
-    (37, 16, 39, 15, 33, 7, 7, (3, 3)),     # ... 49 taps
-    (5, 16, 56, 56, 97, 3, 3, (1, 1)),      # ... the widest rows
-    (37, 32, 55, 21, 33, 3, 3, (1, 1)),     # 64 x 256
-    (9, 16, 86, 21, 250, 3, 3, (2, 0)),     # ...
-    (37, 16, 43, 23, 33, 5, 5, (3, 2)),     # ... the largest patches
-    (37, 32, 45, 10, 129, 9, 1, (5, 0)),    # ...
-])
+# N, C, H, W, K, R, S, pad; the tile that the rule gives each (tests/test_conv_f32_pieces_plan.py)
+CASES = [
+    ((5, 32, 80, 67, 97, 3, 3, (2, 1)), 0),      # 128 x 128: 97 filters; more padding than the taps need
+    ((100, 32, 31, 6, 97, 1, 9, (0, 5)), 0),      # one row of taps
+    ((102, 32, 11, 20, 97, 9, 1, (4, 1)), 0),     # one column
+    ((215, 16, 55, 4, 97, 5, 5, (3, 1)), 0),     # one block of channels, 25 taps
+    ((9, 32, 54, 49, 65, 3, 3, (0, 0)), 1),      # 96 x 128
+    ((37, 48, 31, 18, 65, 9, 1, (5, 1)), 1),     # three blocks of channels: blocks start in the middle of a slice
+    ((150, 32, 8, 12, 129, 1, 9, (1, 3)), 1),    # one image and a bit under a tile
+    ((12, 16, 61, 31, 65, 5, 5, (2, 2)), 1),
+    ((300, 32, 7, 7, 65, 3, 3, (1, 1)), 2),      # 64 x 128: three images under a tile, one filter in the last block
+    ((732, 32, 5, 4, 72, 3, 3, (1, 1)), 2),      # seven
+    ((5, 32, 56, 56, 97, 3, 3, (1, 1)), 2),      # the widest rows
+    ((51, 16, 51, 11, 33, 7, 7, (1, 2)), 2),     # 49 taps
+    ((13, 48, 18, 47, 127, 3, 3, (2, 1)), 2),
+    ((29, 32, 52, 35, 33, 3, 3, (0, 1)), 3),     # 64 x 256
+    ((55, 16, 29, 33, 33, 5, 5, (3, 0)), 3),     # the largest patches
+    ((85, 32, 51, 11, 33, 9, 1, (5, 0)), 3),
+]
+# N, C, H, W, K, R, S, stride, pad; the tile that the rule gives each
+STRIDED = [
+    ((37, 32, 39, 31, 200, 3, 3, (2, 2), (1, 2)), 0),
+    ((19, 16, 78, 150, 200, 4, 4, (4, 4), (1, 0)), 0),
+    ((3, 16, 123, 119, 200, 5, 5, (2, 2), (3, 0)), 0),      # an odd number of k-steps: half of the last slice is empty
+    ((5, 32, 137, 74, 200, 1, 9, (2, 2), (1, 2)), 0),
+    ((19, 32, 40, 135, 65, 3, 3, (2, 2), (1, 0)), 1),
+    ((37, 16, 49, 91, 65, 4, 4, (3, 2), (2, 0)), 1),
+    ((9, 48, 123, 36, 129, 3, 3, (2, 2), (1, 2)), 2),
+    ((2, 16, 118, 101, 257, 5, 5, (2, 2), (2, 3)), 2),
+]
+
+
+@pytest.mark.parametrize("case", [c[:7] + ((1, 1), c[7]) for c, _ in CASES] + [c for c, _ in STRIDED])
 def test_pieces(case):
-    N, C, H, W, K, R, S, pad = case
+    N, C, H, W, K, R, S, stride, pad = case
     rng = np.random.default_rng(case_seed(case))
     x = rng.standard_normal((N, C, H, W)).astype(np.float32)
     w = rng.standard_normal((K, C, R, S)).astype(np.float32) * np.float32(np.sqrt(2.0 / (C * R * S)))
     b = rng.standard_normal(K).astype(np.float32)
-    ref = oracle.conv2d(x, w, b, 1, pad, True)
-    got = run(x, w, b, pad, True)
+    ref = oracle.conv2d(x, w, b, stride, pad, True)
+    got = run(x, w, b, pad, True, stride)
     assert close(got, ref, TOL_F32)
     # C R S / 16 sums of 16 products with 2^-24 of rounding each, and the pieces' small products at 2^-8 of that
     assert note("rms", rms_err(got, ref), 4 * 2.0 ** -24 * np.sqrt(C * R * S / 16) + 2.0 ** -24)
-    assert close(run(x, w, None, pad, False), oracle.conv2d(x, w, np.zeros(K, np.float32), 1, pad, False), TOL_F32)
+    assert close(run(x, w, None, pad, False, stride), oracle.conv2d(x, w, np.zeros(K, np.float32), stride, pad, False), TOL_F32)
 
 
-def test_operands_beyond_bf16_pieces():
+@pytest.mark.parametrize("stride", (1, 2))
+def test_operands_beyond_bf16_pieces(stride):
     """Infinities, NaN, values that round to infinity in 8 bits, and operands whose lower pieces are too small for a bf16: as fp32 arithmetic has them."""
-    N, C, H, W, K = 20, 32, 30, 30, 96
+    N, C, H, W, K = (28, 32, 30, 30, 96) if stride == 1 else (40, 32, 41, 33, 200)
+    ss = (stride, stride)
     rng = np.random.default_rng(7)
     x = rng.standard_normal((N, C, H, W)).astype(np.float32)
     w = rng.standard_normal((K, C, 3, 3)).astype(np.float32) * np.float32(0.1)
-    plain = run(x, w, None, (1, 1), False)
+    plain = run(x, w, None, (1, 1), False, ss)
     big = x.copy()
     big[1, 3, 5, 7], big[2, 4, 0, 0], big[3, 31, 29, 29], big[4, 0, 9, 9] = np.inf, -np.inf, np.nan, 3.4e38
-    got = run(big, w, None, (1, 1), False)
+    got = run(big, w, None, (1, 1), False, ss)
     with np.errstate(all="ignore"):
-        ref = torch.nn.functional.conv2d(torch.from_numpy(big).double(), torch.from_numpy(w).double(), padding=1).numpy()
+        ref = torch.nn.functional.conv2d(torch.from_numpy(big).double(), torch.from_numpy(w).double(), padding=1, stride=stride).numpy()
     assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
     assert np.array_equal(np.sign(got[np.isinf(ref)]), np.sign(ref[np.isinf(ref)]))
     there = np.isfinite(ref)
     near = there & (np.abs(ref) > 1e30)
-    assert near.sum() == 9 * K and np.max(np.abs(got[near] / ref[near] - 1)) < 1e-6
+    assert near.sum() == (9 if stride == 1 else 4) * K and np.max(np.abs(got[near] / ref[near] - 1)) < 1e-6
     assert close(got[there & ~near], ref[there & ~near], TOL_F32)
     wi = w.copy()
     wi[5, 2, 1, 1] = np.inf
-    got, ref = run(x, wi, None, (0, 0), False), torch.nn.functional.conv2d(torch.from_numpy(x).double(), torch.from_numpy(wi).double()).numpy()
+    got, ref = run(x, wi, None, (0, 0), False, ss), torch.nn.functional.conv2d(torch.from_numpy(x).double(), torch.from_numpy(wi).double(), stride=stride).numpy()
     assert np.isinf(got[:, 5]).all() and np.array_equal(np.sign(got[:, 5]), np.sign(ref[:, 5]))
-    assert np.array_equal(np.delete(got, 5, 1), np.delete(run(x, w, None, (0, 0), False), 5, 1)) or close(np.delete(got, 5, 1), np.delete(ref, 5, 1), TOL_F32)
+    assert np.array_equal(np.delete(got, 5, 1), np.delete(run(x, w, None, (0, 0), False, ss), 5, 1)) or close(np.delete(got, 5, 1), np.delete(ref, 5, 1), TOL_F32)
     # images and filters of their own magnitudes: 2^-118 .. 2^-90 beside 1
     for scale in (2.0 ** -118, 2.0 ** -103, 2.0 ** -90):
         small = x.copy()
         small[::2] *= np.float32(scale)
-        got = run(small, w, None, (1, 1), False)
-        ref = oracle.conv2d(small, w, np.zeros(K, np.float32), 1, 1, False)
+        got = run(small, w, None, (1, 1), False, ss)
+        ref = oracle.conv2d(small, w, np.zeros(K, np.float32), stride, 1, False)
         assert close(got[::2], ref[::2], TOL_F32, "2^%d" % np.log2(scale)) and close(got[1::2], ref[1::2], TOL_F32)
         ws = w.copy()
         ws[::3] *= np.float32(scale)
-        got = run(x, ws, None, (1, 1), False)
-        ref = oracle.conv2d(x, ws, np.zeros(K, np.float32), 1, 1, False)
+        got = run(x, ws, None, (1, 1), False, ss)
+        ref = oracle.conv2d(x, ws, np.zeros(K, np.float32), stride, 1, False)
         assert close(got[:, ::3], ref[:, ::3], TOL_F32, "2^%d" % np.log2(scale)) and close(np.delete(got, np.s_[::3], 1), np.delete(ref, np.s_[::3], 1), TOL_F32)
-    assert np.array_equal(plain, run(x, w, None, (1, 1), False))
+    assert np.array_equal(plain, run(x, w, None, (1, 1), False, ss))
 
 
 def test_layers_of_a_module_share_a_launch():
