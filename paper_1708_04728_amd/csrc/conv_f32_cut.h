@@ -211,26 +211,10 @@ __device__ __forceinline__ void multiply_tile(const unsigned char* const lds, in
         stage ^= 1;
         ring_barrier();
     };
-    if constexpr (STEPS == 2) {
-        for (int k = 0; k < slices; ++k) {
-            step(IC<0>{}, 1);
-            turn();
-            step(IC<1>{}, 0);                    // (after the tile's last slice it reads what is read again)
-        }
-    } else {
-        static_assert(STEPS == 3, "k-steps of a slice");
-        for (int k = 0; k < slices; k += 2) {    // the register sets change roles from slice to slice
-            step(IC<0>{}, 1);
-            step(IC<1>{}, 2);
-            turn();
-            step(IC<0>{}, 0);
-            if (k + 1 < slices) {
-                step(IC<1>{}, 1);
-                step(IC<0>{}, 2);
-                turn();
-                step(IC<1>{}, 0);
-            }
-        }
+    for (int k = 0; k < slices; ++k) {
+        step(IC<0>{}, 1);
+        turn();
+        step(IC<1>{}, 0);                        // (after the tile's last slice it reads what is read again)
     }
 }
 
