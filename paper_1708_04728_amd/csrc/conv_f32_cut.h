@@ -1,29 +1,10 @@
 // fp32 operands as three bf16 pieces: the device code that the kernels on them share (conv_f32_pieces.hip has the arithmetic and what it measures).
 #pragma once
 #include "conv_f32_dev.h"
+#include "f32_pieces.h"
 
 namespace dr {
 namespace {
-
-// Eight operands as three vectors of bf16: high + middle + low == v, exactly (8 bits of the significand each, the lower ones with a sign of their own).
-__device__ __forceinline__ void split8(const float (&v)[8], u32x4& high, u32x4& middle, u32x4& low)
-{
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const unsigned h = pack_bf16x2(v[2 * i], v[2 * i + 1]);
-        const float ra = v[2 * i] - __uint_as_float(h << 16), rb = v[2 * i + 1] - __uint_as_float(h & 0xFFFF0000u);
-        const unsigned m = pack_bf16x2(ra, rb);
-        const float la = ra - __uint_as_float(m << 16), lb = rb - __uint_as_float(m & 0xFFFF0000u);
-        high[i] = h;
-        middle[i] = m;
-        low[i] = __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), 0x07060302u);
-    }
-}
-
-__device__ __forceinline__ f32x16 mfma(u32x4 a, u32x4 b, f32x16 c)
-{
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
 
 // The pieces of eight operands to LDS, one `stride` behind the other; least: of the largest magnitudes of eight, as bits, less one (zeros count as large)
 __device__ __forceinline__ void put_pieces(const float (&v)[8], unsigned char* at, int stride, unsigned& least)
@@ -32,13 +13,9 @@ __device__ __forceinline__ void put_pieces(const float (&v)[8], unsigned char* a
     split8(v, p[0], p[1], p[2]);
 #pragma unroll
     for (int e = 0; e < 3; ++e) *reinterpret_cast<u32x4*>(at + e * stride) = p[e];
-    float m = fmaxf(fabsf(v[0]), fabsf(v[1]));
-#pragma unroll
-    for (int e = 2; e < 8; e += 2) m = fmaxf(fmaxf(m, fabsf(v[e])), fabsf(v[e + 1]));
-    least = min(least, __float_as_uint(m) - 1);
+    least = min(least, magnitude8(v));
     asm volatile("" : "+v"(least));              // (here: later it would keep v from being loaded again into the same registers)
 }
-__device__ __forceinline__ bool too_small(unsigned least) { return __any(least < __float_as_uint(0x1p-100f) - 1); }
 
 // One block of 32 x 32 outputs by fp32 matrix instructions, straight from memory: for operands that three bf16 pieces do not hold.  Lane half h: channel c + h.
 __device__ __forceinline__ f32x16 exact_block(const KArgs& a, int m, int n, int half)

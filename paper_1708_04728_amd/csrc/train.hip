@@ -9,8 +9,8 @@
 //
 // The weight gradient is a GEMM  D[m][n] = sum_l A[m][l] B[l][n]  with m = filter, n = (tap, channel) and the
 // contraction over l = (image, p, q): A is dz (for one image and filter the (p, q) run is contiguous), B is
-// gathered from x.  A workgroup owns a 64 x 64 tile of D for a range of slices of 32 l (each inside one image), stages
-// a slice at a time in LDS (l contiguous per row, rows padded by 4 floats) and multiplies with v_mfma_f32_32x32x2_f32,
+// gathered from x.  A workgroup owns a tile of 64, 128 or 192 x 64 of D for a range of slices of 32 l (each inside one image), stages
+// a slice at a time in LDS (l contiguous per row, rows padded by 4 floats) and multiplies,
 // each lane half taking 16 consecutive l of the slice so that an operand is four 128-bit LDS reads.  The ranges
 // give enough workgroups to fill the device; their partial sums go to workspace and are added in a fixed
 // order by a second kernel, so the result does not depend on scheduling.
@@ -18,6 +18,7 @@
 #include <type_traits>
 
 #include "dr_internal.h"
+#include "f32_pieces.h"
 
 namespace dr {
 namespace {
@@ -106,7 +107,7 @@ struct WArgs {
     int x_bytes, dz_bytes;
 };
 
-constexpr int BM = 64, BN = 64, BL = 32, LDT = BL + 4;
+constexpr int BN = 64, BL = 32, LDT = BL + 4;
 
 // dw[m][c R S + rs] of column `col`: tile col / BN holds 64 >> cb_log2 taps x (1 << cb_log2) channels; -1 for padding
 __device__ __forceinline__ int wgrad_column(int col, int C, int RS, int cb_log2, int cblocks)
@@ -126,22 +127,28 @@ __device__ __forceinline__ void lds_barrier()
 
 // TPT: taps per column tile (64 channels of one tap, 32 of two, 16 of four; 8 of eight or 4 of sixteen where a layer on the
 // image would leave most of 16 channels empty: 11x11 3 -> 96 at stride 4 on 227 x 227 x 32 images 531 us with 16, 173 with 4; 7x7 3 -> 64 at
-// stride 2 453 and 184; 5x5 8 -> 64 on 56 x 56 x 32 75 and 59).  Bound by the fp32 matrix cores; what the loop adds to the
-// 16 matrix instructions of a slice is kept to a couple of instructions per loaded element: a thread's eight columns
+// stride 2 453 and 184; 5x5 8 -> 64 on 56 x 56 x 32 75 and 59).  A thread's eight columns
 // belong to TPT taps, so the padding test is made TPT times per slice (with columns in (c, r, s) order it was made for every
 // element and that arithmetic took longer than the multiplications), the rest of an address is a per-thread constant, and
-// (p, q) advances by addition.  Two LDS buffers, one barrier per slice, loads two slices ahead; the next slice goes to LDS in the middle of the
-// products, which 64 cycles each leave time for.  3x3 64 -> 192 at stride 2 on 56 x 56 x 32 images, the call with the sum of its ranges (5.6 us): 118 us
-// with columns in (c, r, s) order, 74.4 with these, 71.5 with that order and EIGHTS; 43 drawn layers 1.040 more, 43 that EIGHTS does not take 1.034.
-// EIGHTS: filters and channels come in eights, so that a row or column exists for all threads of its group of eight or for none: its offset is then the
-// load's scalar offset, and a slice takes an address for the gradient and one per tap instead of one per element.
-// Four workgroups per compute unit, for which the registers are bounded: left to itself the compiler takes a few more without EIGHTS and three fit
-// (3x3 68 -> 68 at stride 2 on 23 x 56 x 32 51.4 us and 43.1, 20 -> 50 on 56 x 56 x 32 37.7 and 33.7; 43 such layers 1.2 % together).
-template <int TPT, bool EIGHTS>
-__global__ __launch_bounds__(256, 4) void conv_wgrad_f32_kernel(const WArgs a)
+// (p, q) advances by addition.  Two LDS buffers, one barrier per slice, loads one slice ahead; the next slice goes to LDS in the middle of the products.
+// EIGHTS: channels come in eights, so that a column exists for all threads of its group of eight or for none: its offset is then the
+// load's scalar offset, and a slice takes one address per tap instead of one per element.
+//
+// The products: operands cut into three bf16 pieces by the waves that read them, six products of 32 cycles for 16 k in the place of eight of 64, the five small
+// ones in a sum of their own (error against 64 bits 0.55 to 0.92 of fp32 instructions', 7 layers).  That alone gained nothing: fp32 matrix instructions
+// hid the gathered loads, 16 of 4 bytes per thread and slice.  So dz comes 16 bytes at a time, and TM blocks of 64 filters share the columns: 24 + 8 loads' worth
+// in 14 for three.  3x3 64 -> 192 at stride 2 on 56 x 56 x 32, the call with the sum of its ranges (5.7 us): 74.2 us with one block and fp32
+// products, 75.6 with pieces, 72.8 with two blocks, 61.5 with three; 64 -> 128 54.6 and 48.6.  Vector instructions, most of them the cutting, now issue in half of the cycles, matrix instructions in
+// a quarter; two waves per SIMD wait for LDS in the rest.  (Loads two slices ahead: three blocks spill, 84.1.)
+// Ranges of fewer than ten slices (four with taller tiles) take fp32 products: they are start and end (32 -> 192 on 22 x 32, one image, 10.8 us before, 11.0 with
+// pieces, 9.7 without; 64 -> 96 on 18 x 64 x 57, two blocks and nine slices, 35.1 and 38.2).  210 drawn layers 0.98 to 1.21, 1.076 on average.
+template <int TPT, bool EIGHTS, int TM>
+__global__ __launch_bounds__(256, TM == 1 ? 3 : 2) void conv_wgrad_f32_kernel(const WArgs a)
 {
+    constexpr int BM = TM * 64, AU = TM * 2;               // rows of a tile; of each thread
     __shared__ __attribute__((aligned(16))) float As[2][BM * LDT];
     __shared__ __attribute__((aligned(16))) float Bs[2][BN * LDT];
+    __shared__ int redo;
     constexpr int CB = BN / TPT, NT = TPT < 8 ? TPT : 8, IPT = 8 / NT;     // channels per tile; taps of a thread's columns; columns per tap
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1, half = lane >> 5, l32 = lane & 31;
@@ -157,31 +164,31 @@ __global__ __launch_bounds__(256, 4) void conv_wgrad_f32_kernel(const WArgs a)
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)a.x, 0, a.x_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rz = __builtin_amdgcn_make_buffer_rsrc((void*)a.dz, 0, a.dz_bytes, 0x00020000);
 
-    // loader: this thread fetches element l = tid % 32 of the slice for rows tid / 32 + 8 i of both tiles.  A row or column that
-    // does not exist has the offset OOB; whatever is then read belongs to an output that is not stored.
+    // loader: this thread fetches four elements of the slice, 4 (tid % 8) on, for rows tid / 8 + 32 i of dz, and element l = tid % 32 for
+    // columns tid / 32 + 8 i.  A row or column that does not exist has the offset OOB; whatever is then read belongs to an output that is not stored.
     const int ll = tid & 31, row0 = tid >> 5;
     const int tg = nt / a.cblocks, c0 = (nt - tg * a.cblocks) * CB;
     // column row0 + 8 i: tap i / IPT and channel row0 + 8 (i % IPT) of the tile; with tiles of 4 channels tap 2 i + row0 / 4, channel row0 % 4
     auto tap_of = [&](int t) __attribute__((always_inline)) { return tg * TPT + (TPT > 8 ? 2 * t + (row0 >> 2) : t); };
     static_assert(!EIGHTS || TPT < 16, "a column tile of four channels");
-    unsigned a_row[EIGHTS ? 1 : 8], b_row[EIGHTS ? 1 : 8];      // EIGHTS: of row, of column row0; the others' distance from it is wave-uniform
-    int a_off[8], b_off[8];                                     // (0: of an eight that does not exist, whose outputs are not stored)
+    unsigned a_row[AU], b_row[EIGHTS ? 1 : 8];           // EIGHTS: of column row0; the others' distance from it is wave-uniform
+    int b_off[8];                                        // (0: of an eight that does not exist, whose outputs are not stored)
+    const int l4 = (tid & 7) * 4, row4 = tid >> 3;
+#pragma unroll
+    for (int i = 0; i < AU; ++i) a_row[i] = m0 + row4 + 32 * i < a.K ? (unsigned)((m0 + row4 + 32 * i) * PQ * 4) : OOB;
     int tap_r[NT], tap_s[NT];
     if constexpr (EIGHTS) {
-        a_row[0] = (unsigned)((m0 + row0) * PQ * 4);
         b_row[0] = (unsigned)((c0 + row0) * HW * 4);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            a_off[i] = m0 + 8 * i < a.K ? 8 * i * PQ * 4 : 0;
             b_off[i] = c0 + 8 * (i % IPT) < a.C ? 8 * (i % IPT) * HW * 4 : 0;
         }
     } else {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const int m = m0 + row0 + 8 * i, c = c0 + (TPT > 8 ? row0 & 3 : row0 + 8 * (i % IPT));
-            a_row[i] = m < a.K ? (unsigned)(m * PQ * 4) : OOB;
+            const int c = c0 + (TPT > 8 ? row0 & 3 : row0 + 8 * (i % IPT));
             b_row[i] = c < a.C && tap_of(i / IPT) < RS ? (unsigned)(c * HW * 4) : OOB;
-            a_off[i] = b_off[i] = 0;
+            b_off[i] = 0;
         }
     }
 #pragma unroll
@@ -190,25 +197,34 @@ __global__ __launch_bounds__(256, 4) void conv_wgrad_f32_kernel(const WArgs a)
         tap_r[t] = r - a.ph; tap_s[t] = rs - r * a.S - a.pw;
     }
     // the slice being fetched: image, first (p, q) run element and this thread's own
-    int img = lo / a.slices_per_img, left = a.slices_per_img - (lo - img * a.slices_per_img);   // slices left in the image
+    int img, left, pq, p, q;                               // left: slices left in the image
     const int p_ll = ll / a.Q, q_ll = ll - p_ll * a.Q, step_p = BL / a.Q, step_q = BL - step_p * a.Q;
-    int pq = (a.slices_per_img - left) * BL + ll, p = pq / a.Q, q = pq - p * a.Q;
-    float ra[2][8], rb[2][8];
-    auto fetch = [&](auto set_c) __attribute__((always_inline)) {
-        constexpr int SET = decltype(set_c)::value;
+    auto start = [&]() __attribute__((always_inline)) {
+        img = lo / a.slices_per_img;
+        left = a.slices_per_img - (lo - img * a.slices_per_img);
+        pq = (a.slices_per_img - left) * BL + ll;
+        p = pq / a.Q;
+        q = pq - p * a.Q;
+    };
+    f32x4 ra[AU];
+    float rb[8];
+    int rest;                                              // elements that are left of the image from this thread's four on
+    auto fetch = [&]() __attribute__((always_inline)) {
         const bool on = pq < PQ;
-        const unsigned za = on ? (unsigned)(pq * 4) : OOB;
+        const int pq4 = pq - ll + l4;
+        rest = PQ - pq4;
+        const unsigned za = pq4 < PQ ? (unsigned)(pq4 * 4) : OOB;
         const int soff_a = img * a.K * PQ * 4, soff_b = img * a.C * HW * 4;
         const int ih0 = p * a.sh, iw0 = q * a.sw;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) ra[SET][i] = buf_load(rz, a_row[EIGHTS ? 0 : i] + za, soff_a + a_off[i]);
+        for (int i = 0; i < AU; ++i) ra[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rz, a_row[i] + za, soff_a, 0));
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const int ih = ih0 + tap_r[t], iw = iw0 + tap_s[t];
             const bool in = on & ((unsigned)ih < (unsigned)a.H) & ((unsigned)iw < (unsigned)a.W) & (!EIGHTS || tap_of(t) < RS);
             const unsigned xo = in ? (unsigned)((ih * a.W + iw) * 4) : OOB;
 #pragma unroll
-            for (int i = t * IPT; i < (t + 1) * IPT; ++i) rb[SET][i] = buf_load(rx, b_row[EIGHTS ? 0 : i] + xo, soff_b + b_off[i]);
+            for (int i = t * IPT; i < (t + 1) * IPT; ++i) rb[i] = buf_load(rx, b_row[EIGHTS ? 0 : i] + xo, soff_b + b_off[i]);
         }
         if (--left == 0) {
             ++img; left = a.slices_per_img;
@@ -218,77 +234,127 @@ __global__ __launch_bounds__(256, 4) void conv_wgrad_f32_kernel(const WArgs a)
             if (q >= a.Q) { q -= a.Q; ++p; }
         }
     };
-    float dbs[8];                                          // this thread's share of the bias gradient (first column tile)
+    float dbs[AU];                                         // this thread's share of the bias gradient (first column tile)
+    auto put = [&](int buf) __attribute__((always_inline)) {
+        if (PQ & 3) {                                      // (behind the image is the next filter's)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) dbs[i] = 0.f;
-    auto put = [&](int buf, auto set_c) __attribute__((always_inline)) {
-        constexpr int SET = decltype(set_c)::value;
+            for (int e = 1; e < 4; ++e)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            As[buf][(row0 + 8 * i) * LDT + ll] = ra[SET][i];
-            Bs[buf][(row0 + 8 * i) * LDT + ll] = rb[SET][i];
+                for (int i = 0; i < AU; ++i) ra[i][e] = e < rest ? ra[i][e] : 0.f;
         }
+#pragma unroll
+        for (int i = 0; i < AU; ++i) *reinterpret_cast<f32x4*>(&As[buf][(row4 + 32 * i) * LDT + l4]) = ra[i];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) Bs[buf][(row0 + 8 * i) * LDT + ll] = rb[i];
         if (nt == 0) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) dbs[i] += ra[SET][i];
+            for (int i = 0; i < AU; ++i) dbs[i] += (ra[i][0] + ra[i][1]) + (ra[i][2] + ra[i][3]);
         }
     };
-    f32x16 acc;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-    auto step = [&](int sl, auto set_c) __attribute__((always_inline)) {     // set_c: the registers that hold slice sl + 1
+    f32x16 acc[TM], small[TM];
+    unsigned least = 0xFFFFFFFFu;
+    auto step = [&](int sl, auto exact_c) __attribute__((always_inline)) {
+        constexpr bool EXACT = decltype(exact_c)::value;
         const int buf = sl & 1;
-        const float* ap = As[buf] + (wm * 32 + l32) * LDT + half * 16;
+        const float* ap = As[buf] + (wm * TM * 32 + l32) * LDT + half * 16;
         const float* bp = Bs[buf] + (wn * 32 + l32) * LDT + half * 16;
-        f32x4 av[4], bv[4];
+        auto multiply = [&](int h) __attribute__((always_inline)) {      // eight of this lane's sixteen
+            float fb[8];
+            auto read = [&](const float* at, float (&v)[8]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            av[j] = *reinterpret_cast<const f32x4*>(ap + 4 * j);
-            bv[j] = *reinterpret_cast<const f32x4*>(bp + 4 * j);
-        }
+                for (int j = 0; j < 2; ++j) {
+                    const f32x4 t = *reinterpret_cast<const f32x4*>(at + 8 * h + 4 * j);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[j >> 2][j & 3], bv[j >> 2][j & 3], acc, 0, 0, 0);
+                    for (int e = 0; e < 4; ++e) v[4 * j + e] = t[e];
+                }
+            };
+            read(bp, fb);
+            u32x4 pb[3];
+            if constexpr (!EXACT) {
+                split8(fb, pb[0], pb[1], pb[2]);
+                least = min(least, magnitude8(fb));
+            }
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                float fa[8];
+                read(ap + i * 32 * LDT, fa);
+                if constexpr (EXACT) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[j], fb[j], acc[i], 0, 0, 0);
+                } else {
+                    u32x4 pa[3];
+                    split8(fa, pa[0], pa[1], pa[2]);
+                    least = min(least, magnitude8(fa));
+                    acc[i] = mfma(pa[0], pb[0], acc[i]);
+                    small[i] = mfma(pa[0], pb[1], small[i]);
+                    small[i] = mfma(pa[1], pb[0], small[i]);
+                    small[i] = mfma(pa[1], pb[1], small[i]);
+                    small[i] = mfma(pa[0], pb[2], small[i]);
+                    small[i] = mfma(pa[2], pb[0], small[i]);
+                }
+            }
+        };
+        multiply(0);
         __builtin_amdgcn_sched_barrier(0);
         if (sl + 1 < total) {
-            put(buf ^ 1, set_c);
-            if (sl + 3 < total) fetch(set_c);
+            put(buf ^ 1);
+            if (sl + 2 < total) fetch();
         }
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int j = 8; j < 16; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[j >> 2][j & 3], bv[j >> 2][j & 3], acc, 0, 0, 0);
+        multiply(1);
         lds_barrier();
     };
-    using S0 = std::integral_constant<int, 0>;
-    using S1 = std::integral_constant<int, 1>;
-    if (total > 0) {
-        fetch(S0{});
-        put(0, S0{});
-        if (1 < total) fetch(S1{});
-        if (2 < total) fetch(S0{});
+    auto walk = [&](auto exact_c) __attribute__((always_inline)) {
+        start();
+#pragma unroll
+        for (int i = 0; i < AU; ++i) dbs[i] = 0.f;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][v] = small[i][v] = 0.f;
+        if (total > 0) {
+            fetch();
+            put(0);
+            if (1 < total) fetch();
+        }
+        lds_barrier();
+        for (int sl = 0; sl < total; ++sl) step(sl, exact_c);
+    };
+    bool exact = a.slices < (TM == 1 ? 10 : 4) * a.splits;      // (uniform)
+    if (!exact) {
+        if (tid == 0) redo = 0;
+        walk(std::false_type{});
+        float z = 0.f;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                acc[i][v] += small[i][v];
+                z = __builtin_fmaf(acc[i][v], 0.f, z);
+            }
+        if (__any(z != 0.f) || too_small(least)) redo = 1;       // operands that pieces do not hold: the range again
+        __syncthreads();
+        exact = __builtin_amdgcn_readfirstlane(*(volatile int*)&redo) != 0;
     }
-    lds_barrier();
-    for (int sl = 0; sl < total; sl += 2) {
-        step(sl, S1{});
-        if (sl + 1 < total) step(sl + 1, S0{});
-    }
+    if (exact) walk(std::true_type{});
     // register v holds row 8 (v / 4) + 4 half + v % 4 of column lane % 32
     const int col = nt * BN + wn * 32 + l32, n = wgrad_column(col, a.C, RS, __builtin_ctz(CB), a.cblocks);
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int m = m0 + wm * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
+    for (int v = 0; v < 16 * TM; ++v) {
+        const int m = m0 + (wm * TM + v / 16) * 32 + 8 * (v % 16 >> 2) + 4 * half + (v & 3);
         if (m >= a.K) continue;
-        if (a.splits > 1) a.out[((size_t)sp * a.K + m) * a.cols + col] = acc[v];
-        else if (n >= 0) a.dw[(size_t)m * a.CRS + n] = acc[v];
+        if (a.splits > 1) a.out[((size_t)sp * a.K + m) * a.cols + col] = acc[v / 16][v % 16];
+        else if (n >= 0) a.dw[(size_t)m * a.CRS + n] = acc[v / 16][v % 16];
     }
     if (nt == 0) {
         float* const db = a.splits > 1 ? a.out + (size_t)a.splits * a.K * a.cols + (size_t)sp * a.K : a.db;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < AU; ++i) {
             float t = dbs[i];
 #pragma unroll
-            for (int d = 16; d >= 1; d >>= 1) t += __shfl_down(t, d, 32);
-            const int m = m0 + row0 + 8 * i;
-            if (ll == 0 && m < a.K && db) db[m] = t;
+            for (int d = 4; d >= 1; d >>= 1) t += __shfl_down(t, d, 8);
+            const int m = m0 + row4 + 32 * i;
+            if ((tid & 7) == 0 && m < a.K && db) db[m] = t;
         }
     }
 }
@@ -320,11 +386,14 @@ __global__ __launch_bounds__(256) void sgd_step_kernel(float* __restrict__ w, co
 }
 
 // How the gradient's GEMM is tiled and split: column tiles of 64 to 4 channels per tap (whichever gives the fewest, the most channels first:
-// a tap costs a padding test), and as many ranges of slices as make up to four workgroups per compute unit, of at least four slices
+// a tap costs a padding test), and as many ranges of slices as make up to three workgroups per compute unit (two with tiles of more than one block of filters; four instead of three: 1.071
+// and 1.072 over 70 layers, with more partial sums), of at least four slices
 // each, but from eight slices on a range per image up to 16 (3x3 8 -> 32 at stride 4 on 15 x 18 x 10 images, ten slices: 14.0 us in two
 // ranges, 11.0 in ten); the sum of the ranges costs what more or shorter ones gain (7x7 128 -> 64 at stride 2 on 10 x 37 x 2, six
 // slices: 12.9 in one range, 15.5 in two, 19.0 in six).
-struct WPlan { int cb_log2, cblocks, grid_m, grid_n, slices_per_img, slices, splits; };
+// Blocks of 64 filters of a tile: three or two where they divide the filters' blocks, padding none, and the tiles still fill the device (7x7 74 -> 192 on 48 x 36 x 2
+// in two blocks, a fourth of them empty, 35.3 us before and 38.1; one 35.9).
+struct WPlan { int tm, cb_log2, cblocks, grid_m, grid_n, slices_per_img, slices, splits; };
 WPlan wgrad_plan(const ConvGeom& g)
 {
     WPlan p{};
@@ -335,11 +404,15 @@ WPlan wgrad_plan(const ConvGeom& g)
         if (best && n >= best) continue;
         best = n; p.cb_log2 = l; p.cblocks = cblocks; p.grid_n = n;
     }
-    p.grid_m = (g.K + BM - 1) / BM;
     p.slices_per_img = std::max(1, (g.P * g.Q + BL - 1) / BL);
     p.slices = g.P * g.Q > 0 ? g.N * p.slices_per_img : 0;
+    const int most = std::max(1, std::max(p.slices / 4, p.slices >= 8 ? std::min(g.N, 16) : 1));
+    const int blocks = (g.K + 63) / 64;
+    p.tm = 3;
+    while (p.tm > 1 && (blocks % p.tm != 0 || (long)(blocks / p.tm) * p.grid_n * most < 2 * device_cus())) --p.tm;
+    p.grid_m = blocks / p.tm;
     const int tiles = p.grid_m * p.grid_n;
-    p.splits = std::max(1, std::min(4 * device_cus() / tiles, std::max(p.slices / 4, p.slices >= 8 ? std::min(g.N, 16) : 1)));
+    p.splits = std::max(1, std::min((p.tm == 1 ? 3 : 2) * device_cus() / tiles, most));
     return p;
 }
 
@@ -381,16 +454,20 @@ int launch_conv_wgrad_f32(const ConvGeom& g, const float* x, const float* dz, fl
         ConvGeom t = g;
         TraceScope trace("conv_wgrad_f32", &t, g.Ng, st);
         const dim3 grid((unsigned)(a.grid_m * a.grid_n * a.splits)), block(256);
-        if (g.K % 8 == 0 && g.C % 8 == 0 && p.cb_log2 >= 3) {
-            if (p.cb_log2 == 6) hipLaunchKernelGGL((conv_wgrad_f32_kernel<1, true>), grid, block, 0, st, a);
-            else if (p.cb_log2 == 5) hipLaunchKernelGGL((conv_wgrad_f32_kernel<2, true>), grid, block, 0, st, a);
-            else if (p.cb_log2 == 4) hipLaunchKernelGGL((conv_wgrad_f32_kernel<4, true>), grid, block, 0, st, a);
-            else hipLaunchKernelGGL((conv_wgrad_f32_kernel<8, true>), grid, block, 0, st, a);
-        } else if (p.cb_log2 == 6) hipLaunchKernelGGL((conv_wgrad_f32_kernel<1, false>), grid, block, 0, st, a);
-        else if (p.cb_log2 == 5) hipLaunchKernelGGL((conv_wgrad_f32_kernel<2, false>), grid, block, 0, st, a);
-        else if (p.cb_log2 == 4) hipLaunchKernelGGL((conv_wgrad_f32_kernel<4, false>), grid, block, 0, st, a);
-        else if (p.cb_log2 == 3) hipLaunchKernelGGL((conv_wgrad_f32_kernel<8, false>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((conv_wgrad_f32_kernel<16, false>), grid, block, 0, st, a);
+        auto launch = [&](auto taps, auto eights) {
+            constexpr int T = decltype(taps)::value;
+            constexpr bool E = decltype(eights)::value;
+            if (p.tm == 3) hipLaunchKernelGGL((conv_wgrad_f32_kernel<T, E, 3>), grid, block, 0, st, a);
+            else if (p.tm == 2) hipLaunchKernelGGL((conv_wgrad_f32_kernel<T, E, 2>), grid, block, 0, st, a);
+            else hipLaunchKernelGGL((conv_wgrad_f32_kernel<T, E, 1>), grid, block, 0, st, a);
+        };
+        using std::integral_constant;
+        const bool eights = g.C % 8 == 0;
+        if (p.cb_log2 == 6) eights ? launch(integral_constant<int, 1>{}, std::true_type{}) : launch(integral_constant<int, 1>{}, std::false_type{});
+        else if (p.cb_log2 == 5) eights ? launch(integral_constant<int, 2>{}, std::true_type{}) : launch(integral_constant<int, 2>{}, std::false_type{});
+        else if (p.cb_log2 == 4) eights ? launch(integral_constant<int, 4>{}, std::true_type{}) : launch(integral_constant<int, 4>{}, std::false_type{});
+        else if (p.cb_log2 == 3) eights ? launch(integral_constant<int, 8>{}, std::true_type{}) : launch(integral_constant<int, 8>{}, std::false_type{});
+        else launch(integral_constant<int, 16>{}, std::false_type{});
     }
     if (const int rc = check_launch("conv_wgrad")) return rc;
     if (a.splits > 1) {

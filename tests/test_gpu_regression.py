@@ -80,6 +80,53 @@ def test_conv_parameter_gradients(case):
     assert np.array_equal(host(dw), first)      # fixed summation order: bit-identical from run to run
 
 
+def parameter_gradients(x, dz, K, R, S, stride, pad):
+    cd = B.conv_desc(K, x.shape[1], R, S, stride, pad, True, B.DR_KCRS)
+    dw, db = torch.full((K, x.shape[1], R, S), float("nan"), device="cuda"), torch.full((K,), float("nan"), device="cuda")
+    B.conv2d_bwd_params(x, cd, dz, dw, db, _ws(B.conv2d_bwd_params_workspace_bytes(x, cd)))
+    torch.cuda.synchronize()
+    return host(dw), host(db)
+
+
+# Tiles of one, two and three blocks of 64 filters; ranges long enough for products of bf16 pieces
+LONG_CASES = [
+    (40, 4, 44, 44, 8, 11, 11, 1, 0),         # one block of filters, ranges of 15 slices
+    (40, 8, 41, 37, 64, 5, 5, 1, 2),          # ... 41 x 37 pixels: not in fours, nor in slices
+    (12, 20, 33, 35, 100, 3, 3, 1, 1),        # two blocks, filters and channels that fill neither tile
+    (20, 32, 53, 50, 128, 3, 3, 2, 1),        # ... channels in eights
+    (10, 64, 54, 54, 192, 3, 3, 2, 1),        # three blocks, 27 x 27 pixels
+    (24, 16, 30, 29, 385, 3, 3, (1, 2), 1),   # seven blocks, one at a time; one filter in the last
+]
+
+
+@pytest.mark.parametrize("case", LONG_CASES)
+def test_conv_parameter_gradients_of_long_ranges(case):
+    """Also with pixels that pieces cannot hold: infinite, near the largest and the smallest values that there are."""
+    N, C, H, W, K, R, S, stride, pad = case
+    rng = np.random.default_rng(11 + N * C)
+    x = rng.standard_normal((N, C, H, W)).astype(np.float32)
+    sh, sw = (stride, stride) if np.isscalar(stride) else stride
+    P, Q = oracle.conv_out_size(H, R, sh, pad), oracle.conv_out_size(W, S, sw, pad)
+    dz = (rng.standard_normal((N, K, P, Q)) * (rng.random((N, K, P, Q)) < 0.6)).astype(np.float32)
+    dw_ref, db_ref = oracle.conv2d_bwd_params(x, dz, R, S, stride, pad)
+    xg = gpu(x)
+    plain, db = parameter_gradients(xg, gpu(dz), K, R, S, stride, pad)
+    assert close(plain, dw_ref, TOL_F32) and close(db, db_ref, TOL_F32)
+    # gradients of one filter, scaled: exact to the same relative error (a power of two)
+    for scale in (2.0 ** -118, 2.0 ** 118):
+        scaled = dz.copy()
+        scaled[:, K // 2] *= np.float32(scale)
+        got, _ = parameter_gradients(xg, gpu(scaled), K, R, S, stride, pad)
+        assert close(got[K // 2] * np.float32(1 / scale), dw_ref[K // 2], TOL_F32, "2^%d" % np.log2(scale))
+        assert close(np.delete(got, K // 2, 0), np.delete(dw_ref, K // 2, 0), TOL_F32)
+    # one infinite gradient: weights of its filter, and of no other
+    wild = dz.copy()
+    wild[N // 2, K // 2, P // 2, Q // 2] = np.inf
+    got, _ = parameter_gradients(xg, gpu(wild), K, R, S, stride, pad)
+    assert not np.isfinite(got[K // 2]).all() and np.isfinite(np.delete(got, K // 2, 0)).all()
+    assert close(np.delete(got, K // 2, 0), np.delete(dw_ref, K // 2, 0), TOL_F32)
+
+
 def test_sgd_step_bit_exact():
     rng = np.random.default_rng(3)
     w = rng.standard_normal(100003).astype(np.float32)
