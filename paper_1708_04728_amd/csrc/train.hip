@@ -135,7 +135,7 @@ __device__ __forceinline__ void lds_barrier()
 // load's scalar offset, and a slice takes one address per tap instead of one per element.
 //
 // The products: operands cut into three bf16 pieces by the waves that read them, six products of 32 cycles for 16 k in the place of eight of 64, the five small
-// ones in a sum of their own (error against 64 bits 0.55 to 0.92 of fp32 instructions', 7 layers).  That alone gained nothing: fp32 matrix instructions
+// ones in a sum of their own (as in conv_f32_pieces.hip).  That alone gained nothing: fp32 matrix instructions
 // hid the gathered loads, 16 of 4 bytes per thread and slice.  So dz comes 16 bytes at a time, and TM blocks of 64 filters share the columns: 24 + 8 loads' worth
 // in 14 for three.  3x3 64 -> 192 at stride 2 on 56 x 56 x 32, the call with the sum of its ranges (5.7 us): 74.2 us with one block and fp32
 // products, 75.6 with pieces, 72.8 with two blocks, 61.5 with three; 64 -> 128 54.6 and 48.6.  Vector instructions, most of them the cutting, now issue in half of the cycles, matrix instructions in
@@ -360,7 +360,9 @@ __global__ __launch_bounds__(256, TM == 1 ? 3 : 2) void conv_wgrad_f32_kernel(co
 }
 
 // The sum of the partial results over the splits, in split order: column by column of the [K][cols] sums, then the bias gradient.
-// (Eight loads in flight per thread: a chain of single loads took 10 us for 14 MB.)
+// (Eight loads in flight per thread: a chain of single loads took 10 us for 14 MB.)  In double: up to 56 ranges one after the other in float were most of the error.  On a
+// fitting step's own operands, relative to 64 bits, 64 -> 192 on 56 x 56 x 32: weights 1.08e-7 in float with 37 ranges of fp32 products, 1.12e-7 with 56 ranges of pieces, 0.28e-7 now; bias 0.92e-7, 1.08e-7
+// and 0.29e-7.  Nine such layers 0.24 to 0.56 and 0.23 to 0.42 of the first; in the same time (memory's).
 __global__ __launch_bounds__(256) void sum_splits_kernel(const float* __restrict__ part, int splits, int K, int C, int RS, int cb_log2, int cblocks, int cols,
                                                          float* __restrict__ dw, float* __restrict__ db)
 {
@@ -372,11 +374,11 @@ __global__ __launch_bounds__(256) void sum_splits_kernel(const float* __restrict
         if (n < 0 || (bias && !db)) continue;
         const float* src = bias ? part + (size_t)splits * count + m : part + i;
         const size_t stride = bias ? (size_t)K : count;
-        float s = 0.f;
+        double s = 0.0;
 #pragma unroll 8
-        for (int sp = 0; sp < splits; ++sp) s += src[(size_t)sp * stride];
-        if (bias) db[m] = s;
-        else dw[m * ((size_t)C * RS) + n] = s;
+        for (int sp = 0; sp < splits; ++sp) s += (double)src[(size_t)sp * stride];
+        if (bias) db[m] = (float)s;
+        else dw[m * ((size_t)C * RS) + n] = (float)s;
     }
 }
 
