@@ -7,7 +7,7 @@
 // 1750 / 6 = 290 TFLOP/s.  The largest product and the five small ones have sums of their own, added once at the end: the matrix instruction cuts what it adds to
 // a sum at the sum's last bit, and with one sum for all of them the error of 9216 positive products grew to four times that of fp32 instructions.  Against 64 bits,
 // relative 2-norm of 32 x 32 blocks over contractions of 144 / 576 / 2400 normal x normal: fp32 instructions 2.2e-7 / 4.3e-7 / 8.8e-7, here 0.7e-7 / 1.4e-7 / 3.0e-7
-// (with one sum 1.9e-7 / 3.7e-7 / 7.7e-7); 9 layers with operands of normal, one-signed and uniform values 0.31 to 0.37 of fp32 instructions', strided ones 0.32 to 0.40.  Where one
+// (with one sum 1.9e-7 / 3.7e-7 / 7.7e-7); 8 layers with operands of normal, one-signed and uniform values 0.30 to 0.37 of fp32 instructions', strided ones 0.32 to 0.40.  Where one
 // product outweighs all others (values spread log-normally over e^+-12) the products left out and the second sum show: 0.6e-7 to 1.1e-7, fp32 instructions 0.3e-7 to 0.7e-7.
 // What three pieces cannot hold shows: an infinity, a NaN or a value that rounds to infinity in 8 bits leaves a NaN among the sums; operands whose lower pieces would
 // fall below the smallest bf16 are noticed where they are cut (eight in a row that are all below 2^-100 and not all zero).  The blocks concerned are then computed
