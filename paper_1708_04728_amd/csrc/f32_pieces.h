@@ -9,6 +9,11 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
+// What operands are multiplied by before they are cut, and their sums of products after.  Every fp32 value is a multiple of 2^-149, so that the pieces of a scaled one
+// are multiples of 2^-125: none falls below the smallest normal bf16, 2^-126, whatever lies beside it.  Values of 2^104 and more, and sums of 2^80 and more, become
+// infinities or NaN among the sums, as infinite operands do, and are then computed without pieces.
+constexpr float PIECES_SCALE = 0x1p24f, PIECES_UNSCALE = 0x1p-48f;
+
 // Eight operands as three vectors of bf16: high + middle + low == v, exactly (8 bits of the significand each, the lower ones with a sign of their own).
 __device__ __forceinline__ void split8(const float (&v)[8], u32x4& high, u32x4& middle, u32x4& low)
 {

@@ -135,7 +135,8 @@ __device__ __forceinline__ void lds_barrier()
 // load's scalar offset, and a slice takes one address per tap instead of one per element.
 //
 // The products: operands cut into three bf16 pieces by the waves that read them, six products of 32 cycles for 16 k in the place of eight of 64, the five small
-// ones in a sum of their own (as in conv_f32_pieces.hip).  That alone gained nothing: fp32 matrix instructions
+// ones in a sum of their own (as in conv_f32_pieces.hip).  Operands are scaled where they are written to LDS, once, so that no value is too small for its pieces
+// (f32_pieces.h; with a look for small operands at every cut instead 57.9 us in the place of 55.7 for 64 -> 192 below, 44.1 and 42.4 for 64 -> 128).  Pieces alone gained nothing: fp32 matrix instructions
 // hid the gathered loads, 16 of 4 bytes per thread and slice.  So dz comes 16 bytes at a time, and TM blocks of 64 filters share the columns: 24 + 8 loads' worth
 // in 14 for three.  3x3 64 -> 192 at stride 2 on 56 x 56 x 32, the call with the sum of its ranges (5.7 us): 74.2 us with one block and fp32
 // products, 75.6 with pieces, 72.8 with two blocks, 61.5 with three; 64 -> 128 54.6 and 48.6.  Vector instructions, most of them the cutting, now issue in half of the cycles, matrix instructions in
@@ -235,7 +236,8 @@ __global__ __launch_bounds__(256, TM == 1 ? 3 : 2) void conv_wgrad_f32_kernel(co
         }
     };
     float dbs[AU];                                         // this thread's share of the bias gradient (first column tile)
-    auto put = [&](int buf) __attribute__((always_inline)) {
+    auto put = [&](int buf, auto exact_c) __attribute__((always_inline)) {
+        constexpr float scale = decltype(exact_c)::value ? 1.f : PIECES_SCALE;      // (here: a value is cut by up to 2 TM of the waves)
         if (PQ & 3) {                                      // (behind the image is the next filter's)
 #pragma unroll
             for (int e = 1; e < 4; ++e)
@@ -243,16 +245,15 @@ __global__ __launch_bounds__(256, TM == 1 ? 3 : 2) void conv_wgrad_f32_kernel(co
                 for (int i = 0; i < AU; ++i) ra[i][e] = e < rest ? ra[i][e] : 0.f;
         }
 #pragma unroll
-        for (int i = 0; i < AU; ++i) *reinterpret_cast<f32x4*>(&As[buf][(row4 + 32 * i) * LDT + l4]) = ra[i];
+        for (int i = 0; i < AU; ++i) *reinterpret_cast<f32x4*>(&As[buf][(row4 + 32 * i) * LDT + l4]) = ra[i] * scale;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) Bs[buf][(row0 + 8 * i) * LDT + ll] = rb[i];
+        for (int i = 0; i < 8; ++i) Bs[buf][(row0 + 8 * i) * LDT + ll] = rb[i] * scale;
         if (nt == 0) {
 #pragma unroll
             for (int i = 0; i < AU; ++i) dbs[i] += (ra[i][0] + ra[i][1]) + (ra[i][2] + ra[i][3]);
         }
     };
     f32x16 acc[TM], small[TM];
-    unsigned least = 0xFFFFFFFFu;
     auto step = [&](int sl, auto exact_c) __attribute__((always_inline)) {
         constexpr bool EXACT = decltype(exact_c)::value;
         const int buf = sl & 1;
@@ -270,10 +271,7 @@ __global__ __launch_bounds__(256, TM == 1 ? 3 : 2) void conv_wgrad_f32_kernel(co
             };
             read(bp, fb);
             u32x4 pb[3];
-            if constexpr (!EXACT) {
-                split8(fb, pb[0], pb[1], pb[2]);
-                least = min(least, magnitude8(fb));
-            }
+            if constexpr (!EXACT) split8(fb, pb[0], pb[1], pb[2]);
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
                 float fa[8];
@@ -284,7 +282,6 @@ __global__ __launch_bounds__(256, TM == 1 ? 3 : 2) void conv_wgrad_f32_kernel(co
                 } else {
                     u32x4 pa[3];
                     split8(fa, pa[0], pa[1], pa[2]);
-                    least = min(least, magnitude8(fa));
                     acc[i] = mfma(pa[0], pb[0], acc[i]);
                     small[i] = mfma(pa[0], pb[1], small[i]);
                     small[i] = mfma(pa[1], pb[0], small[i]);
@@ -297,7 +294,7 @@ __global__ __launch_bounds__(256, TM == 1 ? 3 : 2) void conv_wgrad_f32_kernel(co
         multiply(0);
         __builtin_amdgcn_sched_barrier(0);
         if (sl + 1 < total) {
-            put(buf ^ 1);
+            put(buf ^ 1, exact_c);
             if (sl + 2 < total) fetch();
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -314,7 +311,7 @@ __global__ __launch_bounds__(256, TM == 1 ? 3 : 2) void conv_wgrad_f32_kernel(co
             for (int v = 0; v < 16; ++v) acc[i][v] = small[i][v] = 0.f;
         if (total > 0) {
             fetch();
-            put(0);
+            put(0, exact_c);
             if (1 < total) fetch();
         }
         lds_barrier();
@@ -331,8 +328,9 @@ __global__ __launch_bounds__(256, TM == 1 ? 3 : 2) void conv_wgrad_f32_kernel(co
             for (int v = 0; v < 16; ++v) {
                 acc[i][v] += small[i][v];
                 z = __builtin_fmaf(acc[i][v], 0.f, z);
+                acc[i][v] *= PIECES_UNSCALE;
             }
-        if (__any(z != 0.f) || too_small(least)) redo = 1;       // operands that pieces do not hold: the range again
+        if (__any(z != 0.f)) redo = 1;                           // operands that pieces do not hold: the range again
         __syncthreads();
         exact = __builtin_amdgcn_readfirstlane(*(volatile int*)&redo) != 0;
     }

@@ -6,7 +6,7 @@ import pytest
 import oracle
 import workloads
 from paper_1708_04728_amd import binding as B
-from util import TOL_F32, gpu, host, close, rel_err
+from util import TOL_F32, gpu, host, close, note, rel_err, rms_err
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -125,6 +125,31 @@ def test_conv_parameter_gradients_of_long_ranges(case):
     got, _ = parameter_gradients(xg, gpu(wild), K, R, S, stride, pad)
     assert not np.isfinite(got[K // 2]).all() and np.isfinite(np.delete(got, K // 2, 0)).all()
     assert close(np.delete(got, K // 2, 0), np.delete(dw_ref, K // 2, 0), TOL_F32)
+
+
+@pytest.mark.parametrize("scale", (-105, -118, -140))
+@pytest.mark.parametrize("r", (1, 3))
+def test_conv_parameter_gradients_of_small_operands(r, scale):
+    """Of every eight pixels one is about 1 where the other operand is 0, the rest about 2^scale (2^-140: subnormal): the sums consist of those alone."""
+    N, C, P, K = (8, 512, 32, 384) if r == 1 else (16, 64, 32, 384)
+    rng = np.random.default_rng(r)
+    x = rng.standard_normal((N, C, P * r, P * r)).astype(np.float32)
+    dz = rng.standard_normal((N, K, P, P)).astype(np.float32)
+    few = np.zeros((P, P), bool)
+    few[:, ::8] = True                                    # 32 pixels a row: one of every eight
+    few_x = few.repeat(r, 0).repeat(r, 1)
+    for small_x in (True, False):
+        a, b = x.copy(), dz.copy()
+        t, u, at, there = (a, b, few_x, few) if small_x else (b, a, few, few_x)
+        t[..., ~at] *= np.float32(2.0 ** scale)
+        u *= np.float32(2.0 ** 30)
+        u[..., there] = 0
+        # (taps do not overlap: a product of matrices)
+        cols = a.astype(np.float64).reshape(N, C, P, r, P, r).transpose(0, 2, 4, 1, 3, 5).reshape(N * P * P, C * r * r)
+        ref = (b.astype(np.float64).transpose(1, 0, 2, 3).reshape(K, N * P * P) @ cols).reshape(K, C, r, r)
+        got, _ = parameter_gradients(gpu(a), gpu(b), K, r, r, r, 0)
+        # N P P / 16 sums of 16 products with 2^-24 of rounding each
+        assert note("rms", rms_err(got, ref), 4 * 2.0 ** -24 * np.sqrt(N * P * P / 16) + 2.0 ** -24)
 
 
 def test_sgd_step_bit_exact():
