@@ -6,15 +6,16 @@
 namespace dr {
 namespace {
 
-// The pieces of eight operands to LDS, one `stride` behind the other; least: of the largest magnitudes of eight, as bits, less one (zeros count as large)
-__device__ __forceinline__ void put_pieces(const float (&v)[8], unsigned char* at, int stride, unsigned& least)
+// The pieces of eight operands, scaled, to LDS, one `stride` behind the other
+__device__ __forceinline__ void put_pieces(const float (&v)[8], unsigned char* at, int stride)
 {
+    float t[8];
     u32x4 p[3];
-    split8(v, p[0], p[1], p[2]);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) t[e] = v[e] * PIECES_SCALE;
+    split8(t, p[0], p[1], p[2]);
 #pragma unroll
     for (int e = 0; e < 3; ++e) *reinterpret_cast<u32x4*>(at + e * stride) = p[e];
-    least = min(least, magnitude8(v));
-    asm volatile("" : "+v"(least));              // (here: later it would keep v from being loaded again into the same registers)
 }
 
 // One block of 32 x 32 outputs by fp32 matrix instructions, straight from memory: for operands that three bf16 pieces do not hold.  Lane half h: channel c + h.
@@ -81,11 +82,11 @@ __device__ __forceinline__ void store_whole(const KArgs& a, const f32x16 (&acc)[
         }
 }
 
-// The end of a tile for a multiplying wave: the two sums, bias, ReLU, the store.  Rows from mw and columns from nw on; img0: the tile's first image;
-// *tiny: operands were too small for pieces.
+// The end of a tile for a multiplying wave: the two sums, bias, ReLU, the store.  Rows from mw and columns from nw on; img0: the tile's first image.  Whether a block
+// of 32 x 32 is computed again depends on its own sums alone, so that a layer has the same bits in tiles of any size.
 template <int TM, int TN>
 __device__ __forceinline__ void finish_tile(const KArgs& a, f32x16 (&acc)[TM][TN], const f32x16 (&small)[TM][TN], int mw, int nw, int n0, int img0,
-                                            unsigned long long by_pq, const int* tiny)
+                                            unsigned long long by_pq)
 {
     const int half = (threadIdx.x >> 5) & 1, l32 = threadIdx.x & 31;
     // (the biases before any store: a load behind stores is waited for together with them)
@@ -95,7 +96,6 @@ __device__ __forceinline__ void finish_tile(const KArgs& a, f32x16 (&acc)[TM][TN
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int q = 0; q < 4; ++q) bias[i][q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rbias, (mw + i * 32 + half * 4 + q * 8) * 4, 0, 0));
-    const bool all = __builtin_amdgcn_readfirstlane(*reinterpret_cast<const volatile int*>(tiny)) != 0;
     unsigned bad = 0;                            // blocks that pieces do not hold (no residual here, which a second store would find changed in place)
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -106,8 +106,9 @@ __device__ __forceinline__ void finish_tile(const KArgs& a, f32x16 (&acc)[TM][TN
             for (int v = 0; v < 16; ++v) {
                 acc[i][j][v] += small[i][j][v];
                 z = __builtin_fmaf(acc[i][j][v], 0.f, z);
+                acc[i][j][v] *= PIECES_UNSCALE;
             }
-            bad |= all || __any(z != 0.f) ? 1u << (i * TN + j) : 0u;
+            bad |= __any(z != 0.f) ? 1u << (i * TN + j) : 0u;
         }
     if (a.far_store || mw + TM * 32 > a.g.K) store_tile<TM, TN, false>(a, acc, mw, nw, n0);
     else store_whole<TM, TN>(a, acc, bias, mw, nw, img0, by_pq);

@@ -34,7 +34,7 @@ struct TileAt {
 };
 
 template <int WGM, int WGN, int TM, int TN>
-__device__ __forceinline__ void direct_tiles(const int tile0, const int count, unsigned char* const lds, int* const tiny)
+__device__ __forceinline__ void direct_tiles(const int tile0, const int count, unsigned char* const lds)
 {
     constexpr int BM = WGM * TM * 32, BN = WGN * TN * 32, STEPS = 2;
     using LA = CutLayout<BM, STEPS>;
@@ -62,7 +62,6 @@ __device__ __forceinline__ void direct_tiles(const int tile0, const int count, u
         const int eight = __builtin_amdgcn_readfirstlane(lt / BN);            // which 8 of a k-step's channels
         const float *const w = a.w, *const x = a.x;
         float ra[2][AU][8], rb[2][2][8];
-        unsigned least = 0xFFFFFFFFu;
         // a walk over (tile, tap, 16 channels), two k-steps at a time
         int tile = tile0, step = 0, r = 0, t = 0, c0 = 0, a_m, ih0, iw0, xoff0;
         auto at_tile = [&]() __attribute__((always_inline)) {
@@ -109,9 +108,9 @@ __device__ __forceinline__ void direct_tiles(const int tile0, const int count, u
             constexpr int SET = decltype(set_c)::value;
 #pragma unroll
             for (int i = 0; i < AU; ++i)
-                if (BM * 4 % 256 == 0 || a_ks[i] < 2) put_pieces(ra[SET][i], lds + SET * STAGE + a_lds[i], LA::PIECE, least);
+                if (BM * 4 % 256 == 0 || a_ks[i] < 2) put_pieces(ra[SET][i], lds + SET * STAGE + a_lds[i], LA::PIECE);
 #pragma unroll
-            for (int u = 0; u < 2; ++u) put_pieces(rb[SET][u], lds + SET * STAGE + LA::BYTES + (u * 2 + eight) * LB::CHUNK + px * 16, LB::PIECE, least);
+            for (int u = 0; u < 2; ++u) put_pieces(rb[SET][u], lds + SET * STAGE + LA::BYTES + (u * 2 + eight) * LB::CHUNK + px * 16, LB::PIECE);
             __builtin_amdgcn_sched_barrier(0);       // (what is loaded goes to the registers that have just been read)
         };
         load(IC<0>{});
@@ -122,7 +121,6 @@ __device__ __forceinline__ void direct_tiles(const int tile0, const int count, u
         auto iterate = [&](auto set_c) __attribute__((always_inline)) {
             write(set_c);
             load(set_c);
-            if (too_small(least)) *tiny = 1;         // (for the rest of the workgroup's tiles)
             ring_barrier();
         };
         for (int at = 0; at < count * slices; at += 2) {
@@ -140,7 +138,7 @@ __device__ __forceinline__ void direct_tiles(const int tile0, const int count, u
         multiply_tile<WGM, WGN, TM, TN, STEPS>(lds, slices, stage, acc, small);
         const DirectArgs& f = fresh_direct();
         const TileAt at(f.k, tile, BM, BN);
-        finish_tile<TM, TN>(f.k, acc, small, at.m0 + wm * TM * 32, at.n0 + wn * TN * 32, at.n0, at.img0, f.by_pq, tiny);
+        finish_tile<TM, TN>(f.k, acc, small, at.m0 + wm * TM * 32, at.n0 + wn * TN * 32, at.n0, at.img0, f.by_pq);
     }
     if (count * slices & 1) ring_barrier();          // (the loading waves go in pairs of slices)
 }
@@ -149,14 +147,12 @@ template <int TILE>
 __global__ __launch_bounds__(512, 2) void conv_f32_direct_kernel(const DirectArgs a)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds[2 * cut_stage<direct_tile[TILE].bm, DIRECT_BN, 2>()];
-    __shared__ int tiny;
-    if (threadIdx.x == 0) tiny = 0;
     // consecutive workgroup ids are dealt to the 8 dies in turn: a range of tiles for each die
     const int G = (int)gridDim.x, id = (int)blockIdx.x, per = G >> 3, odd = G & 7, w = (id & 7) * per + min(id & 7, odd) + (id >> 3);
     const int tiles = a.k.grid_m * a.k.grid_n, whole = tiles / G, rest = tiles - whole * G, tile = w * whole + min(w, rest), count = whole + (w < rest);
-    if constexpr (TILE == 0) direct_tiles<2, 2, 2, 2>(tile, count, lds, &tiny);
-    else if constexpr (TILE == 1) direct_tiles<1, 4, 3, 1>(tile, count, lds, &tiny);
-    else direct_tiles<2, 2, 1, 2>(tile, count, lds, &tiny);
+    if constexpr (TILE == 0) direct_tiles<2, 2, 2, 2>(tile, count, lds);
+    else if constexpr (TILE == 1) direct_tiles<1, 4, 3, 1>(tile, count, lds);
+    else direct_tiles<2, 2, 1, 2>(tile, count, lds);
 }
 
 PiecesLayer layer_of(const ConvGeom& g) { return PiecesLayer{g.N, g.C, g.H, g.W, g.K, g.R, g.S, g.sh, g.sw, g.P, g.Q}; }

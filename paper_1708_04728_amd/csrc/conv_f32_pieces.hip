@@ -3,15 +3,16 @@
 //   D[m][n] = sum_k A[m][k] * B[k][n]     m = output channel, n = (image, p, q), k = (16 channels, r, s, channel)
 //
 // Arithmetic.  The fp32 matrix instructions reach 156 TFLOP/s here, those of bf16 1750.  An fp32 operand is the sum of three bf16 values, exactly (24 bits of
-// significand, 8 each); of the nine products of two operands the six largest are taken, the three left out are below 2^-25 of the product, so the ceiling is
-// 1750 / 6 = 290 TFLOP/s.  The largest product and the five small ones have sums of their own, added once at the end: the matrix instruction cuts what it adds to
+// significand, 8 each; Henry, Tang, Heinecke, "Leveraging the bfloat16 artificial intelligence datatype for higher-precision computations", 2019); of the nine products
+// of two operands the six largest are taken, the three left out are together at most 2^-24 of the product, so the ceiling is 1750 / 6 = 290 TFLOP/s.  The largest product and the five small ones have sums of their own, added once at the end: the matrix instruction cuts what it adds to
 // a sum at the sum's last bit, and with one sum for all of them the error of 9216 positive products grew to four times that of fp32 instructions.  Against 64 bits,
 // relative 2-norm of 32 x 32 blocks over contractions of 144 / 576 / 2400 normal x normal: fp32 instructions 2.2e-7 / 4.3e-7 / 8.8e-7, here 0.7e-7 / 1.4e-7 / 3.0e-7
 // (with one sum 1.9e-7 / 3.7e-7 / 7.7e-7); 8 layers with operands of normal, one-signed and uniform values 0.30 to 0.37 of fp32 instructions', strided ones 0.32 to 0.40.  Where one
 // product outweighs all others (values spread log-normally over e^+-12) the products left out and the second sum show: 0.6e-7 to 1.1e-7, fp32 instructions 0.3e-7 to 0.7e-7.
-// What three pieces cannot hold shows: an infinity, a NaN or a value that rounds to infinity in 8 bits leaves a NaN among the sums; operands whose lower pieces would
-// fall below the smallest bf16 are noticed where they are cut (eight in a row that are all below 2^-100 and not all zero).  The blocks concerned are then computed
-// again by fp32 instructions (exact_block): the values that those give, at about a third of their speed.
+// Operands are scaled by 2^24 where they are cut, sums by 2^-48 at the end: the lower pieces of small values, subnormal ones too, then stay above the smallest normal bf16.
+// (Unscaled, channels of 2^-118 beside one of 1 whose filters are 0 had an error of 8.8e-6 in the place of 0.9e-7.  Looking for eights of small operands took six
+// instructions where scaling takes eight; 15 layers 0.99 to 1.05 times as fast as with that.)  What is too large for pieces then shows among the sums: infinities, NaN, operands of 2^104 and more, sums of 2^80 and more leave an
+// infinity or a NaN.  The blocks of 32 x 32 outputs concerned are computed again by fp32 instructions (exact_block): the values that those give, at about a third of their speed.
 //
 // Structure.  One workgroup per compute unit walks its share of the tiles (conv_f32_pieces_plan.h).  Four waves load, cut operands into pieces and write LDS, four multiply;
 // vector instructions and bf16 matrix instructions of different waves overlap (six per matrix instruction cost 9 %, the clock that the power leaves).  A slice is 32
@@ -78,7 +79,7 @@ __device__ __forceinline__ const PatchArgs& fresh_args(int job)
 
 // tiles [tile0, tile0 + count) of a layer, by one workgroup
 template <int TILE, int WGM, int WGN, int TM, int TN>
-__device__ __forceinline__ void patch_tiles(const int job, const int tile0, const int count, unsigned char* const lds, int* const tiny)
+__device__ __forceinline__ void patch_tiles(const int job, const int tile0, const int count, unsigned char* const lds)
 {
     constexpr int BM = WGM * TM * 32, BN = WGN * TN * 32, PATCH = pieces_tiles[TILE].patch, PATCH_UNITS = PATCH * 2 / 256;
     static_assert(BM == pieces_tiles[TILE].bm && BN == pieces_tiles[TILE].bn, "tile");
@@ -108,7 +109,6 @@ __device__ __forceinline__ void patch_tiles(const int job, const int tile0, cons
         const int plane = HW * 4, C = g.C, w_bytes = a.w_bytes, x_bytes = a.x_bytes, grid_m = a.grid_m;
         const float *const w = a.w, *const x = a.x;
         float ra[2][AU][8], rb[8];
-        unsigned least = 0xFFFFFFFFu;            // of the largest values of eight, as bits, less one: zeros count as large
         // A: the filters, a walk over (tile, 16 channels, tap) that runs three slices ahead
         int a_tile = tile0, a_step = 0, a_tap = 0, a_blk = 0, a_m = Patch(pa, tile0, BM, BN).m0 * g.Kg * 4;
         const int a_end = tile0 + count;
@@ -145,7 +145,7 @@ __device__ __forceinline__ void patch_tiles(const int job, const int tile0, cons
             constexpr int SET = decltype(set_c)::value;
 #pragma unroll
             for (int i = 0; i < AU; ++i)
-                if (BM * 4 % 256 == 0 || a_ks[i] < 2) put_pieces(ra[SET][i], lds + SET * STAGE + a_lds[i], PSA, least);
+                if (BM * 4 % 256 == 0 || a_ks[i] < 2) put_pieces(ra[SET][i], lds + SET * STAGE + a_lds[i], PSA);
         };
 
         // B: the patches, a walk over (tile, 16 channels, unit)
@@ -205,7 +205,7 @@ __device__ __forceinline__ void patch_tiles(const int job, const int tile0, cons
             load_a(IC<0>{});
 #pragma unroll
             for (int i = 0; i < PATCH_UNITS; ++i)
-                if (i < b_units) put_pieces(first[i], patch + place(i), PATCH_PIECE, least);
+                if (i < b_units) put_pieces(first[i], patch + place(i), PATCH_PIECE);
             b_unit = b_units - 1;
             b_next();
         }
@@ -220,12 +220,11 @@ __device__ __forceinline__ void patch_tiles(const int job, const int tile0, cons
             load_a(set_c);
             if (k >= next_start) { ++m_blk; ++m_serial; next_start = ((m_blk + 1) * T + 1) >> 1; }
             if (b_serial == m_serial + 1) {
-                put_pieces(rb, patch + (b_serial & 1) * PATCH_BYTES + b_at, PATCH_PIECE, least);
+                put_pieces(rb, patch + (b_serial & 1) * PATCH_BYTES + b_at, PATCH_PIECE);
                 __builtin_amdgcn_sched_barrier(0);
                 b_next();
             }
             if (++k == slices) { k = 0; m_blk = 0; ++m_serial; next_start = (T + 1) >> 1; }
-            if (too_small(least)) *tiny = 1;      // (for the rest of the workgroup's tiles)
             ring_barrier();
         };
         for (int at = 0; at < total; at += 2) {
@@ -321,7 +320,7 @@ __device__ __forceinline__ void patch_tiles(const int job, const int tile0, cons
         }
         const KArgs& a = fresh_args(job).k;
         const Patch t(fresh_args(job), tile, BM, BN);
-        finish_tile<TM, TN>(a, acc, small, t.m0 + wm * TM * 32, t.n0 + wn * TN * 32, t.n0, t.img0, fresh_args(job).by_pq, tiny);
+        finish_tile<TM, TN>(a, acc, small, t.m0 + wm * TM * 32, t.n0 + wn * TN * 32, t.n0, t.img0, fresh_args(job).by_pq);
         t_buf = PATCH_BYTES - t_buf;
     }
     if (count * slices & 1) ring_barrier();      // (the loading waves go in pairs of slices)
@@ -338,8 +337,6 @@ template <int TILE>
 __global__ __launch_bounds__(512, 2) void conv_f32_pieces_kernel(const PiecesArgs a)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds[pieces_lds()];
-    __shared__ int tiny;
-    if (threadIdx.x == 0) tiny = 0;
     // consecutive workgroup ids are dealt to the 8 dies in turn: a range of tiles for each die
     const int G = (int)gridDim.x, id = (int)blockIdx.x, per = G >> 3, odd = G & 7, w = (id & 7) * per + min(id & 7, odd) + (id >> 3);
     for (int j = 0; j < a.n; ++j) {
@@ -348,10 +345,10 @@ __global__ __launch_bounds__(512, 2) void conv_f32_pieces_kernel(const PiecesArg
         while (i + 1 < s.n && w >= s.first[i + 1]) ++i;
         const int count = s.per[i], tile = s.tile[i] + (w - s.first[i]) * count, type = TILE < PIECES_TILES ? TILE : a.type[j];
         if (count == 0) continue;
-        if (type == 0) patch_tiles<0, 2, 2, 2, 2>(j, tile, count, lds, &tiny);
-        else if (type == 1) patch_tiles<1, 1, 4, 3, 1>(j, tile, count, lds, &tiny);
-        else if (type == 2) patch_tiles<2, 2, 2, 1, 2>(j, tile, count, lds, &tiny);
-        else patch_tiles<3, 1, 4, 2, 2>(j, tile, count, lds, &tiny);
+        if (type == 0) patch_tiles<0, 2, 2, 2, 2>(j, tile, count, lds);
+        else if (type == 1) patch_tiles<1, 1, 4, 3, 1>(j, tile, count, lds);
+        else if (type == 2) patch_tiles<2, 2, 2, 1, 2>(j, tile, count, lds);
+        else patch_tiles<3, 1, 4, 2, 2>(j, tile, count, lds);
     }
 }
 

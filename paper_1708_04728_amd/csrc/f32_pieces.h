@@ -1,4 +1,4 @@
-// fp32 operands as three bf16 pieces: cutting, multiplying, and what tells operands that they do not hold (conv_f32_pieces.hip has the arithmetic).
+// fp32 operands as three bf16 pieces: cutting and multiplying (conv_f32_pieces.hip has the arithmetic).
 #pragma once
 #include "dr_store.h"
 
@@ -33,16 +33,6 @@ __device__ __forceinline__ f32x16 mfma(u32x4 a, u32x4 b, f32x16 c)
 {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
-
-// The largest magnitude of eight, as bits, less one (zeros count as large)
-__device__ __forceinline__ unsigned magnitude8(const float (&v)[8])
-{
-    float m = fmaxf(fabsf(v[0]), fabsf(v[1]));
-#pragma unroll
-    for (int e = 2; e < 8; e += 2) m = fmaxf(fmaxf(m, fabsf(v[e])), fabsf(v[e + 1]));
-    return __float_as_uint(m) - 1;
-}
-__device__ __forceinline__ bool too_small(unsigned least) { return __any(least < __float_as_uint(0x1p-100f) - 1); }
 
 }  // namespace
 }  // namespace dr

@@ -110,6 +110,39 @@ def test_operands_beyond_bf16_pieces(stride):
     assert np.array_equal(plain, run(x, w, None, (1, 1), False, ss))
 
 
+@pytest.mark.parametrize("scale", (-105, -118, -140))
+@pytest.mark.parametrize("stride", (1, 2))
+def test_small_operands_beside_a_larger_one(stride, scale):
+    """Of every eight channels one is about 1 where the other operand is 0, the rest about 2^scale (2^-140: subnormal): the sums consist of those alone."""
+    N, C, H, W, K = (28, 32, 30, 30, 96) if stride == 1 else (40, 32, 41, 33, 200)
+    rng = np.random.default_rng(-scale)
+    x = rng.standard_normal((N, C, H, W)).astype(np.float32)
+    w = rng.standard_normal((K, C, 3, 3)).astype(np.float32)
+    few, many = np.s_[:, ::8], np.arange(C) % 8 != 0
+    for tiny, other in ((x, w), (w, x)):
+        tiny, other = tiny.copy(), other * np.float32(2.0 ** 30)
+        tiny[:, many] *= np.float32(2.0 ** scale)
+        other[few] = 0
+        a, b = (tiny, other) if tiny.shape == x.shape else (other, tiny)
+        ref = torch.nn.functional.conv2d(torch.from_numpy(a).double(), torch.from_numpy(b).double(), padding=1, stride=stride).numpy()
+        # as test_pieces
+        assert note("rms", rms_err(run(a, b, None, (1, 1), False, (stride, stride)), ref), 4 * 2.0 ** -24 * np.sqrt(C * 9 / 16) + 2.0 ** -24)
+
+
+@pytest.mark.parametrize("stride", (1, 2))
+def test_sums_of_large_operands(stride):
+    """Sums of about 2^80 to 2^122, image by image: on both sides of where pieces end."""
+    N, C, H, W, K = (28, 32, 30, 30, 96) if stride == 1 else (40, 32, 41, 33, 200)
+    rng = np.random.default_rng(stride)
+    x = rng.standard_normal((N, C, H, W)).astype(np.float32)
+    w = rng.standard_normal((K, C, 3, 3)).astype(np.float32)
+    ref = torch.nn.functional.conv2d(torch.from_numpy(x).double(), torch.from_numpy(w).double(), padding=1, stride=stride).numpy()
+    scale = np.float32(2.0) ** (np.linspace(37, 78, N).round().astype(np.float32).reshape(N, 1, 1, 1))
+    got = run(x * scale, w * np.float32(2.0 ** 40), None, (1, 1), False, (stride, stride)) / (scale.astype(np.float64) * 2.0 ** 40)
+    # products of fp32 instructions: C R S / 2 sums
+    assert close(got, ref, TOL_F32) and note("rms", rms_err(got, ref), 4 * 2.0 ** -24 * np.sqrt(C * 9 / 2) + 2.0 ** -24)
+
+
 def test_layers_of_a_module_share_a_launch():
     """A 3x3 and a 5x5 layer side by side, with tiles of their own: the bits of each by itself."""
     N, side = 24, 28
