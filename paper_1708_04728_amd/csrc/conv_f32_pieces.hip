@@ -365,36 +365,14 @@ bool conv_f32_pieces_takes(const ConvGeom& g)
 int launch_conv_f32_pieces(const ConvSmall* jobs, int n, hipStream_t st)
 {
     const int cus = device_cus();
-    int order[PIECES_LAYERS], type[PIECES_LAYERS], best_type[PIECES_LAYERS] = {};
+    int order[PIECES_LAYERS], best_type[PIECES_LAYERS] = {};
     PiecesLayer layer[PIECES_LAYERS];
     for (int i = 0; i < n; ++i) { order[i] = i; layer[i] = layer_of(jobs[i].g); }
     std::sort(order, order + n, [&](int p, int q) { return pieces_slices(layer[p]) > pieces_slices(layer[q]); });      // the longest tiles first
-    // the tiles that end first: all combinations of two layers, else each layer's own best
-    PiecesPlan plan, best;
-    bool found = false;
-    auto attempt = [&]() {
-        long tiles[PIECES_LAYERS];
-        double cost[PIECES_LAYERS];
-        for (int i = 0; i < n; ++i) {
-            const PiecesTile& t = pieces_tiles[type[i]];
-            tiles[i] = pieces_count(layer[order[i]], t);
-            cost[i] = pieces_cost(layer[order[i]], t);
-        }
-        if (!pieces_plan(n, tiles, cost, cus, &plan) || (found && plan.us >= best.us)) return;
-        best = plan;
-        found = true;
-        for (int i = 0; i < n; ++i) best_type[i] = type[i];
-    };
-    if (n <= 2) {
-        for (type[0] = 0; type[0] < PIECES_TILES; ++type[0])
-            for (type[1] = 0; type[1] < (n == 2 ? PIECES_TILES : 1); ++type[1])
-                if (pieces_fits(layer[order[0]], pieces_tiles[type[0]]) && (n == 1 || pieces_fits(layer[order[1]], pieces_tiles[type[1]]))) attempt();
-    } else {
-        double us;
-        for (int i = 0; i < n; ++i) type[i] = pieces_best(layer[order[i]], cus, &us);
-        attempt();
-    }
-    if (!found) return fail(DR_ERR_UNSUPPORTED, "conv_f32_pieces: no plan for %d layers", n);
+    PiecesPlan best;
+    PiecesLayer sorted[PIECES_LAYERS];
+    for (int i = 0; i < n; ++i) sorted[i] = layer[order[i]];
+    if (!pieces_choose(n, sorted, cus, best_type, &best)) return fail(DR_ERR_UNSUPPORTED, "conv_f32_pieces: no plan for %d layers", n);
     PiecesArgs a{};
     a.n = n;
     for (int i = 0; i < n; ++i) {

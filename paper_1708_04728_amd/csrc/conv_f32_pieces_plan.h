@@ -127,4 +127,34 @@ inline bool pieces_plan(int n, const long* tiles, const double* cost, int cus, P
     return true;
 }
 
+// The tiles of up to 4 layers, in the given order, that end first: all combinations of two layers, else each layer's own best
+inline bool pieces_choose(int n, const PiecesLayer* layer, int cus, int* type, PiecesPlan* plan)
+{
+    int at[PIECES_LAYERS];
+    bool found = false;
+    auto attempt = [&]() {
+        long tiles[PIECES_LAYERS];
+        double cost[PIECES_LAYERS];
+        for (int i = 0; i < n; ++i) {
+            tiles[i] = pieces_count(layer[i], pieces_tiles[at[i]]);
+            cost[i] = pieces_cost(layer[i], pieces_tiles[at[i]]);
+        }
+        PiecesPlan p;
+        if (!pieces_plan(n, tiles, cost, cus, &p) || (found && p.us >= plan->us)) return;
+        *plan = p;
+        found = true;
+        for (int i = 0; i < n; ++i) type[i] = at[i];
+    };
+    if (n <= 2) {
+        for (at[0] = 0; at[0] < PIECES_TILES; ++at[0])
+            for (at[1] = 0; at[1] < (n == 2 ? PIECES_TILES : 1); ++at[1])
+                if (pieces_fits(layer[0], pieces_tiles[at[0]]) && (n == 1 || pieces_fits(layer[1], pieces_tiles[at[1]]))) attempt();
+    } else {
+        double us;
+        for (int i = 0; i < n; ++i) at[i] = pieces_best(layer[i], cus, &us);
+        attempt();
+    }
+    return found;
+}
+
 }  // namespace dr

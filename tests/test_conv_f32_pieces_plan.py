@@ -32,6 +32,23 @@ int main(int argc, char** argv)
         }
         return 0;
     }
+    if (argc > 1 && !strcmp(argv[1], "choose")) {
+        int n;
+        while (scanf("%d", &n) == 1) {
+            dr::PiecesLayer l[dr::PIECES_LAYERS];
+            for (int i = 0; i < n; ++i) {
+                if (scanf("%d %d %d %d %d", &l[i].N, &l[i].C, &l[i].H, &l[i].K, &l[i].R) != 5) return 1;
+                l[i].S = l[i].R; l[i].W = l[i].P = l[i].Q = l[i].H; l[i].sh = l[i].sw = 1;
+                printf("%d ", dr::pieces_pays(l[i], 256));
+            }
+            int type[dr::PIECES_LAYERS];
+            dr::PiecesPlan p;
+            if (!dr::pieces_choose(n, l, 256, type, &p)) return 1;
+            for (int i = 0; i < n; ++i) printf("%d ", type[i]);
+            printf("\n");
+        }
+        return 0;
+    }
     dr::PiecesLayer l;
     int ph, pw;
     while (scanf("%d %d %d %d %d %d %d %d %d %d %d", &l.N, &l.C, &l.H, &l.W, &l.K, &l.R, &l.S, &l.sh, &l.sw, &ph, &pw) == 11) {
@@ -98,6 +115,17 @@ def test_the_kernel_and_tile_of_the_gpu_cases(program):
     assert [v[:2] for v in program(["28 32 30 30 96 3 3 1 1 1 1", "28 32 30 30 96 3 3 1 1 0 0", "40 32 41 33 200 3 3 2 2 1 1", "40 32 41 33 200 3 3 2 2 0 0"])] == [["1", "0"]] * 2 + [["0", "1"]] * 2
 
 
+def test_the_tiles_of_layers_that_share_a_launch(program):
+    """The modules of the GPU test: every layer is taken, and the launches have one tile for all and several."""
+    from test_gpu_conv_f32_pieces import SHARED
+    lines, expect = [], []
+    for n, layers, tiles in SHARED:
+        order = sorted(range(len(layers)), key=lambda i: -((layers[i][2] ** 2 * (layers[i][0] // 16) + 1) // 2))      # the longest contraction first
+        lines.append("%d " % len(layers) + " ".join("%d %d 28 %d %d" % (n, layers[i][0], layers[i][1], layers[i][2]) for i in order))
+        expect.append([1] * len(layers) + [tiles[i] for i in order])
+    assert [list(map(int, v)) for v in program(lines, "choose")] == expect
+
+
 def test_what_stays_with_the_other_kernels(program):
     taken = ((32, 96, 28, 28, 128, 3, 3, 1, 1, 1, 1), (52, 160, 28, 28, 288, 3, 3, 2, 2, 1, 1))
     beside = [(32, 96, 28, 28, 128, 1, 1, 1, 1, 0, 0),       # one tap
@@ -108,6 +136,8 @@ def test_what_stays_with_the_other_kernels(program):
               (2, 16, 28, 300, 128, 3, 3, 1, 1, 1, 1),       # a row of 300 pixels
               (4, 16, 1200, 60, 64, 3, 3, 1, 1, 1, 1),       # 72000 pixels
               (64, 160, 7, 7, 320, 3, 3, 1, 1, 1, 1),        # tiles for half of the compute units
+              (24, 16, 28, 28, 96, 3, 3, 1, 1, 1, 1),        # a block of 16 channels: short contractions
+              (24, 16, 28, 28, 96, 5, 5, 1, 1, 2, 2),
               (128, 96, 28, 28, 256, 5, 5, 2, 2, 2, 2),      # strided, whole tiles of 64 filters
               (5, 64, 56, 56, 96, 3, 3, 2, 2, 1, 1),         # strided: not enough faster
               (97, 128, 35, 34, 40, 5, 5, 2, 2, 2, 2)]       # strided, 40 filters

@@ -272,6 +272,7 @@ def _strided_module():
     ("5a", 64, 7, 832, False),      # 784, 490 and 98
     ("5b", 64, 7, 832, False),      # 1176, 588 and 196
     ("5a slim", 64, 7, 832, True),  # three small layers and one that is not: by levels also with streams asked for
+    ("3a slim", 32, 28, 192, False),    # 3x3 and 5x5 on bf16 pieces, in one launch with tiles of their own
     ("strided", 4, 64, 64, False),
 ])
 def test_fp32_module_bits_do_not_depend_on_what_shares_a_launch(case):

@@ -72,7 +72,7 @@ def test_pieces(case):
 
 @pytest.mark.parametrize("stride", (1, 2))
 def test_operands_beyond_bf16_pieces(stride):
-    """Infinities, NaN, values that round to infinity in 8 bits, and operands whose lower pieces are too small for a bf16: as fp32 arithmetic has them."""
+    """Infinities, NaN, values that round to infinity in 8 bits, and images and filters of small operands: as fp32 arithmetic has them."""
     N, C, H, W, K = (28, 32, 30, 30, 96) if stride == 1 else (40, 32, 41, 33, 200)
     ss = (stride, stride)
     rng = np.random.default_rng(7)
@@ -144,7 +144,7 @@ def test_sums_of_large_operands(stride):
 
 
 def test_layers_of_a_module_share_a_launch():
-    """A 3x3 and a 5x5 layer side by side, with tiles of their own: the bits of each by itself."""
+    """A 3x3 and a 5x5 layer of 16 channels side by side, which stay with the other kernels: the bits of each by itself."""
     N, side = 24, 28
     branches = [[("conv", {"k": 16, "r": 1, "s": 1, "stride": 1, "pad": 0}), ("relu", {}), ("conv", {"k": 96, "r": r, "s": r, "stride": 1, "pad": r // 2}), ("relu", {})] for r in (3, 5)]
     from paper_1708_04728_amd import graph as G
@@ -166,3 +166,52 @@ def test_layers_of_a_module_share_a_launch():
         B.conv2d_fwd(t, B.conv_desc(96, 16, r, r, 1, r // 2, True, B.DR_KRSC), weights[2 * i + 1], biases[2 * i + 1], alone, 96 * i)
     torch.cuda.synchronize()
     assert torch.equal(y, alone)
+
+
+# images of 28 x 28; channels, filters and side of each layer behind a 1x1; the tile that each has in the launch they share
+SHARED = [
+    (32, ((96, 128, 3), (16, 128, 5)), (0, 2)),
+    (32, ((32, 96, 3), (32, 96, 5)), (2, 1)),
+    (40, ((32, 96, 3), (32, 96, 5), (32, 96, 3)), (1, 1, 1)),                   # one tile for all
+    (40, ((32, 96, 3), (32, 96, 5), (32, 128, 3), (32, 64, 5)), (1, 1, 3, 2)),
+]
+
+
+@pytest.mark.parametrize("case", SHARED)
+def test_layers_on_pieces_share_a_launch(case):
+    """Layers side by side, with tiles of their own: the bits of each by itself, every time.  Among the images some whose pixels are small all over, some with sums
+    beyond pieces, whose blocks are computed again, and ordinary ones, which are not touched by what a workgroup computed before."""
+    from paper_1708_04728_amd import graph as G
+    n, layers, _ = case
+    side, c0 = 28, 64
+    branches = [[("conv", {"k": c, "r": 1, "s": 1, "stride": 1, "pad": 0}), ("relu", {}), ("conv", {"k": k, "r": r, "s": r, "stride": 1, "pad": r // 2}), ("relu", {})]
+                for c, k, r in layers]
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn((n, c0, side, side), device="cuda", generator=gen).abs()
+    plain = x.clone()
+    x[1::3] *= 2.0 ** -104
+    x[2::6] *= 2.0 ** 90
+    weights, biases = [], []
+    for c, k, r in layers:
+        for m, ch, s in ((c, c0, 1), (k, c, r)):
+            weights.append(B.pack_filters(torch.randn((m, ch, s, s), device="cuda", generator=gen) * (2.0 / (ch * s * s)) ** 0.5))
+            biases.append(torch.zeros(m, device="cuda"))
+    desc = G.inception_desc({"branches": branches}, c0, B.DR_FUSE_RELU | B.DR_FUSE_CONCAT, "f32")
+    ktot = sum(k for _, k, _ in layers)
+    ws = torch.empty(max(B.inception_workspace_bytes(x, desc), 256), dtype=torch.uint8, device="cuda")
+    reference = torch.empty((n, ktot, side, side), device="cuda")
+    B.inception_fwd(plain, desc, weights, biases, reference, ws)
+    y, alone = torch.empty_like(reference), torch.empty_like(reference)
+    at = 0
+    for i, (c, k, r) in enumerate(layers):
+        t = torch.empty((n, c, side, side), device="cuda")
+        B.conv2d_fwd(x, B.conv_desc(c, c0, 1, 1, 1, 0, True, B.DR_KRSC), weights[2 * i], biases[2 * i], t)
+        B.conv2d_fwd(t, B.conv_desc(k, c, r, r, 1, r // 2, True, B.DR_KRSC), weights[2 * i + 1], biases[2 * i + 1], alone, at)
+        at += k
+    for _ in range(3):
+        y.fill_(float("nan"))
+        B.inception_fwd(x, desc, weights, biases, y, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(y, alone)
+    assert torch.equal(y[0::6], reference[0::6])      # (784 pixels: an image of odd number shares a block of 32 with the one before it)
+    assert close(host(y[1::3]) * 2.0 ** 104, host(reference[1::3]), TOL_F32) and close(host(y[2::6]) * 2.0 ** -90, host(reference[2::6]), TOL_F32)
