@@ -813,11 +813,11 @@ int launch_conv_f32(const ConvGeom& g, const float* x, const float* w, const flo
                     float* y, hipStream_t st, void* ws, size_t ws_bytes, const ConvSplit* split)
 {
     TraceScope trace("conv_f32", &g, g.Ng, st);
-    if (!residual && conv_f32_pieces_takes(g)) {
+    if (conv_f32_pieces_takes(g)) {
         const ConvSmall job{g, x, w, bias, residual, y, split};
         return launch_conv_f32_pieces(&job, 1, st);
     }
-    if (!residual && conv_f32_direct_takes(g)) return launch_conv_f32_direct(ConvSmall{g, x, w, bias, nullptr, y, split}, st);
+    if (conv_f32_direct_takes(g)) return launch_conv_f32_direct(ConvSmall{g, x, w, bias, residual, y, split}, st);
     if (conv_f32_small_takes(g, w, ws != nullptr)) {
         const ConvSmall job{g, x, w, bias, residual, y, split};
         return launch_conv_f32_small(&job, 1, st);

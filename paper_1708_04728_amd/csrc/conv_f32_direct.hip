@@ -162,15 +162,16 @@ PiecesLayer layer_of(const ConvGeom& g) { return PiecesLayer{g.N, g.C, g.H, g.W,
 bool conv_f32_direct_takes(const ConvGeom& g)
 {
     const size_t xb = (size_t)g.N * g.C * g.H * g.W * 4, wb = (size_t)g.K * g.Kg * 4;
-    return !g.nhwc && g.w_krsc && xb < (1ull << 31) && wb < (1ull << 31) && direct_pays(layer_of(g), device_cus());
+    return !g.nhwc && g.w_krsc && g.res_ctot == 0 && xb < (1ull << 31) && wb < (1ull << 31) && direct_pays(layer_of(g), device_cus());
 }
 
 int launch_conv_f32_direct(const ConvSmall& c, hipStream_t st)
 {
+    if (c.res || (c.split && c.split->n > 1)) return fail(DR_ERR_UNSUPPORTED, "conv_f32_direct: a residual or several destinations");
     double us;
     const int cus = device_cus(), tile = direct_best(layer_of(c.g), cus, &us), bm = direct_tile[tile].bm;
     DirectArgs a;
-    a.k = conv_f32_args(c.g, (const float*)c.x, (const float*)c.w, c.bias, (const float*)c.res, (float*)c.y, c.split);
+    a.k = conv_f32_args(c.g, (const float*)c.x, (const float*)c.w, c.bias, nullptr, (float*)c.y, nullptr);
     a.k.grid_m = (c.g.K + bm - 1) / bm;
     a.k.grid_n = (int)(((long)c.g.Ng + DIRECT_BN - 1) / DIRECT_BN);
     auto magic = [](int d) { return ((1ull << 40) + (unsigned)d - 1) / (unsigned)d; };

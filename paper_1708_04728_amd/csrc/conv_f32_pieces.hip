@@ -359,7 +359,7 @@ PiecesLayer layer_of(const ConvGeom& g) { return PiecesLayer{g.N, g.C, g.H, g.W,
 bool conv_f32_pieces_takes(const ConvGeom& g)
 {
     const size_t xb = (size_t)g.N * g.C * g.H * g.W * 4, wb = (size_t)g.K * g.Kg * 4;
-    return !g.nhwc && g.w_krsc && xb < (1ull << 31) && wb < (1ull << 31) && pieces_pays(layer_of(g), device_cus());
+    return !g.nhwc && g.w_krsc && g.res_ctot == 0 && xb < (1ull << 31) && wb < (1ull << 31) && pieces_pays(layer_of(g), device_cus());
 }
 
 int launch_conv_f32_pieces(const ConvSmall* jobs, int n, hipStream_t st)
@@ -367,7 +367,11 @@ int launch_conv_f32_pieces(const ConvSmall* jobs, int n, hipStream_t st)
     const int cus = device_cus();
     int order[PIECES_LAYERS], best_type[PIECES_LAYERS] = {};
     PiecesLayer layer[PIECES_LAYERS];
-    for (int i = 0; i < n; ++i) { order[i] = i; layer[i] = layer_of(jobs[i].g); }
+    for (int i = 0; i < n; ++i) {
+        if (jobs[i].res || (jobs[i].split && jobs[i].split->n > 1)) return fail(DR_ERR_UNSUPPORTED, "conv_f32_pieces: a residual or several destinations");
+        order[i] = i;
+        layer[i] = layer_of(jobs[i].g);
+    }
     std::sort(order, order + n, [&](int p, int q) { return pieces_slices(layer[p]) > pieces_slices(layer[q]); });      // the longest tiles first
     PiecesPlan best;
     PiecesLayer sorted[PIECES_LAYERS];
@@ -379,7 +383,7 @@ int launch_conv_f32_pieces(const ConvSmall* jobs, int n, hipStream_t st)
         const ConvSmall& c = jobs[order[i]];
         const PiecesTile& t = pieces_tiles[best_type[i]];
         PatchArgs& p = a.job[i];
-        p.k = conv_f32_args(c.g, (const float*)c.x, (const float*)c.w, c.bias, (const float*)c.res, (float*)c.y, c.split, t.bn);
+        p.k = conv_f32_args(c.g, (const float*)c.x, (const float*)c.w, c.bias, nullptr, (float*)c.y, nullptr, t.bn);
         p.k.grid_m = (c.g.K + t.bm - 1) / t.bm;
         p.k.grid_n = (int)(((long)c.g.Ng + t.bn - 1) / t.bn);
         auto magic = [](int d) { return ((1ull << 40) + (unsigned)d - 1) / (unsigned)d; };

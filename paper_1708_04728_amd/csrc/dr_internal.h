@@ -76,7 +76,8 @@ int launch_conv_f32_small(const ConvSmall* jobs, int n, hipStream_t st);
 // conv_f32.hip: several larger fp32 layers (KRSC filters, C % 16 == 0) in one launch
 bool conv_f32_group_takes(const ConvGeom& g);
 int launch_conv_f32_group(const ConvSmall* jobs, int n, hipStream_t st);
-// conv_f32_pieces.hip: layers of several taps at stride 1 on the bf16 matrix cores, with fp32 operands in three pieces; up to SMALL_GROUP_MAX in one launch
+// conv_f32_pieces.hip: layers of several taps at stride 1, without a residual, on the bf16 matrix cores, with fp32 operands in three pieces; up to SMALL_GROUP_MAX in one
+// launch
 bool conv_f32_pieces_takes(const ConvGeom& g);
 int launch_conv_f32_pieces(const ConvSmall* jobs, int n, hipStream_t st);
 // conv_f32_direct.hip: strided layers of several taps so

@@ -173,3 +173,44 @@ def test_every_tile_has_one_workgroup(program):
         assert max(load) == pytest.approx(us, rel=1e-6)
         # no longer than the work spread evenly and one more tile of each layer
         assert us <= sum(t * c for t, c in layers) / cus + sum(c for _, c in layers) + 1e-6
+
+
+RULES = r"""
+#include <cstdio>
+#include "dr_internal.h"
+using namespace dr;
+int main()
+{
+    int stride, K, N, H, residual;
+    while (scanf("%d %d %d %d %d", &stride, &K, &N, &H, &residual) == 5) {
+        ConvGeom g{};
+        g.N = N; g.C = 160; g.H = g.W = H; g.K = K; g.R = g.S = 3; g.sh = g.sw = stride; g.ph = g.pw = 1;
+        g.P = g.Q = (H - 1) / stride + 1; g.Kg = g.C * 9; g.Ng = N * g.P * g.Q; g.y_ctot = K; g.w_krsc = 1;
+        g.res_ctot = residual ? K : 0;
+        ConvSmall job{};
+        job.g = g;
+        job.res = residual ? &g : nullptr;
+        printf("%d %d %d %d", conv_f32_pieces_takes(g), conv_f32_direct_takes(g), conv_f32_small_takes(g, nullptr, false), conv_f32_scratch_bytes(g) != 0);
+        // (refused before anything is launched)
+        if (residual) printf(" %d", stride == 1 ? launch_conv_f32_pieces(&job, 1, nullptr) : launch_conv_f32_direct(job, nullptr));
+        printf("\n");
+    }
+}
+"""
+
+
+def test_a_residual_stays_with_the_other_kernels(tmp_path):
+    """A 3x3 layer with a residual is not counted as theirs, and keeps the kernel for small layers; the launchers refuse it."""
+    rocm = "/opt/rocm"
+    if not os.path.exists(os.path.join(rocm, "include", "hip", "hip_runtime.h")):
+        pytest.skip("no HIP headers")
+    from paper_1708_04728_amd import binding as B
+    (tmp_path / "rules.cpp").write_text(RULES)
+    subprocess.check_call(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-w", "-I", CSRC, "-I", os.path.join(rocm, "include"), str(tmp_path / "rules.cpp"), B.LIB_PATH,
+                           "-Wl,--allow-shlib-undefined", "-Wl,-rpath," + os.path.dirname(B.LIB_PATH), "-o", str(tmp_path / "rules")])
+    cases = ((1, 96, 16, 28), (1, 128, 14, 28), (2, 288, 52, 28))
+    lines = ["%d %d %d %d %d" % (c + (r,)) for c in cases for r in (0, 1)]
+    out = subprocess.run([str(tmp_path / "rules")], input="\n".join(lines), capture_output=True, text=True, check=True, timeout=60).stdout.splitlines()
+    # pieces, direct, small layers, scratch; the launcher's answer
+    refused = " %d" % B.DR_ERR_UNSUPPORTED
+    assert out == ["1 0 0 0", "0 0 1 0" + refused, "1 0 0 0", "0 0 1 0" + refused, "0 1 0 0", "0 0 0 0" + refused]
