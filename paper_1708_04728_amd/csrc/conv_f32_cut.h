@@ -22,11 +22,10 @@ __device__ __forceinline__ void put_pieces(const float (&v)[8], unsigned char* a
 __device__ __forceinline__ f32x16 exact_block(const KArgs& a, int m, int n, int half)
 {
     const ConvGeom& g = a.g;
-    const int HW = g.H * g.W, PQ = g.P * g.Q, RS = g.R * g.S;
+    const int HW = g.H * g.W, PQ = g.P * g.Q;
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)a.x, 0, a.x_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, a.w_bytes, 0x00020000);
     const int nn = n < g.Ng ? n : 0, img = nn / PQ, pix = nn - img * PQ, p = pix / g.Q, q = pix - p * g.Q, ih0 = p * g.sh - g.ph, iw0 = q * g.sw - g.pw;
-    const int w_tap = a.w_krsc ? g.C : 1, w_chan = a.w_krsc ? 1 : RS;
     f32x16 acc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.f;
@@ -34,18 +33,17 @@ __device__ __forceinline__ f32x16 exact_block(const KArgs& a, int m, int n, int 
         for (int s = 0; s < g.S; ++s) {
             const bool ok = (n < g.Ng) & ((unsigned)(ih0 + r) < (unsigned)g.H) & ((unsigned)(iw0 + s) < (unsigned)g.W);
             const int xo = ok ? ((img * g.C + half) * HW + (ih0 + r) * g.W + iw0 + s) * 4 : OOB;
-            const int wo = m < g.K ? (m * g.Kg + (r * g.S + s) * w_tap + half * w_chan) * 4 : OOB;
+            const int wo = m < g.K ? (m * g.Kg + (r * g.S + s) * g.C + half) * 4 : OOB;
 #pragma unroll 2
             for (int c = 0; c < g.C; c += 2) {
-                const bool in = c + half < g.C;
-                const float fa = buf_load(rw, in ? wo : OOB, c * w_chan * 4), fb = buf_load(rx, in ? xo : OOB, c * HW * 4);
+                const float fa = buf_load(rw, wo, c * 4), fb = buf_load(rx, xo, c * HW * 4);
                 acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa, fb, acc, 0, 0, 0);
             }
         }
     return acc;
 }
 
-// Whole blocks: a store per element whose filter is the scalar offset; eight filters have one destination
+// Whole blocks: a store per element whose filter is the scalar offset, with a descriptor for every eight
 template <int TM, int TN>
 __device__ __forceinline__ void store_whole(const KArgs& a, const f32x16 (&acc)[TM][TN], const f32x4 (&bias)[TM][4], int mw, int nw, int img0, unsigned long long by_pq)
 {
@@ -62,10 +60,8 @@ __device__ __forceinline__ void store_whole(const KArgs& a, const f32x16 (&acc)[
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int m8 = mw + i * 32 + q * 8, d = a.nsplit <= 1 ? 0 : (m8 >= a.split_end[0]) + (m8 >= a.split_end[1]) + (m8 >= a.split_end[2]);
-            const int ct = d == 0 ? a.ctot_seg[0] : d == 1 ? a.ctot_seg[1] : d == 2 ? a.ctot_seg[2] : a.ctot_seg[3];
-            float* const yd = d == 0 ? a.y_seg[0] : d == 1 ? a.y_seg[1] : d == 2 ? a.y_seg[2] : a.y_seg[3];
-            const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void*)(yd + ((size_t)img0 * ct + m8) * PQ), 0, 0x7FFFFFFF, 0x00020000);
+            const int m8 = mw + i * 32 + q * 8, ct = a.ctot_seg[0];
+            const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void*)(a.y_seg[0] + ((size_t)img0 * ct + m8) * PQ), 0, 0x7FFFFFFF, 0x00020000);
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
                 const int vy = nw + j * 32 + l32 < a.g.Ng ? img[j] * ct * plane + pix[j] : OOB;
