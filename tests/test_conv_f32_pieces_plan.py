@@ -108,9 +108,10 @@ def test_a_tile_that_fits_has_room_for_every_patch(program):
 
 
 def test_the_kernel_and_tile_of_the_gpu_cases(program):
-    from test_gpu_conv_f32_pieces import CASES, STRIDED
+    from test_gpu_conv_f32_pieces import CASES, FAR, STRIDED
     got = program([" ".join(map(str, c[:7] + (1, 1) + c[7])) for c, _ in CASES] + [" ".join(map(str, c[:7] + c[7] + c[8])) for c, _ in STRIDED])
     assert [tuple(map(int, v[:3])) for v in got] == [(1, 0, t) for _, t in CASES] + [(0, 1, t) for _, t in STRIDED]
+    assert [v[:2] for v in program([" ".join(map(str, FAR[s] + (s, s, 1, 1))) for s in (1, 2)])] == [["1", "0"], ["0", "1"]]
     # the layers with operands that pieces cannot hold
     assert [v[:2] for v in program(["28 32 30 30 96 3 3 1 1 1 1", "28 32 30 30 96 3 3 1 1 0 0", "40 32 41 33 200 3 3 2 2 1 1", "40 32 41 33 200 3 3 2 2 0 0"])] == [["1", "0"]] * 2 + [["0", "1"]] * 2
 

@@ -28,6 +28,7 @@ CASES = [
     (1, 4460, 4460, True, False),
     (1, 4459, 4459, True, True),             # 27 planes: 500 KB below 2 GiB
     (544, 1024, 1024, False, False),         # 2.3 GB of channels
+    (4480, 1000, 60, False, False),          # 2.15 GB in two images
     (13, 4459, 4459, True, True),
     (14, 4459, 4459, True, False),           # two images of 14
     (4096, 1, 1, True, True),

@@ -143,6 +143,51 @@ def test_sums_of_large_operands(stride):
     assert close(got, ref, TOL_F32) and note("rms", rms_err(got, ref), 4 * 2.0 ** -24 * np.sqrt(C * 9 / 2) + 2.0 ** -24)
 
 
+# the layer that test_channels_2_gib_apart runs at each stride, with 1 pixel of padding, into a tensor of FAR_CHANNELS
+FAR, FAR_CHANNELS = {1: (1, 32, 1000, 60, 97, 3, 3), 2: (1, 32, 2000, 120, 200, 3, 3)}, 4480
+
+
+@pytest.mark.parametrize("stride", (1, 2))
+def test_channels_2_gib_apart(stride):
+    """The last channels of a tensor of 1000 x 60 pixels and 1.07 GB an image: two images' worth of offsets do not fit the short form of the store."""
+    N, C, H, W, K, R, S = FAR[stride]
+    rng = np.random.default_rng(stride)
+    x, w, b = (rng.standard_normal(s).astype(np.float32) for s in ((N, C, H, W), (K, C, R, S), K))
+    x[0, 5, 700, 9] = np.inf                              # a block that is computed again
+    y = torch.empty((N, FAR_CHANNELS, 1000, 60), device="cuda")
+    y[:, FAR_CHANNELS - K - 2:] = 7.0
+    B.conv2d_fwd(gpu(x), B.conv_desc(K, C, R, S, stride, 1, True, B.DR_KRSC), B.pack_filters(gpu(w)), gpu(b), y, FAR_CHANNELS - K - 1)
+    torch.cuda.synchronize()
+    got = host(y[:, FAR_CHANNELS - K - 1:FAR_CHANNELS - 1])
+    assert bool((y[:, FAR_CHANNELS - K - 2] == 7.0).all()) and bool((y[:, FAR_CHANNELS - 1] == 7.0).all())
+    ref = torch.nn.functional.conv2d(*(torch.from_numpy(t).double() for t in (x, w, b)), padding=1, stride=stride).clamp(min=0).numpy()
+    there = np.isfinite(ref)
+    assert (~there).sum() > 0 and np.array_equal(np.isposinf(got), np.isposinf(ref)) and close(got[there], ref[there], TOL_F32)
+
+
+@pytest.mark.parametrize("case", (CASES[4][0][:7] + ((1, 1), CASES[4][0][7]), STRIDED[4][0]))
+def test_filters_on_any_word(case):
+    """Filters and biases that start 4 bytes behind a 16-byte boundary (slices of a parameter buffer): the same bits."""
+    N, C, H, W, K, R, S, stride, pad = case
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    x, w, b = (torch.randn(s, device="cuda", generator=gen) for s in ((N, C, H, W), (K, C, R, S), (K,)))
+    cd = B.conv_desc(K, C, R, S, stride, pad, True, B.DR_KRSC)
+    P, Q = (oracle.conv_out_size(*v) for v in ((H, R, stride[0], pad[0]), (W, S, stride[1], pad[1])))
+    got = []
+    for shift in (0, 1):
+        y = torch.full((N, K, P, Q), float("nan"), device="cuda")
+        params = []
+        for t in (B.pack_filters(w), b):
+            room = torch.full((t.numel() + 4,), float("nan"), device="cuda")
+            params.append(room[shift:shift + t.numel()].view(t.shape))
+            params[-1].copy_(t)
+            assert params[-1].data_ptr() % 16 == 4 * shift
+        B.conv2d_fwd(x, cd, *params, y)
+        torch.cuda.synchronize()
+        got.append(y)
+    assert bool(torch.isfinite(got[0]).all()) and torch.equal(got[0], got[1])
+
+
 def test_layers_of_a_module_share_a_launch():
     """A 3x3 and a 5x5 layer of 16 channels side by side, which stay with the other kernels: the bits of each by itself."""
     N, side = 24, 28
