@@ -1,7 +1,7 @@
 // fp32 convolution on the bf16 matrix cores, strided layers (NCHW, filters in KRSC order, C % 16 == 0): the arithmetic and the structure of conv_f32_pieces.hip, with
 // the activations cut for every tap.  (A patch of strided layers is four times as large per output and serves a quarter of the taps.)
 // Bound by the loading waves: a slice of 32 k is four units of eight operands to load, cut and write for each of their lanes (128 x 128 tiles), 2700 cycles for
-// 1536 of matrix work.  5x5 256 -> 96 at stride 2 on 20 x 23 x 112 628 us in the fp32 kernel, 269 here; 3x3 96 -> 256 on 41 x 41 x 104 320 and 154.
+// 1536 of matrix work.  At stride 2 5x5 256 -> 96 on 20 x 23 x 112 651 us in the fp32 kernel, 256 here; 3x3 96 -> 208 on 56 x 56 x 99 750 and 243.
 #include <algorithm>
 
 #include "conv_f32_cut.h"

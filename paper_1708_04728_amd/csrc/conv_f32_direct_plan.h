@@ -27,7 +27,7 @@ inline int direct_best(const PiecesLayer& l, int cus, double* us)
 
 // Layers of nine taps and more, strided in both directions, with more than 64 filters, where the other fp32 kernels use tiles of 32 filters (K % 64 from 1 to 32), whose
 // strided rows cost them most; from 1.9 units of the operations at 125 TFLOP/s (filters in whole 32) on.  Of 36 such layers on rectified operands all gain, 1.04 to 3.2
-// (3x3 96 -> 208 on 56 x 56 x 99 3.06, 160 -> 288 on 28 x 28 x 52 1.42, 64 -> 96 on 64 x 64 x 69 1.08).  Beyond the line 0.2 to 2.2.
+// (3x3 96 -> 208 on 56 x 56 x 99 3.09, 160 -> 288 on 28 x 28 x 52 1.48, 64 -> 96 on 64 x 64 x 69 1.11).  Beyond the line 0.2 to 2.2.
 // Whole tiles of 64 filters stay there: of 30 that a line at 1.2 units would take 7 lose (3x3 and 5x5; 5x5 96 -> 192 on 27 x 27 x 128 215 us there, 248 here; 96 -> 256 on
 // 27 x 27 x 256 541 and 588) and 23 gain 1.07 to 2.0, and a gain measured alone need not hold between other layers: 96 -> 256 on 28 x 28 x 128 gains 1.10 alone, while
 // AlexNet's slim blocks, whose second convolution it is, took 360 us with the other kernel and 389 with this one.

@@ -21,8 +21,8 @@
 // on 27 x 27 x 128 637 us, with the patch 534).  The walk is one stream: the next tile's patch and filters are loaded and cut while the tile before it is
 // multiplied and stored.  What matters in the loading waves: no wait for loads just sent (a register copy where two paths meet costs the full latency per slice:
 // 540 -> 509), scalar registers that do not spill (fresh_args), biases loaded before the first store and stores without a branch each (21 000 -> 5 000 cycles a tile).
-// Measured, fp32 kernels before -> here: 5x5 96 -> 256 on 27 x 27 x 128 (115 GFLOP) 831 -> 489 us, 235 TFLOP/s at the 1.75 GHz that the power leaves; 3x3 96 -> 128 on
-// 28 x 28 x 32 59 -> 37, 64 -> 192 on 56 x 56 x 32 178 -> 138; 64 -> 128 5x5 on 29 x 25 x 120 285 -> 174.  In the loop the matrix cores are busy 75 to 85 %.
+// Measured on rectified operands, fp32 kernels before -> here: 5x5 96 -> 256 on 27 x 27 x 128 (115 GFLOP) 870 -> 500 us, 229 TFLOP/s at the 1.75 GHz that the power leaves;
+// 3x3 96 -> 128 on 28 x 28 x 32 59 -> 35, 64 -> 192 on 56 x 56 x 32 182 -> 141; 64 -> 128 5x5 on 29 x 25 x 120 280 -> 167.  In the loop the matrix cores are busy 75 to 85 %.
 #include <algorithm>
 
 #include "conv_f32_cut.h"
